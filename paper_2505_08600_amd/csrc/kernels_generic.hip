@@ -1096,6 +1096,57 @@ struct PickScratch {
     int seg_last; // last index of positive weight inside the segment that holds the target
 };
 
+// The search inside vectors [v_begin, v_end) for a target that lies `base` or more into the sum: segments of blockDim
+// vectors, then a scan of the one that holds the target.  Without a crossing: the chosen segment's last index of
+// positive weight, or the range's if no segment was chosen.  At most 64 segments.
+template <typename F>
+__device__ int block_pick_range(F wfun, int v_begin, int v_end, int V, float base, float target, PickScratch *ps)
+{
+    const int T = blockDim.x;
+    const int nseg = (v_end - v_begin + T - 1) / T;
+    if (threadIdx.x == 0) {
+        ps->pick = 0x7fffffff;
+        ps->last_pos = 0;
+        ps->seg_last = -1;
+    }
+    __syncthreads();
+    int lastp = -1;
+    for (int it = 0; it < nseg; it++) {
+        const int v = v_begin + it * T + threadIdx.x;
+        const float4 f = v < v_end ? wfun(v) : make_float4(0.f, 0.f, 0.f, 0.f);
+        lastp = max(lastp, last_positive(f, 4 * v));
+        const float ssum = block_sum(((f.x + f.y) + f.z) + f.w, ps->red);
+        if (threadIdx.x == 0) ps->seg[it] = ssum;
+    }
+    if (lastp >= 0) atomicMax(&ps->last_pos, lastp);
+    __syncthreads();
+    float cum = base;
+    int sit = -1;
+    for (int it = 0; it < nseg && sit < 0; it++) {
+        if (cum + ps->seg[it] > target) sit = it;
+        else cum += ps->seg[it];
+    }
+    if (sit >= 0) { // (uniform)
+        const int v = v_begin + sit * T + threadIdx.x;
+        const float4 f = v < v_end ? wfun(v) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float loc = ((f.x + f.y) + f.z) + f.w;
+        const float pre = block_excl_scan(loc, ps->red);
+        int k = first_over(cum + pre, f, target, 4 * v);
+        if (k >= V) k = 0x7fffffff;
+        k = wave_min_i(k);
+        const int ls = wave_max_i(last_positive(f, 4 * v));
+        if (threadIdx.x % WAVE == 0) {
+            if (k != 0x7fffffff) atomicMin(&ps->pick, k);
+            if (ls >= 0) atomicMax(&ps->seg_last, ls);
+        }
+    }
+    __syncthreads();
+    int pick = ps->pick;
+    if (pick == 0x7fffffff) pick = sit >= 0 && ps->seg_last >= 0 ? min(ps->seg_last, V - 1) : ps->last_pos;
+    __syncthreads();
+    return pick;
+}
+
 template <typename F>
 __device__ int block_pick_cdf(F wfun, int V, float u, PickScratch *ps, float *total_out)
 {
@@ -1843,110 +1894,210 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 }
 
 // ---------------------------------------------------------------- verify tail
-// Fused vocabulary softmax + accept scan + residual + resample, one block per
-// sequence.  Row statistics (max, sum of exponentials, argmax) of the gamma+1
-// logit rows are block reductions; the accept scan runs on thread 0; only the
-// row that decides the next token is traversed again.
-__global__ __launch_bounds__(1024) void verify_tail_kernel(const float *logits, int gamma, int V, float T,
-                                                           const int32_t *cand, const float *q, const float *u,
-                                                           const int32_t *seq_ids, int32_t *n_acc_out,
-                                                           int32_t *next_out, int commit, CtxView cv)
+// Fused vocabulary softmax + accept scan + residual + resample.  Rows of more than ROW_NSEG * ROW_THREADS * 4 = 32768
+// columns do not fit a block's registers; they take three launches:
+//   verify_stats_wide_kernel  one block per logits row, one pass: (max, sum of exponentials, argmax);
+//   verify_mass_wide_kernel   the acceptance tests, then the mass of one slice of the deciding row per block;
+//   verify_pick_wide_kernel   one block per sequence: the slice that holds u * Z is searched for the token; commit.
+// Bound: one read of all rows.  The caller's workspace is three floats per row, so what a row's blocks could hand on is
+// limited to that: a row's statistics come from one block, and the slice masses (gamma + 1 per sequence) take the
+// argmax entries, which sampling does not use.  A block keeps 8 float4 per thread in flight; 512 threads when there are
+// rows enough to put two blocks on every compute unit (64 sequences, gamma 8, 128000 columns: 295 MB).
+// Measured at that size: 102 us for the three launches (3.2 TB/s of logits and q; 455 us with a block per sequence that
+// ran its rows one after the other, three passes each).
+#define WIDE_U 8
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int V, float T, float *stats)
 {
-    __shared__ PickScratch ps;
     __shared__ float redv[32];
     __shared__ int redi[32];
-    __shared__ float s_mx[SD_MAX_GAMMA + 1], s_z[SD_MAX_GAMMA + 1];
-    __shared__ int s_am[SD_MAX_GAMMA + 1];
-    __shared__ int s_nacc;
-    __shared__ float s_zr;
-    int j = blockIdx.x;
-    const float *rows = logits + (size_t)j * (gamma + 1) * V;
-    const int32_t *cj = cand + (size_t)j * gamma;
-    float invT = T > 0.f ? 1.0f / T : 0.f;
-    const int stride_g = gamma; // row slots of the call: strides of cand, q and u
+    const float4 *row = (const float4 *)(logits + (size_t)blockIdx.x * V);
+    const int nvec = V / 4; // (V is a multiple of 4)
+    const float invT = T > 0.f ? 1.0f / T : 0.f;
+    // thread-local running maximum m (from -3e38: masked columns may lie below it, their exponentials are 0) and the
+    // sum of exp((x - m) / T), rescaled when a batch of WIDE_U vectors raises m
+    float m = -3.0e38f, z = 0.f;
+    int am = 0x7fffffff;
+    for (int v0 = threadIdx.x; v0 < nvec; v0 += WIDE_U * THREADS) {
+        float4 f[WIDE_U];
+#pragma unroll
+        for (int k = 0; k < WIDE_U; k++) {
+            const int v = v0 + k * THREADS;
+            f[k] = v < nvec ? row[v] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+        const float m_old = m;
+#pragma unroll
+        for (int k = 0; k < WIDE_U; k++) {
+            const int i = 4 * (v0 + k * THREADS);
+            if (f[k].x > m) { m = f[k].x; am = i; }
+            if (f[k].y > m) { m = f[k].y; am = i + 1; }
+            if (f[k].z > m) { m = f[k].z; am = i + 2; }
+            if (f[k].w > m) { m = f[k].w; am = i + 3; }
+        }
+        if (invT > 0.f) { // (uniform)
+            float s = 0.f;
+#pragma unroll
+            for (int k = 0; k < WIDE_U; k++) {
+                s += (expf((f[k].x - m) * invT) + expf((f[k].y - m) * invT)) +
+                     (expf((f[k].z - m) * invT) + expf((f[k].w - m) * invT));
+            }
+            z = m > m_old ? z * expf((m_old - m) * invT) + s : z + s;
+        }
+    }
+    float mx = m;
+    block_argmax(mx, am, redv, redi);
+    if (invT > 0.f) {
+        __syncthreads(); // redv is read above
+        z = block_sum(m < mx ? z * expf((m - mx) * invT) : z, redv);
+    } else {
+        z = 1.f;
+    }
+    if (threadIdx.x == 0) {
+        stats[3 * blockIdx.x] = mx;
+        stats[3 * blockIdx.x + 1] = z;
+        stats[3 * blockIdx.x + 2] = __int_as_float(am);
+    }
+}
+
+// The acceptance tests of one sequence by the block's first threads: candidate i is accepted iff u_i < p_i / q_i (T > 0)
+// or it is the row's argmax (T == 0).  Returns the length of the accepted prefix; s_ok: SD_MAX_GAMMA ints of LDS.
+__device__ int accept_scan(const float *rows, const float *st, int gamma, int stride_g, int V, float T, float invT,
+                           const int32_t *cj, const float *qj, const float *uj, int *s_ok)
+{
+    if ((int)threadIdx.x < gamma) {
+        const int i = threadIdx.x;
+        const int c = cj[i];
+        bool ok;
+        if (T == 0.f) ok = c == __float_as_int(st[3 * i + 2]);
+        else if (c < 0 || c >= V) ok = false;
+        else {
+            const float p = expf((rows[(size_t)i * V + c] - st[3 * i]) * invT) / st[3 * i + 1];
+            float qc = qj[(size_t)i * V + c];
+            qc = fmaxf(qc, 1.17549435e-38f);
+            ok = uj[i] < p / qc;
+        }
+        s_ok[i] = ok ? 1 : 0;
+    }
+    __syncthreads();
+    int n = 0;
+    while (n < gamma && s_ok[n]) n++;
+    return n;
+}
+
+// Weights the next token is drawn from: p of the deciding row, or max(0, p - q) where it was rejected (q != nullptr).
+struct DrawWeights {
+    const float4 *row, *q;
+    float mx, invT, invZ;
+    __device__ __forceinline__ float4 operator()(int v) const
+    {
+        const float4 f = row[v];
+        float4 p;
+        p.x = expf((f.x - mx) * invT) * invZ;
+        p.y = expf((f.y - mx) * invT) * invZ;
+        p.z = expf((f.z - mx) * invT) * invZ;
+        p.w = expf((f.w - mx) * invT) * invZ;
+        if (q) { // (uniform)
+            const float4 w = q[v];
+            p = make_float4(fmaxf(p.x - w.x, 0.f), fmaxf(p.y - w.y, 0.f), fmaxf(p.z - w.z, 0.f), fmaxf(p.w - w.w, 0.f));
+        }
+        return p;
+    }
+};
+
+// T > 0.  Block (s, j): mass of slice s of sequence j's deciding row, left in the argmax entry of its row s.
+__global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logits, float *stats, int gamma, int V, float T,
+                                                               const int32_t *cand, const float *q, const float *u,
+                                                               const int32_t *seq_ids, int32_t *n_acc_out, CtxView cv)
+{
+    __shared__ int s_ok[SD_MAX_GAMMA];
+    __shared__ float red[32];
+    const int j = blockIdx.y, s = blockIdx.x, n_slices = gridDim.x, stride_g = gamma;
     {   // with per-sequence candidate counts this sequence has gj <= gamma candidates (and gj + 1 live rows)
         const int bb = seq_ids ? seq_ids[j] : j;
         if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
     }
-    for (int i = 0; i <= gamma; i++) {
-        float mx;
-        int am;
-        row_max_argmax(rows + (size_t)i * V, V, redv, redi, mx, am);
-        float z = 1.f;
-        if (T > 0.f) z = row_sumexp(rows + (size_t)i * V, V, mx, invT, redv);
-        if (threadIdx.x == 0) {
-            s_mx[i] = mx;
-            s_z[i] = z;
-            s_am[i] = am;
-        }
+    const float *rows = logits + (size_t)j * (stride_g + 1) * V, *qj = q + (size_t)j * stride_g * V;
+    float *st = stats + (size_t)j * (stride_g + 1) * 3;
+    const float invT = 1.0f / T;
+    const int n_acc = accept_scan(rows, st, gamma, stride_g, V, T, invT, cand + (size_t)j * stride_g, qj,
+                                  u + (size_t)j * (stride_g + 1), s_ok);
+    const DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
+                           n_acc < gamma ? (const float4 *)(qj + (size_t)n_acc * V) : nullptr, st[3 * n_acc], invT,
+                           1.0f / st[3 * n_acc + 1]};
+    const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices, v_end = min(nvec, (s + 1) * per);
+    float mass = 0.f;
+#pragma unroll 4
+    for (int v = s * per + threadIdx.x; v < v_end; v += 512) {
+        const float4 f = w(v);
+        mass += ((f.x + f.y) + f.z) + f.w;
     }
-    __syncthreads();
+    mass = block_sum(mass, red);
     if (threadIdx.x == 0) {
-        int n_acc = 0;
-        for (int i = 0; i < gamma; i++) {
-            int c = cj[i];
-            bool ok;
-            if (T == 0.f) ok = c == s_am[i];
-            else if (c < 0 || c >= V) ok = false;
-            else {
-                float p = expf((rows[(size_t)i * V + c] - s_mx[i]) * invT) / s_z[i];
-                float qc = q[((size_t)j * stride_g + i) * V + c];
-                qc = fmaxf(qc, 1.17549435e-38f);
-                ok = u[j * (stride_g + 1) + i] < p / qc;
-            }
-            if (!ok) break;
-            n_acc++;
-        }
-        s_nacc = n_acc;
+        st[3 * s + 2] = mass;
+        if (s == 0) n_acc_out[j] = n_acc;
     }
-    __syncthreads();
-    int n_acc = s_nacc;
+}
+
+// T > 0.  One block per sequence: the slice whose masses pass u * Z, searched with the rule of block_pick_cdf (segments
+// of 1024 vectors, then a scan of the segment that holds the target).
+__global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *logits, const float *stats, int gamma, int V, float T,
+                                                                const int32_t *cand, const float *q, const float *u,
+                                                                const int32_t *seq_ids, const int32_t *n_acc_in,
+                                                                int32_t *next_out, int commit, CtxView cv)
+{
+    __shared__ PickScratch ps;
+    const int j = blockIdx.x, stride_g = gamma, n_slices = gamma + 1;
+    const int bb = seq_ids ? seq_ids[j] : j;
+    if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
+    const float *rows = logits + (size_t)j * (stride_g + 1) * V;
+    const float *st = stats + (size_t)j * (stride_g + 1) * 3;
+    const int n_acc = min(max(n_acc_in[j], 0), gamma);
+    const float uu = u[(size_t)j * (stride_g + 1) + gamma];
+    DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
+                     n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc], 1.0f / T,
+                     1.0f / st[3 * n_acc + 1]};
+    const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
+    float Z = 0.f;
+    for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
     int next;
-    if (T == 0.f) {
-        next = s_am[n_acc];
+    if (w.q && !(Z > 0.f)) { // numerically empty residual: draw from p
+        w.q = nullptr;
+        next = block_pick_cdf(w, V, uu, &ps, nullptr);
     } else {
-        const float *row = rows + (size_t)n_acc * V;
-        float mx = s_mx[n_acc], invZ = 1.0f / s_z[n_acc];
-        float uu = u[j * (stride_g + 1) + gamma];
-        auto pfun = [&](int v) {
-            float4 f = load4_guard(row, v, V, -3.0e38f);
-            float4 p;
-            p.x = expf((f.x - mx) * invT) * invZ;
-            p.y = 4 * v + 1 < V ? expf((f.y - mx) * invT) * invZ : 0.f;
-            p.z = 4 * v + 2 < V ? expf((f.z - mx) * invT) * invZ : 0.f;
-            p.w = 4 * v + 3 < V ? expf((f.w - mx) * invT) * invZ : 0.f;
-            return p;
-        };
-        bool use_p = n_acc >= gamma;
-        if (!use_p) {
-            const float *qrow = q + ((size_t)j * stride_g + n_acc) * V;
-            auto rfun = [&](int v) {
-                float4 p = pfun(v);
-                float4 qq = load4_guard(qrow, v, V, 0.f);
-                return make_float4(fmaxf(p.x - qq.x, 0.f), fmaxf(p.y - qq.y, 0.f), fmaxf(p.z - qq.z, 0.f),
-                                   fmaxf(p.w - qq.w, 0.f));
-            };
-            float zr = 0.f;
-            next = block_pick_cdf(rfun, V, uu, &ps, &zr);
-            if (threadIdx.x == 0) s_zr = zr;
-            __syncthreads();
-            if (!(s_zr > 0.f)) use_p = true; // numerically empty residual: draw from p
-            __syncthreads();
+        // every thread walks the slice masses in the same order: first slice whose running sum exceeds the target, else
+        // (rounding) the last slice of positive mass
+        const float target = uu * Z;
+        float cum = 0.f, base = 0.f, base_last = 0.f;
+        int s_pick = -1, s_last = 0;
+        for (int s = 0; s < n_slices; s++) {
+            const float mass = st[3 * s + 2];
+            if (mass > 0.f) {
+                s_last = s;
+                base_last = cum;
+            }
+            if (s_pick < 0 && cum + mass > target) {
+                s_pick = s;
+                base = cum;
+            }
+            cum += mass;
         }
-        if (use_p) next = block_pick_cdf(pfun, V, uu, &ps, nullptr);
+        if (s_pick < 0) {
+            s_pick = s_last;
+            base = base_last;
+        }
+        const int v_begin = s_pick * per;
+        next = block_pick_range(w, v_begin, min(nvec, v_begin + per), V, base, target, &ps);
     }
     if (threadIdx.x == 0) {
-        n_acc_out[j] = n_acc;
         next_out[j] = next;
         if (commit) {
-            int b = seq_ids ? seq_ids[j] : j;
-            if (b >= 0 && b < cv.B) commit_one(cv, b, gamma, cj, n_acc, next);
+            if (bb >= 0 && bb < cv.B) commit_one(cv, bb, gamma, cand + (size_t)j * stride_g, n_acc, next);
             else atomicOr(cv.status, 4);
         }
     }
 }
 
-// Same decisions as verify_tail_kernel in two launches.  verify_stats_kernel: one block per logits row
+// Rows that fit a block's registers, in two launches.  verify_stats_kernel: one block per logits row
 // (n_seq * (gamma + 1) blocks, so the exponentials of the rows run on different compute units), each row
 // read once into registers; writes max, z and argmax per row.  verify_decide_kernel: one block per
 // sequence; the gamma acceptance tests are evaluated by gamma threads in parallel and scanned by
@@ -1974,7 +2125,6 @@ __global__ __launch_bounds__(ROW_THREADS) void verify_decide_kernel(const float 
 {
     __shared__ FastScratch fs;
     __shared__ int s_ok[SD_MAX_GAMMA];
-    __shared__ int s_nacc;
     __shared__ float s_zr;
     const int j = blockIdx.x;
     const float *rows = logits + (size_t)j * (gamma + 1) * V;
@@ -1986,28 +2136,8 @@ __global__ __launch_bounds__(ROW_THREADS) void verify_decide_kernel(const float 
         const int bb = seq_ids ? seq_ids[j] : j;
         if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
     }
-    if ((int)threadIdx.x < gamma) {
-        const int i = threadIdx.x;
-        const int c = cj[i];
-        bool ok;
-        if (T == 0.f) ok = c == __float_as_int(st[3 * i + 2]);
-        else if (c < 0 || c >= V) ok = false;
-        else {
-            const float p = expf((rows[(size_t)i * V + c] - st[3 * i]) * invT) / st[3 * i + 1];
-            float qc = q[((size_t)j * stride_g + i) * V + c];
-            qc = fmaxf(qc, 1.17549435e-38f);
-            ok = u[j * (stride_g + 1) + i] < p / qc;
-        }
-        s_ok[i] = ok ? 1 : 0;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int n = 0;
-        while (n < gamma && s_ok[n]) n++;
-        s_nacc = n;
-    }
-    __syncthreads();
-    const int n_acc = s_nacc;
+    const int n_acc = accept_scan(rows, st, gamma, stride_g, V, T, invT, cj, q + (size_t)j * stride_g * V,
+                                  u + (size_t)j * (stride_g + 1), s_ok);
     int next;
     if (T == 0.f) {
         next = __float_as_int(st[3 * n_acc + 2]);
@@ -2061,13 +2191,23 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
                               const int32_t *cand, const float *q, const float *u, const int32_t *seq_ids,
                               int32_t *n_acc, int32_t *next_tok, int commit, CtxView cv, float *stats)
 {
-    if (V <= ROW_NSEG * ROW_THREADS * 4 && stats) {
-        hipLaunchKernelGGL(verify_stats_kernel, dim3(n_seq * (gamma + 1)), dim3(ROW_THREADS), 0, s, logits, V, T, stats);
+    const int n_rows = n_seq * (gamma + 1);
+    if (V <= ROW_NSEG * ROW_THREADS * 4) {
+        hipLaunchKernelGGL(verify_stats_kernel, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, V, T, stats);
         hipLaunchKernelGGL(verify_decide_kernel, dim3(n_seq), dim3(ROW_THREADS), 0, s, logits, stats, gamma, V, T, cand, q,
                            u, seq_ids, n_acc, next_tok, commit, cv);
-    } else
-        hipLaunchKernelGGL(verify_tail_kernel, dim3(n_seq), dim3(1024), 0, s, logits, gamma, V, T, cand, q, u, seq_ids,
+        return hipGetLastError();
+    }
+    if (n_rows >= 512) hipLaunchKernelGGL(verify_stats_wide_kernel<512>, dim3(n_rows), dim3(512), 0, s, logits, V, T, stats);
+    else hipLaunchKernelGGL(verify_stats_wide_kernel<1024>, dim3(n_rows), dim3(1024), 0, s, logits, V, T, stats);
+    if (T > 0.f) {
+        hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(gamma + 1, n_seq), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
+                           u, seq_ids, n_acc, cv);
+        hipLaunchKernelGGL(verify_pick_wide_kernel, dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, seq_ids,
                            n_acc, next_tok, commit, cv);
+    } else // (greedy: the decision needs the argmax entries only)
+        hipLaunchKernelGGL(verify_decide_kernel, dim3(n_seq), dim3(ROW_THREADS), 0, s, logits, stats, gamma, V, T, cand, q,
+                           u, seq_ids, n_acc, next_tok, commit, cv);
     return hipGetLastError();
 }
 

@@ -72,6 +72,36 @@ def test_accept_alone_matches_oracle(V, gamma, T, rho):
         assert len(set(na_h.tolist())) >= 2   # the case exercises accept, reject and the residual draw
 
 
+@pytest.mark.parametrize("V,gamma,T", [(32772, 15, 1.0), (32772, 1, 0.7), (65536, 0, 1.0), (100004, 7, 1.0), (262144, 1, 0.7),
+                                       (131072, 4, 0.0)])
+def test_rows_beyond_a_blocks_registers(V, gamma, T):
+    """Rows of more than 32768 columns: one vector past the boundary, slices of unequal length, a single slice (gamma 0),
+    slices whose columns are all masked (-inf, and the lowest float), up to 16 slices; residual draws and draws from p."""
+    print(f"wide rows V={V} gamma={gamma} T={T}", flush=True)
+    B = 5
+    logits, q, cand, u = synthetic_case(37, B, gamma, V, 0.9, T)
+    if T > 0:
+        logits[:, :, V // 3:V // 2] = -np.inf
+        logits[:, :, V - 4:] = np.float32(-3.4028235e38)
+        logits[1, :, V // 4:] = -np.inf          # everything after the first quarter: the later slices have no mass
+        logits[2, :, :3 * V // 4] = -np.inf      # everything before the last quarter
+        if gamma:
+            q = np.stack([np.stack([oracle.softmax_T(logits[b, i] * np.float32(0.9), T) for i in range(gamma)]) for b in range(B)])
+            q[3] = np.stack([oracle.softmax_T(logits[3, i], T) for i in range(gamma)])   # q = p: everything is accepted
+            cand = np.stack([[oracle.sample_cdf(q[b, i].astype(np.float64), 0.37 + 0.05 * i / 16)[0] for i in range(gamma)] for b in range(B)]).astype(np.int32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * B * (gamma + 1),), float("nan"), device="cuda")
+    for _ in range(2):   # the workspace holds the first call's slice masses when the second starts
+        api.sd_accept(dev(logits), gamma, T, dev(cand) if gamma else None, dev(q) if gamma and T > 0 else None,
+                      dev(u) if T > 0 else None, na, nx, ws)
+        torch.cuda.synchronize()
+        na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+        assert check_against_oracle(logits, q, cand, u, T, na_h, nx_h) <= 1
+        assert all(np.isfinite(logits[b, na_h[b], nx_h[b]]) and logits[b, na_h[b], nx_h[b]] > -1e38 for b in range(B))
+    print(f"  n_acc={na_h.tolist()}", flush=True)
+
+
 @pytest.mark.parametrize("V,gamma,n_trials", [(2772, 0, 1500), (2772, 1, 1500), (32000, 0, 900), (32000, 1, 600),
                                               (50000, 0, 450), (262144, 0, 99)])
 def test_next_token_for_uniforms_on_the_boundaries_of_the_cdf(V, gamma, n_trials):
