@@ -372,7 +372,8 @@ int sd_debug_read(sd_model *m, const char *name, float *out, int32_t rows);
  * kind 3: key cache of one head, same arguments (32-token tiles in MFMA operand order).
  * Returns -1 for an unknown kind or arguments outside the layout's domain. */
 int64_t sd_debug_layout_index(int32_t kind, int64_t a, int64_t b, int64_t c, int64_t d);
-/* Host-only (no GPU call): the launch plan of a bf16 GEMM with more than 32 rows (the row-blocked kernel).
+/* Host-only (no GPU call): the launch plan of a bf16 GEMM with more than 32 rows on the row-blocked kernel (up to 64
+ * rows most shapes run on the few-row kernel instead).
  * mode 0 = plain projection, 2 = gate/up pair with the SwiGLU epilogue (n = output columns);
  * n_per_seg = output columns per weight segment (n for one matrix, n / 3 for q | k | v).
  * plan[0] = weight rows per block, [1] = rows per block, [2] = column tiles, [3] = row blocks,
@@ -398,8 +399,8 @@ int sd_debug_stream_read(const void *buf, size_t bytes, uint32_t *scratch_word, 
  * layer can be split between the projection before them (adds the residual, applies the gains,
  * leaves per-block sums of squares) and the GEMM after them (scales its sums by 1 / rms); the
  * operand is then rounded to its two bf16 terms before the division by rms instead of after.
- * 0 or 1 = wherever the shapes allow (bf16, no adapters loaded, widths multiples of 128: the
- * default), 2 = never.
+ * 1 = wherever the shapes allow (bf16, no adapters loaded, widths multiples of 128), 0 = there, and where
+ * it is the faster form (the default: up to 8 rows always, up to 32 in narrow models), 2 = never.
  * option "rope_group": on the split attention path (prefill, long contexts) RoPE + cache append of a bf16 model
  * runs one block per (head, group of up to 16 consecutive rows) with 16-byte stores (1, the default) or one block
  * per row (0); both give the same bits.

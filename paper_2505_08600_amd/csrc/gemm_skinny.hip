@@ -15,9 +15,10 @@
 //    planes ride in ONE operand: MFMA columns 0..7 carry the hi rows, columns 8..15
 //    the lo rows, and the epilogue adds the two halves; for larger M every weight
 //    fragment is multiplied twice;
-//  * M <= 32 (gemm_ksplit_kernel): the waves of a block split K, fetch their
-//    activation fragments straight from L2 and meet in LDS - no barrier in the K loop;
-//    M > 32 (gemm_tile_kernel): 48-row blocks share a staged activation chunk in LDS;
+//  * few rows (gemm_ksplit_kernel up to 8 rows or where the norm is split, gemm_wide_kernel
+//    from 9 to 64): the waves of a block split K, fetch their activation fragments straight
+//    from L2 and meet in LDS - no barrier in the K loop;
+//    more rows (gemm_tile_kernel): row blocks share a staged activation chunk in LDS;
 //  * results leave either directly (store; SwiGLU: silu(gate)*up split to bf16
 //    hi/lo) or as fp32 partial sums per K split, which the consuming kernel adds in
 //    a fixed order (the fused attention prologue for QKV, add_rmsnorm for the residual
@@ -26,6 +27,8 @@
 // Paper (arXiv 2505.08600): Section 1, Figure 1 (draft steps and the parallel
 // verify pass whose linear layers these are); Section 3.1 (LLaMA blocks).
 #include "sd_internal.h"
+
+#include <algorithm>
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -519,6 +522,190 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_ksplit_kernel(const uint16_t 
     }
 }
 
+// Wide few-row GEMM (9 to 64 rows): like gemm_ksplit_kernel the waves of a block share out the K steps and meet in LDS,
+// but a block owns NW weight tiles instead of one or two.
+// Bound: bytes through L2 into the compute units (about 8.5 TB/s on this part for 16-byte loads), of which HBM only
+// supplies the weights: a block re-reads the activation rows of its K range, 4 M bytes per K element against 32 NW of
+// weights, so at M = 24 one gate/up pair per block pulled 270 MB of rows beside 180 MB of weights; six tiles pull 90 MB.
+// The loads of a wave's next step go out group by group while the current one is multiplied, into the registers just
+// used.  Measured at M = 24, 7B shape, weights from HBM (before: gemm_ksplit_kernel; us): QKV 27.3 -> 20.3, O 11.1 -> 9,
+// gate/up 50.0 -> 36.3, down 24.3 -> 19.0, LM head 66.3 -> 46.7; at M = 64 (before: gemm_tile_kernel in 48-row blocks)
+// 36.4 -> 29.4, 15.1 -> 12.7, 61.2 -> 53.1, 28.5 -> 25.5, 67.4 -> 63.7, and a 768-wide QKV 10.5 -> 5.0.
+#define WIDE_WAVES 4
+template <int NMAT, int MT, int NW, bool NT_HINT>
+__global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16_t *__restrict__ A, ActView a_av, WeightSeg w, int M,
+                                                               int N, int K, int steps_per_split, float *__restrict__ C,
+                                                               size_t c_split_stride, uint16_t *__restrict__ Cact, ActView c_av,
+                                                               LmStats ls)
+{
+    constexpr int WAVES = WIDE_WAVES;
+    static_assert(NW % 2 == 0, "tiles are finished in pairs");
+    __shared__ f32x4 red[WAVES][NW][MT][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = lane & 15, grp = lane >> 4;
+    const size_t tile_elems = (size_t)(K >> 7) * 2048;
+    constexpr int CT = NW / NMAT; // 16-column tiles of the result per block
+    const int t0 = blockIdx.x * CT, n_t = N / 16;
+    // tile c of the block (NMAT = 2: gate and up alternate); tiles past the end (last block) re-read the last one
+    const uint16_t *Wp[NW];
+    const int seg_tiles = w.n_per_seg / 16;
+#pragma unroll
+    for (int c = 0; c < NW; c++) {
+        const int t = min(t0 + c / NMAT, n_t - 1), seg = NMAT == 2 ? c & 1 : t / seg_tiles;
+        const uint16_t *base = (const uint16_t *)(seg == 0 ? w.p[0] : seg == 1 ? w.p[1] : w.p[2]);
+        Wp[c] = base + (size_t)(NMAT == 2 ? t : t - seg * seg_tiles) * tile_elems;
+    }
+    const uint16_t *Ap[MT]; // rows past M re-read the last one; they only reach result columns that are never stored
+#pragma unroll
+    for (int t = 0; t < MT; t++) Ap[t] = A + (size_t)min(t * 16 + row, M - 1) * 128 + grp * 8;
+    const size_t step_stride = (size_t)a_av.rows * 128;
+    f32x4 acc[NW][MT];
+#pragma unroll
+    for (int c = 0; c < NW; c++)
+#pragma unroll
+        for (int t = 0; t < MT; t++) acc[c][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    bf16x8 wv[NW][4], ah[MT][4], al[MT][4];
+    auto issue = [&](int st, int i) { // group i (32 of the step's 128 elements)
+#pragma unroll
+        for (int t = 0; t < MT; t++) {
+            ah[t][i] = *(const bf16x8 *)(Ap[t] + step_stride * st + i * 32);
+            al[t][i] = *(const bf16x8 *)(Ap[t] + a_av.plane + step_stride * st + i * 32);
+        }
+#pragma unroll
+        for (int c = 0; c < NW; c++)
+            wv[c][i] = ld_stream<NT_HINT>((const bf16x8 *)(Wp[c] + (size_t)st * 2048 + i * 512 + lane * 8));
+    };
+    auto consume = [&](int i) {
+#pragma unroll
+        for (int t = 0; t < MT; t++)
+#pragma unroll
+            for (int c = 0; c < NW; c++) acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[c][i], ah[t][i], acc[c][t], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < MT; t++)
+#pragma unroll
+            for (int c = 0; c < NW; c++) acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[c][i], al[t][i], acc[c][t], 0, 0, 0);
+    };
+    const int s_begin = blockIdx.y * steps_per_split, s_end = min(K / 128, s_begin + steps_per_split);
+    int st = s_begin + wave;
+    if (st < s_end) { // (uniform over the wave)
+#pragma unroll
+        for (int i = 0; i < 4; i++) issue(st, i);
+        for (; st + WAVES < s_end; st += WAVES) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                consume(i);
+                issue(st + WAVES, i);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) consume(i);
+    }
+#pragma unroll
+    for (int c = 0; c < NW; c++)
+#pragma unroll
+        for (int t = 0; t < MT; t++) red[wave][c][t][lane] = acc[c][t];
+    __syncthreads();
+    // unit = (pair of tiles, row tile): lane (m' = lane % 16, g = lane / 16) finishes columns 4 g .. 4 g + 3 of row m'
+    for (int u = wave; u < NW / 2 * MT; u += WAVES) {
+        const int c = u / MT * 2, t = u % MT, m = t * 16 + row;
+        f32x4 v0 = red[0][c][t][lane], v1 = red[0][c + 1][t][lane];
+#pragma unroll
+        for (int x = 1; x < WAVES; x++) {
+            v0 += red[x][c][t][lane];
+            v1 += red[x][c + 1][t][lane];
+        }
+        if (NMAT == 2) {
+            const int n = (t0 + c / 2) * 16 + 4 * grp;
+            if (m < M && n < N) {
+                float y[4];
+#pragma unroll
+                for (int r = 0; r < 4; r++) y[r] = v0[r] / (1.0f + expf(-v0[r])) * v1[r];
+                uint32_t h0, l0, h1, l1;
+                bf16x2_split(y[0], y[1], h0, l0);
+                bf16x2_split(y[2], y[3], h1, l1);
+                const size_t o = act_index(c_av, m, n, N); // 4 columns inside one K step
+                *(uint2 *)(Cact + o) = make_uint2(h0, h1);
+                *(uint2 *)(Cact + c_av.plane + o) = make_uint2(l0, l1);
+            }
+        } else {
+            const int n = (t0 + c) * 16 + 4 * grp;
+            float *dst = C + (size_t)blockIdx.y * c_split_stride + (size_t)m * N + n;
+            if (m < M && n < N) *(f32x4 *)dst = v0;
+            if (m < M && n + 16 < N) *(f32x4 *)(dst + 16) = v1;
+            if (ls.p && n < N) { // (uniform; N is a multiple of 32) partials of the 32 columns this unit covers
+                float mx = v0[0];
+                int ai = n;
+#pragma unroll
+                for (int r = 1; r < 4; r++)
+                    if (v0[r] > mx) mx = v0[r], ai = n + r;
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    if (v1[r] > mx) mx = v1[r], ai = n + 16 + r;
+#pragma unroll
+                for (int o = 16; o <= 32; o <<= 1) {
+                    const float ov = __shfl_xor(mx, o, 64);
+                    const int oi = __shfl_xor(ai, o, 64);
+                    if (ov > mx || (ov == mx && oi < ai)) mx = ov, ai = oi;
+                }
+                float ex = 0.f;
+                if (ls.invT > 0.f) {
+#pragma unroll
+                    for (int r = 0; r < 4; r++) ex += expf((v0[r] - mx) * ls.invT) + expf((v1[r] - mx) * ls.invT);
+                }
+                ex += __shfl_xor(ex, 16, 64);
+                ex += __shfl_xor(ex, 32, 64);
+                if (grp == 0 && m < M) {
+                    float *sp = ls.p + ((size_t)m * (N / 32) + (t0 + c) / 2) * 3;
+                    sp[0] = mx;
+                    sp[1] = ex;
+                    sp[2] = __int_as_float(ai);
+                }
+            }
+        }
+    }
+}
+
+// Block shape of the wide kernel: NW weight tiles per block and the K splits (nw = 0: not a shape of it).  The estimate
+// is what the busiest compute unit pulls in, in KiB: rounds of blocks over 256 units x K steps per split x (4 NW for the
+// weights + M / 2 for the rows), plus the splits' fp32 slabs, written here and read by the consumer (32 bytes per element
+// spread over the units).  Against a sweep of NW, 4 and 8 waves and 1 to 8 splits over QKV / O / gate-up / down / LM head of the
+// 7B, 13B and draft shapes at 9 to 64 rows its choice is the fastest or within 8 % of it (8 waves were never more than 2 % ahead).
+struct WidePlan {
+    int nw, ncol, ks;
+};
+static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks)
+{
+    WidePlan best = {0, 0, 1};
+    if (M < 9 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || K < 128) return best;
+    // 41 to 48 rows fit one 48-row block of the row-blocked kernel, which stages them once for 128 weight rows: where
+    // its unsplit grid fills the chip it is ahead (gate/up at M = 48: 44.7 against 45.9 us at 4096 / 11008, 55.5 against 65.2
+    // at 5120 / 13824; the 32000-column head 52.8 against 55.0)
+    const int nmat = mode == GEMM_SWIGLU ? 2 : 1, rows_w = N * nmat, steps = K / 128;
+    if (M > 40 && M <= 48 && steps >= 16 && rows_w % 128 == 0 && n_per_seg % 128 == 0 && N == n_per_seg && rows_w / 128 >= 160) return best;
+    float best_cost = 0.f;
+    for (int nw = 2; nw <= 8; nw += 2) {
+        const int ct = nw / nmat, ncol = (N / 16 + ct - 1) / ct;
+        for (int ks = force_ks > 0 ? force_ks : 1; ks <= (force_ks > 0 ? force_ks : mode == GEMM_SWIGLU ? 1 : 8); ks++) {
+            int kps, ny;
+            split_geometry(K, ks, &kps, &ny);
+            if (force_ks <= 0 && ks > 1 && (ny != ks || kps < 256)) continue;
+            const float rounds = (float)((ncol * ny + 255) / 256);
+            const float cost = rounds * (float)(kps / 128) * (4.f * nw + 0.5f * M) + (ny > 1 ? (float)ny * M * N * (32.f / (256 * 1024)) : 0.f);
+            if (best.nw == 0 || cost < best_cost) {
+                best = {nw, ncol, ny};
+                best_cost = cost;
+            }
+        }
+    }
+    return best;
+}
+
+// Does the norm split between producer and consumer GEMM (NormFold) pay at M rows?  Its producers run without a K split in
+// blocks of 16 columns, each of which pulls K x (32 bytes of weights + 4 M of rows) into one compute unit - 10 us at about
+// 430 KB - while the unfused projection is split over the chip and followed by a launch of 4 - 5 us.  Up to 8 rows (hi and lo
+// rows share one operand) the weights dominate and the fold is ahead at every width.
+bool gemm_normfold_pays(int M, int d, int F) { return M <= 8 || (long)std::max(d, F) * (32 + 4 * M) <= 430000; }
+
 // Block shapes of the row-blocked kernel.  More than 64 rows: 96 rows x 256 columns (4 waves x 4 tiles; chunks
 // of half a K step) - the bytes a block pulls through L2 per MFMA halve against 48 x 128, which is what
 // bounds these GEMMs - or x 192 columns (3 tiles per wave) where that fills the 256 compute units better
@@ -640,7 +827,51 @@ static hipError_t tile_launch(hipStream_t s, const uint16_t *a, ActView a_av, We
     return hipGetLastError();
 }
 
+template <int NMAT, int MT, bool NT>
+static void wide_launch_nw(hipStream_t s, WidePlan p, const uint16_t *a, ActView a_av, WeightSeg w, int M, int N, int K, int sps,
+                           float *C, size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls)
+{
+    const dim3 grid(p.ncol, p.ks), block(WIDE_WAVES * 64);
+#define SD_WIDE(NW_)                                                                                                          \
+    hipLaunchKernelGGL((gemm_wide_kernel<NMAT, MT, NW_, NT>), grid, block, 0, s, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls)
+    if (p.nw == 2) SD_WIDE(2);
+    else if (p.nw == 4) SD_WIDE(4);
+    else if (p.nw == 6) SD_WIDE(6);
+    else SD_WIDE(8);
+#undef SD_WIDE
+}
+template <int NMAT>
+static hipError_t wide_launch(hipStream_t s, WidePlan p, const uint16_t *a, ActView a_av, WeightSeg w, int M, int N, int K, float *C,
+                              size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls)
+{
+    int kps, ny;
+    split_geometry(K, p.ks, &kps, &ny);
+    const int mt = (M + 15) / 16, sps = kps / 128;
+#define SD_WIDE_MT(MT_)                                                                                                   \
+    do {                                                                                                                  \
+        if (w.nt) wide_launch_nw<NMAT, MT_, true>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls);        \
+        else wide_launch_nw<NMAT, MT_, false>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls);            \
+    } while (0)
+    if (mt == 1) SD_WIDE_MT(1);
+    else if (mt == 2) SD_WIDE_MT(2);
+    else if (mt == 3) SD_WIDE_MT(3);
+    else SD_WIDE_MT(4);
+#undef SD_WIDE_MT
+    return hipGetLastError();
+}
+
 int g_force_splits[3] = {0, 0, 0}; // [mode] -> K splits (0 = automatic); a tuning knob for sweeps
+
+// K splits of the row-blocked kernel.  Measured at M = 192: a block costs about five K steps of fixed time, so one round
+// of blocks with the K range cut as finely as that allows beats several rounds of shorter blocks.
+static int tile_ks(int mode, int M, int N, int K, int n_per_seg)
+{
+    if (mode == GEMM_SWIGLU) return 1;
+    const TileShape t = tile_shape(mode, M, N, n_per_seg, K);
+    int kps, ny;
+    split_geometry(K, g_force_splits[mode] > 0 ? g_force_splits[mode] : t.cols ? tile_splits(t.ncol, t.nmb, t.slots, K / 128) : 1, &kps, &ny);
+    return ny;
+}
 
 // Number of K splits the launcher will use for this shape (the caller sizes and reduces the partials).
 int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg)
@@ -653,14 +884,14 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg)
     }
     const int steps = K / 128;
     int ks;
+    const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0);
+    if (wp.nw) return wp.ks;
     if (M <= 32) { // K-split kernel: 32 columns per block, each wave at least 2 steps
         const int blocks = N / 32;
         ks = steps >= 16 ? 2 : 1; // measured: two half-length blocks per tile stream faster than one
         while (blocks * ks < 256 && ks < 8 && steps / (ks * 2) >= 4) ks *= 2;
-    } else { // row-blocked kernel.  Measured at M = 192: a block costs about five K steps of fixed time, so one
-             // round of blocks with the K range cut as finely as that allows beats several rounds of shorter blocks
-        const TileShape t = tile_shape(mode, M, N, n_per_seg, K);
-        ks = t.cols ? tile_splits(t.ncol, t.nmb, t.slots, steps) : 1;
+    } else {
+        ks = tile_ks(mode, M, N, K, n_per_seg);
     }
     split_geometry(K, ks, &kps, &ny);
     return ny;
@@ -672,7 +903,7 @@ int gemm_tile_plan(int mode, int M, int N, int K, int n_per_seg, int plan[6])
     if (M <= 32 || K < 128 || K % 128 != 0 || (mode != GEMM_STORE && mode != GEMM_SWIGLU)) return -1;
     const TileShape t = tile_shape(mode, M, N, n_per_seg, K);
     if (!t.cols) return -1;
-    const int ks = gemm_skinny_splits(mode, M, N, K, n_per_seg);
+    const int ks = tile_ks(mode, M, N, K, n_per_seg);
     plan[0] = t.cols;
     plan[1] = t.bm;
     plan[2] = t.ncol;
@@ -707,6 +938,15 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
     if (mode == GEMM_SWIGLU && (!c_av.sm || (c_av.plane & 7) || N % 128 != 0 || ((uintptr_t)Cact & 15))) return hipErrorNotSupported;
     const uint16_t *a = (const uint16_t *)A;
     uint16_t *ca = (uint16_t *)Cact;
+    if (M > 8 && !folded) {
+        const WidePlan wp = wide_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
+        if (wp.nw) {
+            const LmStats lsk = mode == GEMM_STORE && wp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
+            if (ls_done && lsk.p) *ls_done = 1;
+            if (mode == GEMM_SWIGLU) return wide_launch<2>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
+            return wide_launch<1>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
+        }
+    }
     if (M > 32) { // row-blocked
         if (mode == GEMM_SWIGLU) return tile_launch<GEMM_SWIGLU>(s, a, a_av, w, M, N, K, 1, C, 0, ca, c_av);
         return tile_launch<GEMM_STORE>(s, a, a_av, w, M, N, K, splits, C, c_split_stride, ca, c_av);

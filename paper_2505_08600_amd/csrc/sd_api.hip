@@ -112,8 +112,8 @@ extern "C" int sd_set_option(const char *name, int32_t value)
         g_force_tile_cols = value;
         return SD_OK;
     }
-    if (!strcmp(name, "norm_fold")) { // add + RMSNorm split between producer and consumer GEMM: 0 or 1 = wherever the shapes
-                                      // allow (the default), 2 = never
+    if (!strcmp(name, "norm_fold")) { // add + RMSNorm split between producer and consumer GEMM: 0 = where the shapes allow
+                                      // and it pays (the default), 1 = wherever the shapes allow, 2 = never
         if (value < 0 || value > 2) return sd_fail(SD_EINVAL, "sd_set_option: norm_fold is 0, 1 or 2");
         g_norm_fold = value;
         return SD_OK;
@@ -806,8 +806,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     hipError_t ge;
     // Few rows (the verify pass of a few sequences, draft tokens): the two add + RMSNorm launches of a layer are
     // split between the projection before them and the GEMM after them (NormFold) - seven dependent launches
-    // per layer become five.  Needs every GEMM of the forward on the few-row kernels.
+    // per layer become five.  Needs every GEMM of the forward on the few-row kernels, and rows few enough (gemm_normfold_pays).
     const bool fold = cf.dtype == SD_BF16 && !(g_force_generic & (1 | 16)) && g_norm_fold != 2 && G == 1 && M <= 32 &&
+                      (g_norm_fold == 1 || gemm_normfold_pays(M, d, F)) &&
                       m->lora_n == 0 && m->tiled_dd && m->tiled_fd && m->tiled_df && (!want_logits || m->tiled_lm) &&
                       d % 128 == 0 && F % 128 == 0 && V % 16 == 0 && d / 16 <= SD_NORMFOLD_MAX_BLOCKS &&
                       cf.n_layers >= 1;

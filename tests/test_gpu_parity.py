@@ -268,6 +268,63 @@ def test_small_bf16_row_blocked_gemm_block_widths_match_reference_kernels(cols, 
     gt.close()
 
 
+@pytest.mark.parametrize("d,F,V", [(384, 640, 2064), (512, 1408, 2080)])
+def test_wide_few_row_gemm_matches_reference_kernels(d, F, V):
+    """9 to 64 rows take the wide few-row GEMM: the edges of its 16-row tiles, K ranges of fewer steps than a block has
+    waves (3 steps) and not a multiple of them (11), numbers of weight tiles that no block shape divides (2064 / 16 = 129
+    logits tiles, 40 and 88 gate/up pairs).  Same caches on both sides; what differs is the order of fp32 sums (1e-6 of a
+    sum) and, where that moves a K or V row across a rounding boundary, one bf16 step (2^-9) of single cache elements."""
+    import dataclasses
+    st_ = dataclasses.replace(dg.SHAPES["small_target_bf16"], n_layers=1, d_model=d, n_heads=d // 128, d_ffn=F, vocab=V, name=f"wide_{d}")
+    gt = api.Model(st_, dg.make_weights(st_, 91, BF16_LM_SCALE), max_rows=64, max_pos=256)
+    api.set_option("norm_fold", 2)
+    try:
+        for B, gamma in ((3, 2), (4, 3), (17, 0), (8, 3), (11, 2), (8, 4), (41, 0), (8, 5), (7, 6), (8, 7)):
+            M = B * (gamma + 1)
+            _say(f"wide GEMM d={d} F={F} V={V} rows={M}")
+            lens = dg.make_prompt_lengths(91 + M, B, 5, 60)
+            prompts = [[int(t) for t in dg.make_prompt(91, b, int(lens[b]), V)] for b in range(B)]
+            ctx = api.Context([int(l) + 16 for l in lens])
+            ctx.attach(gt)
+            H.gpu_prefill(ctx, [gt], prompts)
+            cand = H.dev(dg.make_prompt(92, B, max(1, B * gamma), V)[:B * gamma].reshape(B, gamma).astype(np.int32))
+            na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+            outs = []
+            for force in (0, 1):
+                api.set_option("force_generic", force)
+                api.sd_verify(gt, ctx, None, B, gamma, 0.0, cand if gamma else None, None, None, na, nx, commit=False)
+                torch.cuda.synchronize()
+                outs.append((gt.last_logits().cpu().numpy(), gt.debug_read("act", M)))
+                api.set_option("force_generic", 0)
+                for b in range(B):
+                    ctx.truncate(gt, b, int(lens[b]) - 1)
+            ctx.close()
+            for got, ref in zip(*outs):
+                assert np.isfinite(got).all() and np.abs(got - ref).max() < 5e-4 * np.abs(ref).max(), (M, np.abs(got - ref).max() / np.abs(ref).max())
+        if V % 32 == 0:   # the LM head's softmax partials, against the sampler that reads the whole row
+            B, gamma = 12, 2
+            prompts = [[int(t) for t in dg.make_prompt(93, b, 9 + b, V)] for b in range(B)]
+            u = H.dev(np.stack([dg.make_uniforms(93, dg.DRAFT_STREAM, b, 0, gamma) for b in range(B)]))
+            outs = []
+            for force in (0, 4):
+                api.set_option("force_generic", force)
+                ctx = api.Context([64] * B)
+                ctx.attach(gt)
+                H.gpu_prefill(ctx, [gt], prompts)
+                cand = torch.zeros((B, gamma), dtype=torch.int32, device="cuda")
+                q = torch.zeros((B, gamma, V), device="cuda")
+                api.sd_draft(gt, ctx, None, B, gamma, 0.8, u, cand, q)
+                ctx.sync()
+                outs.append((cand.cpu().numpy(), q.cpu().numpy()))
+                ctx.close()
+                api.set_option("force_generic", 0)
+            assert np.array_equal(outs[0][0], outs[1][0]) and np.abs(outs[0][1] - outs[1][1]).max() < 1e-6
+    finally:
+        api.set_option("force_generic", 0)
+        api.set_option("norm_fold", 0)
+    gt.close()
+
+
 @pytest.mark.parametrize("waves", [4, 8])
 def test_small_bf16_both_fused_attention_block_shapes_match_reference_kernels(waves):
     """The fused attention kernel runs as 8-wave blocks (few sequences) or 4-wave blocks (many); the
