@@ -694,92 +694,109 @@ hipError_t launch_add_rmsnorm(hipStream_t s, int dtype, float *x, const float *p
 }
 
 // ---------------------------------------------------------------- low-rank adapters
-// One block per row.  The row (hi + lo summed) goes to LDS; the 4 waves share the n_proj * rank dot
-// products with the A factors; every thread then produces outputs n = tid, tid + 256, ...
+// Block (row, projection, part of LORA_PART outputs).  Bound: latency - a row reads 2 * rank * (K + N) floats of factors
+// per projection (49 KB at rank 8, width 768) and multiplies each once - so the block is laid out to have everything in
+// flight at once: the rows of B that its threads will need go out first, then wave w takes the dot products
+// w, w + LORA_WAVES, ... with A, row of X and row of A straight into registers, and one barrier later every thread
+// finishes its outputs from registers.  A grid dimension per projection puts three times the blocks on the chip.
+// RQ = rank / 4 reads the rows of B (rank contiguous floats) as 16-byte vectors; 0 takes any rank, element by element.
+// Measured at width 768, rank 8: 4.6 us for 32 or 64 rows and one or three projections (18.9 us with one block of 256
+// threads per row, all projections in it, the factors fetched after the dot products); below that the launch itself remains.
 #define LORA_MAX_RANK 16
 #define LORA_MAX_K 8192
+#define LORA_WAVES 8
+#define LORA_OUT 2 // outputs per thread
+#define LORA_PART (LORA_OUT * LORA_WAVES * 64)
 struct LoraPtrs {
     const float *a[3], *b[3];
 };
-template <typename T>
-__global__ __launch_bounds__(256) void lora_delta_kernel(const T *X, ActView x_av, int K, int N, int n_proj, PlanView pv,
-                                                         const int32_t *adapter, int n_adapters, int rank, float scale,
-                                                         LoraPtrs lp, float *out, int accumulate)
+__device__ __forceinline__ float4 load_act4(const float *b, size_t i, size_t) { return *(const float4 *)(b + i); }
+__device__ __forceinline__ float4 load_act4(const bf16_t *b, size_t i, size_t plane)
 {
-    __shared__ __attribute__((aligned(16))) float sx[LORA_MAX_K];
-    __shared__ float st[3][LORA_MAX_RANK];
-    const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int a = pv.row_valid[r] ? adapter[pv.row_b[r]] : -1;
-    if (a >= n_adapters) a = -1;
-    float *orow = out + (size_t)r * n_proj * N;
-    if (a < 0) {
-        if (!accumulate)
-            for (int n = threadIdx.x; n < n_proj * N; n += 256) orow[n] = 0.f;
+    const uint2 h = *(const uint2 *)(b + i), l = *(const uint2 *)(b + i + plane);
+    return make_float4(__uint_as_float(h.x << 16) + __uint_as_float(l.x << 16),
+                       __uint_as_float(h.x & 0xffff0000u) + __uint_as_float(l.x & 0xffff0000u),
+                       __uint_as_float(h.y << 16) + __uint_as_float(l.y << 16),
+                       __uint_as_float(h.y & 0xffff0000u) + __uint_as_float(l.y & 0xffff0000u));
+}
+template <typename T, int RQ>
+__global__ __launch_bounds__(LORA_WAVES * 64) void lora_delta_kernel(const T *X, ActView x_av, int K, int N, int n_proj, PlanView pv,
+                                                                     const int32_t *adapter, int n_adapters, int rank, float scale,
+                                                                     LoraPtrs lp, float *out, int accumulate)
+{
+    constexpr int THREADS = LORA_WAVES * 64, NB = RQ > 0 ? RQ * 4 : LORA_MAX_RANK;
+    __shared__ float st[LORA_MAX_RANK];
+    const int r = blockIdx.x, p = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float *Ap = p == 0 ? lp.a[0] : p == 1 ? lp.a[1] : lp.a[2], *Bp = p == 0 ? lp.b[0] : p == 1 ? lp.b[1] : lp.b[2];
+    const int valid = pv.row_valid[r];
+    int a = adapter[pv.row_b[r]]; // (row_b of an unused row is in range too)
+    if (!valid || a >= n_adapters) a = -1;
+    float *orow = out + (size_t)r * n_proj * N + (size_t)p * N;
+    const int n0 = blockIdx.z * LORA_PART + threadIdx.x;
+    if (a < 0 || !Ap || !Bp) { // (uniform) no update for this row and projection
+        if (!accumulate) {
+#pragma unroll
+            for (int o = 0; o < LORA_OUT; o++)
+                if (n0 + o * THREADS < N) orow[n0 + o * THREADS] = 0.f;
+        }
         return;
     }
-    for (int k = threadIdx.x; k < K; k += 256) sx[k] = load_act(X, act_index(x_av, r, k, K), x_av.plane);
-    __syncthreads();
-    // wave w takes the dot products pj = w, w + 4, ...: six at a time, so that their loads are in flight together
-    constexpr int PJ = 6;
-    for (int pj0 = wave; pj0 < n_proj * rank; pj0 += 4 * PJ) {
-        const float *arow[PJ];
-        float acc[PJ];
+    float bv[LORA_OUT][NB], old[LORA_OUT];
 #pragma unroll
-        for (int u = 0; u < PJ; u++) {
-            const int pj = pj0 + 4 * u;
-            const int p = pj < n_proj * rank ? pj / rank : 0, j = pj % rank;
-            arow[u] = pj < n_proj * rank && lp.a[p] ? lp.a[p] + ((size_t)a * rank + j) * K : nullptr;
-            acc[u] = 0.f;
-        }
-#pragma unroll 2
-        for (int k = 4 * lane; k < K; k += 256) { // 16 bytes per lane and load (K is a multiple of 4)
-            const float4 xv = *(const float4 *)&sx[k];
+    for (int o = 0; o < LORA_OUT; o++) {
+        const int n = min(n0 + o * THREADS, N - 1); // (outputs past the end re-read the last one; never stored)
+        old[o] = accumulate ? orow[n] : 0.f;
+        const float *brow = Bp + ((size_t)a * N + n) * rank;
+        if (RQ > 0) {
 #pragma unroll
-            for (int u = 0; u < PJ; u++)
-                if (arow[u]) {
-                    const float4 av = *(const float4 *)(arow[u] + k);
-                    acc[u] += av.x * xv.x + av.y * xv.y + av.z * xv.z + av.w * xv.w;
-                }
-        }
-#pragma unroll
-        for (int u = 0; u < PJ; u++) {
-            float v = acc[u];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            const int pj = pj0 + 4 * u;
-            if (lane == 0 && pj < n_proj * rank) st[pj / rank][pj % rank] = v;
-        }
-    }
-    __syncthreads();
-    // outputs n = tid, tid + 256, ...: four at a time (independent loads of the B rows)
-    const int n_out = n_proj * N;
-    for (int n0 = threadIdx.x; n0 < n_out; n0 += 4 * 256) {
-        float acc[4], old[4];
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int n = n0 + 256 * u;
-            acc[u] = 0.f;
-            old[u] = 0.f;
-            if (n < n_out) {
-                const int p = n / N, nn = n % N;
-                if (accumulate) old[u] = orow[n];
-                if (lp.a[p] && lp.b[p]) {
-                    const float *brow = lp.b[p] + ((size_t)a * N + nn) * rank;
-                    float bv[LORA_MAX_RANK]; // all loads of the row go out before the first is used
-#pragma unroll
-                    for (int j = 0; j < LORA_MAX_RANK; j++) bv[j] = j < rank ? brow[j] : 0.f;
-#pragma unroll
-                    for (int j = 0; j < LORA_MAX_RANK; j++)
-                        if (j < rank) acc[u] += bv[j] * st[p][j];
-                }
+            for (int i = 0; i < RQ; i++) {
+                const float4 v = *(const float4 *)(brow + 4 * i);
+                bv[o][4 * i] = v.x, bv[o][4 * i + 1] = v.y, bv[o][4 * i + 2] = v.z, bv[o][4 * i + 3] = v.w;
             }
-        }
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int n = n0 + 256 * u;
-            if (n < n_out) orow[n] = old[u] + scale * acc[u];
+            for (int i = 0; i < NB; i++) bv[o][i] = i < rank ? brow[i] : 0.f;
         }
     }
+    for (int j = wave; j < rank; j += LORA_WAVES) {
+        const float *arow = Ap + ((size_t)a * rank + j) * K;
+        float acc = 0.f;
+#pragma unroll 4
+        for (int k = 4 * lane; k < K; k += 256) { // 16 bytes per lane and load (K is a multiple of 4)
+            const float4 xv = load_act4(X, act_index(x_av, r, k, K), x_av.plane), av = *(const float4 *)(arow + k);
+            acc += av.x * xv.x + av.y * xv.y + av.z * xv.z + av.w * xv.w;
+        }
+        acc = wave_sum_dpp(acc);
+        if (lane == 0) st[j] = acc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < LORA_OUT; o++) {
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+            if (RQ > 0 || i < rank) acc += bv[o][i] * st[i];
+        if (n0 + o * THREADS < N) orow[n0 + o * THREADS] = old[o] + scale * acc;
+    }
+}
+
+template <typename T>
+static hipError_t lora_launch(hipStream_t s, const T *X, ActView x_av, int M, int K, int N, int n_proj, PlanView pv, const int32_t *adapter,
+                              int n_adapters, int rank, float scale, LoraPtrs lp, float *out, int accumulate)
+{
+    bool vec = rank % 4 == 0;
+    for (int p = 0; p < n_proj; p++)
+        if ((uintptr_t)lp.b[p] & 15) vec = false;
+    const dim3 grid(M, n_proj, (N + LORA_PART - 1) / LORA_PART), block(LORA_WAVES * 64);
+#define SD_LORA(RQ_) \
+    hipLaunchKernelGGL((lora_delta_kernel<T, RQ_>), grid, block, 0, s, X, x_av, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate)
+    if (!vec) SD_LORA(0);
+    else if (rank == 4) SD_LORA(1);
+    else if (rank == 8) SD_LORA(2);
+    else if (rank == 12) SD_LORA(3);
+    else SD_LORA(4);
+#undef SD_LORA
+    return hipGetLastError();
 }
 
 hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_av, int M, int K, int N, int n_proj,
@@ -791,12 +808,8 @@ hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_
     LoraPtrs lp;
     for (int p = 0; p < 3; p++) lp.a[p] = p < n_proj ? A[p] : nullptr, lp.b[p] = p < n_proj ? B[p] : nullptr;
     if (dtype == SD_BF16)
-        hipLaunchKernelGGL(lora_delta_kernel<bf16_t>, dim3(M), dim3(256), 0, s, (const bf16_t *)X, x_av, K, N, n_proj, pv,
-                           adapter, n_adapters, rank, scale, lp, out, accumulate);
-    else
-        hipLaunchKernelGGL(lora_delta_kernel<float>, dim3(M), dim3(256), 0, s, (const float *)X, x_av, K, N, n_proj, pv,
-                           adapter, n_adapters, rank, scale, lp, out, accumulate);
-    return hipGetLastError();
+        return lora_launch(s, (const bf16_t *)X, x_av, M, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate);
+    return lora_launch(s, (const float *)X, x_av, M, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate);
 }
 
 template <typename T>

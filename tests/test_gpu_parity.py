@@ -1228,6 +1228,43 @@ def test_lora_adapters_chosen_per_sequence_match_oracle(shape_name, tol):
     gm.close()
 
 
+@pytest.mark.parametrize("rank", [1, 4, 6, 12, 16])
+@pytest.mark.parametrize("d,dtype,tol", [(256, dg.BF16, 2e-2), (1280, dg.FP32, 1e-4)])
+def test_lora_ranks_and_widths_match_oracle(d, dtype, tol, rank):
+    """Low-rank updates of every rank class (16-byte rows of B: 4, 12, 16; any other rank) at a width of a quarter block
+    part and one of more than a part (1280 outputs in parts of 1024), with rows that have no adapter between the others:
+    logits of a verify pass against the oracle run per sequence."""
+    _say(f"LoRA rank {rank}, width {d}, dtype {dtype}")
+    st_ = dg.ModelShape("lora_t", 1, d, d // 64, 64, 384, 512, dtype)
+    w = dg.make_weights(st_, 97, BF16_LM_SCALE if dtype == dg.BF16 else 20.0)
+    lora = dg.make_lora(st_, 98, n_adapters=2, rank=rank, std_a=0.05, std_b=0.05)
+    gamma, V, scale = 2, st_.vocab, 1.5
+    om = oracle.OracleModel(st_, w)
+    om.set_lora(lora, scale)
+    gm = api.Model(st_, w, max_rows=32, max_pos=128)
+    gm.set_lora(lora, scale)
+    adapters, lens = [1, -1, 0], [9, 5, 18]
+    B = len(lens)
+    prompts = [[int(t) for t in dg.make_prompt(97, b, n, V)] for b, n in enumerate(lens)]
+    ctx = api.Context([n + 16 for n in lens])
+    ctx.attach(gm)
+    ctx.set_adapters(gm, adapters)
+    H.gpu_prefill(ctx, [gm], prompts)
+    cand = np.stack([[int(t) for t in dg.make_prompt(99, b, gamma, V)] for b in range(B)]).astype(np.int32)
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_verify(gm, ctx, None, B, gamma, 0.0, H.dev(cand), None, None, na, nx, commit=False)
+    lg = gm.last_logits().cpu().numpy().reshape(B, gamma + 1, V)
+    for b in range(B):
+        seq = om.new_seq(lens[b] + 16, adapters[b])
+        oracle.prefill(seq, prompts[b])
+        u = dg.make_uniforms(97, dg.VERIFY_STREAM, b, 0, gamma + 1)
+        ref = seq.verify(prompts[b], gamma, 0.0, cand[b], None, u, want_logits=True)[3].reshape(gamma + 1, V)
+        err = np.abs(lg[b] - ref).max() / np.abs(ref).max()
+        assert err < tol, (b, err)
+    ctx.close()
+    gm.close()
+
+
 def test_online_path_classifier_routes_to_adapters_of_one_base_draft():
     """The whole online path in its shared-base form (Sections 2.3, 2.4): the prompt classifier labels each
     prompt from its token ids, the label names the low-rank adapter of the one base draft (the last class
