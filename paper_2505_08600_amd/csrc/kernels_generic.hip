@@ -29,6 +29,8 @@ __device__ __forceinline__ float wave_max(float v)
 // of LDS shuffles, combine the 16 waves' partial results one entry per lane, and use barriers that wait
 // for LDS traffic only, so that global stores issued before a reduction (the updated residual row, the q
 // row a sampler has just written) drain behind it instead of stalling its first barrier.
+// nothing is moved across it by the scheduler
+#define SD_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ int row16_max(int v)
 {
@@ -1327,7 +1329,7 @@ __device__ __forceinline__ void row_load(const float *row, int V, float fill, Ro
 // max, lowest-index argmax and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
 // -3e38 past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
 // e(x) / z need no second exponential.
-__device__ void row_stats_regs(RowRegs &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
+__device__ __forceinline__ void row_stats_regs(RowRegs &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
 {
     float bv = -3.0e38f;
     int bi = 0x7fffffff;
@@ -1364,7 +1366,7 @@ __device__ void row_stats_regs(RowRegs &r, float invT, FastScratch *fs, float &m
 }
 
 // Inverse-CDF pick (same rule as block_pick_cdf) over weights held in registers.
-__device__ int pick_regs(const RowRegs &w, int V, float u, FastScratch *fs, float *total_out)
+__device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastScratch *fs, float *total_out)
 {
     // Index order is (segment it, thread t, component c).  Segment totals are the waves' totals added as a
     // tree; every thread works out the total Z, the segment holding u * Z and the sum before it for itself
@@ -1418,8 +1420,13 @@ __device__ int pick_regs(const RowRegs &w, int V, float u, FastScratch *fs, floa
     if (sit >= 0) { // uniform over the block
         float4 f = w.f[0];
 #pragma unroll
-        for (int it = 1; it < ROW_NSEG; it++)
-            if (it == sit) f = w.f[it];
+        for (int it = 1; it < ROW_NSEG; it++) { // (component selects: an indexed copy would put the whole row into scratch memory)
+            const float4 c = w.f[it];
+            f.x = it == sit ? c.x : f.x;
+            f.y = it == sit ? c.y : f.y;
+            f.z = it == sit ? c.z : f.z;
+            f.w = it == sit ? c.w : f.w;
+        }
         const int v = sit * ROW_THREADS + threadIdx.x;
         const float l4 = ((f.x + f.y) + f.z) + f.w;
         const float inc = wave_incl_scan_dpp(l4, lane);
@@ -1820,29 +1827,36 @@ hipError_t launch_draft_sample(hipStream_t s, const float *logits, int n_seq, in
 }
 
 // ---------------------------------------------------------------- commit (KV rollback)
+// (one thread; every value it updates is read before the first store, so that the reads are in flight together)
 __device__ void commit_one(CtxView cv, int b, int gamma, const int32_t *cand_j, int n_acc, int next_tok)
 {
-    int n = cv.ntok[b];
-    int64_t off = cv.off[b];
-    int cap = cv.cap[b];
+    const int n = cv.ntok[b], cap = cv.cap[b];
+    const int64_t off = cv.off[b];
+    const int acc0 = cv.pol[b], exam0 = cv.pol[cv.B + b];
+    int kv[SD_MAX_SLOTS], c[SD_MAX_GAMMA];
+#pragma unroll
+    for (int sl = 0; sl < SD_MAX_SLOTS; sl++) kv[sl] = sl < cv.n_slots ? cv.kvlen[(size_t)sl * cv.B + b] : 0;
     if (n_acc < 0) n_acc = 0;
     if (n_acc > gamma) n_acc = gamma;
+#pragma unroll
+    for (int i = 0; i < SD_MAX_GAMMA; i++) c[i] = i < n_acc ? cand_j[i] : 0;
     if (n + n_acc + 1 > cap) {
         atomicOr(cv.status, 1);
         return;
     }
-    for (int i = 0; i < n_acc; i++) cv.tokens[off + n + i] = cand_j[i];
+#pragma unroll
+    for (int i = 0; i < SD_MAX_GAMMA; i++)
+        if (i < n_acc) cv.tokens[off + n + i] = c[i];
     cv.tokens[off + n + n_acc] = next_tok;
     // running estimate of Equation 1's alpha: accepted over examined candidates (a step that rejects at
     // position k has examined k + 1 of them)
-    cv.pol[b] += n_acc;
-    cv.pol[cv.B + b] += n_acc < gamma ? n_acc + 1 : gamma;
-    int nn = n + n_acc + 1;
+    cv.pol[b] = acc0 + n_acc;
+    cv.pol[cv.B + b] = exam0 + (n_acc < gamma ? n_acc + 1 : gamma);
+    const int nn = n + n_acc + 1;
     cv.ntok[b] = nn;
-    for (int sl = 0; sl < cv.n_slots; sl++) {
-        int *kv = cv.kvlen + (size_t)sl * cv.B + b;
-        if (*kv > nn - 1) *kv = nn - 1;
-    }
+#pragma unroll
+    for (int sl = 0; sl < SD_MAX_SLOTS; sl++)
+        if (sl < cv.n_slots && kv[sl] > nn - 1) cv.kvlen[(size_t)sl * cv.B + b] = nn - 1;
 }
 
 __global__ void commit_kernel(CtxView cv, const int32_t *seq_ids, int n_seq, int gamma, const int32_t *cand,
@@ -2017,14 +2031,14 @@ struct DrawWeights {
     }
 };
 
-// T > 0.  Block (s, j): mass of slice s of sequence j's deciding row, left in the argmax entry of its row s.
+// T > 0.  Block j * (gamma + 1) + s: mass of slice s of sequence j's deciding row, left in the argmax entry of its row s.
 __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logits, float *stats, int gamma, int V, float T,
                                                                const int32_t *cand, const float *q, const float *u,
                                                                const int32_t *seq_ids, int32_t *n_acc_out, CtxView cv)
 {
     __shared__ int s_ok[SD_MAX_GAMMA];
     __shared__ float red[32];
-    const int j = blockIdx.y, s = blockIdx.x, n_slices = gridDim.x, stride_g = gamma;
+    const int n_slices = gamma + 1, j = blockIdx.x / n_slices, s = blockIdx.x % n_slices, stride_g = gamma;
     {   // with per-sequence candidate counts this sequence has gj <= gamma candidates (and gj + 1 live rows)
         const int bb = seq_ids ? seq_ids[j] : j;
         if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
@@ -2110,91 +2124,130 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
     }
 }
 
-// Rows that fit a block's registers, in two launches.  verify_stats_kernel: one block per logits row
-// (n_seq * (gamma + 1) blocks, so the exponentials of the rows run on different compute units), each row
-// read once into registers; writes max, z and argmax per row.  verify_decide_kernel: one block per
-// sequence; the gamma acceptance tests are evaluated by gamma threads in parallel and scanned by
-// thread 0, then the deciding row is read once more for the resample.
-__global__ __launch_bounds__(ROW_THREADS) void verify_stats_kernel(const float *logits, int V, float T, float *stats)
+// Rows that fit a block's registers, in two launches.  verify_rows_kernel: one block per logits row (n_seq * (gamma + 1)
+// blocks), which reads the row once into registers and settles everything that row could decide: its acceptance test
+// and - if its candidate is rejected, or it is the row behind the last candidate - the token that would be drawn there,
+// from registers it holds anyway.  Later rows of a sequence do that in vain; they run beside the others.  The verdicts
+// take the three words per row of the caller's workspace: (accepted, token drawn, argmax).  verify_finish_kernel: one
+// wave per sequence reads its verdicts: accepted prefix, token of the row behind it, commit.
+// Bound: latency of one row's chain (load, max, exponentials, sum, q, scan).  Measured, 32000 columns (before: row
+// statistics in one launch, the decision from a second reading of the deciding row in another): 6 rows 8.1 + 17.9 ->
+// 14.8 + 3.9 us, 192 rows 10.2 + 25.1 -> 21.1 + 4.1, 576 rows 23.2 + 26.7 -> 40.9 + 4.1.
+// EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
+// (6 rows: 15.9 -> 14.8 us); with more rows than units two blocks share one, q is read only where it is needed.
+template <bool EARLY_Q>
+__global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
+                                                                  const float *q, const float *u, const int32_t *seq_ids,
+                                                                  CtxView cv, float *stats)
 {
     __shared__ FastScratch fs;
+    __shared__ PickScratch ps;
+    const int stride_g = gamma; // row slots of the call: strides of cand, q and u
+    const int j = blockIdx.x / (gamma + 1), i = blockIdx.x % (gamma + 1);
+    const int bb = seq_ids ? seq_ids[j] : j;
+    // with per-sequence candidate counts this sequence has gj <= gamma candidates (and gj + 1 live rows)
+    if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
+    const float *row = logits + ((size_t)j * (stride_g + 1) + i) * V;
+    float *st = stats + ((size_t)j * (stride_g + 1) + i) * 3;
+    if (i > gamma) return; // (uniform) not a live row
     RowRegs r;
-    row_load(logits + (size_t)blockIdx.x * V, V, -3.0e38f, r);
+    row_load(row, V, -3.0e38f, r);
+    const int c = i < gamma ? cand[(size_t)j * stride_g + i] : -1;
+    const bool c_in = c >= 0 && c < V;
+    float lc = 0.f, qc = 1.f, ui = 0.f, uu = 0.f;
+    const float *qrow = q + ((size_t)j * stride_g + i) * V;
+    if (T > 0.f) {
+        ui = u[(size_t)j * (stride_g + 1) + i];
+        uu = u[(size_t)j * (stride_g + 1) + gamma];
+        if (c_in) {
+            lc = row[c];
+            qc = qrow[c];
+        }
+    }
+    const int nvec = (V + 3) / 4;
+    RowRegs qr;
+    if (EARLY_Q && T > 0.f && i < gamma) row_load(qrow, V, 0.f, qr);
+    const float invT = T > 0.f ? 1.0f / T : 0.f;
     float mx, z;
     int am;
-    row_stats_regs(r, T > 0.f ? 1.0f / T : 0.f, &fs, mx, am, z);
+    row_stats_regs(r, invT, &fs, mx, am, z);
+    // candidate i is accepted iff u_i < p_i / q_i (T > 0) or it is the row's argmax (T == 0)
+    bool ok = false;
+    int pick = am;
+    if (T == 0.f) {
+        ok = i < gamma && c == am;
+    } else {
+        if (c_in) ok = ui < expf((lc - mx) * invT) / z / fmaxf(qc, 1.17549435e-38f);
+        if (!ok) { // (uniform) the draw this row would make: from max(0, p - q), behind the last candidate from p
+            const float invZ = 1.0f / z;
+            row_scale(r, invZ);
+            if (i < gamma) {
+#pragma unroll
+                for (int h = 0; h < ROW_NSEG; h += 4) { // (four segments of q at a time: registers for two blocks per unit)
+                    float4 w[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        const int v = (h + k) * ROW_THREADS + threadIdx.x;
+                        if (EARLY_Q) w[k] = qr.f[h + k];
+                        else w[k] = v < nvec ? load4_guard(qrow, v, V, 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        r.f[h + k].x = fmaxf(r.f[h + k].x - w[k].x, 0.f);
+                        r.f[h + k].y = fmaxf(r.f[h + k].y - w[k].y, 0.f);
+                        r.f[h + k].z = fmaxf(r.f[h + k].z - w[k].z, 0.f);
+                        r.f[h + k].w = fmaxf(r.f[h + k].w - w[k].w, 0.f);
+                    }
+                    if (!EARLY_Q) SD_SCHED_FENCE();
+                }
+            }
+            float mass;
+            pick = pick_regs(r, V, uu, &fs, &mass);
+            if (i < gamma && !(mass > 0.f)) { // (uniform) numerically empty residual: draw from p
+                auto p_of = [&](int v) {
+                    float4 f = load4_guard(row, v, V, -3.0e38f);
+                    f.x = expf((f.x - mx) * invT) * invZ;
+                    f.y = expf((f.y - mx) * invT) * invZ;
+                    f.z = expf((f.z - mx) * invT) * invZ;
+                    f.w = expf((f.w - mx) * invT) * invZ;
+                    return f;
+                };
+                pick = block_pick_cdf(p_of, V, uu, &ps, nullptr);
+            }
+        }
+    }
     if (threadIdx.x == 0) {
-        stats[3 * blockIdx.x] = mx;
-        stats[3 * blockIdx.x + 1] = z;
-        stats[3 * blockIdx.x + 2] = __int_as_float(am);
+        st[0] = __int_as_float(ok ? 1 : 0);
+        st[1] = __int_as_float(pick);
+        st[2] = __int_as_float(am);
     }
 }
 
-__global__ __launch_bounds__(ROW_THREADS) void verify_decide_kernel(const float *logits, const float *stats, int gamma,
-                                                                     int V, float T, const int32_t *cand,
-                                                                     const float *q, const float *u,
-                                                                     const int32_t *seq_ids, int32_t *n_acc_out,
-                                                                     int32_t *next_out, int commit, CtxView cv)
+// One wave per sequence.  T > 0: the verdicts of verify_rows_kernel; T == 0: the rows' argmax entries, whichever kernel
+// left them.
+__global__ __launch_bounds__(WAVE) void verify_finish_kernel(const float *stats, int gamma, float T, const int32_t *cand,
+                                                             const int32_t *seq_ids, int32_t *n_acc_out, int32_t *next_out,
+                                                             int commit, CtxView cv)
 {
-    __shared__ FastScratch fs;
-    __shared__ int s_ok[SD_MAX_GAMMA];
-    __shared__ float s_zr;
-    const int j = blockIdx.x;
-    const float *rows = logits + (size_t)j * (gamma + 1) * V;
-    const float *st = stats + (size_t)j * (gamma + 1) * 3;
-    const int32_t *cj = cand + (size_t)j * gamma;
-    const float invT = T > 0.f ? 1.0f / T : 0.f;
-    const int stride_g = gamma; // row slots of the call: strides of cand, q and u
-    {   // with per-sequence candidate counts this sequence has gj <= gamma candidates (and gj + 1 live rows)
-        const int bb = seq_ids ? seq_ids[j] : j;
-        if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
+    const int j = blockIdx.x, i = threadIdx.x, stride_g = gamma;
+    const int bb = seq_ids ? seq_ids[j] : j;
+    const bool in = bb >= 0 && bb < cv.B;
+    const float *st = stats + (size_t)j * (stride_g + 1) * 3;
+    const int32_t *cj = cand + (size_t)j * stride_g;
+    if (cv.gam && in) gamma = seq_gamma(cv, bb, gamma);
+    int ok = 0, tok = 0;
+    if (i <= gamma) {
+        const int am = __float_as_int(st[3 * i + 2]);
+        tok = T == 0.f ? am : __float_as_int(st[3 * i + 1]);
+        if (i < gamma) ok = T == 0.f ? cj[i] == am : __float_as_int(st[3 * i]) != 0;
     }
-    const int n_acc = accept_scan(rows, st, gamma, stride_g, V, T, invT, cj, q + (size_t)j * stride_g * V,
-                                  u + (size_t)j * (stride_g + 1), s_ok);
-    int next;
-    if (T == 0.f) {
-        next = __float_as_int(st[3 * n_acc + 2]);
-    } else {
-        const float mx = st[3 * n_acc], invZ = 1.0f / st[3 * n_acc + 1];
-        const float uu = u[j * (stride_g + 1) + gamma];
-        RowRegs r;
-        row_load(rows + (size_t)n_acc * V, V, -3.0e38f, r);
-#pragma unroll
-        for (int it = 0; it < ROW_NSEG; it++) {
-            float4 f = r.f[it];
-            f.x = expf((f.x - mx) * invT) * invZ;
-            f.y = expf((f.y - mx) * invT) * invZ;
-            f.z = expf((f.z - mx) * invT) * invZ;
-            f.w = expf((f.w - mx) * invT) * invZ;
-            r.f[it] = f;
-        }
-        bool use_p = n_acc >= gamma;
-        next = 0;
-        if (!use_p) {
-            RowRegs w;
-            row_load(q + ((size_t)j * stride_g + n_acc) * V, V, 0.f, w);
-#pragma unroll
-            for (int it = 0; it < ROW_NSEG; it++) {
-                w.f[it].x = fmaxf(r.f[it].x - w.f[it].x, 0.f);
-                w.f[it].y = fmaxf(r.f[it].y - w.f[it].y, 0.f);
-                w.f[it].z = fmaxf(r.f[it].z - w.f[it].z, 0.f);
-                w.f[it].w = fmaxf(r.f[it].w - w.f[it].w, 0.f);
-            }
-            float zr = 0.f;
-            next = pick_regs(w, V, uu, &fs, &zr);
-            if (threadIdx.x == 0) s_zr = zr;
-            __syncthreads();
-            if (!(s_zr > 0.f)) use_p = true; // numerically empty residual: draw from p
-            __syncthreads();
-        }
-        if (use_p) next = pick_regs(r, V, uu, &fs, nullptr);
-    }
-    if (threadIdx.x == 0) {
+    const int n_acc = __ffsll((unsigned long long)~__ballot(ok)) - 1; // (lane gamma <= SD_MAX_GAMMA always votes 0)
+    const int next = __builtin_amdgcn_readlane(tok, n_acc);
+    if (i == 0) {
         n_acc_out[j] = n_acc;
         next_out[j] = next;
         if (commit) {
-            const int b = seq_ids ? seq_ids[j] : j;
-            if (b >= 0 && b < cv.B) commit_one(cv, b, gamma, cj, n_acc, next);
+            if (in) commit_one(cv, bb, gamma, cj, n_acc, next);
             else atomicOr(cv.status, 4);
         }
     }
@@ -2206,21 +2259,26 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
 {
     const int n_rows = n_seq * (gamma + 1);
     if (V <= ROW_NSEG * ROW_THREADS * 4) {
-        hipLaunchKernelGGL(verify_stats_kernel, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, V, T, stats);
-        hipLaunchKernelGGL(verify_decide_kernel, dim3(n_seq), dim3(ROW_THREADS), 0, s, logits, stats, gamma, V, T, cand, q,
-                           u, seq_ids, n_acc, next_tok, commit, cv);
+        if (n_rows <= 256)
+            hipLaunchKernelGGL(verify_rows_kernel<true>, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, gamma, V, T, cand, q, u, seq_ids,
+                               cv, stats);
+        else
+            hipLaunchKernelGGL(verify_rows_kernel<false>, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, gamma, V, T, cand, q, u, seq_ids,
+                               cv, stats);
+        hipLaunchKernelGGL(verify_finish_kernel, dim3(n_seq), dim3(WAVE), 0, s, stats, gamma, T, cand, seq_ids, n_acc, next_tok, commit,
+                           cv);
         return hipGetLastError();
     }
     if (n_rows >= 512) hipLaunchKernelGGL(verify_stats_wide_kernel<512>, dim3(n_rows), dim3(512), 0, s, logits, V, T, stats);
     else hipLaunchKernelGGL(verify_stats_wide_kernel<1024>, dim3(n_rows), dim3(1024), 0, s, logits, V, T, stats);
     if (T > 0.f) {
-        hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(gamma + 1, n_seq), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
+        hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(n_rows), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
                            u, seq_ids, n_acc, cv);
         hipLaunchKernelGGL(verify_pick_wide_kernel, dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, seq_ids,
                            n_acc, next_tok, commit, cv);
     } else // (greedy: the decision needs the argmax entries only)
-        hipLaunchKernelGGL(verify_decide_kernel, dim3(n_seq), dim3(ROW_THREADS), 0, s, logits, stats, gamma, V, T, cand, q,
-                           u, seq_ids, n_acc, next_tok, commit, cv);
+        hipLaunchKernelGGL(verify_finish_kernel, dim3(n_seq), dim3(WAVE), 0, s, stats, gamma, T, cand, seq_ids, n_acc, next_tok, commit,
+                           cv);
     return hipGetLastError();
 }
 

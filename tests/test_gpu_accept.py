@@ -163,6 +163,55 @@ def test_next_token_for_uniforms_on_the_boundaries_of_the_cdf(V, gamma, n_trials
     print(f"  {B} uniforms, {other} resolved to the neighbouring token", flush=True)
 
 
+def row_verdict_case(V, gamma):
+    """One sequence per place of the first rejection (none for the last); the rows behind it hold candidates that would be
+    accepted, rejected or lie outside the vocabulary.  From gamma 2 on, two sequences reject a row whose q is twice p."""
+    rng = np.random.default_rng(17 + V)
+    B = gamma + 2
+    logits = rng.normal(0, 2, (B, gamma + 1, V)).astype(np.float32)
+    logits[:, :, V // 3] = -np.inf
+    q = np.zeros((B, gamma, V), np.float32)
+    cand = np.zeros((B, gamma), np.int32)
+    u = np.full((B, gamma + 1), 0.25, np.float32)
+    u[:, gamma] = dg.make_uniforms(23, dg.VERIFY_STREAM, 0, 0, B)
+    for b in range(B):
+        for i in range(gamma):
+            p = oracle.softmax_T(logits[b, i], 1.0)
+            c = int(np.argmax(p))
+            q[b, i] = oracle.softmax_T((logits[b, i] + rng.normal(0, 1, V)).astype(np.float32), 1.0)
+            q[b, i, c] = p[c] * np.float32(4.0 if i == b else 2.0)   # accepted below 1/4 or 1/2
+            cand[b, i] = c
+            if i == b:
+                u[b, i] = 0.75
+            elif i > b:
+                cand[b, i] = (c, V, -1)[i % 3]
+                u[b, i] = 0.9 if i % 2 else 0.25
+    expect = [min(b, gamma) for b in range(B)]
+    if gamma >= 2:
+        for b, i in ((gamma, 0), (gamma + 1, 1)):
+            q[b, i] = 2.0 * oracle.softmax_T(logits[b, i], 1.0)
+            u[b, i] = 0.75
+            expect[b] = i
+    return logits, q, cand, u, expect
+
+
+@pytest.mark.parametrize("V,gamma", [(4, 2), (1024, 15), (4100, 1), (32000, 5), (32768, 3)])
+def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
+    """Rows that fit a block's registers: the verdicts of the rows behind the first rejection must not matter, and a
+    rejection without residual mass draws from p."""
+    print(f"row verdicts V={V} gamma={gamma}", flush=True)
+    logits, q, cand, u, expect = row_verdict_case(V, gamma)
+    B = len(expect)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * B * (gamma + 1),), float("nan"), device="cuda")
+    api.sd_accept(dev(logits), gamma, 1.0, dev(cand), dev(q), dev(u), na, nx, ws)
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert na_h.tolist() == expect
+    assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1   # (a uniform next to an edge of the CDF)
+
+
 @pytest.mark.parametrize("V", [1024, 32000, 50000])
 def test_greedy_rows_with_equal_maxima_take_the_lowest_index(V):
     """T = 0: every logits row holds its largest value two to four times, at positions in different threads, waves
