@@ -475,6 +475,93 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const T *A, ActView a
     }
 }
 
+// fp32 models: the same product with 16-byte loads.  One wave per output column and MR rows, lane l takes elements
+// 4 l .. 4 l + 3 of every 256, four such chunks (two where 16 rows fill the registers) in flight at once.
+// Bound: latency of L2 - a wave of the small fp32 shapes reads a few KiB - so what counts is that all its loads are under
+// way before the first is used (the kernel above waits for each 64 elements) and that the rows' sums are finished by
+// one lane each.  Measured at 5 rows: 688 -> 256 with residual 16.2 -> 3.2 us, 256 -> 688 gate and up 13.6 -> 3.9 us,
+// 256 -> 768 10.4 -> 3.2 us; at one row 344 -> 128 6.3 -> 2.6 us.
+// Needs K % 4 == 0 and 16-byte aligned operands (launch_gemm_generic); everything else takes the kernel above.
+#define GF_WAVES 2
+template <int MODE, int MR>
+__global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const float *__restrict__ A, WeightSeg w, int M, int N, int K, float *C,
+                                                                      float *__restrict__ Cact)
+{
+    constexpr int U = MR > 8 ? 2 : 4, NM = MODE == GEMM_SWIGLU ? 2 : 1;
+    const int n = blockIdx.x * GF_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63, m0 = blockIdx.y * MR;
+    if (n >= N) return;
+    const float *W[NM];
+    if (MODE == GEMM_SWIGLU) {
+#pragma unroll
+        for (int c = 0; c < NM; c++) W[c] = (const float *)w.p[c] + (size_t)n * K;
+    } else {
+        const int seg = n / w.n_per_seg;
+        W[0] = (const float *)(seg == 0 ? w.p[0] : seg == 1 ? w.p[1] : w.p[2]) + (size_t)(n - seg * w.n_per_seg) * K;
+    }
+    const float *Ar[MR]; // rows past M re-read the last one; never stored
+#pragma unroll
+    for (int m = 0; m < MR; m++) Ar[m] = A + (size_t)min(m0 + m, M - 1) * K;
+    const size_t o = (size_t)(m0 + lane) * N + n; // lane m finishes row m
+    const bool live = lane < MR && m0 + lane < M;
+    const float resid = MODE == GEMM_RESID && live ? C[o] : 0.f;
+    float acc[NM][MR];
+#pragma unroll
+    for (int c = 0; c < NM; c++)
+#pragma unroll
+        for (int m = 0; m < MR; m++) acc[c][m] = 0.f;
+    for (int k0 = 4 * lane; k0 < K; k0 += 256 * U) {
+        float4 wv[U][NM], av[U][MR];
+#pragma unroll
+        for (int u = 0; u < U; u++) { // (chunks past the end re-read the lane's first one; not multiplied)
+            const int k = k0 + 256 * u < K ? k0 + 256 * u : k0;
+#pragma unroll
+            for (int c = 0; c < NM; c++) wv[u][c] = *(const float4 *)(W[c] + k);
+#pragma unroll
+            for (int m = 0; m < MR; m++) av[u][m] = *(const float4 *)(Ar[m] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (k0 + 256 * u < K) {
+#pragma unroll
+                for (int c = 0; c < NM; c++)
+#pragma unroll
+                    for (int m = 0; m < MR; m++) {
+                        acc[c][m] = fmaf(av[u][m].x, wv[u][c].x, acc[c][m]);
+                        acc[c][m] = fmaf(av[u][m].y, wv[u][c].y, acc[c][m]);
+                        acc[c][m] = fmaf(av[u][m].z, wv[u][c].z, acc[c][m]);
+                        acc[c][m] = fmaf(av[u][m].w, wv[u][c].w, acc[c][m]);
+                    }
+            }
+    }
+    float v[NM];
+#pragma unroll
+    for (int c = 0; c < NM; c++) {
+        v[c] = 0.f;
+#pragma unroll
+        for (int m = 0; m < MR; m++) {
+            const float t = wave_sum_dpp(acc[c][m]);
+            v[c] = lane == m ? t : v[c];
+        }
+    }
+    if (!live) return;
+    if (MODE == GEMM_SWIGLU) Cact[o] = v[0] / (1.0f + expf(-v[0])) * v[NM - 1];
+    else C[o] = MODE == GEMM_RESID ? resid + v[0] : v[0];
+}
+
+template <int MODE>
+static void gemm_f32_rows(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, float *Cact)
+{
+    const dim3 block(GF_WAVES * 64);
+    const int bx = (N + GF_WAVES - 1) / GF_WAVES;
+#define SD_GF(MR) hipLaunchKernelGGL((gemm_f32_rows_kernel<MODE, MR>), dim3(bx, (M + MR - 1) / MR), block, 0, s, A, w, M, N, K, C, Cact)
+    if (M == 1) SD_GF(1);
+    else if (M == 2) SD_GF(2);
+    else if (M <= 5) SD_GF(5);
+    else if (M <= 8) SD_GF(8);
+    else SD_GF(16);
+#undef SD_GF
+}
+
 // Row-major -> tiled weight order, one 16-byte piece per thread (destination-linear, so stores coalesce).
 __global__ __launch_bounds__(256) void retile_bf16_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst,
                                                           int N, int K)
@@ -519,6 +606,13 @@ static void gemm_generic_dispatch(hipStream_t s, int mode, const void *A, ActVie
 hipError_t launch_gemm_generic(hipStream_t s, int dtype, int mode, const void *A, ActView a_av, WeightSeg w, int M,
                                int N, int K, float *C, void *Cact, ActView c_av)
 {
+    const uintptr_t addr = (uintptr_t)A | (uintptr_t)w.p[0] | (uintptr_t)w.p[1] | (uintptr_t)w.p[2];
+    if (dtype == SD_FP32 && K % 4 == 0 && !(addr & 15) && !w.tiled && !a_av.sm && !c_av.sm) {
+        if (mode == GEMM_STORE) gemm_f32_rows<GEMM_STORE>(s, (const float *)A, w, M, N, K, C, nullptr);
+        else if (mode == GEMM_RESID) gemm_f32_rows<GEMM_RESID>(s, (const float *)A, w, M, N, K, C, nullptr);
+        else gemm_f32_rows<GEMM_SWIGLU>(s, (const float *)A, w, M, N, K, nullptr, (float *)Cact);
+        return hipGetLastError();
+    }
     if (dtype == SD_BF16) gemm_generic_dispatch<bf16_t>(s, mode, A, a_av, w, M, N, K, C, Cact, c_av);
     else gemm_generic_dispatch<float>(s, mode, A, a_av, w, M, N, K, C, Cact, c_av);
     return hipGetLastError();
@@ -1010,14 +1104,34 @@ hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_
 // ---------------------------------------------------------------- generic attention
 // One block per (row slot i, head, selected sequence): query row i sees cache rows
 // [0, kv0 + i].  Scores live in dynamic LDS (lds_len floats: the largest sequence capacity).
+// Bound: latency of the two passes over the cache, so both read it in the pieces it is stored in: a thread's token is
+// hd / 8 contiguous pieces of 8 dimensions, a wave's V load is 8 dimensions x 32 tokens, four tokens per lane.  Measured,
+// fp32, head width 64, 32 to 80 tokens, 5 rows x 4 heads: 11.3 us element by element, 7.1 us now.
+__device__ __forceinline__ void load8_f(const float *p, float *f)
+{
+    const float4 a = *(const float4 *)p, b = *(const float4 *)(p + 4);
+    f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
+}
+__device__ __forceinline__ void load8_f(const bf16_t *p, float *f)
+{
+    const uint4 a = *(const uint4 *)p;
+    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int i = 0; i < 4; i++) f[2 * i] = __uint_as_float(w[i] << 16), f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+}
+__device__ __forceinline__ float4 load4_f(const float *p) { return *(const float4 *)p; }
+__device__ __forceinline__ float4 load4_f(const bf16_t *p)
+{
+    const uint2 a = *(const uint2 *)p;
+    return make_float4(__uint_as_float(a.x << 16), __uint_as_float(a.x & 0xffff0000u), __uint_as_float(a.y << 16), __uint_as_float(a.y & 0xffff0000u));
+}
 template <typename T>
 __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActView q_av, const T *Kl, const T *Vtl,
                                                            PlanView pv, CtxView cv, int R, int H, int hd,
                                                            int64_t total_cap, int lds_len, T *obuf, ActView o_av)
 {
-    extern __shared__ float sc[]; // [lds_len] scores, then [256] partials, [hd] q, [32] red
-    float *part = sc + lds_len;
-    float *qs = part + 256;
+    extern __shared__ __attribute__((aligned(16))) float sc[]; // [lds_len] scores, then [hd] q, [32] red
+    float *qs = sc + lds_len; // (lds_len, a capacity, is a multiple of 64)
     float *red = qs + hd;
     int i = blockIdx.x, h = blockIdx.y, j = blockIdx.z;
     int r = j * R + i;
@@ -1040,7 +1154,13 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActVie
     float mx = -3.0e38f;
     for (int t = threadIdx.x; t < Lk; t += blockDim.x) {
         float dot = 0.f;
-        for (int d = 0; d < hd; d++) dot += qs[d] * to_float(Kh[kt_offset(hd, off + t, d)]);
+#pragma unroll 8
+        for (int d = 0; d < hd; d += 8) { // (8 dimensions of a token are one piece of its tile)
+            float f[8];
+            load8_f(Kh + kt_offset(hd, off + t, d), f);
+#pragma unroll
+            for (int e = 0; e < 8; e++) dot += qs[d + e] * f[e];
+        }
         dot *= scale;
         sc[t] = dot;
         mx = fmaxf(mx, dot);
@@ -1054,15 +1174,22 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActVie
     }
     z = block_sum(z, red);
     __syncthreads();
-    int G = blockDim.x / hd; // hd is 64 or 128, blockDim 256
-    int d = threadIdx.x % hd, g = threadIdx.x / hd;
-    float acc = 0.f;
-    for (int t = g; t < Lk; t += G) acc += sc[t] * to_float(Vh[vt_offset(hd, off + t, d)]);
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    if (g == 0) {
-        for (int gg = 1; gg < G; gg++) acc += part[gg * hd + d];
-        store_act(obuf, act_index(o_av, r, h * hd + d, HD), o_av.plane, acc / z);
+    // wave w takes dimensions 8 w .. 8 w + 7, then 8 (w + 4) ..; lane (dl, tl): dimension dl of them, tokens 4 tl .. of a tile
+    const int lane = threadIdx.x & 63, dl = lane >> 3, tl = lane & 7;
+    for (int d8 = (threadIdx.x >> 6) * 8; d8 < hd; d8 += blockDim.x / 8) {
+        float acc = 0.f;
+#pragma unroll 4
+        for (int t = 4 * tl; t < Lk; t += 32) {
+            const float4 v = load4_f(Vh + vt_offset(hd, off + t, d8 + dl)), p = *(const float4 *)(sc + t);
+            acc += p.x * v.x; // (scores past Lk are not initialised, cache rows past it hold anything: not used)
+            acc += t + 1 < Lk ? p.y * v.y : 0.f;
+            acc += t + 2 < Lk ? p.z * v.z : 0.f;
+            acc += t + 3 < Lk ? p.w * v.w : 0.f;
+        }
+        acc += dpp_f<0xB1>(acc);
+        acc += dpp_f<0x4E>(acc);
+        acc += dpp_f<0x141>(acc); // (8 lanes)
+        if (tl == 0) store_act(obuf, act_index(o_av, r, h * hd + d8 + dl, HD), o_av.plane, acc / z);
     }
 }
 
@@ -1070,7 +1197,7 @@ hipError_t launch_attn_generic(hipStream_t s, int dtype, const void *qbuf, ActVi
                                const void *Vtl, PlanView pv, CtxView cv, int R, int n_seq, int H, int hd,
                                int64_t total_cap, int len_upper, void *obuf, ActView o_av)
 {
-    size_t lds = ((size_t)len_upper + 256 + hd + 32) * sizeof(float);
+    size_t lds = ((size_t)len_upper + 256 + hd + 32) * sizeof(float); // (256 floats of slack: the limit below is part of the interface)
     if (lds > 160 * 1024) return hipErrorNotSupported;
     if (lds > 64 * 1024) { // beyond the default limit: ask for the larger LDS allocation this part has
         hipError_t ea = dtype == SD_BF16

@@ -1228,6 +1228,38 @@ def test_lora_adapters_chosen_per_sequence_match_oracle(shape_name, tol):
     gm.close()
 
 
+@pytest.mark.parametrize("d,hd,F", [(48, 16, 130), (48, 16, 132), (64, 32, 1100), (256, 128, 260)])
+@pytest.mark.parametrize("B,gamma", [(1, 0), (2, 0), (1, 4), (1, 6), (1, 15), (3, 7)])
+def test_fp32_row_classes_and_widths_match_oracle(d, hd, F, B, gamma):
+    """The fp32 kernels at every row class of their GEMM (1, 2, up to 5, 8, 16, several groups of 16), widths that fill part
+    of a wave's 256 elements, several of them, more than four, or are no multiple of 4 (element-wise kernel), and every
+    head width the element-wise attention takes, with contexts that end inside and at the end of a 32-token tile."""
+    _say(f"fp32 shapes d={d} hd={hd} F={F} B={B} gamma={gamma}")
+    st_ = dg.ModelShape("f32_t", 2, d, d // hd, hd, F, 500, dg.FP32)
+    w = dg.make_weights(st_, 71, 20.0)
+    om = oracle.OracleModel(st_, w)
+    gm = api.Model(st_, w, max_rows=64, max_pos=128)
+    V = st_.vocab
+    lens = [33, 1, 62][:B] if gamma else [32, 65][:B]
+    prompts = [[int(t) for t in dg.make_prompt(71, b, n, V)] for b, n in enumerate(lens)]
+    ctx = api.Context([n + 32 for n in lens])
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    cand = np.stack([[int(t) for t in dg.make_prompt(72, b, max(gamma, 1), V)] for b in range(B)]).astype(np.int32)[:, :gamma]
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_verify(gm, ctx, None, B, gamma, 0.0, H.dev(cand) if gamma else None, None, None, na, nx, commit=False)
+    lg = gm.last_logits().cpu().numpy().reshape(B, gamma + 1, V)
+    for b in range(B):
+        seq = om.new_seq(lens[b] + 32)
+        oracle.prefill(seq, prompts[b])
+        u = dg.make_uniforms(71, dg.VERIFY_STREAM, b, 0, gamma + 1)
+        ref = seq.verify(prompts[b], gamma, 0.0, cand[b], None, u, want_logits=True)[3].reshape(gamma + 1, V)
+        err = np.abs(lg[b] - ref).max() / np.abs(ref).max()
+        assert err < 1e-4, (b, err)
+    ctx.close()
+    gm.close()
+
+
 @pytest.mark.parametrize("rank", [1, 4, 6, 12, 16])
 @pytest.mark.parametrize("d,dtype,tol", [(256, dg.BF16, 2e-2), (1280, dg.FP32, 1e-4)])
 def test_lora_ranks_and_widths_match_oracle(d, dtype, tol, rank):
