@@ -129,6 +129,18 @@ __device__ float block_sum(float v, float *red)
     for (int i = 0; i < nw; i++) t += red[i];
     return t;
 }
+// The same for any block of whole waves, with barriers that wait for LDS traffic only.
+__device__ __forceinline__ float block_sum_lds(float v, float *red)
+{
+    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE, nw = blockDim.x / WAVE;
+    v = wave_sum_dpp(v);
+    lds_barrier();
+    if (l == 0) red[w] = v;
+    lds_barrier();
+    float t = 0.f;
+    for (int i = 0; i < nw; i++) t += red[i];
+    return t;
+}
 __device__ float block_max(float v, float *red)
 {
     int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE, nw = (blockDim.x + WAVE - 1) / WAVE;
@@ -628,47 +640,60 @@ hipError_t launch_gemm_generic(hipStream_t s, int dtype, int mode, const void *A
 __device__ void embed_rmsnorm_row_vec(const bf16_t *E, int tok, int r, int d, float *x, const float *g, float eps,
                                       bf16_t *out, ActView av, float *red)
 {
-    constexpr int KEEP = 4; // 8-column pieces a thread holds (d <= 8 * KEEP * blockDim.x, else the rest is re-read)
+    constexpr int KEEP = 4; // 8-column pieces a thread holds, with their gains (d <= 8 * KEEP * blockDim.x, else the rest is re-read)
     const uint4 *src = (const uint4 *)(E + (size_t)tok * d);
     float *xr = x + (size_t)r * d;
-    const int npiece = d >> 3;
-    float v[KEEP][8];
+    const int npiece = d >> 3, bd = blockDim.x;
+    uint4 raw[KEEP];
+    float4 gain[KEEP][2];
     float ss = 0.f;
-    int it = 0;
-    for (int p = threadIdx.x; p < npiece; p += blockDim.x, it++) {
-        const uint4 w = src[p];
+    auto unpack = [](const uint4 w, float *f) {
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-        float f[8];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             f[2 * e] = __uint_as_float(ws[e] << 16);
             f[2 * e + 1] = __uint_as_float(ws[e] & 0xffff0000u);
         }
+    };
+    auto take = [&](int p, const uint4 w) {
+        float f[8];
+        unpack(w, f);
         *(float4 *)(xr + 8 * p) = make_float4(f[0], f[1], f[2], f[3]);
         *(float4 *)(xr + 8 * p + 4) = make_float4(f[4], f[5], f[6], f[7]);
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            ss += f[e] * f[e];
-            if (it < KEEP) v[it < KEEP ? it : 0][e] = f[e];
-        }
-    }
-    ss = block_sum(ss, red); // (its barriers also make the x row visible to the re-reads below)
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    it = 0;
-    for (int p = threadIdx.x; p < npiece; p += blockDim.x, it++) {
+        for (int e = 0; e < 8; e++) ss += f[e] * f[e];
+    };
+    auto give = [&](int p, const uint4 w, const float4 g0, const float4 g1, float inv) {
         float f[8];
-        if (it < KEEP) {
-#pragma unroll
-            for (int e = 0; e < 8; e++) f[e] = v[it < KEEP ? it : 0][e];
-        } else {
-            const float4 a = *(const float4 *)(xr + 8 * p), b = *(const float4 *)(xr + 8 * p + 4);
-            f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
-        }
-        const float4 g0 = *(const float4 *)(g + 8 * p), g1 = *(const float4 *)(g + 8 * p + 4);
+        unpack(w, f);
         const size_t o = act_index(av, r, 8 * p, d);
         store_act4(out, o, av.plane, f[0] * inv * g0.x, f[1] * inv * g0.y, f[2] * inv * g0.z, f[3] * inv * g0.w);
         store_act4(out, o + 4, av.plane, f[4] * inv * g1.x, f[5] * inv * g1.y, f[6] * inv * g1.z, f[7] * inv * g1.w);
+    };
+#pragma unroll
+    for (int it = 0; it < KEEP; it++) {
+        const int p = threadIdx.x + it * bd;
+        if (p < npiece) {
+            raw[it] = src[p];
+            gain[it][0] = *(const float4 *)(g + 8 * p);
+            gain[it][1] = *(const float4 *)(g + 8 * p + 4);
+        }
     }
+#pragma unroll
+    for (int it = 0; it < KEEP; it++) {
+        const int p = threadIdx.x + it * bd;
+        if (p < npiece) take(p, raw[it]);
+    }
+    for (int p = threadIdx.x + KEEP * bd; p < npiece; p += bd) take(p, src[p]);
+    ss = block_sum_lds(ss, red);
+    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+    for (int it = 0; it < KEEP; it++) {
+        const int p = threadIdx.x + it * bd;
+        if (p < npiece) give(p, raw[it], gain[it][0], gain[it][1], inv);
+    }
+    for (int p = threadIdx.x + KEEP * bd; p < npiece; p += bd)
+        give(p, src[p], *(const float4 *)(g + 8 * p), *(const float4 *)(g + 8 * p + 4), inv);
 }
 template <typename T>
 __device__ void embed_rmsnorm_row(const T *E, int tok, int r, int d, float *x, const float *g, float eps, T *out,
@@ -1402,15 +1427,28 @@ __device__ float row_sumexp(const float *row, int V, float mx, float invT, float
 }
 
 // ---------------------------------------------------------------- register-resident vocabulary rows
-// For V <= 32768 a 1024-thread block holds a whole fp32 row in registers: thread t keeps the float4s
-// number it*1024 + t, it < ROW_NSEG - the same element-to-thread assignment as the strided loops of the
+// For V <= 32768 a block of RT threads holds a whole fp32 row in registers: thread t keeps the float4s
+// number it * RT + t, it < NSEG - with 1024 threads the same element-to-thread assignment as the strided loops of the
 // general kernels above; the block-wide sums are added as trees here, so the two paths agree to rounding
 // (and exactly in the maximum and the arg max).  One pass over memory per row and a handful of barriers
 // instead of one block reduction per 4096 elements.
+// The block's shape follows the row: one vector per thread up to 4096 columns, then 2, 4, 8 (an 8-vector block of a
+// 1024-column row spends its time on 31 exponentials of padding per thread); 256 threads up to 1024 columns, where most
+// of 16 waves would only meet at the barriers.  Measured, 1024 columns (8 vectors x 1024 threads before): draft sampler
+// 12.2 -> 4.2 us, row verdicts 13.3 -> 4.8 us.
 #define ROW_NSEG 8
 #define ROW_THREADS 1024
+#define SD_ROW_SHAPES(V, CALL)                    \
+    do {                                          \
+        if ((V) <= 1024) CALL(256, 1);            \
+        else if ((V) <= 4096) CALL(1024, 1);      \
+        else if ((V) <= 8192) CALL(1024, 2);      \
+        else if ((V) <= 16384) CALL(1024, 4);     \
+        else CALL(ROW_THREADS, ROW_NSEG);         \
+    } while (0)
+template <int NSEG>
 struct RowRegs {
-    float4 f[ROW_NSEG];
+    float4 f[NSEG];
 };
 struct FastScratch {
     float wsum[ROW_THREADS / WAVE][ROW_NSEG];
@@ -1419,10 +1457,20 @@ struct FastScratch {
     int pick;
     int seg_last; // last index of positive weight inside the segment that holds the target
 };
-static_assert(ROW_THREADS / WAVE == 16, "the cross-wave steps below read one LDS entry per lane of a 16-lane row");
-
-// Block-wide arg max / sum for ROW_THREADS threads; every thread gets the result.
-__device__ void block_argmax_rows(float &v, int &idx, FastScratch *fs)
+// Cross-wave steps: NW = 4 or 16 waves leave one LDS entry each, lane l of every wave reads entry l % NW and the entries
+// meet inside groups of NW lanes (the maxima may meet their repetitions in a 16-lane row as well).
+template <int NW>
+__device__ __forceinline__ float sum_waves(float v)
+{
+    static_assert(NW == 4 || NW == 16, "a quad or a 16-lane row");
+    if (NW == 16) return row16_sum(v);
+    v += dpp_f<0xB1>(v);
+    v += dpp_f<0x4E>(v);
+    return v;
+}
+// Block-wide arg max / sum for RT threads; every thread gets the result.
+template <int RT>
+__device__ __forceinline__ void block_argmax_rows(float &v, int &idx, FastScratch *fs)
 {
     const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
     row16_argmax(v, idx);
@@ -1437,18 +1485,28 @@ __device__ void block_argmax_rows(float &v, int &idx, FastScratch *fs)
         fs->redi[w] = bi;
     }
     lds_barrier();
-    v = fs->red[l & 15];
-    idx = fs->redi[l & 15];
+    v = fs->red[l & (RT / WAVE - 1)];
+    idx = fs->redi[l & (RT / WAVE - 1)];
     row16_argmax(v, idx);
 }
-__device__ float block_sum_rows(float v, FastScratch *fs) { return block_sum16(v, fs->red); }
+template <int RT>
+__device__ __forceinline__ float block_sum_rows(float v, FastScratch *fs)
+{
+    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
+    v = wave_sum_dpp(v);
+    lds_barrier();
+    if (l == 0) fs->red[w] = v;
+    lds_barrier();
+    return sum_waves<RT / WAVE>(fs->red[l & (RT / WAVE - 1)]);
+}
 
-__device__ __forceinline__ void row_load(const float *row, int V, float fill, RowRegs &r)
+template <int RT, int NSEG>
+__device__ __forceinline__ void row_load(const float *row, int V, float fill, RowRegs<NSEG> &r)
 {
     const int nvec = (V + 3) / 4;
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) {
-        const int v = it * ROW_THREADS + threadIdx.x;
+    for (int it = 0; it < NSEG; it++) {
+        const int v = it * RT + threadIdx.x;
         r.f[it] = v < nvec ? load4_guard(row, v, V, fill) : make_float4(fill, fill, fill, fill);
     }
 }
@@ -1456,27 +1514,28 @@ __device__ __forceinline__ void row_load(const float *row, int V, float fill, Ro
 // max, lowest-index argmax and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
 // -3e38 past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
 // e(x) / z need no second exponential.
-__device__ __forceinline__ void row_stats_regs(RowRegs &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
+template <int RT, int NSEG>
+__device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
 {
     float bv = -3.0e38f;
     int bi = 0x7fffffff;
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) {
-        const int v = it * ROW_THREADS + threadIdx.x;
+    for (int it = 0; it < NSEG; it++) {
+        const int v = it * RT + threadIdx.x;
         const float4 f = r.f[it];
         if (f.x > bv) { bv = f.x; bi = 4 * v; }
         if (f.y > bv) { bv = f.y; bi = 4 * v + 1; }
         if (f.z > bv) { bv = f.z; bi = 4 * v + 2; }
         if (f.w > bv) { bv = f.w; bi = 4 * v + 3; }
     }
-    block_argmax_rows(bv, bi, fs);
+    block_argmax_rows<RT>(bv, bi, fs);
     mx = bv;
     am = bi;
     z = 1.f;
     if (invT > 0.f) {
         float zl = 0.f;
 #pragma unroll
-        for (int it = 0; it < ROW_NSEG; it++) {
+        for (int it = 0; it < NSEG; it++) {
             float4 f = r.f[it];
             f.x = expf((f.x - mx) * invT);
             f.y = expf((f.y - mx) * invT);
@@ -1488,22 +1547,23 @@ __device__ __forceinline__ void row_stats_regs(RowRegs &r, float invT, FastScrat
             zl += f.w;
             r.f[it] = f;
         }
-        z = block_sum_rows(zl, fs);
+        z = block_sum_rows<RT>(zl, fs);
     }
 }
 
 // Inverse-CDF pick (same rule as block_pick_cdf) over weights held in registers.
-__device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastScratch *fs, float *total_out)
+template <int RT, int NSEG>
+__device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u, FastScratch *fs, float *total_out)
 {
     // Index order is (segment it, thread t, component c).  Segment totals are the waves' totals added as a
     // tree; every thread works out the total Z, the segment holding u * Z and the sum before it for itself
     // (no single-thread phase), then one block-wide scan of that segment's float4 sums places the element.
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
     int lastp = -1;
-    float loc[ROW_NSEG];
+    float loc[NSEG];
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) {
-        const int v = it * ROW_THREADS + threadIdx.x;
+    for (int it = 0; it < NSEG; it++) {
+        const int v = it * RT + threadIdx.x;
         const float4 f = w.f[it];
         if (f.x > 0.f) lastp = 4 * v;
         if (f.y > 0.f) lastp = 4 * v + 1;
@@ -1517,7 +1577,7 @@ __device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastS
     lds_barrier(); // the scratch may still be in use by a previous call
     if (lane == 0) {
 #pragma unroll
-        for (int it = 0; it < ROW_NSEG; it++) fs->wsum[wv][it] = loc[it];
+        for (int it = 0; it < NSEG; it++) fs->wsum[wv][it] = loc[it];
         fs->redi[wv] = lastp;
     }
     if (threadIdx.x == 0) {
@@ -1525,20 +1585,20 @@ __device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastS
         fs->seg_last = -1;
     }
     lds_barrier();
-    const int nseg = ((V + 3) / 4 + ROW_THREADS - 1) / ROW_THREADS;
-    float seg[ROW_NSEG];
+    const int nseg = ((V + 3) / 4 + RT - 1) / RT;
+    float seg[NSEG];
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) seg[it] = row16_sum(fs->wsum[lane & 15][it]);
-    const int lp = max(row16_max(fs->redi[lane & 15]), 0); // last index with a positive weight (0 if there is none)
+    for (int it = 0; it < NSEG; it++) seg[it] = sum_waves<RT / WAVE>(fs->wsum[lane & (RT / WAVE - 1)][it]);
+    const int lp = max(row16_max(fs->redi[lane & (RT / WAVE - 1)]), 0); // last index with a positive weight (0 if there is none)
     float Z = 0.f;
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++)
+    for (int it = 0; it < NSEG; it++)
         if (it < nseg) Z += seg[it];
     const float target = u * Z;
     float base = 0.f;
     int sit = -1;
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++)
+    for (int it = 0; it < NSEG; it++)
         if (it < nseg && sit < 0) {
             if (base + seg[it] > target) sit = it;
             else base += seg[it];
@@ -1547,19 +1607,19 @@ __device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastS
     if (sit >= 0) { // uniform over the block
         float4 f = w.f[0];
 #pragma unroll
-        for (int it = 1; it < ROW_NSEG; it++) { // (component selects: an indexed copy would put the whole row into scratch memory)
+        for (int it = 1; it < NSEG; it++) { // (component selects: an indexed copy would put the whole row into scratch memory)
             const float4 c = w.f[it];
             f.x = it == sit ? c.x : f.x;
             f.y = it == sit ? c.y : f.y;
             f.z = it == sit ? c.z : f.z;
             f.w = it == sit ? c.w : f.w;
         }
-        const int v = sit * ROW_THREADS + threadIdx.x;
+        const int v = sit * RT + threadIdx.x;
         const float l4 = ((f.x + f.y) + f.z) + f.w;
         const float inc = wave_incl_scan_dpp(l4, lane);
         if (lane == WAVE - 1) fs->red[wv] = inc; // red was last read before the barrier above
         lds_barrier();
-        const float before = row16_sum((lane & 15) < wv ? fs->red[lane & 15] : 0.f);
+        const float before = sum_waves<RT / WAVE>((lane & (RT / WAVE - 1)) < wv ? fs->red[lane & (RT / WAVE - 1)] : 0.f);
         int k = first_over(base + (before + inc - l4), f, target, 4 * v);
         if (k >= V) k = 0x7fffffff;
         k = wave_min_i(k);
@@ -1579,10 +1639,11 @@ __device__ __forceinline__ int pick_regs(const RowRegs &w, int V, float u, FastS
 }
 
 // e(x) -> probabilities e(x) * (1 / z), in place
-__device__ __forceinline__ void row_scale(RowRegs &r, float invZ)
+template <int NSEG>
+__device__ __forceinline__ void row_scale(RowRegs<NSEG> &r, float invZ)
 {
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) {
+    for (int it = 0; it < NSEG; it++) {
         r.f[it].x *= invZ;
         r.f[it].y *= invZ;
         r.f[it].z *= invZ;
@@ -1594,12 +1655,33 @@ __device__ __forceinline__ void row_scale(RowRegs &r, float invZ)
 // checks and cache-length update as plan_kernel makes for that mode, written by the sampler block that has
 // just drawn the token.  seq_order keeps the order the catch-up plan of this draft call left (every
 // sequence grows by one row, so the ranking by length does not change).  One thread calls this.
-__device__ int plan_next_cand(const NextPlan &np, int j, int tok)
+// The sequence state it needs is read by plan_cand_load when the sampler starts (three dependent reads that would
+// otherwise stand at its end).
+struct CandState {
+    int b, n, kv, cap, g;
+    bool in;
+};
+__device__ __forceinline__ CandState plan_cand_load(const NextPlan &np, int j)
+{
+    const CtxView &cv = np.cv;
+    CandState c = {j, 0, 0, 0, 0, false};
+    if (!np.enabled) return c;
+    if (np.seq_ids) c.b = np.seq_ids[j];
+    c.in = c.b >= 0 && c.b < cv.B;
+    if (c.in) {
+        c.n = cv.ntok[c.b];
+        c.kv = cv.kvlen[(size_t)np.slot * cv.B + c.b];
+        c.cap = cv.cap[c.b];
+        c.g = seq_gamma(cv, c.b, np.gamma);
+    }
+    return c;
+}
+__device__ int plan_next_cand(const NextPlan &np, int j, int tok, const CandState &cs)
 {
     const PlanView &pv = np.pv;
     const CtxView &cv = np.cv;
-    const int b = np.seq_ids ? np.seq_ids[j] : j;
-    if (b < 0 || b >= cv.B) { // refuse out-of-range ids: the row stays unused
+    const int b = cs.b;
+    if (!cs.in) { // refuse out-of-range ids: the row stays unused
         atomicOr(cv.status, 4);
         pv.seq_b[j] = 0;
         pv.seq_kv0[j] = 0;
@@ -1611,11 +1693,9 @@ __device__ int plan_next_cand(const NextPlan &np, int j, int tok)
         pv.lm_row[j] = j;
         return 0;
     }
-    const int n = cv.ntok[b];
-    int *kvp = cv.kvlen + (size_t)np.slot * cv.B + b;
-    int kv0 = *kvp, nq = 1;
-    const int cap = cv.cap[b];
-    if (np.next_idx >= seq_gamma(cv, b, np.gamma)) nq = 0; // the sequence has drawn all its candidates
+    const int n = cs.n, cap = cs.cap;
+    int kv0 = cs.kv, nq = 1;
+    if (np.next_idx >= cs.g) nq = 0; // the sequence has drawn all its candidates
     if (n < 1) { // an empty sequence has no pending token
         atomicOr(cv.status, 2);
         nq = 0;
@@ -1637,7 +1717,7 @@ __device__ int plan_next_cand(const NextPlan &np, int j, int tok)
     pv.seq_kv0[j] = kv0;
     pv.seq_nq[j] = nq;
     pv.lm_row[j] = j;
-    *kvp = kv0 + nq;
+    cv.kvlen[(size_t)np.slot * cv.B + b] = kv0 + nq;
     return nq > 0 ? tok : 0; // (= row_tok[j]: what the planned forward embeds)
 }
 
@@ -1652,25 +1732,27 @@ __device__ __forceinline__ bool draft_seq_active(const NextPlan &np, int j, int 
     return idx < seq_gamma(np.cv, b, gamma);
 }
 
-__global__ __launch_bounds__(ROW_THREADS) void draft_sample_fast_kernel(const float *logits, int V, float T,
+template <int RT, int NSEG>
+__global__ __launch_bounds__(RT) void draft_sample_fast_kernel(const float *logits, int V, float T,
                                                                          const float *u, int gamma, int idx,
                                                                          int32_t *cand, float *q, NextPlan next)
 {
     __shared__ FastScratch fs;
     const int j = blockIdx.x;
+    const CandState cs = plan_cand_load(next, j);
     if (!draft_seq_active(next, j, gamma, idx)) { // (uniform over the block) nothing to draw: keep its plan entry empty
-        if (threadIdx.x == 0 && next.enabled) plan_next_cand(next, j, 0);
+        if (threadIdx.x == 0 && next.enabled) plan_next_cand(next, j, 0, cs);
         return;
     }
-    RowRegs r;
-    row_load(logits + (size_t)j * V, V, -3.0e38f, r);
+    RowRegs<NSEG> r;
+    row_load<RT>(logits + (size_t)j * V, V, -3.0e38f, r);
     float mx, z;
     int am;
-    row_stats_regs(r, T > 0.f ? 1.0f / T : 0.f, &fs, mx, am, z);
+    row_stats_regs<RT>(r, T > 0.f ? 1.0f / T : 0.f, &fs, mx, am, z);
     if (T == 0.f) {
         if (threadIdx.x == 0) {
             cand[j * gamma + idx] = am;
-            if (next.enabled) plan_next_cand(next, j, am);
+            if (next.enabled) plan_next_cand(next, j, am, cs);
         }
         return;
     }
@@ -1678,8 +1760,8 @@ __global__ __launch_bounds__(ROW_THREADS) void draft_sample_fast_kernel(const fl
     float *qrow = q + ((size_t)j * gamma + idx) * V;
     const int nvec = (V + 3) / 4;
 #pragma unroll
-    for (int it = 0; it < ROW_NSEG; it++) {
-        const int v = it * ROW_THREADS + threadIdx.x;
+    for (int it = 0; it < NSEG; it++) {
+        const int v = it * RT + threadIdx.x;
         const float4 p = r.f[it];
         if (4 * v + 3 < V) *(float4 *)(qrow + 4 * v) = p;
         else if (v < nvec) {
@@ -1688,10 +1770,10 @@ __global__ __launch_bounds__(ROW_THREADS) void draft_sample_fast_kernel(const fl
             if (4 * v + 2 < V) qrow[4 * v + 2] = p.z;
         }
     }
-    const int pick = pick_regs(r, V, u[j * gamma + idx], &fs, nullptr);
+    const int pick = pick_regs<RT>(r, V, u[j * gamma + idx], &fs, nullptr);
     if (threadIdx.x == 0) {
         cand[j * gamma + idx] = pick;
-        if (next.enabled) plan_next_cand(next, j, pick);
+        if (next.enabled) plan_next_cand(next, j, pick, cs);
     }
 }
 
@@ -1715,12 +1797,12 @@ struct SplitScratch {
     int pick, lastp, tok;
 };
 
-__device__ void next_forward_first_step(const NextPlan &next, int j, int tok, SplitScratch *ss)
+__device__ void next_forward_first_step(const NextPlan &next, int j, int tok, const CandState &cs, SplitScratch *ss)
 {
     // (all threads of the block) thread 0 plans; then the block gathers and norms the row
-    if (threadIdx.x == 0) ss->tok = next.enabled ? plan_next_cand(next, j, tok) : 0;
+    if (threadIdx.x == 0) ss->tok = next.enabled ? plan_next_cand(next, j, tok, cs) : 0;
     if (!next.enabled || !next.embed) return;
-    __syncthreads();
+    lds_barrier(); // (the q slice written before need not have landed)
     embed_rmsnorm_row((const bf16_t *)next.E, ss->tok, j, next.d, next.x, next.g, next.eps, (bf16_t *)next.out, next.av,
                       ss->red);
 }
@@ -1732,11 +1814,12 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
     __shared__ SplitScratch ss;
     const int j = blockIdx.y, k = blockIdx.x, n_slices = gridDim.x;
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
+    const CandState cs = plan_cand_load(next, j);
     if (!draft_seq_active(next, j, gamma, idx)) { // (uniform over the block) nothing to draw: keep its plan entry empty
-        if (k == 0) next_forward_first_step(next, j, 0, &ss);
+        if (k == 0) next_forward_first_step(next, j, 0, cs, &ss);
         return;
     }
-    const float invT = 1.0f / T;
+    const float invT = 1.0f / T, uj = u[j * gamma + idx];
     const float *st = stats + (size_t)j * nb * 3;
     // this block's slice of the logits row: requested first, needed only once the maximum and Z are known
     const float *row = logits + (size_t)j * V;
@@ -1776,7 +1859,7 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
         if (s == k) base = Z;
         Z += ss.slice[s];
     }
-    const float target = u[j * gamma + idx] * Z;
+    const float target = uj * Z;
     int owner = -1, last_pos = 0;
     {
         float cum = 0.f;
@@ -1823,7 +1906,7 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
         if (lane == WAVE - 1) ss.wtot[it][wv] = inc[it];
     }
     if (lastp >= 0) atomicMax(&ss.lastp, lastp);
-    __syncthreads();
+    lds_barrier();
     float seg_before = base;
 #pragma unroll
     for (int it = 0; it < 2; it++) {
@@ -1839,11 +1922,11 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
         pk = wave_min_i(pk);
         if (lane == 0 && pk != 0x7fffffff) atomicMin(&ss.pick, pk);
     }
-    __syncthreads();
+    lds_barrier();
     int pick = ss.pick;
     if (pick == 0x7fffffff) pick = max(ss.lastp, 0);
     if (threadIdx.x == 0) cand[j * gamma + idx] = pick;
-    next_forward_first_step(next, j, pick, &ss);
+    next_forward_first_step(next, j, pick, cs, &ss);
 }
 
 // Greedy candidate from the partials: the largest block maximum, lowest column among equals.
@@ -1853,8 +1936,9 @@ __global__ __launch_bounds__(256) void draft_argmax_split_kernel(const float *st
     __shared__ SplitScratch ss;
     __shared__ int redi[32];
     const int j = blockIdx.x;
+    const CandState cs = plan_cand_load(next, j);
     if (!draft_seq_active(next, j, gamma, idx)) {
-        next_forward_first_step(next, j, 0, &ss);
+        next_forward_first_step(next, j, 0, cs, &ss);
         return;
     }
     const float *st = stats + (size_t)j * nb * 3;
@@ -1864,7 +1948,7 @@ __global__ __launch_bounds__(256) void draft_argmax_split_kernel(const float *st
     block_argmax(bv, bi, ss.red, redi);
     if (threadIdx.x == 0) cand[j * gamma + idx] = bi;
     __syncthreads(); // (block_argmax read ss.red last)
-    next_forward_first_step(next, j, bi, &ss);
+    next_forward_first_step(next, j, bi, cs, &ss);
 }
 
 // ---------------------------------------------------------------- draft: softmax + sample
@@ -1877,8 +1961,9 @@ __global__ __launch_bounds__(1024) void draft_sample_kernel(const float *logits,
     __shared__ float redv[32];
     __shared__ int redi[32];
     int j = blockIdx.x;
+    const CandState cs = plan_cand_load(next, j);
     if (!draft_seq_active(next, j, gamma, idx)) { // (uniform over the block) nothing to draw: keep its plan entry empty
-        if (threadIdx.x == 0 && next.enabled) plan_next_cand(next, j, 0);
+        if (threadIdx.x == 0 && next.enabled) plan_next_cand(next, j, 0, cs);
         return;
     }
     const float *row = logits + (size_t)j * V;
@@ -1888,7 +1973,7 @@ __global__ __launch_bounds__(1024) void draft_sample_kernel(const float *logits,
     if (T == 0.f) {
         if (threadIdx.x == 0) {
             cand[j * gamma + idx] = am;
-            if (next.enabled) plan_next_cand(next, j, am);
+            if (next.enabled) plan_next_cand(next, j, am, cs);
         }
         return;
     }
@@ -1924,7 +2009,7 @@ __global__ __launch_bounds__(1024) void draft_sample_kernel(const float *logits,
     int pick = block_pick_cdf(wfun, V, u[j * gamma + idx], &ps, nullptr);
     if (threadIdx.x == 0) {
         cand[j * gamma + idx] = pick;
-        if (next.enabled) plan_next_cand(next, j, pick);
+        if (next.enabled) plan_next_cand(next, j, pick, cs);
     }
 }
 
@@ -1944,9 +2029,10 @@ hipError_t launch_draft_sample(hipStream_t s, const float *logits, int n_seq, in
                                next);
         return hipGetLastError();
     }
-    if (V <= ROW_NSEG * ROW_THREADS * 4)
-        hipLaunchKernelGGL(draft_sample_fast_kernel, dim3(n_seq), dim3(ROW_THREADS), 0, s, logits, V, T, u, gamma, idx,
-                           cand, q, next);
+#define SD_SAMPLE_FAST(RT, NSEG)                                                                                             \
+    hipLaunchKernelGGL((draft_sample_fast_kernel<RT, NSEG>), dim3(n_seq), dim3(RT), 0, s, logits, V, T, u, gamma, idx, cand, q, \
+                       next)
+    if (V <= ROW_NSEG * ROW_THREADS * 4) SD_ROW_SHAPES(V, SD_SAMPLE_FAST);
     else
         hipLaunchKernelGGL(draft_sample_kernel, dim3(n_seq), dim3(1024), 0, s, logits, V, T, u, gamma, idx, cand, q,
                            next);
@@ -2262,11 +2348,12 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
 // 14.8 + 3.9 us, 192 rows 10.2 + 25.1 -> 21.1 + 4.1, 576 rows 23.2 + 26.7 -> 40.9 + 4.1.
 // EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
 // (6 rows: 15.9 -> 14.8 us); with more rows than units two blocks share one, q is read only where it is needed.
-template <bool EARLY_Q>
-__global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
+template <bool EARLY_Q, int RT, int NSEG>
+__global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
                                                                   const float *q, const float *u, const int32_t *seq_ids,
                                                                   CtxView cv, float *stats)
 {
+    constexpr int QH = NSEG < 4 ? NSEG : 4;
     __shared__ FastScratch fs;
     __shared__ PickScratch ps;
     const int stride_g = gamma; // row slots of the call: strides of cand, q and u
@@ -2277,8 +2364,8 @@ __global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kern
     const float *row = logits + ((size_t)j * (stride_g + 1) + i) * V;
     float *st = stats + ((size_t)j * (stride_g + 1) + i) * 3;
     if (i > gamma) return; // (uniform) not a live row
-    RowRegs r;
-    row_load(row, V, -3.0e38f, r);
+    RowRegs<NSEG> r;
+    row_load<RT>(row, V, -3.0e38f, r);
     const int c = i < gamma ? cand[(size_t)j * stride_g + i] : -1;
     const bool c_in = c >= 0 && c < V;
     float lc = 0.f, qc = 1.f, ui = 0.f, uu = 0.f;
@@ -2292,12 +2379,12 @@ __global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kern
         }
     }
     const int nvec = (V + 3) / 4;
-    RowRegs qr;
-    if (EARLY_Q && T > 0.f && i < gamma) row_load(qrow, V, 0.f, qr);
+    RowRegs<NSEG> qr;
+    if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, 0.f, qr);
     const float invT = T > 0.f ? 1.0f / T : 0.f;
     float mx, z;
     int am;
-    row_stats_regs(r, invT, &fs, mx, am, z);
+    row_stats_regs<RT>(r, invT, &fs, mx, am, z);
     // candidate i is accepted iff u_i < p_i / q_i (T > 0) or it is the row's argmax (T == 0)
     bool ok = false;
     int pick = am;
@@ -2310,16 +2397,16 @@ __global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kern
             row_scale(r, invZ);
             if (i < gamma) {
 #pragma unroll
-                for (int h = 0; h < ROW_NSEG; h += 4) { // (four segments of q at a time: registers for two blocks per unit)
-                    float4 w[4];
+                for (int h = 0; h < NSEG; h += QH) { // (four segments of q at a time: registers for two blocks per unit)
+                    float4 w[QH];
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        const int v = (h + k) * ROW_THREADS + threadIdx.x;
+                    for (int k = 0; k < QH; k++) {
+                        const int v = (h + k) * RT + threadIdx.x;
                         if (EARLY_Q) w[k] = qr.f[h + k];
                         else w[k] = v < nvec ? load4_guard(qrow, v, V, 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
                     }
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
+                    for (int k = 0; k < QH; k++) {
                         r.f[h + k].x = fmaxf(r.f[h + k].x - w[k].x, 0.f);
                         r.f[h + k].y = fmaxf(r.f[h + k].y - w[k].y, 0.f);
                         r.f[h + k].z = fmaxf(r.f[h + k].z - w[k].z, 0.f);
@@ -2329,7 +2416,7 @@ __global__ __launch_bounds__(ROW_THREADS, EARLY_Q ? 4 : 8) void verify_rows_kern
                 }
             }
             float mass;
-            pick = pick_regs(r, V, uu, &fs, &mass);
+            pick = pick_regs<RT>(r, V, uu, &fs, &mass);
             if (i < gamma && !(mass > 0.f)) { // (uniform) numerically empty residual: draw from p
                 auto p_of = [&](int v) {
                     float4 f = load4_guard(row, v, V, -3.0e38f);
@@ -2386,12 +2473,13 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
 {
     const int n_rows = n_seq * (gamma + 1);
     if (V <= ROW_NSEG * ROW_THREADS * 4) {
-        if (n_rows <= 256)
-            hipLaunchKernelGGL(verify_rows_kernel<true>, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, gamma, V, T, cand, q, u, seq_ids,
-                               cv, stats);
-        else
-            hipLaunchKernelGGL(verify_rows_kernel<false>, dim3(n_rows), dim3(ROW_THREADS), 0, s, logits, gamma, V, T, cand, q, u, seq_ids,
-                               cv, stats);
+#define SD_VERIFY_ROWS(EARLY, RT, NSEG)                                                                                      \
+    hipLaunchKernelGGL((verify_rows_kernel<EARLY, RT, NSEG>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, q, u, \
+                       seq_ids, cv, stats)
+#define SD_VERIFY_ROWS_EARLY(RT, NSEG) SD_VERIFY_ROWS(true, RT, NSEG)
+#define SD_VERIFY_ROWS_LATE(RT, NSEG) SD_VERIFY_ROWS(false, RT, NSEG)
+        if (n_rows <= 256) SD_ROW_SHAPES(V, SD_VERIFY_ROWS_EARLY);
+        else SD_ROW_SHAPES(V, SD_VERIFY_ROWS_LATE);
         hipLaunchKernelGGL(verify_finish_kernel, dim3(n_seq), dim3(WAVE), 0, s, stats, gamma, T, cand, seq_ids, n_acc, next_tok, commit,
                            cv);
         return hipGetLastError();

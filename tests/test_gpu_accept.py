@@ -195,7 +195,8 @@ def row_verdict_case(V, gamma):
     return logits, q, cand, u, expect
 
 
-@pytest.mark.parametrize("V,gamma", [(4, 2), (1024, 15), (4100, 1), (32000, 5), (32768, 3)])
+@pytest.mark.parametrize("V,gamma", [(4, 2), (1024, 15), (1028, 2), (4096, 3), (4100, 1), (8192, 2), (8196, 2), (16384, 2), (16388, 2),
+                                     (32000, 5), (32768, 3)])
 def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     """Rows that fit a block's registers: the verdicts of the rows behind the first rejection must not matter, and a
     rejection without residual mass draws from p."""

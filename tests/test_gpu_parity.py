@@ -1260,6 +1260,40 @@ def test_fp32_row_classes_and_widths_match_oracle(d, hd, F, B, gamma):
     gm.close()
 
 
+@pytest.mark.parametrize("V", [4, 1024, 1028, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
+def test_fp32_draft_sampler_row_shapes_match_oracle(V):
+    """The one-block draft sampler at both ends of every block shape (columns per thread and threads): candidates and q of a
+    draft call of two sequences against the oracle, sampled at T = 0.8."""
+    _say(f"fp32 draft sampler V={V}")
+    st_ = dg.ModelShape("f32_v", 1, 48, 3, 16, 64, V, dg.FP32)
+    w = dg.make_weights(st_, 73, 20.0)
+    om = oracle.OracleModel(st_, w)
+    gm = api.Model(st_, w, max_rows=32, max_pos=64)
+    lens, gamma, T = [5, 9], 3, 0.8
+    prompts = [[int(t) for t in dg.make_prompt(73, b, n, V)] for b, n in enumerate(lens)]
+    ctx = api.Context([n + 16 for n in lens])
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    ud = np.stack([dg.make_uniforms(73, dg.DRAFT_STREAM, b, 0, gamma) for b in range(2)])
+    cand = torch.zeros((2, gamma), dtype=torch.int32, device="cuda")
+    q = torch.zeros((2, gamma, V), dtype=torch.float32, device="cuda")
+    api.sd_draft(gm, ctx, None, 2, gamma, T, H.dev(ud), cand, q)
+    cg, qg = cand.cpu().numpy(), q.cpu().numpy()
+    for b in range(2):
+        seq = om.new_seq(lens[b] + 16)
+        oracle.prefill(seq, prompts[b])
+        r_c, r_q, mg = seq.draft(prompts[b], gamma, T, ud[b])
+        k = 0
+        while k < gamma and cg[b][k] == r_c[k]:
+            assert np.abs(qg[b][k] - r_q[k]).max() < 1e-5, (b, k)
+            k += 1
+        if k < gamma:   # a differing token must be a low-margin draw
+            assert mg[k] < 1e-4, (b, k, cg[b], r_c, mg)
+    ctx.sync()
+    ctx.close()
+    gm.close()
+
+
 @pytest.mark.parametrize("rank", [1, 4, 6, 12, 16])
 @pytest.mark.parametrize("d,dtype,tol", [(256, dg.BF16, 2e-2), (1280, dg.FP32, 1e-4)])
 def test_lora_ranks_and_widths_match_oracle(d, dtype, tol, rank):
