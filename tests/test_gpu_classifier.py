@@ -71,6 +71,21 @@ def test_labels_and_logits_match_oracle(shape, n, max_len, seed):
     assert np.array_equal(ids, ids2)
 
 
+@pytest.mark.parametrize("d_inner,d_state,dt_rank,d_conv,d_model,n_classes", [
+    (64, 16, 16, 4, 512, 64), (64, 1, 1, 1, 1, 2), (128, 5, 7, 2, 40, 3), (192, 16, 6, 4, 96, 4), (192, 3, 16, 3, 7, 33), (256, 4, 2, 4, 24, 5)])
+def test_every_channel_count_and_rank_matches_oracle(d_inner, d_state, dt_rank, d_conv, d_model, n_classes):
+    """Both sides of the line between the kernels (192 and 256 channels), every wave count of the four-threads-per-channel
+    kernel, the smallest and largest state, rank, taps, output and class counts, prompts that end on and beside its chunks."""
+    shape = dg.ClassifierShape("classifier_edge", vocab=61, d_model=d_model, d_inner=d_inner, d_state=d_state, dt_rank=dt_rank,
+                               d_conv=d_conv, n_classes=n_classes)
+    print(f"classifier d_inner={d_inner} d_state={d_state}", flush=True)
+    w = dg.make_classifier(shape, 31)
+    lens = np.array([0, 1, 2, 3, 4, 5, 15, 16, 17, 31, 32, 33, 48, 49, 70, 77], np.int32)   # (the last one is clamped to 70)
+    tokens = dg._rng(31, 52).integers(0, shape.vocab, size=(len(lens), 70), dtype=np.int32)
+    ids, logits = _run(shape, w, tokens, lens)
+    assert _check(shape, w, tokens, lens, ids, logits) <= 1
+
+
 def test_padding_is_ignored_and_batch_position_does_not_matter():
     shape = dg.CLASSIFIER_TINY
     w = dg.make_classifier(shape, 5)
