@@ -40,6 +40,19 @@ __device__ __forceinline__ int row16_max(int v)
     v = max(v, dpp_i<0x140>(v));
     return v;
 }
+__device__ __forceinline__ float row16_maxf(float v)
+{
+    v = fmaxf(v, dpp_f<0xB1>(v));
+    v = fmaxf(v, dpp_f<0x4E>(v));
+    v = fmaxf(v, dpp_f<0x141>(v));
+    v = fmaxf(v, dpp_f<0x140>(v));
+    return v;
+}
+__device__ __forceinline__ float wave_max_dpp(float v)
+{
+    v = row16_maxf(v);
+    return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
+}
 // smallest value over the wave's 64 lanes (every lane gets it)
 __device__ __forceinline__ int wave_min_i(int v)
 {
@@ -1490,6 +1503,16 @@ __device__ __forceinline__ void block_argmax_rows(float &v, int &idx, FastScratc
     row16_argmax(v, idx);
 }
 template <int RT>
+__device__ __forceinline__ float block_max_rows(float v, FastScratch *fs)
+{
+    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
+    v = wave_max_dpp(v);
+    lds_barrier();
+    if (l == 0) fs->red[w] = v;
+    lds_barrier();
+    return row16_maxf(fs->red[l & (RT / WAVE - 1)]);
+}
+template <int RT>
 __device__ __forceinline__ float block_sum_rows(float v, FastScratch *fs)
 {
     const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
@@ -1511,26 +1534,34 @@ __device__ __forceinline__ void row_load(const float *row, int V, float fill, Ro
     }
 }
 
-// max, lowest-index argmax and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
+// max, lowest-index argmax (T == 0 only) and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
 // -3e38 past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
 // e(x) / z need no second exponential.
 template <int RT, int NSEG>
 __device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
 {
-    float bv = -3.0e38f;
-    int bi = 0x7fffffff;
+    if (invT > 0.f) { // (uniform) sampling needs the maximum alone: a third of the instructions
+        float bv = -3.0e38f;
 #pragma unroll
-    for (int it = 0; it < NSEG; it++) {
-        const int v = it * RT + threadIdx.x;
-        const float4 f = r.f[it];
-        if (f.x > bv) { bv = f.x; bi = 4 * v; }
-        if (f.y > bv) { bv = f.y; bi = 4 * v + 1; }
-        if (f.z > bv) { bv = f.z; bi = 4 * v + 2; }
-        if (f.w > bv) { bv = f.w; bi = 4 * v + 3; }
+        for (int it = 0; it < NSEG; it++) bv = fmaxf(bv, fmaxf(fmaxf(r.f[it].x, r.f[it].y), fmaxf(r.f[it].z, r.f[it].w)));
+        mx = block_max_rows<RT>(bv, fs);
+        am = 0;
+    } else {
+        float bv = -3.0e38f;
+        int bi = 0x7fffffff;
+#pragma unroll
+        for (int it = 0; it < NSEG; it++) {
+            const int v = it * RT + threadIdx.x;
+            const float4 f = r.f[it];
+            if (f.x > bv) { bv = f.x; bi = 4 * v; }
+            if (f.y > bv) { bv = f.y; bi = 4 * v + 1; }
+            if (f.z > bv) { bv = f.z; bi = 4 * v + 2; }
+            if (f.w > bv) { bv = f.w; bi = 4 * v + 3; }
+        }
+        block_argmax_rows<RT>(bv, bi, fs);
+        mx = bv;
+        am = bi;
     }
-    block_argmax_rows<RT>(bv, bi, fs);
-    mx = bv;
-    am = bi;
     z = 1.f;
     if (invT > 0.f) {
         float zl = 0.f;
@@ -1559,26 +1590,16 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
     // tree; every thread works out the total Z, the segment holding u * Z and the sum before it for itself
     // (no single-thread phase), then one block-wide scan of that segment's float4 sums places the element.
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
-    int lastp = -1;
     float loc[NSEG];
 #pragma unroll
     for (int it = 0; it < NSEG; it++) {
-        const int v = it * RT + threadIdx.x;
         const float4 f = w.f[it];
-        if (f.x > 0.f) lastp = 4 * v;
-        if (f.y > 0.f) lastp = 4 * v + 1;
-        if (f.z > 0.f) lastp = 4 * v + 2;
-        if (f.w > 0.f) lastp = 4 * v + 3;
         loc[it] = wave_sum_dpp(((f.x + f.y) + f.z) + f.w);
     }
-    lastp = row16_max(lastp);
-    lastp = max(max(__builtin_amdgcn_readlane(lastp, 0), __builtin_amdgcn_readlane(lastp, 16)),
-                max(__builtin_amdgcn_readlane(lastp, 32), __builtin_amdgcn_readlane(lastp, 48)));
     lds_barrier(); // the scratch may still be in use by a previous call
     if (lane == 0) {
 #pragma unroll
         for (int it = 0; it < NSEG; it++) fs->wsum[wv][it] = loc[it];
-        fs->redi[wv] = lastp;
     }
     if (threadIdx.x == 0) {
         fs->pick = 0x7fffffff;
@@ -1589,7 +1610,6 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
     float seg[NSEG];
 #pragma unroll
     for (int it = 0; it < NSEG; it++) seg[it] = sum_waves<RT / WAVE>(fs->wsum[lane & (RT / WAVE - 1)][it]);
-    const int lp = max(row16_max(fs->redi[lane & (RT / WAVE - 1)]), 0); // last index with a positive weight (0 if there is none)
     float Z = 0.f;
 #pragma unroll
     for (int it = 0; it < NSEG; it++)
@@ -1633,7 +1653,18 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
     int pick = fs->pick;
     // rounding left every running sum of the chosen segment at or below the target: its last index of positive
     // weight; no segment chosen (u * Z not below Z): the last one of the row
-    if (pick == 0x7fffffff) pick = sit >= 0 && fs->seg_last >= 0 ? min(fs->seg_last, V - 1) : lp;
+    if (pick == 0x7fffffff) { // (uniform, rare)
+        if (sit >= 0 && fs->seg_last >= 0) pick = min(fs->seg_last, V - 1);
+        else { // last index of the row with a positive weight (0 if there is none)
+            int lastp = -1;
+#pragma unroll
+            for (int it = 0; it < NSEG; it++) lastp = max(lastp, last_positive(w.f[it], 4 * (it * RT + (int)threadIdx.x)));
+            lastp = wave_max_i(lastp);
+            if (lane == 0) fs->redi[wv] = lastp;
+            lds_barrier();
+            pick = max(row16_max(fs->redi[lane & (RT / WAVE - 1)]), 0);
+        }
+    }
     lds_barrier();
     return pick;
 }
@@ -2141,11 +2172,12 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 //   verify_pick_wide_kernel   one block per sequence: the slice that holds u * Z is searched for the token; commit.
 // Bound: one read of all rows.  The caller's workspace is three floats per row, so what a row's blocks could hand on is
 // limited to that: a row's statistics come from one block, and the slice masses (gamma + 1 per sequence) take the
-// argmax entries, which sampling does not use.  A block keeps 8 float4 per thread in flight; 512 threads when there are
+// argmax entries, which sampling does not use.  A block keeps two batches of 4 float4 per thread, one in flight while the
+// other is summed (one batch of 8, maximum and argmax together: 65 us for the first launch at the size below); 512 threads when there are
 // rows enough to put two blocks on every compute unit (64 sequences, gamma 8, 128000 columns: 295 MB).
-// Measured at that size: 102 us for the three launches (3.2 TB/s of logits and q; 455 us with a block per sequence that
+// Measured at that size: 100 us for the three launches (3.2 TB/s of logits and q; 455 us with a block per sequence that
 // ran its rows one after the other, three passes each).
-#define WIDE_U 8
+#define WIDE_U 4
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int V, float T, float *stats)
 {
@@ -2158,31 +2190,44 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
     // sum of exp((x - m) / T), rescaled when a batch of WIDE_U vectors raises m
     float m = -3.0e38f, z = 0.f;
     int am = 0x7fffffff;
-    for (int v0 = threadIdx.x; v0 < nvec; v0 += WIDE_U * THREADS) {
-        float4 f[WIDE_U];
+    float4 fa[WIDE_U], fb[WIDE_U];
+    auto load = [&](int v0, float4 *f) {
 #pragma unroll
         for (int k = 0; k < WIDE_U; k++) {
             const int v = v0 + k * THREADS;
             f[k] = v < nvec ? row[v] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
         }
-        const float m_old = m;
-#pragma unroll
-        for (int k = 0; k < WIDE_U; k++) {
-            const int i = 4 * (v0 + k * THREADS);
-            if (f[k].x > m) { m = f[k].x; am = i; }
-            if (f[k].y > m) { m = f[k].y; am = i + 1; }
-            if (f[k].z > m) { m = f[k].z; am = i + 2; }
-            if (f[k].w > m) { m = f[k].w; am = i + 3; }
-        }
+    };
+    auto take = [&](int v0, const float4 *f) {
         if (invT > 0.f) { // (uniform)
+            const float m_old = m;
             float s = 0.f;
+#pragma unroll
+            for (int k = 0; k < WIDE_U; k++) m = fmaxf(m, fmaxf(fmaxf(f[k].x, f[k].y), fmaxf(f[k].z, f[k].w)));
 #pragma unroll
             for (int k = 0; k < WIDE_U; k++) {
                 s += (expf((f[k].x - m) * invT) + expf((f[k].y - m) * invT)) +
                      (expf((f[k].z - m) * invT) + expf((f[k].w - m) * invT));
             }
             z = m > m_old ? z * expf((m_old - m) * invT) + s : z + s;
+        } else {
+#pragma unroll
+            for (int k = 0; k < WIDE_U; k++) {
+                const int i = 4 * (v0 + k * THREADS);
+                if (f[k].x > m) { m = f[k].x; am = i; }
+                if (f[k].y > m) { m = f[k].y; am = i + 1; }
+                if (f[k].z > m) { m = f[k].z; am = i + 2; }
+                if (f[k].w > m) { m = f[k].w; am = i + 3; }
+            }
         }
+    };
+    constexpr int STEP = WIDE_U * THREADS;
+    load(threadIdx.x, fa);
+    for (int v0 = threadIdx.x; v0 < nvec; v0 += 2 * STEP) {
+        load(v0 + STEP, fb); // (past the row: -inf, exponentials 0)
+        take(v0, fa);
+        if (v0 + 2 * STEP < nvec) load(v0 + 2 * STEP, fa);
+        if (v0 + STEP < nvec) take(v0 + STEP, fb);
     }
     float mx = m;
     block_argmax(mx, am, redv, redi);
@@ -2345,9 +2390,9 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
 // wave per sequence reads its verdicts: accepted prefix, token of the row behind it, commit.
 // Bound: latency of one row's chain (load, max, exponentials, sum, q, scan).  Measured, 32000 columns (before: row
 // statistics in one launch, the decision from a second reading of the deciding row in another): 6 rows 8.1 + 17.9 ->
-// 14.8 + 3.9 us, 192 rows 10.2 + 25.1 -> 21.1 + 4.1, 576 rows 23.2 + 26.7 -> 40.9 + 4.1.
+// 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1, 576 rows 23.2 + 26.7 -> 33.5 + 4.2.
 // EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
-// (6 rows: 15.9 -> 14.8 us); with more rows than units two blocks share one, q is read only where it is needed.
+// (6 rows: 1.1 us); with more rows than units two blocks share one, q is read only where it is needed.
 template <bool EARLY_Q, int RT, int NSEG>
 __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
                                                                   const float *q, const float *u, const int32_t *seq_ids,
