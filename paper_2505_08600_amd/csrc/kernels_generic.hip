@@ -508,9 +508,14 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const T *A, ActView a
 // 256 -> 768 10.4 -> 3.2 us; at one row 344 -> 128 6.3 -> 2.6 us.
 // Needs K % 4 == 0 and 16-byte aligned operands (launch_gemm_generic); everything else takes the kernel above.
 #define GF_WAVES 2
-template <int MODE, int MR>
+// NORM: A is the residual stream, its RMSNorm is part of the launch: every wave multiplies the rows by the gains as it
+// reads them, adds up their squares beside the products and scales its sums by 1 / rms (row_map: source row of output
+// row m).  A norm launch costs the small shapes as much as the GEMM behind it; above 16 rows the waves would repeat too
+// much of it (launch_gemm_f32_norm).  Whole step of the tiny pair, 12 norm launches of 67 fewer: 277 -> 233 us.
+template <int MODE, int MR, bool NORM>
 __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const float *__restrict__ A, WeightSeg w, int M, int N, int K, float *C,
-                                                                      float *__restrict__ Cact)
+                                                                      float *__restrict__ Cact, const float *__restrict__ gain,
+                                                                      const int32_t *row_map, float eps)
 {
     constexpr int U = MR > 8 ? 2 : 4, NM = MODE == GEMM_SWIGLU ? 2 : 1;
     const int n = blockIdx.x * GF_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63, m0 = blockIdx.y * MR;
@@ -525,17 +530,22 @@ __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const floa
     }
     const float *Ar[MR]; // rows past M re-read the last one; never stored
 #pragma unroll
-    for (int m = 0; m < MR; m++) Ar[m] = A + (size_t)min(m0 + m, M - 1) * K;
+    for (int m = 0; m < MR; m++) {
+        const int r = min(m0 + m, M - 1);
+        Ar[m] = A + (size_t)(NORM && row_map ? row_map[r] : r) * K;
+    }
     const size_t o = (size_t)(m0 + lane) * N + n; // lane m finishes row m
     const bool live = lane < MR && m0 + lane < M;
     const float resid = MODE == GEMM_RESID && live ? C[o] : 0.f;
-    float acc[NM][MR];
+    float acc[NM][MR], ss[MR];
 #pragma unroll
-    for (int c = 0; c < NM; c++)
+    for (int m = 0; m < MR; m++) {
+        ss[m] = 0.f;
 #pragma unroll
-        for (int m = 0; m < MR; m++) acc[c][m] = 0.f;
+        for (int c = 0; c < NM; c++) acc[c][m] = 0.f;
+    }
     for (int k0 = 4 * lane; k0 < K; k0 += 256 * U) {
-        float4 wv[U][NM], av[U][MR];
+        float4 wv[U][NM], av[U][MR], gv[U];
 #pragma unroll
         for (int u = 0; u < U; u++) { // (chunks past the end re-read the lane's first one; not multiplied)
             const int k = k0 + 256 * u < K ? k0 + 256 * u : k0;
@@ -543,10 +553,22 @@ __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const floa
             for (int c = 0; c < NM; c++) wv[u][c] = *(const float4 *)(W[c] + k);
 #pragma unroll
             for (int m = 0; m < MR; m++) av[u][m] = *(const float4 *)(Ar[m] + k);
+            if (NORM) gv[u] = *(const float4 *)(gain + k);
         }
 #pragma unroll
         for (int u = 0; u < U; u++)
             if (k0 + 256 * u < K) {
+                if (NORM) {
+#pragma unroll
+                    for (int m = 0; m < MR; m++) {
+                        float4 &a = av[u][m];
+                        ss[m] = fmaf(a.x, a.x, fmaf(a.y, a.y, fmaf(a.z, a.z, fmaf(a.w, a.w, ss[m]))));
+                        a.x *= gv[u].x;
+                        a.y *= gv[u].y;
+                        a.z *= gv[u].z;
+                        a.w *= gv[u].w;
+                    }
+                }
 #pragma unroll
                 for (int c = 0; c < NM; c++)
 #pragma unroll
@@ -568,23 +590,48 @@ __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const floa
             v[c] = lane == m ? t : v[c];
         }
     }
+    if (NORM) {
+        float q = 0.f;
+#pragma unroll
+        for (int m = 0; m < MR; m++) {
+            const float t = wave_sum_dpp(ss[m]);
+            q = lane == m ? t : q;
+        }
+        const float inv = 1.0f / sqrtf(q / (float)K + eps);
+#pragma unroll
+        for (int c = 0; c < NM; c++) v[c] *= inv;
+    }
     if (!live) return;
     if (MODE == GEMM_SWIGLU) Cact[o] = v[0] / (1.0f + expf(-v[0])) * v[NM - 1];
     else C[o] = MODE == GEMM_RESID ? resid + v[0] : v[0];
 }
 
-template <int MODE>
-static void gemm_f32_rows(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, float *Cact)
+template <int MODE, bool NORM>
+static void gemm_f32_rows(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, float *Cact, const float *gain,
+                          const int32_t *row_map, float eps)
 {
     const dim3 block(GF_WAVES * 64);
     const int bx = (N + GF_WAVES - 1) / GF_WAVES;
-#define SD_GF(MR) hipLaunchKernelGGL((gemm_f32_rows_kernel<MODE, MR>), dim3(bx, (M + MR - 1) / MR), block, 0, s, A, w, M, N, K, C, Cact)
+#define SD_GF(MR)                                                                                                            \
+    hipLaunchKernelGGL((gemm_f32_rows_kernel<MODE, MR, NORM>), dim3(bx, (M + MR - 1) / MR), block, 0, s, A, w, M, N, K, C, Cact, gain, \
+                       row_map, eps)
     if (M == 1) SD_GF(1);
     else if (M == 2) SD_GF(2);
     else if (M <= 5) SD_GF(5);
     else if (M <= 8) SD_GF(8);
     else SD_GF(16);
 #undef SD_GF
+}
+
+// RMSNorm of x's rows and the product behind it in one launch; hipErrorNotSupported where the two belong apart.
+hipError_t launch_gemm_f32_norm(hipStream_t s, int mode, const float *x, const float *gain, const int32_t *row_map, float eps, WeightSeg w,
+                                int M, int N, int K, float *C, float *Cact)
+{
+    const uintptr_t addr = (uintptr_t)x | (uintptr_t)gain | (uintptr_t)w.p[0] | (uintptr_t)w.p[1] | (uintptr_t)w.p[2];
+    if (M > 16 || K % 4 != 0 || (addr & 15) || w.tiled || (mode != GEMM_STORE && mode != GEMM_SWIGLU)) return hipErrorNotSupported;
+    if (mode == GEMM_STORE) gemm_f32_rows<GEMM_STORE, true>(s, x, w, M, N, K, C, nullptr, gain, row_map, eps);
+    else gemm_f32_rows<GEMM_SWIGLU, true>(s, x, w, M, N, K, nullptr, Cact, gain, row_map, eps);
+    return hipGetLastError();
 }
 
 // Row-major -> tiled weight order, one 16-byte piece per thread (destination-linear, so stores coalesce).
@@ -633,9 +680,9 @@ hipError_t launch_gemm_generic(hipStream_t s, int dtype, int mode, const void *A
 {
     const uintptr_t addr = (uintptr_t)A | (uintptr_t)w.p[0] | (uintptr_t)w.p[1] | (uintptr_t)w.p[2];
     if (dtype == SD_FP32 && K % 4 == 0 && !(addr & 15) && !w.tiled && !a_av.sm && !c_av.sm) {
-        if (mode == GEMM_STORE) gemm_f32_rows<GEMM_STORE>(s, (const float *)A, w, M, N, K, C, nullptr);
-        else if (mode == GEMM_RESID) gemm_f32_rows<GEMM_RESID>(s, (const float *)A, w, M, N, K, C, nullptr);
-        else gemm_f32_rows<GEMM_SWIGLU>(s, (const float *)A, w, M, N, K, nullptr, (float *)Cact);
+        if (mode == GEMM_STORE) gemm_f32_rows<GEMM_STORE, false>(s, (const float *)A, w, M, N, K, C, nullptr, nullptr, nullptr, 0.f);
+        else if (mode == GEMM_RESID) gemm_f32_rows<GEMM_RESID, false>(s, (const float *)A, w, M, N, K, C, nullptr, nullptr, nullptr, 0.f);
+        else gemm_f32_rows<GEMM_SWIGLU, false>(s, (const float *)A, w, M, N, K, nullptr, (float *)Cact, nullptr, nullptr, 0.f);
         return hipGetLastError();
     }
     if (dtype == SD_BF16) gemm_generic_dispatch<bf16_t>(s, mode, A, a_av, w, M, N, K, C, Cact, c_av);

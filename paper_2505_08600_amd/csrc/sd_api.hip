@@ -821,9 +821,21 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     if (!embed_ready) { ProfScope ps(T_EMBED, s); // embedding gather + the first layer's norm in one launch
     FWD(launch_embed_rmsnorm(s, cf.dtype, m->embed, pv.row_tok, M, d, m->x, m->norm_attn[0], cf.rms_eps, m->abuf, avd)); }
     int pending = 0; // split-K slabs of the previous down projection not yet added to x
+    // fp32 models at few rows: the norms are part of the GEMMs that read them (low-rank updates read the normed rows too)
+    const bool norm32 = cf.dtype == SD_FP32 && M <= 16 && !(g_force_generic & (1 | 16)) && m->lora_n == 0;
+    auto norm_gemm32 = [&](int mode_g, const float *gain, const int32_t *row_map, WeightSeg wg, int rows, int N, float *C, void *Cact) {
+        return norm32 ? launch_gemm_f32_norm(s, mode_g, m->x, gain, row_map, cf.rms_eps, wg, rows, N, d, C, (float *)Cact) : hipErrorNotSupported;
+    };
     for (int l = 0; l < cf.n_layers; l++) {
         void *Kl = (char *)c->kcache[slot] + l * lstride, *Vtl = (char *)c->vcache[slot] + l * lstride;
-        if (l > 0 && !fold) { ProfScope ps(T_RMSNORM, s);
+        WeightSeg wqkv = {{m->wq[l], m->wk[l], m->wv[l]}, d, m->tiled_dd, m->stream_nt};
+        bool qkv_done = false;
+        if (l > 0 && norm32) { ProfScope ps(T_QKV, s);
+            const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[l], nullptr, wqkv, M, 3 * d, m->qkv, nullptr);
+            if (en != hipErrorNotSupported) FWD(en);
+            qkv_done = en == hipSuccess;
+        }
+        if (l > 0 && !fold && !qkv_done) { ProfScope ps(T_RMSNORM, s);
         if (pending)
             FWD(launch_add_rmsnorm(s, cf.dtype, m->x, m->gpart_r, pending, (size_t)M * d, m->norm_attn[l], nullptr, M, d,
                                    cf.rms_eps, m->abuf, avd));
@@ -831,7 +843,6 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             FWD(launch_rmsnorm(s, cf.dtype, m->x, m->norm_attn[l], nullptr, M, d, cf.rms_eps, m->abuf, avd));
         }
         pending = 0;
-        WeightSeg wqkv = {{m->wq[l], m->wk[l], m->wv[l]}, d, m->tiled_dd, m->stream_nt};
         int nq_slabs;
         const float *qkv_src;
         // low-rank adapters (sequences of one batch may use different ones): their update of q, k, v is one more
@@ -846,7 +857,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         qkv_src = m->gpart_q;
         if (!nq_slabs && fold) return sd_fail(SD_EHIP, "forward: QKV shape left the few-row kernels under the split norm");
         if (!nq_slabs) {
-            FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, 3 * d, d, m->qkv, nullptr, av0));
+            if (!qkv_done) FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, 3 * d, d, m->qkv, nullptr, av0));
             nq_slabs = 1;
             qkv_src = m->qkv;
             qkv_in_place = true;
@@ -909,15 +920,21 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
                                   m->lora_rank, m->lora_scale, A1, B1, dst, no_slabs ? 0 : 1));
             if (no_slabs) no_slabs++;
         }
-        if (!fold) { ProfScope ps(T_RMSNORM, s);
+        WeightSeg wgu = {{m->wgate[l], m->wup[l], nullptr}, F, m->tiled_fd, m->stream_nt};
+        bool gu_done = false;
+        if (norm32 && !no_slabs) { ProfScope ps(T_GATEUP, s);
+            const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act);
+            if (en != hipErrorNotSupported) FWD(en);
+            gu_done = en == hipSuccess;
+        }
+        if (!fold && !gu_done) { ProfScope ps(T_RMSNORM, s);
         if (no_slabs)
             FWD(launch_add_rmsnorm(s, cf.dtype, m->x, m->gpart_r, no_slabs, (size_t)M * d, m->norm_ffn[l], nullptr, M, d,
                                    cf.rms_eps, m->abuf, avd));
         else
             FWD(launch_rmsnorm(s, cf.dtype, m->x, m->norm_ffn[l], nullptr, M, d, cf.rms_eps, m->abuf, avd));
         }
-        WeightSeg wgu = {{m->wgate[l], m->wup[l], nullptr}, F, m->tiled_fd, m->stream_nt};
-        { ProfScope ps(T_GATEUP, s);
+        if (!gu_done) { ProfScope ps(T_GATEUP, s);
         hipError_t eg = hipErrorNotSupported;
         if (cf.dtype == SD_BF16 && !(g_force_generic & 1))
             eg = launch_gemm_skinny_bf16(s, GEMM_SWIGLU, m->abuf, avd, wgu, M, F, d, nullptr, 0, 1, m->act,
@@ -944,15 +961,22 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         int n_lm = mode == PLAN_VERIFY ? M : n_seq;
         const ActView avlm = fold ? avd : ActView{m->plane_d, n_lm, sm_d}; // (split norm: the rows stay where the last down projection put them)
         m->last_a_rows = fold ? M : n_lm;
-        if (!fold) { ProfScope ps(T_RMSNORM, s);
+        WeightSeg wl = {{m->lm_head, nullptr, nullptr}, V, m->tiled_lm, m->stream_nt};
+        bool lm_done = false;
+        if (norm32 && !pending) { ProfScope ps(T_LMHEAD, s);
+            const hipError_t en = norm_gemm32(GEMM_STORE, m->final_norm, pv.lm_row, wl, n_lm, V, m->logits, nullptr);
+            if (en != hipErrorNotSupported) FWD(en);
+            lm_done = en == hipSuccess;
+            if (lm_done) m->lm_stats_nb = 0;
+        }
+        if (!fold && !lm_done) { ProfScope ps(T_RMSNORM, s);
         if (pending)
             FWD(launch_add_rmsnorm(s, cf.dtype, m->x, m->gpart_r, pending, (size_t)M * d, m->final_norm, pv.lm_row, n_lm,
                                    d, cf.rms_eps, m->abuf, avlm));
         else
             FWD(launch_rmsnorm(s, cf.dtype, m->x, m->final_norm, pv.lm_row, n_lm, d, cf.rms_eps, m->abuf, avlm));
         }
-        WeightSeg wl = {{m->lm_head, nullptr, nullptr}, V, m->tiled_lm, m->stream_nt};
-        { ProfScope ps(T_LMHEAD, s);
+        if (!lm_done) { ProfScope ps(T_LMHEAD, s);
         const LmStats ls = {lm_invT >= 0.f && V % 32 == 0 ? m->lm_stats : nullptr, lm_invT >= 0.f ? lm_invT : 0.f};
         int ls_done = 0;
         NormFold nf_lm = kNoFold;

@@ -384,6 +384,10 @@ hipError_t launch_rmsnorm(hipStream_t s, int dtype, const float *x, const float 
 hipError_t launch_retile_bf16(hipStream_t s, const void *src, void *dst, int N, int K);
 hipError_t launch_gemm_generic(hipStream_t s, int dtype, int mode, const void *A, ActView a_av, WeightSeg w, int M,
                                int N, int K, float *C, void *Cact, ActView c_av);
+// fp32 models, few rows: RMSNorm of the residual rows (row_map: source row of each) and the GEMM behind it in one launch;
+// hipErrorNotSupported where the caller should run the two itself
+hipError_t launch_gemm_f32_norm(hipStream_t s, int mode, const float *x, const float *gain, const int32_t *row_map, float eps, WeightSeg w,
+                                int M, int N, int K, float *C, float *Cact);
 // (R: rows per plan slot; the rows of a slot hold consecutive positions of one sequence)
 hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                               CtxView cv, int M, int R, int H,
