@@ -881,6 +881,11 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
                                         cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt,
                                         try_oproj ? m->wo[l] : nullptr, d, m->gpart_r, m->gpart_r_floats, &oproj_done);
         }
+        if (cf.dtype == SD_FP32 && G == 1 && nq_slabs == 1 && !(g_force_generic & (1 | 2))) {
+            ProfScope ps(T_ATTN, s);
+            ea = launch_attn_f32_fused(s, qkv_src, m->rope, cf.max_pos, (float *)Kl, (float *)Vtl, pv, cv, R, n_seq, H, hd, c->total_cap, c->max_cap,
+                                       (float *)m->obuf, avd);
+        }
         if (ea == hipErrorNotSupported) {
             { ProfScope ps(T_ROPE, s);
             FWD(launch_rope_append(s, cf.dtype, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, M, R, H, hd, m->rope,

@@ -297,7 +297,7 @@ struct sd_model {
     void *act;      // [planes][max_rows][d_ffn]
     size_t plane_d, plane_f; // element offsets between the planes
     float *logits;  // [max_rows][vocab]
-    float *vstats;  // [max_rows][3] per-row (max, sum of exponentials, argmax) of the verify tail
+    float *vstats;  // [max_rows][3] what the verify tail's first launch hands to the next: per row its verdict, or (wide rows) max, sum of exponentials, argmax
     float *ss_part;  // [32][SD_NORMFOLD_MAX_BLOCKS] per-block sums of squares between a producer and its consumer (see NormFold)
     float *lm_stats; // [max_rows][vocab / 32][3] per-block softmax partials of the last LM head (see LmStats)
     int lm_stats_nb; // blocks per row the last forward's LM head left there (0: none)
@@ -393,9 +393,10 @@ hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_
                               CtxView cv, int M, int R, int H,
                               int hd, const float2 *rope, int max_pos, void *qbuf, ActView q_av, void *Kl, void *Vtl,
                               int64_t total_cap);
-hipError_t launch_attn_generic(hipStream_t s, int dtype, const void *qbuf, ActView q_av, const void *Kl,
-                               const void *Vtl, PlanView pv, CtxView cv, int R, int n_seq, int H, int hd,
-                               int64_t total_cap, int len_upper, void *obuf, ActView o_av);
+hipError_t launch_attn_generic(hipStream_t s, int dtype, const void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
+                               int n_seq, int H, int hd, int64_t total_cap, int len_upper, void *obuf, ActView o_av);
+hipError_t launch_attn_f32_fused(hipStream_t s, const float *qkv, const float2 *rope, int max_pos, float *Kl, float *Vtl, PlanView pv, CtxView cv,
+                                 int R, int n_seq, int H, int hd, int64_t total_cap, int len_upper, float *obuf, ActView o_av);
 // stats / stats_nb: the per-block softmax partials the LM head left (LmStats), stats_nb blocks of 32 columns per
 // row (0: none - the one-block-per-row samplers read the whole row first).  *did_embed: whether the sampler
 // honoured next.embed (only the kernels that work from the partials do).
