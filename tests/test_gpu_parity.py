@@ -1260,6 +1260,39 @@ def test_fp32_row_classes_and_widths_match_oracle(d, hd, F, B, gamma):
     gm.close()
 
 
+def test_fp32_attention_keeps_its_capacity_limit():
+    """The fp32 attention holds scores for a whole capacity in LDS.  Beside the new rows of the fused launch they fit up to
+    40192 tokens (5 rows, head width 64), in the separate launches up to 40576, as before: both capacities and a small
+    one give the same logits, one 64-token granule more is refused."""
+    _say("fp32 attention at its capacity limits")
+    st_ = dg.SHAPES["tiny_target"]
+    w = dg.make_weights(st_, 75, 20.0)
+    gm = api.Model(st_, w, max_rows=32, max_pos=128)
+    gamma, V = 4, st_.vocab
+    prompt = [int(t) for t in dg.make_prompt(75, 0, 37, V)]
+    cand = H.dev(dg.make_prompt(76, 0, gamma, V).reshape(1, gamma).astype(np.int32))
+    na, nx = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    outs = []
+    for cap in (64, 40192, 40256, 40576):
+        ctx = api.Context([cap])
+        ctx.attach(gm)
+        H.gpu_prefill(ctx, [gm], [prompt])
+        api.sd_verify(gm, ctx, None, 1, gamma, 0.0, cand, None, None, na, nx, commit=False)
+        outs.append(gm.last_logits().cpu().numpy())
+        ctx.close()
+    for o in outs[1:]:   # (sums of at most 41 terms in another order: a few 2^-24 of the largest logit per layer)
+        assert np.isfinite(o).all() and np.abs(o - outs[0]).max() < 1e-5 * np.abs(outs[0]).max()
+    ctx = api.Context([40640])
+    ctx.attach(gm)
+    ctx.set_tokens([prompt])
+    with pytest.raises(api.SdError) as ei:
+        api.sd_prefill(gm, ctx, None, 1, len(prompt) - 1)
+    assert ei.value.code == api.SD_ECAP
+    torch.cuda.synchronize()
+    ctx.close()
+    gm.close()
+
+
 @pytest.mark.parametrize("V", [4, 1024, 1028, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
 def test_fp32_draft_sampler_row_shapes_match_oracle(V):
     """The one-block draft sampler at both ends of every block shape (columns per thread and threads): candidates and q of a
