@@ -203,7 +203,8 @@ int sd_verify(sd_model *target, sd_ctx *c, const int32_t *seq_ids /*dev*/, int32
  *   next_token as for sd_verify (q 16-byte aligned);
  *   workspace dev fp32 [3 * n_seq * (gamma+1)]: per-row (max, sum of exponentials, argmax) passed
  *   from the first kernel to the second; contents on entry do not matter.
- * vocab a multiple of 4 in [4, 262144]; 0 <= gamma <= 15.  Only enqueues kernels on `stream`. */
+ * vocab a multiple of 4 in [4, 262144]; 0 <= gamma <= 15; temperature = infinity makes p uniform over the columns that
+ * are not -inf.  Only enqueues kernels on `stream`. */
 int sd_accept(const float *logits, int32_t n_seq, int32_t gamma, int32_t vocab, float temperature,
               const int32_t *cand, const float *q, const float *uniforms, int32_t *n_accepted,
               int32_t *next_token, float *workspace, void *stream);

@@ -67,6 +67,12 @@ __device__ __forceinline__ int wave_max_i(int v)
     return max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
                max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
 }
+// 1 / T of a sampling call.  T = inf is the uniform distribution over the columns that are not masked: the smallest
+// positive factor makes every finite difference vanish and keeps -inf at weight 0 (0 would turn it into a NaN, and reads as
+// "greedy" where a zero factor stands for T == 0).
+__device__ __forceinline__ float inv_temperature(float T) { return T > 0.f ? fmaxf(1.0f / T, SD_MIN_INV_T) : 0.f; }
+// Value that fills a row past its end, where the exponential must be 0: at the largest temperatures a finite one would not do.
+__device__ __forceinline__ float row_filler(float T) { return T > 1e30f ? -INFINITY : -3.0e38f; }
 // Inverse-CDF placement inside one thread's four weights (indices i0 .. i0 + 3), the running sum continued from
 // `cum`: the first index of positive weight whose inclusive sum exceeds the target, 0x7fffffff if there is none.
 // Every thread of a scan evaluates it, whatever its starting sum, and the smallest index wins.  A thread's
@@ -1633,7 +1639,7 @@ __device__ __forceinline__ void row_load(const float *row, int V, float fill, Ro
 }
 
 // max, lowest-index argmax (T == 0 only) and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
-// -3e38 past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
+// row_filler past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
 // e(x) / z need no second exponential.
 template <int RT, int NSEG>
 __device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, FastScratch *fs, float &mx, int &am, float &z)
@@ -1874,10 +1880,10 @@ __global__ __launch_bounds__(RT) void draft_sample_fast_kernel(const float *logi
         return;
     }
     RowRegs<NSEG> r;
-    row_load<RT>(logits + (size_t)j * V, V, -3.0e38f, r);
+    row_load<RT>(logits + (size_t)j * V, V, row_filler(T), r);
     float mx, z;
     int am;
-    row_stats_regs<RT>(r, T > 0.f ? 1.0f / T : 0.f, &fs, mx, am, z);
+    row_stats_regs<RT>(r, inv_temperature(T), &fs, mx, am, z);
     if (T == 0.f) {
         if (threadIdx.x == 0) {
             cand[j * gamma + idx] = am;
@@ -1948,7 +1954,7 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
         if (k == 0) next_forward_first_step(next, j, 0, cs, &ss);
         return;
     }
-    const float invT = 1.0f / T, uj = u[j * gamma + idx];
+    const float invT = inv_temperature(T), uj = u[j * gamma + idx];
     const float *st = stats + (size_t)j * nb * 3;
     // this block's slice of the logits row: requested first, needed only once the maximum and Z are known
     const float *row = logits + (size_t)j * V;
@@ -2106,7 +2112,7 @@ __global__ __launch_bounds__(1024) void draft_sample_kernel(const float *logits,
         }
         return;
     }
-    float invT = 1.0f / T;
+    float invT = inv_temperature(T);
     float z = row_sumexp(row, V, mx, invT, redv);
     float invZ = 1.0f / z;
     float *qrow = q + ((size_t)j * gamma + idx) * V;
@@ -2283,7 +2289,7 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
     __shared__ int redi[32];
     const float4 *row = (const float4 *)(logits + (size_t)blockIdx.x * V);
     const int nvec = V / 4; // (V is a multiple of 4)
-    const float invT = T > 0.f ? 1.0f / T : 0.f;
+    const float invT = inv_temperature(T);
     // thread-local running maximum m (from -3e38: masked columns may lie below it, their exponentials are 0) and the
     // sum of exp((x - m) / T), rescaled when a batch of WIDE_U vectors raises m
     float m = -3.0e38f, z = 0.f;
@@ -2401,7 +2407,7 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
     }
     const float *rows = logits + (size_t)j * (stride_g + 1) * V, *qj = q + (size_t)j * stride_g * V;
     float *st = stats + (size_t)j * (stride_g + 1) * 3;
-    const float invT = 1.0f / T;
+    const float invT = inv_temperature(T);
     const int n_acc = accept_scan(rows, st, gamma, stride_g, V, T, invT, cand + (size_t)j * stride_g, qj,
                                   u + (size_t)j * (stride_g + 1), s_ok);
     const DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
@@ -2437,8 +2443,8 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
     const int n_acc = min(max(n_acc_in[j], 0), gamma);
     const float uu = u[(size_t)j * (stride_g + 1) + gamma];
     DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
-                     n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc], 1.0f / T,
-                     1.0f / st[3 * n_acc + 1]};
+                     n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc],
+                     inv_temperature(T), 1.0f / st[3 * n_acc + 1]};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
     float Z = 0.f;
     for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
@@ -2508,7 +2514,7 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
     float *st = stats + ((size_t)j * (stride_g + 1) + i) * 3;
     if (i > gamma) return; // (uniform) not a live row
     RowRegs<NSEG> r;
-    row_load<RT>(row, V, -3.0e38f, r);
+    row_load<RT>(row, V, row_filler(T), r);
     const int c = i < gamma ? cand[(size_t)j * stride_g + i] : -1;
     const bool c_in = c >= 0 && c < V;
     float lc = 0.f, qc = 1.f, ui = 0.f, uu = 0.f;
@@ -2524,7 +2530,7 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
     const int nvec = (V + 3) / 4;
     RowRegs<NSEG> qr;
     if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, 0.f, qr);
-    const float invT = T > 0.f ? 1.0f / T : 0.f;
+    const float invT = inv_temperature(T);
     float mx, z;
     int am;
     row_stats_regs<RT>(r, invT, &fs, mx, am, z);

@@ -1040,7 +1040,7 @@ extern "C" int sd_draft(sd_model *draft, sd_ctx *c, const int32_t *seq_ids, int3
     if (2 * n_seq > draft->cfg.max_rows) return sd_fail(SD_ECAP, "sd_draft: 2*n_seq exceeds the model's max_rows");
     hipStream_t s = (hipStream_t)stream;
     const sd_model_config &cf = draft->cfg;
-    const float lm_invT = temperature > 0.f ? 1.0f / temperature : 0.f;
+    const float lm_invT = temperature > 0.f ? std::max(1.0f / temperature, SD_MIN_INV_T) : 0.f;
     int embedded = 0; // the previous sampler has run the first step of this forward
     for (int i = 0; i < gamma; i++) {
         if (i == 0) rc = forward(draft, c, slot, s, PLAN_CATCHUP, 2, n_seq, seq_ids, 0, nullptr, gamma, 0, true, 1, false, false, lm_invT);

@@ -11,6 +11,7 @@
 #define SD_MAX_SLOTS 8
 #define SD_MAX_GAMMA 15
 #define SD_ATTN_MAX_SPLITS 32
+#define SD_MIN_INV_T 1.4e-45f // 1 / T at T = inf (see inv_temperature)
 
 // ---------------------------------------------------------------- element types
 struct bf16_t {

@@ -213,6 +213,60 @@ def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1   # (a uniform next to an edge of the CDF)
 
 
+@pytest.mark.parametrize("V", [1024, 1028, 32000, 32772, 100004])
+def test_infinite_temperature_draws_from_the_uniform_distribution(V):
+    """T = inf is the limit of the rule: p = 1 / V whatever the logits are, in rows that fit a block's registers and in
+    wider ones.  Candidate i carries q = 2 / V or 8 / V against u = 1/4 (accepted, rejected); sequence b rejects at place b."""
+    print(f"infinite temperature V={V}", flush=True)
+    gamma, T = 3, float("inf")
+    B = gamma + 2
+    rng = np.random.default_rng(V)
+    logits = rng.normal(0, 3, (B, gamma + 1, V)).astype(np.float32)
+    cand = rng.integers(0, V, (B, gamma)).astype(np.int32)
+    q = np.zeros((B, gamma, V), np.float32)
+    u = np.full((B, gamma + 1), 0.25, np.float32)
+    u[:, gamma] = [0.011, 0.27, 0.5003, 0.713, 0.986]
+    for b in range(B):
+        for i in range(gamma):
+            q[b, i] = oracle.softmax_T(rng.normal(0, 1, V).astype(np.float32), 1.0)
+            q[b, i, cand[b, i]] = np.float32((8.0 if i == b else 2.0) / V)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.zeros(3 * B * (gamma + 1), device="cuda")
+    api.sd_accept(dev(logits), gamma, T, dev(cand), dev(q), dev(u), na, nx, ws)
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert na_h.tolist() == [min(b, gamma) for b in range(B)]
+    check_against_oracle(logits, q, cand, u, T, na_h, nx_h)
+    # masked columns stay out of it: a draw from the first half alone, index u V / 2 (sums of V terms: 1e-6 of them)
+    half = V // 2
+    logits[:, 0, half:] = -np.inf
+    api.sd_accept(dev(logits[:, :1]), 0, T, None, None, dev(u[:, gamma:]), na, nx, ws)
+    torch.cuda.synchronize()
+    assert np.abs(nx.cpu().numpy() - np.floor(u[:, gamma].astype(np.float64) * half)).max() <= 1 + 1e-6 * V
+
+
+@pytest.mark.parametrize("dtype", [dg.FP32, dg.BF16])
+def test_draft_at_infinite_temperature_is_uniform(dtype):
+    """The samplers of the draft phase at T = inf: q = 1 / V and the candidate at u V, in both data types."""
+    print(f"draft at infinite temperature dtype={dtype}", flush=True)
+    shape = dg.ModelShape("t_inf", 1, 128, 2, 64, 384, 2048, dtype)
+    m = api.Model(shape, dg.make_weights(shape, 3, 1.0), max_rows=16, max_pos=64)
+    ctx = api.Context([32])
+    ctx.attach(m)
+    ctx.set_tokens([[5, 9, 77]])
+    api.sd_prefill(m, ctx, None, 1, 2)
+    u = np.array([[0.1, 0.77]], np.float32)
+    cand = torch.zeros((1, 2), dtype=torch.int32, device="cuda")
+    q = torch.zeros((1, 2, shape.vocab), device="cuda")
+    api.sd_draft(m, ctx, None, 1, 2, float("inf"), torch.from_numpy(u).cuda(), cand, q)
+    ctx.sync()
+    assert np.abs(q.cpu().numpy() * shape.vocab - 1.0).max() < 1e-5
+    assert np.abs(cand.cpu().numpy() - np.floor(u * shape.vocab)).max() <= 1
+    ctx.close()
+    m.close()
+
+
 @pytest.mark.parametrize("V", [1024, 32000, 50000])
 def test_greedy_rows_with_equal_maxima_take_the_lowest_index(V):
     """T = 0: every logits row holds its largest value two to four times, at positions in different threads, waves
