@@ -2270,7 +2270,7 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 
 // ---------------------------------------------------------------- verify tail
 // Fused vocabulary softmax + accept scan + residual + resample.  Rows of more than ROW_NSEG * ROW_THREADS * 4 = 32768
-// columns do not fit a block's registers; they take three launches:
+// columns do not fit a block's registers; they take three launches (two where there is nothing to accept or nothing to draw):
 //   verify_stats_wide_kernel  one block per logits row, one pass: (max, sum of exponentials, argmax);
 //   verify_mass_wide_kernel   the acceptance tests, then the mass of one slice of the deciding row per block;
 //   verify_pick_wide_kernel   one block per sequence: the slice that holds u * Z is searched for the token; commit.
@@ -2428,10 +2428,12 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
 }
 
 // T > 0.  One block per sequence: the slice whose masses pass u * Z, searched with the rule of block_pick_cdf (segments
-// of 1024 vectors, then a scan of the segment that holds the target).
+// of 1024 vectors, then a scan of the segment that holds the target).  Without candidates (gamma == 0) there is one slice,
+// the whole row: its masses are left to block_pick_cdf and no launch before this one adds them up (one row of 32772
+// / 128000 / 262144 columns, whole call: 34 / 86 / 158 us with that launch, 27 / 65 / 118 without).
 __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *logits, const float *stats, int gamma, int V, float T,
                                                                 const int32_t *cand, const float *q, const float *u,
-                                                                const int32_t *seq_ids, const int32_t *n_acc_in,
+                                                                const int32_t *seq_ids, int32_t *n_acc_io,
                                                                 int32_t *next_out, int commit, CtxView cv)
 {
     __shared__ PickScratch ps;
@@ -2440,16 +2442,18 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
     if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
     const float *rows = logits + (size_t)j * (stride_g + 1) * V;
     const float *st = stats + (size_t)j * (stride_g + 1) * 3;
-    const int n_acc = min(max(n_acc_in[j], 0), gamma);
+    const int n_acc = stride_g ? min(max(n_acc_io[j], 0), gamma) : 0;
     const float uu = u[(size_t)j * (stride_g + 1) + gamma];
     DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
                      n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc],
                      inv_temperature(T), 1.0f / st[3 * n_acc + 1]};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
     float Z = 0.f;
-    for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
+    if (stride_g)
+        for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
     int next;
-    if (w.q && !(Z > 0.f)) { // numerically empty residual: draw from p
+    if (!stride_g) next = block_pick_cdf(w, V, uu, &ps, nullptr);
+    else if (w.q && !(Z > 0.f)) { // numerically empty residual: draw from p
         w.q = nullptr;
         next = block_pick_cdf(w, V, uu, &ps, nullptr);
     } else {
@@ -2478,6 +2482,7 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
         next = block_pick_range(w, v_begin, min(nvec, v_begin + per), V, base, target, &ps);
     }
     if (threadIdx.x == 0) {
+        if (!stride_g) n_acc_io[j] = 0;
         next_out[j] = next;
         if (commit) {
             if (bb >= 0 && bb < cv.B) commit_one(cv, bb, gamma, cand + (size_t)j * stride_g, n_acc, next);
@@ -2636,8 +2641,9 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
     if (n_rows >= 512) hipLaunchKernelGGL(verify_stats_wide_kernel<512>, dim3(n_rows), dim3(512), 0, s, logits, V, T, stats);
     else hipLaunchKernelGGL(verify_stats_wide_kernel<1024>, dim3(n_rows), dim3(1024), 0, s, logits, V, T, stats);
     if (T > 0.f) {
-        hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(n_rows), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
-                           u, seq_ids, n_acc, cv);
+        if (gamma > 0)
+            hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(n_rows), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
+                               u, seq_ids, n_acc, cv);
         hipLaunchKernelGGL(verify_pick_wide_kernel, dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, seq_ids,
                            n_acc, next_tok, commit, cv);
     } else // (greedy: the decision needs the argmax entries only)
