@@ -2499,10 +2499,11 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
 // wave per sequence reads its verdicts: accepted prefix, token of the row behind it, commit.
 // Bound: latency of one row's chain (load, max, exponentials, sum, q, scan).  Measured, 32000 columns (before: row
 // statistics in one launch, the decision from a second reading of the deciding row in another): 6 rows 8.1 + 17.9 ->
-// 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1, 576 rows 23.2 + 26.7 -> 33.5 + 4.2.
+// 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1.
 // EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
 // (6 rows: 1.1 us); with more rows than units two blocks share one, q is read only where it is needed.
-template <bool EARLY_Q, int RT, int NSEG>
+// DRAW false (more rows, see launch_verify_tail): the row settles its test only and leaves (max, sum, accepted) for verify_draw_kernel.
+template <bool DRAW, bool EARLY_Q, int RT, int NSEG>
 __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
                                                                   const float *q, const float *u, const int32_t *seq_ids,
                                                                   CtxView cv, float *stats)
@@ -2546,7 +2547,7 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
         ok = i < gamma && c == am;
     } else {
         if (c_in) ok = ui < expf((lc - mx) * invT) / z / fmaxf(qc, 1.17549435e-38f);
-        if (!ok) { // (uniform) the draw this row would make: from max(0, p - q), behind the last candidate from p
+        if (DRAW && !ok) { // (uniform) the draw this row would make: from max(0, p - q), behind the last candidate from p
             const float invZ = 1.0f / z;
             row_scale(r, invZ);
             if (i < gamma) {
@@ -2585,9 +2586,61 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
         }
     }
     if (threadIdx.x == 0) {
-        st[0] = __int_as_float(ok ? 1 : 0);
-        st[1] = __int_as_float(pick);
-        st[2] = __int_as_float(am);
+        st[0] = DRAW ? __int_as_float(ok ? 1 : 0) : mx;
+        st[1] = DRAW ? __int_as_float(pick) : z;
+        st[2] = __int_as_float(DRAW ? am : ok ? 1 : 0);
+    }
+}
+
+// Behind verify_rows_kernel<false>: one block per sequence finds the accepted prefix and draws from the row behind it, which
+// it reads again with the maximum and sum that are known.
+template <int RT, int NSEG>
+__global__ __launch_bounds__(RT, 4) void verify_draw_kernel(const float *logits, const float *stats, int gamma, int V, float T,
+                                                            const int32_t *cand, const float *q, const float *u,
+                                                            const int32_t *seq_ids, int32_t *n_acc_out, int32_t *next_out,
+                                                            int commit, CtxView cv)
+{
+    __shared__ FastScratch fs;
+    const int j = blockIdx.x, lane = threadIdx.x % WAVE, stride_g = gamma;
+    const int bb = seq_ids ? seq_ids[j] : j;
+    if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
+    const float *st = stats + (size_t)j * (stride_g + 1) * 3;
+    const int ok = lane < gamma ? __float_as_int(st[3 * lane + 2]) : 0;
+    const int n_acc = __ffsll((unsigned long long)~__ballot(ok)) - 1; // (lane gamma <= SD_MAX_GAMMA always votes 0)
+    const float uu = u[(size_t)j * (stride_g + 1) + gamma], invT = inv_temperature(T);
+    const float mx = st[3 * n_acc], invZ = 1.0f / st[3 * n_acc + 1];
+    RowRegs<NSEG> r, w;
+    row_load<RT>(logits + ((size_t)j * (stride_g + 1) + n_acc) * V, V, row_filler(T), r);
+    if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, 0.f, w);
+#pragma unroll
+    for (int it = 0; it < NSEG; it++) {
+        float4 &f = r.f[it];
+        f.x = expf((f.x - mx) * invT) * invZ;
+        f.y = expf((f.y - mx) * invT) * invZ;
+        f.z = expf((f.z - mx) * invT) * invZ;
+        f.w = expf((f.w - mx) * invT) * invZ;
+    }
+    float mass = 0.f;
+    int next = 0;
+    if (n_acc < gamma) { // (uniform)
+#pragma unroll
+        for (int it = 0; it < NSEG; it++) {
+            float4 &f = w.f[it];
+            f.x = fmaxf(r.f[it].x - f.x, 0.f);
+            f.y = fmaxf(r.f[it].y - f.y, 0.f);
+            f.z = fmaxf(r.f[it].z - f.z, 0.f);
+            f.w = fmaxf(r.f[it].w - f.w, 0.f);
+        }
+        next = pick_regs<RT>(w, V, uu, &fs, &mass);
+    }
+    if (!(mass > 0.f)) next = pick_regs<RT>(r, V, uu, &fs, nullptr); // everything accepted, or a numerically empty residual: draw from p
+    if (threadIdx.x == 0) {
+        n_acc_out[j] = n_acc;
+        next_out[j] = next;
+        if (commit) {
+            if (bb >= 0 && bb < cv.B) commit_one(cv, bb, gamma, cand + (size_t)j * stride_g, n_acc, next);
+            else atomicOr(cv.status, 4);
+        }
     }
 }
 
@@ -2627,11 +2680,25 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
 {
     const int n_rows = n_seq * (gamma + 1);
     if (V <= ROW_NSEG * ROW_THREADS * 4) {
-#define SD_VERIFY_ROWS(EARLY, RT, NSEG)                                                                                      \
-    hipLaunchKernelGGL((verify_rows_kernel<EARLY, RT, NSEG>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, q, u, \
-                       seq_ids, cv, stats)
-#define SD_VERIFY_ROWS_EARLY(RT, NSEG) SD_VERIFY_ROWS(true, RT, NSEG)
-#define SD_VERIFY_ROWS_LATE(RT, NSEG) SD_VERIFY_ROWS(false, RT, NSEG)
+#define SD_VERIFY_ROWS(DRAW, EARLY, RT, NSEG)                                                                                \
+    hipLaunchKernelGGL((verify_rows_kernel<DRAW, EARLY, RT, NSEG>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, \
+                       q, u, seq_ids, cv, stats)
+#define SD_VERIFY_ROWS_EARLY(RT, NSEG) SD_VERIFY_ROWS(true, true, RT, NSEG)
+#define SD_VERIFY_ROWS_LATE(RT, NSEG) SD_VERIFY_ROWS(true, false, RT, NSEG)
+#define SD_VERIFY_ROWS_TEST(RT, NSEG) SD_VERIFY_ROWS(false, false, RT, NSEG)
+#define SD_VERIFY_DRAW(RT, NSEG)                                                                                             \
+    hipLaunchKernelGGL((verify_draw_kernel<RT, NSEG>), dim3(n_seq), dim3(RT), 0, s, logits, stats, gamma, V, T, cand, q, u,  \
+                       seq_ids, n_acc, next_tok, commit, cv)
+        // More rows than compute units: a draw made in vain takes the unit from a row that still waits for one, so the rows
+        // settle their tests only and one block per sequence draws.  Measured, 32000 columns, draws in every row / in the
+        // deciding row (us; all candidates rejected, three in four accepted, all accepted): 288 rows 28.0 / 24.5, 26.8 / 24.9,
+        // 21.2 / 22.8; 576 rows 41.6 / 31.4, 34.8 / 31.7, 29.0 / 29.6; 4096 rows 225 / 107, 152 / 106, 127 / 102.  With one
+        // candidate every other row draws anyway (512 sequences: 53.9 / 58.1, 44.4 / 51.9, 40.3 / 50.3).
+        if (T > 0.f && gamma > 1 && n_rows > 256) {
+            SD_ROW_SHAPES(V, SD_VERIFY_ROWS_TEST);
+            SD_ROW_SHAPES(V, SD_VERIFY_DRAW);
+            return hipGetLastError();
+        }
         if (n_rows <= 256) SD_ROW_SHAPES(V, SD_VERIFY_ROWS_EARLY);
         else SD_ROW_SHAPES(V, SD_VERIFY_ROWS_LATE);
         hipLaunchKernelGGL(verify_finish_kernel, dim3(n_seq), dim3(WAVE), 0, s, stats, gamma, T, cand, seq_ids, n_acc, next_tok, commit,

@@ -213,6 +213,28 @@ def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1   # (a uniform next to an edge of the CDF)
 
 
+@pytest.mark.parametrize("V,gamma,copies", [(1024, 15, 1), (1028, 15, 1), (8192, 15, 1), (16384, 2, 22), (32000, 15, 1),
+                                            (32768, 2, 22), (8192, 1, 44), (16384, 1, 44)])
+def test_more_rows_than_compute_units(V, gamma, copies):
+    """257 rows and more: from two candidates on one block per sequence draws behind the rows' tests, with one candidate
+    every row draws for itself (both read q late).  Verdicts and draws of every sequence against the oracle."""
+    print(f"many rows V={V} gamma={gamma}", flush=True)
+    logits, q, cand, u, expect = row_verdict_case(V, gamma)
+    tile = lambda a: np.ascontiguousarray(np.concatenate([a] * copies))
+    logits, q, cand, u, expect = tile(logits), tile(q), tile(cand), tile(u), expect * copies
+    B = len(expect)
+    assert B * (gamma + 1) > 256
+    u[:, gamma] = dg.make_uniforms(29, dg.VERIFY_STREAM, 0, 0, B)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * B * (gamma + 1),), float("nan"), device="cuda")
+    api.sd_accept(dev(logits), gamma, 1.0, dev(cand), dev(q), dev(u), na, nx, ws)
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert na_h.tolist() == expect
+    assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1 + B // 50
+
+
 @pytest.mark.parametrize("V", [1024, 1028, 32000, 32772, 100004])
 def test_infinite_temperature_draws_from_the_uniform_distribution(V):
     """T = inf is the limit of the rule: p = 1 / V whatever the logits are, in rows that fit a block's registers and in

@@ -165,6 +165,28 @@ def test_counts_follow_equation_1_step_by_step(shapes, dtype, T):
     pair.close()
 
 
+@pytest.mark.parametrize("V,B,G", [(32772, 4, 3), (1024, 52, 4)])
+def test_counts_in_wide_rows_and_in_large_batches(V, B, G):
+    """Counts per sequence in the other two forms of the acceptance rule: rows above 32768 columns, whose slices follow the
+    call's row slots and not the sequence's own count, and more than 256 rows, where one block per sequence draws."""
+    import dataclasses
+    print(f"per-sequence counts V={V} B={B} gamma={G}", flush=True)
+    st = dataclasses.replace(dg.SHAPES["tiny_target"], vocab=V, n_layers=1, name=f"policy_{V}")
+    wt = dg.make_weights(st, 81, 20.0)
+    pair = H.Pair(st, st, 81, target_weights=wt, draft_weights=dg.perturbed_copy(wt, st, seed=82, rel=0.1), max_rows=B * (G + 1))
+    prompts = [dg.make_prompt(81, b, 3 + b % 7, V) for b in range(B)]
+
+    def gamma_fn(k, history, ctx):
+        counts = [(b + k) % (G + 1) for b in range(B)]
+        ctx.policy_set(counts)
+        return counts
+
+    flagged, used = _run(pair, prompts, G, 1.0, 2, 81, gamma_fn, dg.FP32)
+    print(f"  flagged={flagged}", flush=True)
+    assert flagged <= 1 + B // 50
+    pair.close()
+
+
 def test_policy_argument_errors():
     ctx = api.Context([32, 32])
     L = api.lib()
