@@ -381,6 +381,10 @@ int64_t sd_debug_layout_index(int32_t kind, int64_t a, int64_t b, int64_t c, int
  * [4] = K splits, [5] = blocks on the busiest of the 8 dies (column tile t runs on die t mod 8).
  * Returns 0, or SD_EINVAL when the kernel does not take the shape. */
 int sd_debug_gemm_plan(int32_t mode, int32_t m, int32_t n, int32_t k, int32_t n_per_seg, int32_t plan[6]);
+/* Host-only (no GPU call): K splits of a bf16 GEMM C[m][n] whose partial sums the next kernel adds (QKV, O, down).
+ * folded: the launch is part of a split norm (option "norm_fold"); extra_slabs: slabs appended behind the GEMM's own (a
+ * low-rank update), which share the 8 a consumer adds.  SD_EINVAL for arguments out of range. */
+int32_t sd_debug_gemm_splits(int32_t m, int32_t n, int32_t k, int32_t n_per_seg, int32_t folded, int32_t extra_slabs);
 /* Measurement helper: one kernel that only reads `bytes` bytes (16-byte aligned, dev) once with 16-byte loads,
  * the practical ceiling that the weight-streaming kernels are compared with.  scratch_word: dev uint32, may be
  * written.  Only enqueues on `stream`. */

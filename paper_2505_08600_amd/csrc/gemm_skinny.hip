@@ -673,7 +673,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16
 struct WidePlan {
     int nw, ncol, ks;
 };
-static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks)
+static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks, int max_ks = 8)
 {
     WidePlan best = {0, 0, 1};
     if (M < 9 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || K < 128) return best;
@@ -685,7 +685,7 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
     float best_cost = 0.f;
     for (int nw = 2; nw <= 8; nw += 2) {
         const int ct = nw / nmat, ncol = (N / 16 + ct - 1) / ct;
-        for (int ks = force_ks > 0 ? force_ks : 1; ks <= (force_ks > 0 ? force_ks : mode == GEMM_SWIGLU ? 1 : 8); ks++) {
+        for (int ks = force_ks > 0 ? force_ks : 1; ks <= (force_ks > 0 ? force_ks : mode == GEMM_SWIGLU ? 1 : max_ks); ks++) {
             int kps, ny;
             split_geometry(K, ks, &kps, &ny);
             if (force_ks <= 0 && ks > 1 && (ny != ks || kps < 256)) continue;
@@ -873,8 +873,9 @@ static int tile_ks(int mode, int M, int N, int K, int n_per_seg)
     return ny;
 }
 
-// Number of K splits the launcher will use for this shape (the caller sizes and reduces the partials).
-int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg)
+// Number of K splits the launcher will use for this shape (the caller sizes and reduces the partials).  folded: the launch is
+// part of a split norm, which stays on the K-split kernel; max_ks: slabs the caller has room for.
+int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded, int max_ks)
 {
     if (mode == GEMM_SWIGLU || K < 128 || K % 128 != 0) return 1; // (the launcher rejects such K)
     int kps, ny;
@@ -884,9 +885,11 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg)
     }
     const int steps = K / 128;
     int ks;
-    const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0);
-    if (wp.nw) return wp.ks;
-    if (M <= 32) { // K-split kernel: 32 columns per block, each wave at least 2 steps
+    if (!folded) {
+        const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0, max_ks);
+        if (wp.nw) return wp.ks;
+    }
+    if (M <= 32) { // K-split kernel: 32 columns per block, a step for each of its four waves
         const int blocks = N / 32;
         ks = steps >= 16 ? 2 : 1; // measured: two half-length blocks per tile stream faster than one
         while (blocks * ks < 256 && ks < 8 && steps / (ks * 2) >= 4) ks *= 2;

@@ -742,6 +742,20 @@ static hipError_t gemm_generic(sd_model *m, hipStream_t s, int mode, const void 
     return launch_gemm_generic(s, m->cfg.dtype, mode, A, a_av, w, M, N, K, C, Cact, c_av);
 }
 
+// K splits of a streamed GEMM behind whose slabs the caller appends extra_slabs of its own (a low-rank update): consumers
+// add up to 8.
+static int stream_splits(int M, int N, int K, int n_per_seg, bool folded, int extra_slabs)
+{
+    const int ns = gemm_skinny_splits(GEMM_STORE, M, N, K, n_per_seg, folded, 8 - extra_slabs);
+    return ns + extra_slabs > 8 ? 1 : ns;
+}
+
+extern "C" int32_t sd_debug_gemm_splits(int32_t m, int32_t n, int32_t k, int32_t n_per_seg, int32_t folded, int32_t extra_slabs)
+{
+    if (m < 1 || n < 1 || k < 1 || n_per_seg < 1 || extra_slabs < 0 || extra_slabs > 7) return sd_fail(SD_EINVAL, "sd_debug_gemm_splits: bad argument");
+    return stream_splits(m, n, k, n_per_seg, folded != 0, extra_slabs);
+}
+
 // Weight-streaming path for a GEMM whose fp32 result is consumed as split-K slabs.  Returns the number
 // of slabs written to `slabs` (slab stride M*N floats), 0 if the shape is outside the kernel's domain.
 static const NormFold kNoFold = {nullptr, 0, 0.f, nullptr, nullptr, nullptr, nullptr};
@@ -752,9 +766,8 @@ static int stream_gemm(sd_model *m, hipStream_t s, const void *A, ActView a_av, 
     if (ls_done) *ls_done = 0;
     *err = hipSuccess;
     if (m->cfg.dtype != SD_BF16 || (g_force_generic & 1)) return 0;
-    int ns = force_splits > 0 ? force_splits : gemm_skinny_splits(GEMM_STORE, M, N, K, w.n_per_seg);
-    // (extra_slabs: slabs the caller appends after the GEMM's own, e.g. a low-rank update)
-    if ((size_t)(ns + extra_slabs) * M * N > slabs_floats || ns + extra_slabs > 8) ns = 1;
+    int ns = force_splits > 0 ? force_splits : stream_splits(M, N, K, w.n_per_seg, nf.ss_in || nf.x || nf.row_map, extra_slabs);
+    if ((size_t)(ns + extra_slabs) * M * N > slabs_floats) ns = 1;
     if ((size_t)(ns + extra_slabs) * M * N > slabs_floats) return 0;
     const ActView none = {0, 0, 0};
     hipError_t e = launch_gemm_skinny_bf16(s, GEMM_STORE, A, a_av, w, M, N, K, slabs, (size_t)M * N, ns, nullptr, none,

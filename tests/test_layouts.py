@@ -105,3 +105,25 @@ def test_row_blocked_gemm_plans_fit_the_busiest_die_in_one_round():
     # config 5 (7B, M = 576): the unsplit QKV launch is one and a half rounds, two splits make three full ones
     assert api.gemm_plan(0, 576, 12288, 4096, 4096) == (192, 96, 64, 6, 2, 96)
     assert api.gemm_plan(0, 768, 12288, 4096, 4096)[4] == 1 and api.gemm_plan(0, 1024, 12288, 4096, 4096)[4] == 1   # whole rounds: no split
+
+
+def test_k_splits_follow_the_kernel_that_runs_and_the_slabs_there_is_room_for():
+    """K splits of the few-row GEMMs (host logic only).  A launch that is part of a split norm runs on the K-split kernel,
+    whose four waves share a split's K steps: none may be left without one, and the plan of the wide kernel, which
+    takes the unfolded launches of 9 to 64 rows, must not reach it.  A low-rank update appended behind the slabs costs one of
+    the eight a consumer adds, never the whole K split."""
+    for d in (256, 384, 768, 1024, 2048, 3072, 4096, 5120, 8192):
+        for n in (3 * d, d):
+            at8 = api.gemm_splits(8, n, d, d, folded=True)
+            for m in range(1, 65):
+                if m <= 32:
+                    ks = api.gemm_splits(m, n, d, d, folded=True)
+                    assert ks == at8 and 1 <= ks <= 8       # (the K-split kernel's rule does not depend on the rows)
+                    assert ks == 1 or d // 128 // ks >= 4, (m, n, d, ks)
+                plain, adapted = api.gemm_splits(m, n, d, d), api.gemm_splits(m, n, d, d, extra_slabs=1)
+                assert 1 <= plain <= 8 and 1 <= adapted <= 7
+                if m <= 64:
+                    assert plain == 1 or adapted > 1, (m, n, d, plain, adapted)
+    assert api.gemm_splits(9, 3 * 768, 768, 768, folded=True) == 1
+    assert api.gemm_splits(18, 3 * 1024, 1024, 1024, folded=True) == 2
+    assert api.gemm_splits(0, 768, 768) == api.SD_EINVAL and api.gemm_splits(9, 768, 768, extra_slabs=8) == api.SD_EINVAL
