@@ -405,7 +405,7 @@ int sd_debug_stream_read(const void *buf, size_t bytes, uint32_t *scratch_word, 
  * leaves per-block sums of squares) and the GEMM after them (scales its sums by 1 / rms); the
  * operand is then rounded to its two bf16 terms before the division by rms instead of after.
  * 1 = wherever the shapes allow (bf16, no adapters loaded, widths multiples of 128), 0 = there, and where
- * it is the faster form (the default: up to 8 rows always, up to 32 in narrow models), 2 = never.
+ * it is the faster form (the default: up to 8 rows, up to 10 at widths of 4096 and 8192), 2 = never.
  * option "rope_group": on the split attention path (prefill, long contexts) RoPE + cache append of a bf16 model
  * runs one block per (head, group of up to 16 consecutive rows) with 16-byte stores (1, the default) or one block
  * per row (0); both give the same bits.

@@ -28,8 +28,6 @@
 // verify pass whose linear layers these are); Section 3.1 (LLaMA blocks).
 #include "sd_internal.h"
 
-#include <algorithm>
-
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -700,11 +698,14 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
     return best;
 }
 
-// Does the norm split between producer and consumer GEMM (NormFold) pay at M rows?  Its producers run without a K split in
-// blocks of 16 columns, each of which pulls K x (32 bytes of weights + 4 M of rows) into one compute unit - 10 us at about
-// 430 KB - while the unfused projection is split over the chip and followed by a launch of 4 - 5 us.  Up to 8 rows (hi and lo
-// rows share one operand) the weights dominate and the fold is ahead at every width.
-bool gemm_normfold_pays(int M, int d, int F) { return M <= 8 || (long)std::max(d, F) * (32 + 4 * M) <= 430000; }
+// Does the norm split between producer and consumer GEMM (NormFold) pay at M rows of width d?  Up to 8 rows (hi and lo rows
+// share one operand) the weights dominate and two launches per layer less are ahead.  From 9 rows on the unfolded launches run on
+// the wide kernel and split K over the chip, while a folded projection runs unsplit in blocks that re-read the rows; only
+// where those blocks cover the compute units in one full round does the fold last two rows longer.  Verify pass of two
+// layers, folded / not (us): 4096 wide 229.9 / 233.6 at 8 rows, 248.0 / 253.9 at 9, 254.4 / 255.1 at 10, 263.2 / 257.4 at 11,
+// 297 / 262 at 16, 442 / 311 at 32; 8192 wide 361 / 370 at 9, 380 / 375 at 11; 5120 wide 391 / 331 at 9; 3072 wide 177 / 171 at
+// 9; 768 wide 81.6 / 78.8 at 9, 89.0 / 82.5 at 16, 120 / 96 at 32.
+bool gemm_normfold_pays(int M, int d) { return M <= 8 || (M <= 10 && gemm_normfold_blocks(d) == 256); }
 
 // Block shapes of the row-blocked kernel.  More than 64 rows: 96 rows x 256 columns (4 waves x 4 tiles; chunks
 // of half a K step) - the bytes a block pulls through L2 per MFMA halve against 48 x 128, which is what

@@ -821,7 +821,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     // split between the projection before them and the GEMM after them (NormFold) - seven dependent launches
     // per layer become five.  Needs every GEMM of the forward on the few-row kernels, and rows few enough (gemm_normfold_pays).
     const bool fold = cf.dtype == SD_BF16 && !(g_force_generic & (1 | 16)) && g_norm_fold != 2 && G == 1 && M <= 32 &&
-                      (g_norm_fold == 1 || gemm_normfold_pays(M, d, F)) &&
+                      (g_norm_fold == 1 || gemm_normfold_pays(M, d)) &&
                       m->lora_n == 0 && m->tiled_dd && m->tiled_fd && m->tiled_df && (!want_logits || m->tiled_lm) &&
                       d % 128 == 0 && F % 128 == 0 && V % 16 == 0 && d / 16 <= SD_NORMFOLD_MAX_BLOCKS &&
                       cf.n_layers >= 1;
