@@ -60,6 +60,12 @@ struct ProfScope {
         e1 = prof_event();
         if (e0) (void)hipEventRecord(e0, s);
     }
+    void drop() // nothing was launched (the kernel does not take the shape): no entry
+    {
+        if (e0) g_pool.push_back(e0);
+        if (e1) g_pool.push_back(e1);
+        e0 = e1 = nullptr;
+    }
     ~ProfScope()
     {
         if (!e0 || !e1) return;
@@ -846,6 +852,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (l > 0 && norm32) { ProfScope ps(T_QKV, s);
             const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[l], nullptr, wqkv, M, 3 * d, m->qkv, nullptr);
             if (en != hipErrorNotSupported) FWD(en);
+            else ps.drop();
             qkv_done = en == hipSuccess;
         }
         if (l > 0 && !fold && !qkv_done) { ProfScope ps(T_RMSNORM, s);
@@ -862,15 +869,18 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         // slab for the consumer to add - or is added in place where the GEMM left a single full result
         const bool lora_qkv = m->lora_n > 0 && (m->lora_a[0][l] || m->lora_a[1][l] || m->lora_a[2][l]);
         const bool lora_o = m->lora_n > 0 && m->lora_a[3][l];
-        bool qkv_in_place = false;
-        { ProfScope ps(T_QKV, s);
+        bool qkv_in_place = qkv_done;
+        if (qkv_done) {
+            nq_slabs = 1;
+            qkv_src = m->qkv;
+        } else { ProfScope ps(T_QKV, s);
         nq_slabs = stream_gemm(m, s, m->abuf, avd, wqkv, M, 3 * d, d, m->gpart_q, m->gpart_q_floats, 0, &ge, lora_qkv ? 1 : 0,
                                LmStats{nullptr, 0.f}, nullptr, a_scaled ? nf_consume : kNoFold);
         FWD(ge);
         qkv_src = m->gpart_q;
         if (!nq_slabs && fold) return sd_fail(SD_EHIP, "forward: QKV shape left the few-row kernels under the split norm");
         if (!nq_slabs) {
-            if (!qkv_done) FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, 3 * d, d, m->qkv, nullptr, av0));
+            FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, 3 * d, d, m->qkv, nullptr, av0));
             nq_slabs = 1;
             qkv_src = m->qkv;
             qkv_in_place = true;
@@ -893,11 +903,13 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             ea = launch_attn_fused_bf16(s, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, R, n_seq, H, hd, m->rope,
                                         cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt,
                                         try_oproj ? m->wo[l] : nullptr, d, m->gpart_r, m->gpart_r_floats, &oproj_done);
+            if (ea == hipErrorNotSupported) ps.drop();
         }
         if (cf.dtype == SD_FP32 && G == 1 && nq_slabs == 1 && !(g_force_generic & (1 | 2))) {
             ProfScope ps(T_ATTN, s);
             ea = launch_attn_f32_fused(s, qkv_src, m->rope, cf.max_pos, (float *)Kl, (float *)Vtl, pv, cv, R, n_seq, H, hd, c->total_cap, c->max_cap,
                                        (float *)m->obuf, avd);
+            if (ea == hipErrorNotSupported) ps.drop();
         }
         if (ea == hipErrorNotSupported) {
             { ProfScope ps(T_ROPE, s);
@@ -943,6 +955,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (norm32 && !no_slabs) { ProfScope ps(T_GATEUP, s);
             const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act);
             if (en != hipErrorNotSupported) FWD(en);
+            else ps.drop();
             gu_done = en == hipSuccess;
         }
         if (!fold && !gu_done) { ProfScope ps(T_RMSNORM, s);
@@ -984,6 +997,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (norm32 && !pending) { ProfScope ps(T_LMHEAD, s);
             const hipError_t en = norm_gemm32(GEMM_STORE, m->final_norm, pv.lm_row, wl, n_lm, V, m->logits, nullptr);
             if (en != hipErrorNotSupported) FWD(en);
+            else ps.drop();
             lm_done = en == hipSuccess;
             if (lm_done) m->lm_stats_nb = 0;
         }

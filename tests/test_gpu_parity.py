@@ -1293,6 +1293,50 @@ def test_fp32_attention_keeps_its_capacity_limit():
     gm.close()
 
 
+def _fp32_pass(gm, prompts, gamma, cap, calls):
+    """A context with the prompts prefilled, then calls(ctx); returns what it returns."""
+    ctx = api.Context([cap] * len(prompts))
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    try:
+        return calls(ctx)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+
+
+@pytest.mark.parametrize("cap,force", [(64, 0), (40256, 0), (64, 1)])
+def test_fp32_profile_counts_every_launch_once(cap, force):
+    """Option "profile" counts launches: one per layer and stage of an fp32 verify pass, whether the stage runs in a launch of
+    its own, inside another one, or after the fused attention has declined (a capacity beyond its LDS)."""
+    _say(f"fp32 profile counts cap={cap} force_generic={force}")
+    st_ = dg.SHAPES["tiny_target"]
+    L, gamma = st_.n_layers, 4
+    gm = api.Model(st_, dg.make_weights(st_, 75, 20.0), max_rows=32, max_pos=128)
+    prompt = [int(t) for t in dg.make_prompt(75, 0, 20, st_.vocab)]
+    cand = H.dev(dg.make_prompt(76, 0, gamma, st_.vocab).reshape(1, gamma).astype(np.int32))
+    na, nx = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+
+    def calls(ctx):
+        api.set_option("force_generic", force)
+        api.set_option("profile", 1)
+        try:
+            api.sd_verify(gm, ctx, None, 1, gamma, 0.0, cand, None, None, na, nx, commit=False)
+        finally:
+            api.set_option("profile", 0)
+            api.set_option("force_generic", 0)
+        return {k: v[0] for k, v in api.profile_read().items()}
+
+    n = _fp32_pass(gm, [prompt], gamma, cap, calls)
+    apart = cap > 40192 or force
+    assert {k: n.get(k, 0) for k in ("gemm_qkv", "attention", "gemm_o", "gemm_gateup", "gemm_down")} == dict.fromkeys(
+        ("gemm_qkv", "attention", "gemm_o", "gemm_gateup", "gemm_down"), L)
+    assert n.get("gemm_lmhead", 0) == 1 and n.get("embed", 0) == 1 and n.get("verify_tail", 0) == 1
+    assert n.get("rope_append", 0) == (L if apart else 0)
+    assert n.get("rmsnorm", 0) == (2 * L if force else 0)   # (the first layer's is part of the embedding launch)
+    gm.close()
+
+
 @pytest.mark.parametrize("V", [4, 1024, 1028, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
 def test_fp32_draft_sampler_row_shapes_match_oracle(V):
     """The one-block draft sampler at both ends of every block shape (columns per thread and threads): candidates and q of a
