@@ -358,7 +358,8 @@ int sd_last_logits(sd_model *m, float *out, int32_t max_rows, int32_t *rows);
  * "x" (residual [rows][d_model]), "qkv" ([rows][3*d_model]), "q", "o", "a"
  * ([rows][d_model]) or "act" ([rows][d_ffn]); "seq_order" / "seq_len" give, for the
  * first `rows` sequences of the last forward, the order attention blocks start in
- * (longest first) and the cache length after that forward.  Synchronises.  Buffers a
+ * (longest first) and the cache length after that forward.  Synchronises.  fp32 models: every
+ * buffer is the last forward's.  bf16 models: buffers a
  * fused kernel skipped hold older data: "qkv" and "q" whenever attention consumes the
  * QKV GEMM's partial sums directly, "o" when a small model's attention blocks apply the
  * output projection themselves (option "force_generic" selects the unfused kernels). */

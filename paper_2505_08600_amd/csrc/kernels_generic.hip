@@ -1222,7 +1222,7 @@ __device__ __forceinline__ float4 load4_f(const bf16_t *p)
 // Measured, tiny pair: 6.3 - 7.1 us here + 2.8 - 3.8 us for the launch that did this before -> 8.0 - 8.3 us; whole step
 // 245 -> 235 us.
 template <typename T, bool FUSED>
-__global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActView q_av, T *Kl, T *Vtl,
+__global__ __launch_bounds__(256) void attn_generic_kernel(T *qbuf, ActView q_av, T *Kl, T *Vtl,
                                                            PlanView pv, CtxView cv, int R, int H, int hd,
                                                            int64_t total_cap, int lds_len, T *obuf, ActView o_av,
                                                            const float *qkv, const float2 *rope, int max_pos)
@@ -1235,7 +1235,10 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActVie
     int r = j * R + i;
     int HD = H * hd;
     if (i >= pv.seq_nq[j]) {
-        for (int d = threadIdx.x; d < hd; d += blockDim.x) store_act(obuf, act_index(o_av, r, h * hd + d, HD), o_av.plane, 0.f);
+        for (int d = threadIdx.x; d < hd; d += blockDim.x) {
+            store_act(obuf, act_index(o_av, r, h * hd + d, HD), o_av.plane, 0.f);
+            if (FUSED) store_act(qbuf, act_index(q_av, r, h * hd + d, HD), q_av.plane, 0.f);
+        }
         return;
     }
     int Lk = pv.seq_kv0[j] + i + 1;
@@ -1261,8 +1264,11 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActVie
             sv[rr * hd + e] = in ? v0 : 0.f;
             sv[rr * hd + e + half] = in ? v1 : 0.f;
             if (rr == i) {
-                qs[e] = in ? q0 * cs.x - q1 * cs.y : 0.f;
-                qs[e + half] = in ? q1 * cs.x + q0 * cs.y : 0.f;
+                const float qa = in ? q0 * cs.x - q1 * cs.y : 0.f, qb = in ? q1 * cs.x + q0 * cs.y : 0.f;
+                qs[e] = qa;
+                qs[e + half] = qb;
+                store_act(qbuf, act_index(q_av, r, h * hd + e, HD), q_av.plane, qa); // (only sd_debug_read looks at it)
+                store_act(qbuf, act_index(q_av, r, h * hd + e + half, HD), q_av.plane, qb);
                 if (in) { // (pos < capacity: the plan sees to it)
                     Kh[kt_offset(hd, off + pos, e)] = from_float<T>(ka);
                     Kh[kt_offset(hd, off + pos, e + half)] = from_float<T>(kb);
@@ -1326,7 +1332,7 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(const T *qbuf, ActVie
 }
 
 template <typename T, bool FUSED>
-static hipError_t attn_generic(hipStream_t s, size_t lds, const T *qbuf, ActView q_av, T *Kl, T *Vtl, PlanView pv, CtxView cv, int R, int n_seq,
+static hipError_t attn_generic(hipStream_t s, size_t lds, T *qbuf, ActView q_av, T *Kl, T *Vtl, PlanView pv, CtxView cv, int R, int n_seq,
                                int H, int hd, int64_t total_cap, int len_upper, T *obuf, ActView o_av, const float *qkv, const float2 *rope,
                                int max_pos)
 {
@@ -1340,25 +1346,25 @@ static hipError_t attn_generic(hipStream_t s, size_t lds, const T *qbuf, ActView
     return hipGetLastError();
 }
 
-hipError_t launch_attn_generic(hipStream_t s, int dtype, const void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
+hipError_t launch_attn_generic(hipStream_t s, int dtype, void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
                                int n_seq, int H, int hd, int64_t total_cap, int len_upper, void *obuf, ActView o_av)
 {
     const size_t lds = ((size_t)len_upper + 256 + hd + 32) * sizeof(float); // (256 floats of slack: the limit is part of the interface)
     if (dtype == SD_BF16)
-        return attn_generic<bf16_t, false>(s, lds, (const bf16_t *)qbuf, q_av, (bf16_t *)Kl, (bf16_t *)Vtl, pv, cv, R, n_seq, H, hd, total_cap,
+        return attn_generic<bf16_t, false>(s, lds, (bf16_t *)qbuf, q_av, (bf16_t *)Kl, (bf16_t *)Vtl, pv, cv, R, n_seq, H, hd, total_cap,
                                            len_upper, (bf16_t *)obuf, o_av, nullptr, nullptr, 0);
-    return attn_generic<float, false>(s, lds, (const float *)qbuf, q_av, (float *)Kl, (float *)Vtl, pv, cv, R, n_seq, H, hd, total_cap, len_upper,
+    return attn_generic<float, false>(s, lds, (float *)qbuf, q_av, (float *)Kl, (float *)Vtl, pv, cv, R, n_seq, H, hd, total_cap, len_upper,
                                       (float *)obuf, o_av, nullptr, nullptr, 0);
 }
 
 // fp32: RoPE, cache append and attention in one launch, from the QKV product (one slab); hipErrorNotSupported where the
 // new rows do not fit in LDS beside the scores, or a slot's rows are many.
 hipError_t launch_attn_f32_fused(hipStream_t s, const float *qkv, const float2 *rope, int max_pos, float *Kl, float *Vtl, PlanView pv, CtxView cv,
-                                 int R, int n_seq, int H, int hd, int64_t total_cap, int len_upper, float *obuf, ActView o_av)
+                                 int R, int n_seq, int H, int hd, int64_t total_cap, int len_upper, float *qbuf, float *obuf, ActView o_av)
 {
     if (R > 16) return hipErrorNotSupported;
     const size_t lds = ((size_t)len_upper + hd + 32 + 2 * (size_t)R * hd) * sizeof(float);
-    return attn_generic<float, true>(s, lds, nullptr, o_av, Kl, Vtl, pv, cv, R, n_seq, H, hd, total_cap, len_upper, obuf, o_av, qkv, rope, max_pos);
+    return attn_generic<float, true>(s, lds, qbuf, o_av, Kl, Vtl, pv, cv, R, n_seq, H, hd, total_cap, len_upper, obuf, o_av, qkv, rope, max_pos);
 }
 
 // ---------------------------------------------------------------- inverse-CDF pick

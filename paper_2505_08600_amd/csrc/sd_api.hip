@@ -288,6 +288,7 @@ extern "C" int sd_load_model(const sd_model_config *cfg, const sd_weights *w, sd
         }
     }
     m->last_lm_rows = 0;
+    m->lm_norm_rows = 0;
     size_t M = c.max_rows, d = c.d_model;
     m->part_floats = attn_part_floats(c);
     hipError_t e = hipSuccess;
@@ -700,6 +701,12 @@ extern "C" int sd_debug_read(sd_model *m, const char *name, float *out_host, int
         for (int r = 0; r < rows; r++) out_host[r] = order ? (float)a[r] : (float)(b[r] > 0 ? a[r] + b[r] : 0);
         return SD_OK;
     }
+    if (!strcmp(name, "a") && m->lm_norm_rows) { // the last norm ran inside the LM head's GEMM: x and its row map are still there
+        SD_HIP(launch_rmsnorm(0, m->cfg.dtype, m->x, m->final_norm, m->plan.lm_row, m->lm_norm_rows, (int)d, m->cfg.rms_eps, m->abuf,
+                              ActView{m->plane_d, m->lm_norm_rows, 0}));
+        SD_HIP(hipDeviceSynchronize());
+        m->lm_norm_rows = 0;
+    }
     const void *src = nullptr;
     size_t w = d, plane = m->plane_d;
     if (!strcmp(name, "q")) src = m->qbuf;
@@ -818,6 +825,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     const ActView avd = {m->plane_d, M, sm_d}, avf = {m->plane_f, M, sm_f}, av0 = {0, 0, 0};
     m->last_rows = M;
     m->last_a_rows = M;
+    m->lm_norm_rows = 0;
     CtxView cv = c->view();
     PlanView pv = m->plan;
     int kv_upper = std::min(c->len_upper + SD_MAX_GAMMA + 1, c->max_cap);
@@ -908,7 +916,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (cf.dtype == SD_FP32 && G == 1 && nq_slabs == 1 && !(g_force_generic & (1 | 2))) {
             ProfScope ps(T_ATTN, s);
             ea = launch_attn_f32_fused(s, qkv_src, m->rope, cf.max_pos, (float *)Kl, (float *)Vtl, pv, cv, R, n_seq, H, hd, c->total_cap, c->max_cap,
-                                       (float *)m->obuf, avd);
+                                       (float *)m->qbuf, (float *)m->obuf, avd);
             if (ea == hipErrorNotSupported) ps.drop();
         }
         if (ea == hipErrorNotSupported) {
@@ -952,7 +960,8 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         }
         WeightSeg wgu = {{m->wgate[l], m->wup[l], nullptr}, F, m->tiled_fd, m->stream_nt};
         bool gu_done = false;
-        if (norm32 && !no_slabs) { ProfScope ps(T_GATEUP, s);
+        // (without logits this norm is the forward's last: a launch of its own leaves it in abuf for sd_debug_read)
+        if (norm32 && !no_slabs && (want_logits || l + 1 < cf.n_layers)) { ProfScope ps(T_GATEUP, s);
             const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act);
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
@@ -999,7 +1008,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
             lm_done = en == hipSuccess;
-            if (lm_done) m->lm_stats_nb = 0;
+            if (lm_done) m->lm_stats_nb = 0, m->lm_norm_rows = n_lm;
         }
         if (!fold && !lm_done) { ProfScope ps(T_RMSNORM, s);
         if (pending)

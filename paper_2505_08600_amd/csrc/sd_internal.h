@@ -311,6 +311,7 @@ struct sd_model {
     PlanView plan;
     int last_lm_rows;
     int last_rows, last_a_rows; // rows of the last forward (layout of the step-major buffers); of abuf
+    int lm_norm_rows; // rows of the LM head's input that a norm inside its GEMM kept out of abuf (0: none); sd_debug_read makes them
 };
 
 struct sd_ctx {
@@ -394,10 +395,10 @@ hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_
                               CtxView cv, int M, int R, int H,
                               int hd, const float2 *rope, int max_pos, void *qbuf, ActView q_av, void *Kl, void *Vtl,
                               int64_t total_cap);
-hipError_t launch_attn_generic(hipStream_t s, int dtype, const void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
+hipError_t launch_attn_generic(hipStream_t s, int dtype, void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
                                int n_seq, int H, int hd, int64_t total_cap, int len_upper, void *obuf, ActView o_av);
 hipError_t launch_attn_f32_fused(hipStream_t s, const float *qkv, const float2 *rope, int max_pos, float *Kl, float *Vtl, PlanView pv, CtxView cv,
-                                 int R, int n_seq, int H, int hd, int64_t total_cap, int len_upper, float *obuf, ActView o_av);
+                                 int R, int n_seq, int H, int hd, int64_t total_cap, int len_upper, float *qbuf, float *obuf, ActView o_av);
 // stats / stats_nb: the per-block softmax partials the LM head left (LmStats), stats_nb blocks of 32 columns per
 // row (0: none - the one-block-per-row samplers read the whole row first).  *did_embed: whether the sampler
 // honoured next.embed (only the kernels that work from the partials do).

@@ -1337,6 +1337,48 @@ def test_fp32_profile_counts_every_launch_once(cap, force):
     gm.close()
 
 
+@pytest.mark.parametrize("max_rows", [16, 64])
+def test_fp32_inspection_buffers_hold_the_last_forward(max_rows):
+    """sd_debug_read after a prefill, a draft and a verify call of an fp32 model: what the fused launches leave (or have
+    re-made on demand) is what the separate launches of force_generic leave.  Same operations in another order: 1e-5."""
+    _say(f"fp32 inspection buffers max_rows={max_rows}")
+    st_ = dg.SHAPES["tiny_target"]
+    V, gamma, T = st_.vocab, 2, 0.8
+    gm = api.Model(st_, dg.make_weights(st_, 77, 20.0), max_rows=max_rows, max_pos=128)
+    prompts = [[int(t) for t in dg.make_prompt(77, b, n, V)] for b, n in enumerate((12, 9))]
+    u = H.dev(np.stack([dg.make_uniforms(77, dg.DRAFT_STREAM, b, 0, 1) for b in range(2)]))
+    cv = H.dev(np.stack([dg.make_prompt(78, b, gamma, V) for b in range(2)]).astype(np.int32))
+    na, nx = (torch.zeros(2, dtype=torch.int32, device="cuda") for _ in range(2))
+    cand, q = torch.zeros((2, 1), dtype=torch.int32, device="cuda"), torch.zeros((2, 1, V), device="cuda")
+
+    def read(rows, a_rows):
+        return {n: gm.debug_read(n, a_rows if n == "a" else rows) for n in ("x", "qkv", "q", "o", "act", "a")}
+
+    def calls(ctx):
+        out = []
+        if max_rows // 2 < 16:   # (the last prefill forward: 8 rows per sequence, three and none of them live)
+            out.append(("prefill", read(16, 16)))
+        api.sd_draft(gm, ctx, None, 2, 1, T, u, cand, q)
+        out.append(("draft", read(4, 2)))
+        for b, p in enumerate(prompts):
+            ctx.truncate(gm, b, len(p) - 1)
+        api.sd_verify(gm, ctx, None, 2, gamma, 0.0, cv, None, None, na, nx, commit=False)
+        out.append(("verify", read(2 * (gamma + 1), 2 * (gamma + 1))))
+        out.append(("verify", read(2 * (gamma + 1), 2 * (gamma + 1))))   # (a second reading finds the same)
+        return out
+
+    try:
+        got = _fp32_pass(gm, prompts, gamma, 64, calls)
+        api.set_option("force_generic", 1)
+        ref = _fp32_pass(gm, prompts, gamma, 64, calls)
+    finally:
+        api.set_option("force_generic", 0)
+    for (call, a), (_, r) in zip(got, ref):
+        for n in r:
+            assert np.isfinite(a[n]).all() and np.abs(a[n] - r[n]).max() < 1e-5 * np.abs(r[n]).max(), (call, n)
+    gm.close()
+
+
 @pytest.mark.parametrize("V", [4, 1024, 1028, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
 def test_fp32_draft_sampler_row_shapes_match_oracle(V):
     """The one-block draft sampler at both ends of every block shape (columns per thread and threads): candidates and q of a
