@@ -201,8 +201,8 @@ int sd_verify(sd_model *target, sd_ctx *c, const int32_t *seq_ids /*dev*/, int32
  * the same softmax / accept scan / residual / resample kernels, no model, no context, no commit.
  *   logits dev fp32 [n_seq][gamma+1][vocab] (16-byte aligned); cand, q, uniforms, n_accepted,
  *   next_token as for sd_verify (q 16-byte aligned);
- *   workspace dev fp32 [3 * n_seq * (gamma+1)]: per-row (max, sum of exponentials, argmax) passed
- *   from the first kernel to the second; contents on entry do not matter.
+ *   workspace dev fp32 [3 * n_seq * (gamma+1)]: three words per row that the kernels of the call hand
+ *   on (a row's verdict, or its statistics and a share of the mass); contents on entry do not matter.
  * vocab a multiple of 4 in [4, 262144]; 0 <= gamma <= 15; temperature = infinity makes p uniform over the columns that
  * are not -inf.  Only enqueues kernels on `stream`. */
 int sd_accept(const float *logits, int32_t n_seq, int32_t gamma, int32_t vocab, float temperature,
@@ -211,7 +211,7 @@ int sd_accept(const float *logits, int32_t n_seq, int32_t gamma, int32_t vocab, 
 
 /* sd_accept for callers that cannot allocate or carry a workspace (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): same arguments and results, but the
- * per-row statistics live in a fixed device array inside the library (48 KiB per GPU, held until
+ * three words per row live in a fixed device array inside the library (48 KiB per GPU, held until
  * the process ends) instead of a caller's workspace.  Calls no allocating routine; the first call
  * on a device only looks up that device's address of the array.
  * n_seq * (gamma + 1) <= 4096, else SD_ECAP (nothing is enqueued).  All calls on one GPU share the

@@ -46,7 +46,7 @@ extern "C" int sd_accept(const float *logits, int32_t n_seq, int32_t gamma, int3
 
 // ---------------------------------------------------------------- the same call without any allocation
 // For callers that cannot allocate or carry a workspace (code under graph capture, tight serving loops):
-// the per-row statistics that sd_accept passes between its two kernels through `workspace` live in a
+// the words per row that sd_accept passes between its kernels through `workspace` live in a
 // file-scope device array instead.  Every device the library runs on holds its own copy of the array at
 // its own address for the life of the process; the address is looked up once per device and kept.
 #define SD_ACCEPT_STATIC_MAX_ROWS 4096 // n_seq * (gamma + 1); 48 KiB of device memory per GPU
@@ -85,7 +85,7 @@ extern "C" int sd_accept_static(const float *logits, int32_t n_seq, int32_t gamm
     float *stats = nullptr;
     rc = scratch_on_current_device(&stats);
     if (rc) return rc;
-    // (nothing to clear: the first kernel writes all 3 * n_seq * (gamma + 1) entries the second one reads)
+    // (nothing to clear: every entry a kernel reads was written by a kernel of the same call)
     return run_accept("sd_accept_static", logits, n_seq, gamma, vocab, temperature, cand, q, uniforms, n_accepted,
                       next_token, stats, (hipStream_t)stream);
 }

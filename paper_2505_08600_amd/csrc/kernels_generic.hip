@@ -2283,10 +2283,11 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // Bound: one read of all rows.  The caller's workspace is three floats per row, so what a row's blocks could hand on is
 // limited to that: a row's statistics come from one block, and the slice masses (gamma + 1 per sequence) take the
 // argmax entries, which sampling does not use.  A block keeps two batches of 4 float4 per thread, one in flight while the
-// other is summed (one batch of 8, maximum and argmax together: 65 us for the first launch at the size below); 512 threads when there are
-// rows enough to put two blocks on every compute unit (64 sequences, gamma 8, 128000 columns: 295 MB).
-// Measured at that size: 100 us for the three launches (3.2 TB/s of logits and q; 455 us with a block per sequence that
-// ran its rows one after the other, three passes each).
+// other is summed; 512 threads when there are rows enough to put two blocks on every compute unit.  One batch of 8 instead
+// measures within a few per cent either way (whole call, T = 1: 6 rows of 50000 columns 29.6 us here / 30.8, 576 rows of
+// 128000 95.8 / 94.6): what counts is that 128 bytes per thread are in flight.
+// Measured at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 96 us for the three launches (3.4 TB/s of logits and
+// q; 455 us with a block per sequence that ran its rows one after the other, three passes each).
 #define WIDE_U 4
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int V, float T, float *stats)
@@ -2354,18 +2355,16 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
     }
 }
 
-// The acceptance tests of one sequence by the block's first threads: candidate i is accepted iff u_i < p_i / q_i (T > 0)
-// or it is the row's argmax (T == 0).  Returns the length of the accepted prefix; s_ok: SD_MAX_GAMMA ints of LDS.
-__device__ int accept_scan(const float *rows, const float *st, int gamma, int stride_g, int V, float T, float invT,
-                           const int32_t *cj, const float *qj, const float *uj, int *s_ok)
+// The acceptance tests of one sequence by the block's first threads (T > 0): candidate i is accepted iff u_i < p_i / q_i.
+// Returns the length of the accepted prefix; s_ok: SD_MAX_GAMMA ints of LDS.
+__device__ int accept_scan(const float *rows, const float *st, int gamma, int V, float invT, const int32_t *cj, const float *qj,
+                           const float *uj, int *s_ok)
 {
     if ((int)threadIdx.x < gamma) {
         const int i = threadIdx.x;
         const int c = cj[i];
-        bool ok;
-        if (T == 0.f) ok = c == __float_as_int(st[3 * i + 2]);
-        else if (c < 0 || c >= V) ok = false;
-        else {
+        bool ok = false;
+        if (c >= 0 && c < V) {
             const float p = expf((rows[(size_t)i * V + c] - st[3 * i]) * invT) / st[3 * i + 1];
             float qc = qj[(size_t)i * V + c];
             qc = fmaxf(qc, 1.17549435e-38f);
@@ -2414,8 +2413,7 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
     const float *rows = logits + (size_t)j * (stride_g + 1) * V, *qj = q + (size_t)j * stride_g * V;
     float *st = stats + (size_t)j * (stride_g + 1) * 3;
     const float invT = inv_temperature(T);
-    const int n_acc = accept_scan(rows, st, gamma, stride_g, V, T, invT, cand + (size_t)j * stride_g, qj,
-                                  u + (size_t)j * (stride_g + 1), s_ok);
+    const int n_acc = accept_scan(rows, st, gamma, V, invT, cand + (size_t)j * stride_g, qj, u + (size_t)j * (stride_g + 1), s_ok);
     const DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
                            n_acc < gamma ? (const float4 *)(qj + (size_t)n_acc * V) : nullptr, st[3 * n_acc], invT,
                            1.0f / st[3 * n_acc + 1]};
@@ -2503,9 +2501,10 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
 // from registers it holds anyway.  Later rows of a sequence do that in vain; they run beside the others.  The verdicts
 // take the three words per row of the caller's workspace: (accepted, token drawn, argmax).  verify_finish_kernel: one
 // wave per sequence reads its verdicts: accepted prefix, token of the row behind it, commit.
-// Bound: latency of one row's chain (load, max, exponentials, sum, q, scan).  Measured, 32000 columns (before: row
-// statistics in one launch, the decision from a second reading of the deciding row in another): 6 rows 8.1 + 17.9 ->
-// 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1.
+// Bound: latency of one row's chain (load, max, exponentials, sum, q, scan).  Measured, 32000 columns, kernel durations
+// under the profiler (before: row statistics in one launch, the decision from a second reading of the deciding row in
+// another): 6 rows 8.1 + 17.9 -> 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1; whole call of 6 rows among others 21.4 ->
+// 13.5 us.
 // EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
 // (6 rows: 1.1 us); with more rows than units two blocks share one, q is read only where it is needed.
 // DRAW false (more rows, see launch_verify_tail): the row settles its test only and leaves (max, sum, accepted) for verify_draw_kernel.

@@ -298,7 +298,7 @@ struct sd_model {
     void *act;      // [planes][max_rows][d_ffn]
     size_t plane_d, plane_f; // element offsets between the planes
     float *logits;  // [max_rows][vocab]
-    float *vstats;  // [max_rows][3] what the verify tail's first launch hands to the next: per row its verdict, or (wide rows) max, sum of exponentials, argmax
+    float *vstats;  // [max_rows][3] what the verify tail's launches hand on: per row its verdict, or max, sum of exponentials, verdict / argmax / slice mass
     float *ss_part;  // [32][SD_NORMFOLD_MAX_BLOCKS] per-block sums of squares between a producer and its consumer (see NormFold)
     float *lm_stats; // [max_rows][vocab / 32][3] per-block softmax partials of the last LM head (see LmStats)
     int lm_stats_nb; // blocks per row the last forward's LM head left there (0: none)
