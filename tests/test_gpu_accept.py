@@ -102,6 +102,35 @@ def test_rows_beyond_a_blocks_registers(V, gamma, T):
     print(f"  n_acc={na_h.tolist()}", flush=True)
 
 
+@pytest.mark.parametrize("T", [1.0, 0.0])
+def test_wide_rows_in_blocks_of_512_threads(T):
+    """512 rows and more above 32768 columns, two blocks to a compute unit: 129 sequences of 4 rows over 33004 columns, with
+    rejections, residual draws, a masked range and everything accepted, against the oracle (sequences repeat five
+    cases with uniforms of their own)."""
+    V, gamma, n = 33004, 3, 5
+    print(f"512-thread blocks V={V} T={T}", flush=True)
+    logits, q, cand, u = synthetic_case(43, n, gamma, V, 0.9, T)
+    logits[:, :, V // 3:V // 2] = -np.inf
+    if T > 0:
+        q = np.stack([np.stack([oracle.softmax_T(logits[b, i] * np.float32(0.9 if b else 1.0), T) for i in range(gamma)]) for b in range(n)])
+        cand = np.stack([[oracle.sample_cdf(q[b, i].astype(np.float64), 0.37 + 0.05 * i)[0] for i in range(gamma)] for b in range(n)]).astype(np.int32)
+    else:
+        cand[0] = logits[0, :gamma].argmax(-1)
+        cand[1, 0] = logits[1, 0].argmax(-1)
+    B = 129
+    pick = np.arange(B) % n
+    logits, q, cand = logits[pick], q[pick], cand[pick]
+    u = np.stack([dg.make_uniforms(43, dg.VERIFY_STREAM, b, 1, gamma + 1) for b in range(B)])
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * B * (gamma + 1),), float("nan"), device="cuda")
+    api.sd_accept(dev(logits), gamma, T, dev(cand), dev(q) if T > 0 else None, dev(u) if T > 0 else None, na, nx, ws)
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert check_against_oracle(logits, q, cand, u, T, na_h, nx_h) <= 2
+    assert len(set(na_h.tolist())) >= 3
+
+
 @pytest.mark.parametrize("V,gamma,n_trials", [(2772, 0, 1500), (2772, 1, 1500), (32000, 0, 900), (32000, 1, 600),
                                               (50000, 0, 450), (262144, 0, 99)])
 def test_next_token_for_uniforms_on_the_boundaries_of_the_cdf(V, gamma, n_trials):

@@ -193,8 +193,8 @@ def test_small_bf16_mfma_matches_reference_kernels():
 @pytest.mark.parametrize("B", [2, 3, 5, 8, 11, 16, 17, 30])
 def test_small_bf16_every_gemm_row_class_matches_reference_kernels(B):
     """Batched verify at gamma = 5 with B ragged sequences puts M = 6B rows through every GEMM: the packed
-    (M <= 8), 16- and 32-row few-row kernels, the 48-row blocks (M <= 64) and the 96-row blocks, with ragged
-    last blocks, plus batched prefill chunks.  The MFMA path must agree with the library's reference
+    few-row kernel (M <= 8), the wide one (up to 64 rows; the 48-row blocks that some shapes take at 41 to 48 rows need
+    widths of their own, see below) and the 96-row blocks, with ragged last blocks, plus batched prefill chunks.  The MFMA path must agree with the library's reference
     kernels (which the oracle tests pin) far inside the bf16 tolerance: both feed hi + lo activations."""
     _say(f"small bf16: batch {B} (M = {6 * B}) MFMA vs reference kernels")
     st_ = dg.SHAPES["small_target_bf16"]
@@ -325,6 +325,42 @@ def test_wide_few_row_gemm_matches_reference_kernels(d, F, V):
     gt.close()
 
 
+def test_48_row_blocks_match_reference_kernels():
+    """41 to 48 rows of a gate/up pair or logits matrix of 20480 weight rows and more, K of 2048 and more, run on the
+    48-row blocks of the row-blocked kernel; 40 and 49 rows of the same shapes on the wide few-row kernel.  Logits and SwiGLU
+    product against the library's reference kernels (fp32 sums in another order, single cache elements one bf16 step)."""
+    import dataclasses
+    st_ = dataclasses.replace(dg.SHAPES["small_target_bf16"], n_layers=1, d_model=2048, n_heads=16, d_ffn=10240, vocab=20480, name="rows48")
+    V = st_.vocab
+    gt = api.Model(st_, dg.make_weights(st_, 95, BF16_LM_SCALE), max_rows=64, max_pos=128)
+    try:
+        for B, gamma in ((40, 0), (41, 0), (8, 5), (49, 0)):
+            M = B * (gamma + 1)
+            _say(f"48-row blocks, rows={M}")
+            lens = dg.make_prompt_lengths(95 + M, B, 3, 20)
+            prompts = [[int(t) for t in dg.make_prompt(95, b, int(lens[b]), V)] for b in range(B)]
+            ctx = api.Context([int(l) + 16 for l in lens])
+            ctx.attach(gt)
+            H.gpu_prefill(ctx, [gt], prompts)
+            cand = H.dev(dg.make_prompt(96, B, max(1, B * gamma), V)[:B * gamma].reshape(B, gamma).astype(np.int32))
+            na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+            outs = []
+            for force in (0, 1):
+                api.set_option("force_generic", force)
+                api.sd_verify(gt, ctx, None, B, gamma, 0.0, cand if gamma else None, None, None, na, nx, commit=False)
+                torch.cuda.synchronize()
+                outs.append((gt.last_logits().cpu().numpy(), gt.debug_read("act", M)))
+                api.set_option("force_generic", 0)
+                for b in range(B):
+                    ctx.truncate(gt, b, int(lens[b]) - 1)
+            ctx.close()
+            for got, ref in zip(*outs):
+                assert np.isfinite(got).all() and np.abs(got - ref).max() < 5e-4 * np.abs(ref).max(), (M, np.abs(got - ref).max() / np.abs(ref).max())
+    finally:
+        api.set_option("force_generic", 0)
+    gt.close()
+
+
 @pytest.mark.parametrize("waves", [4, 8])
 def test_small_bf16_both_fused_attention_block_shapes_match_reference_kernels(waves):
     """The fused attention kernel runs as 8-wave blocks (few sequences) or 4-wave blocks (many); the
@@ -366,7 +402,7 @@ def test_small_bf16_norm_split_between_its_neighbour_gemms_matches_oracle(T, ple
     """With few rows the add + RMSNorm launches of a layer can be split between the projection before them (which
     adds the residual, applies the gains and leaves per-block sums of squares) and the GEMM after them (which
     scales its sums by 1 / rms): the operand is then rounded to its two bf16 terms before the division by rms
-    instead of after it.  This is the library's default where the shapes allow; option norm_fold = 2 switches it
+    instead of after it.  This is the library's default up to 8 rows where the shapes allow; option norm_fold = 2 switches it
     off, and the same oracle comparison must hold both ways, with the same limits (target and draft both take
     the path, draft rows included: 1-2 rows, LM head through a row map)."""
     _say(f"small bf16, split norm, T={T} prompt={plen} gamma={gamma}")
@@ -387,7 +423,7 @@ def test_small_bf16_norm_split_between_its_neighbour_gemms_matches_oracle(T, ple
 @pytest.mark.parametrize("shape_name,B", [("small_target_bf16", 1), ("small_target_bf16", 5), ("small_draft_bf16", 3),
                                           ("draft_a_1layer", 1)])
 def test_norm_split_between_its_neighbour_gemms_matches_the_norm_launches(shape_name, B):
-    """The same forward with the split norm on (the default) and off (option norm_fold = 2): the logits differ
+    """The same forward with the split norm on (option norm_fold = 1) and off (2): the logits differ
     by the rounding of the operand at another point only - a few 1e-5 of their range at these widths, four orders
     of magnitude inside the tolerance; 1 to 30 rows (packed, 16- and 32-row kernels)."""
     import dataclasses
