@@ -1555,16 +1555,18 @@ __device__ float row_sumexp(const float *row, int V, float mx, float invT, float
 // general kernels above; the block-wide sums are added as trees here, so the two paths agree to rounding
 // (and exactly in the maximum and the arg max).  One pass over memory per row and a handful of barriers
 // instead of one block reduction per 4096 elements.
-// The block's shape follows the row: one vector per thread up to 4096 columns, then 2, 4, 8 (an 8-vector block of a
-// 1024-column row spends its time on 31 exponentials of padding per thread); 256 threads up to 1024 columns, where most
-// of 16 waves would only meet at the barriers.  Measured, 1024 columns (8 vectors x 1024 threads before): draft sampler
-// 12.2 -> 4.2 us, row verdicts 13.3 -> 4.8 us.
+// The block's shape follows the row (an 8-vector block of 1024 threads spends a 1024-column row's time on 31 exponentials of
+// padding per thread): 256 threads with 1, 2 or 4 vectors up to 4096 columns, where most of 16 waves would only meet at the
+// barriers, then 1024 threads with 2, 4 or 8.  Measured, 1024 columns (8 vectors x 1024 threads before): draft sampler
+// 12.2 -> 4.2 us, row verdicts 13.3 -> 4.8 us.  Whole acceptance call, 1024 / 256 threads: 256 rows of 1028, 2048, 4096 columns
+// 12.4 / 11.7, 12.4 / 11.8, 11.5 / 11.5 us; 2048 rows 18.4 / 11.5, 18.3 / 11.4, 19.2 / 15.9.
 #define ROW_NSEG 8
 #define ROW_THREADS 1024
 #define SD_ROW_SHAPES(V, CALL)                    \
     do {                                          \
         if ((V) <= 1024) CALL(256, 1);            \
-        else if ((V) <= 4096) CALL(1024, 1);      \
+        else if ((V) <= 2048) CALL(256, 2);       \
+        else if ((V) <= 4096) CALL(256, 4);       \
         else if ((V) <= 8192) CALL(1024, 2);      \
         else if ((V) <= 16384) CALL(1024, 4);     \
         else CALL(ROW_THREADS, ROW_NSEG);         \

@@ -224,7 +224,7 @@ def row_verdict_case(V, gamma):
     return logits, q, cand, u, expect
 
 
-@pytest.mark.parametrize("V,gamma", [(4, 2), (1024, 15), (1028, 2), (4096, 3), (4100, 1), (8192, 2), (8196, 2), (16384, 2), (16388, 2),
+@pytest.mark.parametrize("V,gamma", [(4, 2), (1024, 15), (1028, 2), (2048, 4), (2052, 2), (4096, 3), (4100, 1), (8192, 2), (8196, 2), (16384, 2), (16388, 2),
                                      (32000, 5), (32768, 3)])
 def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     """Rows that fit a block's registers: the verdicts of the rows behind the first rejection must not matter, and a
@@ -242,7 +242,7 @@ def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1   # (a uniform next to an edge of the CDF)
 
 
-@pytest.mark.parametrize("V,gamma,copies", [(1024, 15, 1), (1028, 15, 1), (8192, 15, 1), (16384, 2, 22), (32000, 15, 1),
+@pytest.mark.parametrize("V,gamma,copies", [(1024, 15, 1), (1028, 15, 1), (4096, 15, 1), (8192, 15, 1), (16384, 2, 22), (32000, 15, 1),
                                             (32768, 2, 22), (8192, 1, 44), (16384, 1, 44)])
 def test_more_rows_than_compute_units(V, gamma, copies):
     """257 rows and more: from two candidates on one block per sequence draws behind the rows' tests, with one candidate

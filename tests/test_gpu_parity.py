@@ -1415,7 +1415,7 @@ def test_fp32_inspection_buffers_hold_the_last_forward(max_rows):
     gm.close()
 
 
-@pytest.mark.parametrize("V", [4, 1024, 1028, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
+@pytest.mark.parametrize("V", [4, 1024, 1028, 2048, 2052, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
 def test_fp32_draft_sampler_row_shapes_match_oracle(V):
     """The one-block draft sampler at both ends of every block shape (columns per thread and threads): candidates and q of a
     draft call of two sequences against the oracle, sampled at T = 0.8."""
