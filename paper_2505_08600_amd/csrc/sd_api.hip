@@ -810,11 +810,12 @@ static int stream_gemm(sd_model *m, hipStream_t s, const void *A, ActView a_av, 
 static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, int R, int n_seq,
                    const int32_t *seq_ids, int upto_off, const int32_t *cand, int gamma, int cand_idx,
                    bool want_logits, int G = 1, bool plan_ready = false, bool embed_ready = false,
-                   float lm_invT = -1.f)
+                   float lm_invT = -1.f, bool more = false)
 {
     // plan_ready / embed_ready: the draft sampler of the previous token has laid out this single-row forward /
     // has also gathered and normed its rows.  lm_invT >= 0: leave the LM head's per-block softmax partials
-    // (1 / temperature, 0 for greedy) for the sampler that follows, where the LM-head kernel can.
+    // (1 / temperature, 0 for greedy) for the sampler that follows, where the LM-head kernel can.  more: another forward of
+    // the same call follows (nothing can look at this one's buffers).
     const sd_model_config &cf = m->cfg;
     const int n_slots = n_seq * G; // plan slots: what the attention kernels see as sequences
     const int M = n_slots * R, d = cf.d_model, H = cf.n_heads, hd = cf.head_dim, F = cf.d_ffn, V = cf.vocab;
@@ -960,8 +961,8 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         }
         WeightSeg wgu = {{m->wgate[l], m->wup[l], nullptr}, F, m->tiled_fd, m->stream_nt};
         bool gu_done = false;
-        // (without logits this norm is the forward's last: a launch of its own leaves it in abuf for sd_debug_read)
-        if (norm32 && !no_slabs && (want_logits || l + 1 < cf.n_layers)) { ProfScope ps(T_GATEUP, s);
+        // (without logits this norm is the call's last: a launch of its own leaves it in abuf for sd_debug_read)
+        if (norm32 && !no_slabs && (want_logits || more || l + 1 < cf.n_layers)) { ProfScope ps(T_GATEUP, s);
             const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act);
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
@@ -1057,7 +1058,8 @@ extern "C" int sd_prefill(sd_model *m, sd_ctx *c, const int32_t *seq_ids, int32_
     // M = n_seq * 16 * G rows and stream the weights once per 16 * G tokens instead of once per 16
     int G = R == 16 ? std::max(1, std::min(m->cfg.max_rows / (16 * n_seq), (max_new + 15) / 16)) : 1;
     for (int done = 0; done < max_new; done += R * G) {
-        rc = forward(m, c, slot, (hipStream_t)stream, PLAN_CATCHUP, R, n_seq, seq_ids, 1, nullptr, 0, 0, false, G);
+        rc = forward(m, c, slot, (hipStream_t)stream, PLAN_CATCHUP, R, n_seq, seq_ids, 1, nullptr, 0, 0, false, G, false, false, -1.f,
+                     done + R * G < max_new);
         if (rc) return rc;
     }
     return SD_OK;
