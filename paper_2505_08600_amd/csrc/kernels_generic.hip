@@ -1694,9 +1694,11 @@ __device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, Fas
     }
 }
 
-// Inverse-CDF pick (same rule as block_pick_cdf) over weights held in registers.
-template <int RT, int NSEG>
-__device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u, FastScratch *fs, float *total_out)
+// Inverse-CDF pick (same rule as block_pick_cdf) over weights held in registers: the whole row, or (pick_regs_range) the
+// float4s v_begin .. v_end of one, for a target that lies `base` or more into the row's sum.  Weights past the end are 0.
+template <bool RANGE, int RT, int NSEG>
+__device__ __forceinline__ int pick_regs_impl(const RowRegs<NSEG> &w, int V, float u, FastScratch *fs, float *total_out, int v_begin, int v_end,
+                                              float base, float target)
 {
     // Index order is (segment it, thread t, component c).  Segment totals are the waves' totals added as a
     // tree; every thread works out the total Z, the segment holding u * Z and the sum before it for itself
@@ -1718,16 +1720,18 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
         fs->seg_last = -1;
     }
     lds_barrier();
-    const int nseg = ((V + 3) / 4 + RT - 1) / RT;
+    const int nseg = (v_end - v_begin + RT - 1) / RT;
     float seg[NSEG];
 #pragma unroll
     for (int it = 0; it < NSEG; it++) seg[it] = sum_waves<RT / WAVE>(fs->wsum[lane & (RT / WAVE - 1)][it]);
-    float Z = 0.f;
+    if (!RANGE) {
+        float Z = 0.f;
 #pragma unroll
-    for (int it = 0; it < NSEG; it++)
-        if (it < nseg) Z += seg[it];
-    const float target = u * Z;
-    float base = 0.f;
+        for (int it = 0; it < NSEG; it++)
+            if (it < nseg) Z += seg[it];
+        target = u * Z;
+        if (total_out) *total_out = Z;
+    }
     int sit = -1;
 #pragma unroll
     for (int it = 0; it < NSEG; it++)
@@ -1735,7 +1739,6 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
             if (base + seg[it] > target) sit = it;
             else base += seg[it];
         }
-    if (total_out) *total_out = Z;
     if (sit >= 0) { // uniform over the block
         float4 f = w.f[0];
 #pragma unroll
@@ -1746,7 +1749,7 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
             f.z = it == sit ? c.z : f.z;
             f.w = it == sit ? c.w : f.w;
         }
-        const int v = sit * RT + threadIdx.x;
+        const int v = v_begin + sit * RT + threadIdx.x;
         const float l4 = ((f.x + f.y) + f.z) + f.w;
         const float inc = wave_incl_scan_dpp(l4, lane);
         if (lane == WAVE - 1) fs->red[wv] = inc; // red was last read before the barrier above
@@ -1770,7 +1773,7 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
         else { // last index of the row with a positive weight (0 if there is none)
             int lastp = -1;
 #pragma unroll
-            for (int it = 0; it < NSEG; it++) lastp = max(lastp, last_positive(w.f[it], 4 * (it * RT + (int)threadIdx.x)));
+            for (int it = 0; it < NSEG; it++) lastp = max(lastp, last_positive(w.f[it], 4 * (v_begin + it * RT + (int)threadIdx.x)));
             lastp = wave_max_i(lastp);
             if (lane == 0) fs->redi[wv] = lastp;
             lds_barrier();
@@ -1779,6 +1782,16 @@ __device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u,
     }
     lds_barrier();
     return pick;
+}
+template <int RT, int NSEG>
+__device__ __forceinline__ int pick_regs(const RowRegs<NSEG> &w, int V, float u, FastScratch *fs, float *total_out)
+{
+    return pick_regs_impl<false, RT>(w, V, u, fs, total_out, 0, (V + 3) / 4, 0.f, 0.f);
+}
+template <int RT, int NSEG>
+__device__ __forceinline__ int pick_regs_range(const RowRegs<NSEG> &w, int V, int v_begin, int v_end, float base, float target, FastScratch *fs)
+{
+    return pick_regs_impl<true, RT>(w, V, 0.f, fs, nullptr, v_begin, v_end, base, target);
 }
 
 // e(x) -> probabilities e(x) * (1 / z), in place
@@ -2279,26 +2292,47 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // ---------------------------------------------------------------- verify tail
 // Fused vocabulary softmax + accept scan + residual + resample.  Rows of more than ROW_NSEG * ROW_THREADS * 4 = 32768
 // columns do not fit a block's registers; they take three launches (two where there is nothing to accept or nothing to draw):
-//   verify_stats_wide_kernel  one block per logits row, one pass: (max, sum of exponentials, argmax);
-//   verify_mass_wide_kernel   the acceptance tests, then the mass of one slice of the deciding row per block;
+//   verify_stats_wide_kernel  one block per logits row, one pass: (max, sum of exponentials, argmax) and the row's acceptance
+//                             test, whose verdict is the sign of the sum;
+//   verify_mass_wide_kernel   the mass of one slice of the deciding row per block;
 //   verify_pick_wide_kernel   one block per sequence: the slice that holds u * Z is searched for the token; commit.
 // Bound: one read of all rows.  The caller's workspace is three floats per row, so what a row's blocks could hand on is
 // limited to that: a row's statistics come from one block, and the slice masses (gamma + 1 per sequence) take the
 // argmax entries, which sampling does not use.  A block keeps two batches of 4 float4 per thread, one in flight while the
-// other is summed; 512 threads when there are rows enough to put two blocks on every compute unit.  One batch of 8 instead
-// measures within a few per cent either way (whole call, T = 1: 6 rows of 50000 columns 29.6 us here / 30.8, 576 rows of
-// 128000 95.8 / 94.6): what counts is that 128 bytes per thread are in flight.
-// Measured at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 96 us for the three launches (3.4 TB/s of logits and
-// q; 455 us with a block per sequence that ran its rows one after the other, three passes each).
+// other is summed.
+// The statistics pass is bound by instruction issue as much as by memory: with expf (13 instructions an element beside the
+// subtraction and the maximum) 576 rows of 128000 columns take 64 us, with the hardware's 2^x on the difference times
+// log2(e) / T 55, and then the nontemporal hint pays (48 us, 6.1 TB/s).  The sum's error against 64 bits is the same either
+// way, that of adding 32-bit numbers in this order (rows of N(0, 2) at T = 0.7 and 1, 33000 to 262144 columns: 5e-8 to 1.3e-7
+// rms; peaked rows 1e-8 and less); the probability an acceptance test or a draw uses keeps expf.
+// The hint and block shape, whole call: 576 x 128000 84.5 us (512 threads) / 77.4 (512, hint) / 75.2 (1024, hint); 360 x 128000
+// 58.5 without, 55.1 with the hint; 144 x 128000 34.5 / 35.8; 540 x 33000 31.3 / 32.7 / 34.2; 100 x 128000, gamma 0, where the
+// pick reads the row again, 64.5 / 73.0: the hint above 128 MB of logits, 512 threads below that where there are rows
+// enough to put two blocks on every compute unit.
+// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 75 us (101 with expf, the acceptance test in the
+// second launch and a pick that read its slice twice).
 #define WIDE_U 4
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int V, float T, float *stats)
+template <int THREADS, bool NT>
+__global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
+                                                                    const float *q, const float *u, float *stats)
 {
     __shared__ float redv[32];
     __shared__ int redi[32];
     const float4 *row = (const float4 *)(logits + (size_t)blockIdx.x * V);
     const int nvec = V / 4; // (V is a multiple of 4)
-    const float invT = inv_temperature(T);
+    const float invT = inv_temperature(T), c2 = fminf(invT * 1.44269504088896f, 3.4e38f); // e^(d / T) = 2^(c2 d); 0 * c2 stays 0
+    // the row's acceptance test: what it needs beside the row's sums is requested first
+    const int j = blockIdx.x / (gamma + 1), i = blockIdx.x % (gamma + 1);
+    int c = -1;
+    float lc = 0.f, qc = 1.f, ui = 0.f;
+    if (T > 0.f && i < gamma) { // (uniform)
+        c = cand[(size_t)j * gamma + i];
+        ui = u[(size_t)j * (gamma + 1) + i];
+        if (c >= 0 && c < V) {
+            lc = ((const float *)row)[c];
+            qc = q[((size_t)j * gamma + i) * V + c];
+        }
+    }
     // thread-local running maximum m (from -3e38: masked columns may lie below it, their exponentials are 0) and the
     // sum of exp((x - m) / T), rescaled when a batch of WIDE_U vectors raises m
     float m = -3.0e38f, z = 0.f;
@@ -2308,7 +2342,10 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
 #pragma unroll
         for (int k = 0; k < WIDE_U; k++) {
             const int v = v0 + k * THREADS;
-            f[k] = v < nvec ? row[v] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+            f32x4_t t = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            if (v < nvec) t = ld_stream<NT>((const f32x4_t *)row + v);
+            f[k] = make_float4(t.x, t.y, t.z, t.w);
         }
     };
     auto take = [&](int v0, const float4 *f) {
@@ -2319,10 +2356,10 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
             for (int k = 0; k < WIDE_U; k++) m = fmaxf(m, fmaxf(fmaxf(f[k].x, f[k].y), fmaxf(f[k].z, f[k].w)));
 #pragma unroll
             for (int k = 0; k < WIDE_U; k++) {
-                s += (expf((f[k].x - m) * invT) + expf((f[k].y - m) * invT)) +
-                     (expf((f[k].z - m) * invT) + expf((f[k].w - m) * invT));
+                s += (__builtin_amdgcn_exp2f((f[k].x - m) * c2) + __builtin_amdgcn_exp2f((f[k].y - m) * c2)) +
+                     (__builtin_amdgcn_exp2f((f[k].z - m) * c2) + __builtin_amdgcn_exp2f((f[k].w - m) * c2));
             }
-            z = m > m_old ? z * expf((m_old - m) * invT) + s : z + s;
+            z = m > m_old ? z * __builtin_amdgcn_exp2f((m_old - m) * c2) + s : z + s;
         } else {
 #pragma unroll
             for (int k = 0; k < WIDE_U; k++) {
@@ -2351,49 +2388,37 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
         z = 1.f;
     }
     if (threadIdx.x == 0) {
+        // candidate i is accepted iff u_i < p_i / q_i: the verdict is the sign bit of z (a NaN accepts nothing)
+        const bool ok = c >= 0 && c < V && ui < expf((lc - mx) * invT) / z / fmaxf(qc, 1.17549435e-38f);
+        z = ok ? -fabsf(z) : fabsf(z);
         stats[3 * blockIdx.x] = mx;
         stats[3 * blockIdx.x + 1] = z;
         stats[3 * blockIdx.x + 2] = __int_as_float(am);
     }
 }
 
-// The acceptance tests of one sequence by the block's first threads (T > 0): candidate i is accepted iff u_i < p_i / q_i.
-// Returns the length of the accepted prefix; s_ok: SD_MAX_GAMMA ints of LDS.
-__device__ int accept_scan(const float *rows, const float *st, int gamma, int V, float invT, const int32_t *cj, const float *qj,
-                           const float *uj, int *s_ok)
+// Length of the accepted prefix of a sequence with `gamma` candidates, from the signs verify_stats_wide_kernel gave its sums
+// (every wave for itself: one load and a vote).
+__device__ __forceinline__ int accepted_prefix(const float *st, int gamma)
 {
-    if ((int)threadIdx.x < gamma) {
-        const int i = threadIdx.x;
-        const int c = cj[i];
-        bool ok = false;
-        if (c >= 0 && c < V) {
-            const float p = expf((rows[(size_t)i * V + c] - st[3 * i]) * invT) / st[3 * i + 1];
-            float qc = qj[(size_t)i * V + c];
-            qc = fmaxf(qc, 1.17549435e-38f);
-            ok = uj[i] < p / qc;
-        }
-        s_ok[i] = ok ? 1 : 0;
-    }
-    __syncthreads();
-    int n = 0;
-    while (n < gamma && s_ok[n]) n++;
-    return n;
+    const int lane = threadIdx.x % WAVE;
+    const int ok = lane < gamma ? __float_as_int(st[3 * lane + 1]) < 0 : 0;
+    return __ffsll((unsigned long long)~__ballot(ok)) - 1; // (lane gamma <= SD_MAX_GAMMA always votes 0)
 }
 
 // Weights the next token is drawn from: p of the deciding row, or max(0, p - q) where it was rejected (q != nullptr).
 struct DrawWeights {
     const float4 *row, *q;
     float mx, invT, invZ;
-    __device__ __forceinline__ float4 operator()(int v) const
+    __device__ __forceinline__ float4 operator()(int v) const { return of(row[v], q ? q[v] : make_float4(0.f, 0.f, 0.f, 0.f)); }
+    __device__ __forceinline__ float4 of(float4 f, float4 w) const
     {
-        const float4 f = row[v];
         float4 p;
         p.x = expf((f.x - mx) * invT) * invZ;
         p.y = expf((f.y - mx) * invT) * invZ;
         p.z = expf((f.z - mx) * invT) * invZ;
         p.w = expf((f.w - mx) * invT) * invZ;
         if (q) { // (uniform)
-            const float4 w = q[v];
             p = make_float4(fmaxf(p.x - w.x, 0.f), fmaxf(p.y - w.y, 0.f), fmaxf(p.z - w.z, 0.f), fmaxf(p.w - w.w, 0.f));
         }
         return p;
@@ -2402,10 +2427,8 @@ struct DrawWeights {
 
 // T > 0.  Block j * (gamma + 1) + s: mass of slice s of sequence j's deciding row, left in the argmax entry of its row s.
 __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logits, float *stats, int gamma, int V, float T,
-                                                               const int32_t *cand, const float *q, const float *u,
-                                                               const int32_t *seq_ids, int32_t *n_acc_out, CtxView cv)
+                                                               const float *q, const int32_t *seq_ids, CtxView cv)
 {
-    __shared__ int s_ok[SD_MAX_GAMMA];
     __shared__ float red[32];
     const int n_slices = gamma + 1, j = blockIdx.x / n_slices, s = blockIdx.x % n_slices, stride_g = gamma;
     {   // with per-sequence candidate counts this sequence has gj <= gamma candidates (and gj + 1 live rows)
@@ -2415,10 +2438,10 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
     const float *rows = logits + (size_t)j * (stride_g + 1) * V, *qj = q + (size_t)j * stride_g * V;
     float *st = stats + (size_t)j * (stride_g + 1) * 3;
     const float invT = inv_temperature(T);
-    const int n_acc = accept_scan(rows, st, gamma, V, invT, cand + (size_t)j * stride_g, qj, u + (size_t)j * (stride_g + 1), s_ok);
+    const int n_acc = accepted_prefix(st, gamma);
     const DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
                            n_acc < gamma ? (const float4 *)(qj + (size_t)n_acc * V) : nullptr, st[3 * n_acc], invT,
-                           1.0f / st[3 * n_acc + 1]};
+                           1.0f / fabsf(st[3 * n_acc + 1])};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices, v_end = min(nvec, (s + 1) * per);
     float mass = 0.f;
 #pragma unroll 4
@@ -2427,32 +2450,31 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
         mass += ((f.x + f.y) + f.z) + f.w;
     }
     mass = block_sum(mass, red);
-    if (threadIdx.x == 0) {
-        st[3 * s + 2] = mass;
-        if (s == 0) n_acc_out[j] = n_acc;
-    }
+    if (threadIdx.x == 0) st[3 * s + 2] = mass;
 }
 
 // T > 0.  One block per sequence: the slice whose masses pass u * Z, searched with the rule of block_pick_cdf (segments
 // of 1024 vectors, then a scan of the segment that holds the target).  Without candidates (gamma == 0) there is one slice,
 // the whole row: its masses are left to block_pick_cdf and no launch before this one adds them up (one row of 32772
 // / 128000 / 262144 columns, whole call: 34 / 86 / 158 us with that launch, 27 / 65 / 118 without).
+template <int NSEG>
 __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *logits, const float *stats, int gamma, int V, float T,
                                                                 const int32_t *cand, const float *q, const float *u,
-                                                                const int32_t *seq_ids, int32_t *n_acc_io,
+                                                                const int32_t *seq_ids, int32_t *n_acc_out,
                                                                 int32_t *next_out, int commit, CtxView cv)
 {
     __shared__ PickScratch ps;
+    __shared__ FastScratch fs;
     const int j = blockIdx.x, stride_g = gamma, n_slices = gamma + 1;
     const int bb = seq_ids ? seq_ids[j] : j;
     if (cv.gam && bb >= 0 && bb < cv.B) gamma = seq_gamma(cv, bb, gamma);
     const float *rows = logits + (size_t)j * (stride_g + 1) * V;
     const float *st = stats + (size_t)j * (stride_g + 1) * 3;
-    const int n_acc = stride_g ? min(max(n_acc_io[j], 0), gamma) : 0;
+    const int n_acc = accepted_prefix(st, gamma);
     const float uu = u[(size_t)j * (stride_g + 1) + gamma];
     DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
                      n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc],
-                     inv_temperature(T), 1.0f / st[3 * n_acc + 1]};
+                     inv_temperature(T), 1.0f / fabsf(st[3 * n_acc + 1])};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
     float Z = 0.f;
     if (stride_g)
@@ -2484,11 +2506,24 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
             s_pick = s_last;
             base = base_last;
         }
-        const int v_begin = s_pick * per;
-        next = block_pick_range(w, v_begin, min(nvec, v_begin + per), V, base, target, &ps);
+        const int v_begin = s_pick * per, v_end = min(nvec, v_begin + per);
+        if constexpr (NSEG > 0) { // the slice fits the block's registers
+            RowRegs<NSEG> f, r;
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int it = 0; it < NSEG; it++) {
+                const int v = v_begin + it * 1024 + threadIdx.x;
+                f.f[it] = v < v_end ? w.row[v] : zero;
+                r.f[it] = w.q && v < v_end ? w.q[v] : zero;
+            }
+#pragma unroll
+            for (int it = 0; it < NSEG; it++) f.f[it] = v_begin + it * 1024 + (int)threadIdx.x < v_end ? w.of(f.f[it], r.f[it]) : zero;
+            next = pick_regs_range<1024>(f, V, v_begin, v_end, base, target, &fs);
+        } else
+            next = block_pick_range(w, v_begin, v_end, V, base, target, &ps);
     }
     if (threadIdx.x == 0) {
-        if (!stride_g) n_acc_io[j] = 0;
+        n_acc_out[j] = n_acc;
         next_out[j] = next;
         if (commit) {
             if (bb >= 0 && bb < cv.B) commit_one(cv, bb, gamma, cand + (size_t)j * stride_g, n_acc, next);
@@ -2712,14 +2747,22 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
                            cv);
         return hipGetLastError();
     }
-    if (n_rows >= 512) hipLaunchKernelGGL(verify_stats_wide_kernel<512>, dim3(n_rows), dim3(512), 0, s, logits, V, T, stats);
-    else hipLaunchKernelGGL(verify_stats_wide_kernel<1024>, dim3(n_rows), dim3(1024), 0, s, logits, V, T, stats);
+#define SD_STATS_WIDE(RT, NT)                                                                                             \
+    hipLaunchKernelGGL((verify_stats_wide_kernel<RT, NT>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, q, u, stats)
+    if ((size_t)n_rows * V > ((size_t)1 << 25)) SD_STATS_WIDE(1024, true); // (128 MB of logits)
+    else if (n_rows >= 512) SD_STATS_WIDE(512, false);
+    else SD_STATS_WIDE(1024, false);
     if (T > 0.f) {
         if (gamma > 0)
-            hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(n_rows), dim3(512), 0, s, logits, stats, gamma, V, T, cand, q,
-                               u, seq_ids, n_acc, cv);
-        hipLaunchKernelGGL(verify_pick_wide_kernel, dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, seq_ids,
-                           n_acc, next_tok, commit, cv);
+            hipLaunchKernelGGL(verify_mass_wide_kernel, dim3(n_rows), dim3(512), 0, s, logits, stats, gamma, V, T, q, seq_ids, cv);
+#define SD_PICK_WIDE(NSEG)                                                                                                    \
+    hipLaunchKernelGGL((verify_pick_wide_kernel<NSEG>), dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, \
+                       seq_ids, n_acc, next_tok, commit, cv)
+        const int per = (V / 4 + gamma) / (gamma + 1); // vectors of a slice
+        if (gamma == 0 || per > 8192) SD_PICK_WIDE(0);
+        else if (per > 4096) SD_PICK_WIDE(8);
+        else if (per > 2048) SD_PICK_WIDE(4);
+        else SD_PICK_WIDE(2);
     } else // (greedy: the decision needs the argmax entries only)
         hipLaunchKernelGGL(verify_finish_kernel, dim3(n_seq), dim3(WAVE), 0, s, stats, gamma, T, cand, seq_ids, n_acc, next_tok, commit,
                            cv);

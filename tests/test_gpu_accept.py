@@ -242,6 +242,28 @@ def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
     assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1   # (a uniform next to an edge of the CDF)
 
 
+@pytest.mark.parametrize("V,gamma,copies", [(32772, 15, 1), (40960, 4, 1), (40964, 4, 1), (65536, 3, 1), (65540, 3, 1), (131072, 3, 1), (131076, 3, 1),
+                                            (131076, 1, 1), (66000, 3, 26), (64000, 3, 26)])
+def test_wide_rows_decide_by_the_sign_of_their_sums(V, gamma, copies):
+    """Rows of more than 32768 columns: verdicts of every row, candidates outside the vocabulary, an empty residual; slices of
+    2048, 4096 and 8192 vectors and one more (the pick's register forms and the form without), more than 128 MB of logits
+    (the nontemporal pass) and just less."""
+    print(f"wide verdicts V={V} gamma={gamma} x{copies}", flush=True)
+    logits, q, cand, u, expect = row_verdict_case(V, gamma)
+    tile = lambda a: np.ascontiguousarray(np.concatenate([a] * copies))
+    logits, q, cand, u, expect = tile(logits), tile(q), tile(cand), tile(u), expect * copies
+    B = len(expect)
+    u[:, gamma] = dg.make_uniforms(31, dg.VERIFY_STREAM, 0, 0, B)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * B * (gamma + 1),), float("nan"), device="cuda")
+    api.sd_accept(dev(logits), gamma, 1.0, dev(cand), dev(q), dev(u), na, nx, ws)
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert na_h.tolist() == expect
+    assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1 + B // 50
+
+
 @pytest.mark.parametrize("V,gamma,copies", [(1024, 15, 1), (1028, 15, 1), (4096, 15, 1), (8192, 15, 1), (16384, 2, 22), (32000, 15, 1),
                                             (32768, 2, 22), (8192, 1, 44), (16384, 1, 44)])
 def test_more_rows_than_compute_units(V, gamma, copies):
