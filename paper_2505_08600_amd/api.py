@@ -24,7 +24,8 @@ EXPORTS = ["sd_load_model", "sd_free_model", "sd_ctx_create", "sd_ctx_free", "sd
            "sd_prefill", "sd_draft", "sd_verify", "sd_commit", "sd_route", "sd_ctx_sync", "sd_ctx_get_tokens",
            "sd_ctx_set_kv", "sd_ctx_truncate", "sd_debug_read", "sd_debug_layout_index", "sd_last_logits", "sd_set_option", "sd_profile_read", "sd_last_error",
            "sd_eq1_speedup", "sd_choose_gamma", "sd_alpha_hat", "sd_model_set_lora", "sd_ctx_set_adapters",
-           "sd_classifier_create", "sd_classifier_destroy", "sd_route_classifier", "sd_accept",
+           "sd_classifier_create", "sd_classifier_destroy", "sd_route_classifier", "sd_route_classifier_ws",
+           "sd_classifier_workspace", "sd_accept",
            "sd_accept_static", "sd_debug_stream_read", "sd_debug_gemm_plan", "sd_debug_gemm_splits",
            "sd_policy_set", "sd_policy_choose", "sd_policy_read"]
 
@@ -108,6 +109,9 @@ def lib():
         L.sd_classifier_destroy.argtypes = [vp]
         L.sd_classifier_destroy.restype = None
         L.sd_route_classifier.argtypes = [vp, vp, vp, i32, i32, vp, vp, vp]
+        L.sd_route_classifier_ws.argtypes = [vp, vp, vp, i32, i32, vp, vp, vp, vp]
+        L.sd_classifier_workspace.argtypes = [vp, i32, i32]
+        L.sd_classifier_workspace.restype = C.c_int64
         L.sd_eq1_speedup.argtypes = [C.c_double, i32, C.c_double]
         L.sd_eq1_speedup.restype = C.c_double
         L.sd_choose_gamma.argtypes = [C.c_double, C.c_double, i32, C.POINTER(C.c_double)]
@@ -431,10 +435,13 @@ class Classifier:
 
     def route(self, tokens: torch.Tensor, lens: torch.Tensor, draft_id: torch.Tensor,
               logits: Optional[torch.Tensor] = None) -> None:
-        """sd_route_classifier on the current stream; tokens int32 [n][max_len], lens int32 [n]."""
+        """sd_route_classifier_ws on the current stream; tokens int32 [n][max_len], lens int32 [n].  The workspace is the caching
+        allocator's, in order with that stream."""
         with torch.cuda.device(self.device):
-            _check(lib().sd_route_classifier(self.h, _dp(tokens), _dp(lens), tokens.shape[0], tokens.shape[1],
-                                             _dp(logits), _dp(draft_id), _stream()))
+            need = lib().sd_classifier_workspace(self.h, tokens.shape[0], tokens.shape[1])
+            ws = torch.empty(need, dtype=torch.uint8, device=tokens.device) if need > 0 else None
+            _check(lib().sd_route_classifier_ws(self.h, _dp(tokens), _dp(lens), tokens.shape[0], tokens.shape[1],
+                                                _dp(logits), _dp(draft_id), _dp(ws), _stream()))
 
     def close(self):
         if getattr(self, "h", None):

@@ -6,13 +6,15 @@
 // projection (dt_rank + 2 d_state outputs) crosses threads, through LDS.  Everything without a
 // dependence between tokens is done for a chunk of tokens at a time.  Pooling and the output
 // projection commute (both linear), so the channel outputs are averaged first and projected once
-// per prompt.  Up to 192 channels four threads share a channel's states (classifier_quad_kernel),
+// per prompt.  Up to 192 channels four threads share a channel's states (classifier_quad_kernel, classifier_run_kernel),
 // above that a thread has a channel to itself (classifier_kernel).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sd.h"
@@ -31,6 +33,9 @@ struct ClsView {
     // table[v] = emb[v] W_in, [vocab][2 d_inner]: the embedding and the input projection are both
     // functions of the token id alone, so the library multiplies them out once at creation.
     const float *table, *conv_w, *conv_b, *w_x, *w_dt, *b_dt, *a_log, *d, *w_out, *w_fc, *b_fc;
+    // w_head[k][c] = sum_m W_out[c][m] W_fc[k][m] (added in 64 bits at creation): pooling, output projection and linear layer are
+    // all linear, so the averaged channels meet one matrix (classifier_run_kernel)
+    const float *w_head;
     int vocab, d_model, d_inner, d_state, dt_rank, d_conv, n_classes;
 };
 
@@ -64,6 +69,18 @@ classifier_table_kernel(const float *__restrict__ emb, const float *__restrict__
         float acc = 0.f;
         for (int k = 0; k < d_model; ++k) acc = fmaf(e[k], w_in[(size_t)k * cols + c], acc);
         table[v * cols + c] = acc;
+    }
+}
+
+// head[k][c] = sum_m w_out[c][m] w_fc[k][m]; one block per class.
+__global__ void __launch_bounds__(256)
+classifier_head_kernel(const float *__restrict__ w_out, const float *__restrict__ w_fc, int d_inner, int d_model, float *__restrict__ head)
+{
+    const int k = blockIdx.x;
+    for (int c = threadIdx.x; c < d_inner; c += blockDim.x) {
+        double acc = 0.0;
+        for (int m = 0; m < d_model; ++m) acc = fma((double)w_out[(size_t)c * d_model + m], (double)w_fc[(size_t)k * d_model + m], acc);
+        head[(size_t)k * d_inner + c] = (float)acc;
     }
 }
 
@@ -481,6 +498,416 @@ classifier_quad_kernel(ClsView v, const int32_t *__restrict__ tokens, const int3
     }
 }
 
+// The same work in equal runs of chunks, a block per compute unit, for callers that bring a workspace.
+// A block per prompt spends 6 us on launch, weights and the first dependent loads of every prompt, and the longest prompt
+// sets the time of a small batch (128 tokens: 34 us of chunks).  Here the chunks of all prompts are dealt out in equal runs, weights
+// are loaded once per run, and the head is one matrix.  A run that starts inside a prompt works from a zero state; with P
+// the product of its decays and G the sum of C P silu(z) over its tokens, the state before it enters the pooled sum as G . h and the
+// state behind it as P h.  So the block leaves the record (G, P, state, sums) of that prompt's part in the workspace, the block a
+// prompt starts in leaves what it has, and classifier_join_kernel joins them in order.
+// Bound: vector issue and barriers of 4.3 - 4.5 us a chunk, 4.4 us from the start of a block to its first chunk, 4.7 us for the
+// second launch.
+// Measured, 192 channels, a block per prompt / runs (us): 8 prompts of up to 64 tokens 21.0 / 16.4, 40 of up to 128 27.7 / 19.3, 100 of
+// up to 40 19.6 / 19.3, 200 of up to 200 52.1 / 25.4, 400 of up to 128 50.2 / 35.0, 1000 93 / 60, 4000 293 / 191; 3000 of up to 16 125 / 76;
+// all of one length: 400 x 128 90 / 88, 200 x 128 44 / 51, 100 x 200 65 / 48, 2000 x 200 516 / 532, 20 of 900 - 1000 288 / 49.
+#define CQ_WIN 64 // chunks whose places are laid out at a time
+#define CQ_BLOCKS 256 // blocks at most: one per compute unit
+__host__ __device__ static constexpr size_t cq_run_lds_floats(int di)
+{
+    // x [TC][di + 4] | delta [TC][di + 4] (the projection's partial sums before that) | (delta x, silu(z)) [TC][di + 4] | r, B, C [TC][52]
+    return 4 * (size_t)CQ_TC * (di + 4) + CQ_TC * CQ_ROW;
+}
+// Workspace of nb blocks of t threads, in floats: records [nb][14][t] | open prompts [nb][6][t] | notes [nb][8]
+__host__ __device__ static inline size_t cq_rec_at(size_t b, int t) { return b * 14 * (size_t)t; }
+__host__ __device__ static inline size_t cq_open_at(size_t nb, size_t b, int t) { return (nb * 14 + b * 6) * (size_t)t; }
+__host__ __device__ static inline size_t cq_note_at(size_t nb, size_t b, int t) { return nb * 20 * (size_t)t + b * 8; }
+// does the prompt the run starts in end in it (a prompt that ended before: 1 as well), its flag; prompt that starts here and is left open or -1, its flag
+enum CqNote { CQ_N_CLOSED, CQ_N_BAD, CQ_N_OPEN, CQ_N_OPEN_BAD };
+
+__device__ __forceinline__ int cls_len(const int32_t *lens, int i, int max_len) { return min(max(lens[i], 0), max_len); }
+__device__ __forceinline__ int cls_chunks(int L) { return max(1, (L + CQ_TC - 1) / CQ_TC); } // (an empty prompt has one, of no tokens)
+
+// Mean over tokens, head, arg max of a prompt whose sums are complete: pooled per (channel, quarter) thread, pooled_d per
+// (channel, token group) thread.  bad: uniform.
+template <int DI>
+__device__ __forceinline__ void classifier_finish(const ClsView &v, int i, int L, float pooled, float pooled_d, bool bad, float *s_pool, float *s_mean,
+                                                  float *s_logit, float *logits, int32_t *draft_id)
+{
+    constexpr int waves = DI / 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    s_pool[(lane >> 4) * DI + wave * 16 + (lane & 15)] = pooled_d;
+    pooled += dpp_f<0xB1>(pooled);
+    pooled += dpp_f<0x4E>(pooled);
+    lds_sync();
+    if ((tid & 3) == 0) {
+        const int c = tid >> 2;
+        const float t = pooled + ((s_pool[c] + s_pool[DI + c]) + (s_pool[2 * DI + c] + s_pool[3 * DI + c]));
+        s_mean[c] = L > 0 ? t / (float)L : 0.f;
+    }
+    lds_sync();
+    for (int k = wave; k < v.n_classes; k += waves) {
+        float o = 0.f;
+#pragma unroll
+        for (int m = 0; m < DI; m += 64) o = fmaf(s_mean[m + lane], v.w_head[(size_t)k * DI + m + lane], o);
+        o = wave_sum_dpp(o);
+        if (lane == 0) {
+            o += v.b_fc[k];
+            s_logit[k] = o;
+            if (logits) logits[(size_t)i * v.n_classes + k] = o;
+        }
+    }
+    lds_sync();
+    if (tid == 0) {
+        int best = 0;
+        for (int k = 1; k < v.n_classes; ++k)
+            if (s_logit[k] > s_logit[best]) best = k;
+        draft_id[i] = bad ? -1 : best;
+    }
+}
+
+__device__ __forceinline__ void cq_record(float *rec, int T, const float *G, const float *P, const float *h, float pooled, float pooled_d)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rec[k * T] = G[k], rec[(4 + k) * T] = P[k], rec[(8 + k) * T] = h[k];
+    rec[12 * T] = pooled;
+    rec[13 * T] = pooled_d;
+}
+
+template <int DI> // d_inner: 64, 128 or 192
+__global__ void __launch_bounds__(4 * DI, DI / 64)
+classifier_run_kernel(ClsView v, const int32_t *__restrict__ tokens, const int32_t *__restrict__ lens, int n, int max_len,
+                       float *__restrict__ logits, int32_t *__restrict__ draft_id, float *__restrict__ ws)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    __shared__ __align__(16) float lds[cq_run_lds_floats(DI)];
+    __shared__ float s_pool[4 * DI], s_mean[DI], s_logit[CLS_MAX_CLASSES];
+    __shared__ int4 s_chunk[CQ_WIN]; // (prompt, first token, length)
+    __shared__ int s_sum[16], s_max[16], s_run[2];
+    constexpr int di = DI, sx = DI + 4, T = 4 * DI; // (rows 4 banks apart)
+    constexpr int waves = DI / 16, nkq = waves / 3, per = DI / 4 / nkq; // (2): a wave's share is `per` instructions
+    static_assert(nkq * per * 4 == DI, "shares of whole instructions");
+    float *s_x = lds, *s_delta = s_x + CQ_TC * sx, *s_part = s_delta;
+    float2 *s_dz = (float2 *)(s_delta + CQ_TC * sx);
+    float *s_dbc = s_delta + 3 * CQ_TC * sx;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, tq = lane >> 4, c = wave * 16 + l16; // (1): channel, group of four tokens
+    const int cs = tid >> 2, sub = tid & 3;                         // (3): channel, quarter of the states
+
+    // chunks of the prompts this thread looks after (pp in a row), and of those before them
+    const int pp = (n + T - 1) / T, p_lo = min(n, tid * pp), p_hi = min(n, p_lo + pp);
+    int mine = 0, longest = 0;
+    for (int p = p_lo; p < p_hi; ++p) {
+        const int nc = cls_chunks(cls_len(lens, p, max_len));
+        mine += nc;
+        longest = max(longest, nc);
+    }
+
+    // (2): this wave's 16 outputs and channels (four per instruction); its 16 channels of the step sizes
+    const int tile = wave % 3, kq = wave / 3;
+    const bool proj = kq < nkq;
+    const int k_lo = proj ? kq * per : 0;
+    const int J = v.dt_rank + 2 * v.d_state;
+    const int col = tile == 0 ? l16 : v.dt_rank + (tile - 1) * v.d_state + l16;
+    const bool has_col = l16 < (tile == 0 ? v.dt_rank : v.d_state);
+    float bd[4];
+    float bw[per];
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        const float w = v.w_x[((k_lo + k) * 4 + tq) * J + (has_col ? col : 0)];
+        bw[k] = has_col ? w : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float w = v.w_dt[min(4 * k + tq, v.dt_rank - 1) * di + c];
+        bd[k] = 4 * k + tq < v.dt_rank ? w : 0.f;
+    }
+    // (1): this channel's constants
+    float cw[CLS_MAX_CONV];
+#pragma unroll
+    for (int j = 0; j < CLS_MAX_CONV; ++j) {
+        const int src = j - (CLS_MAX_CONV - v.d_conv); // taps right-aligned: the last one meets the current token
+        cw[j] = src >= 0 ? v.conv_w[c * v.d_conv + src] : 0.f;
+    }
+    const float cb = v.conv_b[c], bdt = v.b_dt[c], D = v.d[c];
+    // (3): decay rates (times log2 e: decay = 2^(Delta A))
+    float A[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int st = sub * 4 + k;
+        A[k] = st < v.d_state ? -expf(v.a_log[cs * v.d_state + st]) * 1.44269504088896f : 0.f;
+    }
+
+    // this block's run of chunks
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += x;
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) longest = max(longest, __shfl_xor(longest, o, 64));
+    if (lane == 63) {
+        s_sum[wave] = incl;
+        s_max[wave] = longest;
+    }
+    lds_sync();
+    int first = incl - mine, total = 0; // (first: chunks before this thread's prompts)
+    for (int w = 0; w < waves; ++w) {
+        const int x = s_sum[w];
+        if (w < wave) first += x;
+        total += x;
+        longest = max(longest, s_max[w]);
+    }
+    total = __builtin_amdgcn_readfirstlane(total); // (the loops below are uniform: keep their bounds in scalar registers)
+    longest = __builtin_amdgcn_readfirstlane(longest);
+    const int nb = gridDim.x, run = (total + nb - 1) / nb;
+    int run0 = (int)min((int64_t)total, (int64_t)blockIdx.x * run), run1 = min(total, run0 + run);
+    if (n <= nb && longest <= run + 1) { // cutting would save a chunk at most: a block per prompt (200 prompts of 128 tokens: 51 us, 54 cut)
+        if (tid == 0) s_run[0] = s_run[1] = total;
+        lds_sync();
+        for (int p = p_lo, q = first; p < p_hi; ++p) {
+            const int nc = cls_chunks(cls_len(lens, p, max_len));
+            if (p == (int)blockIdx.x) {
+                s_run[0] = q;
+                s_run[1] = q + nc;
+            }
+            q += nc;
+        }
+        lds_sync();
+        run0 = __builtin_amdgcn_readfirstlane(s_run[0]);
+        run1 = __builtin_amdgcn_readfirstlane(s_run[1]);
+    }
+
+    // The table rows of this lane's four tokens.  Ids run one chunk ahead of the rows (lane t of every wave holds the id of
+    // token t), the rows one chunk ahead of their use; the convolution's history is the neighbouring token group's.
+    float nx[4], nz[4], px[4]; // next rows; this lane's inputs of the chunk before (the last three count)
+    bool bad = false, bad_next = false;
+    int idv = 0;
+    auto load_ids = [&](int k) {
+        const int4 e = s_chunk[k];
+        idv = e.y + l16 < e.z ? tokens[(size_t)e.x * max_len + e.y + l16] : 0;
+    };
+    auto gather = [&](int k) {
+        const int4 e = s_chunk[k];
+        bad_next = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int id = __shfl(idv, 4 * tq + j, 64);
+            const bool live = e.y + 4 * tq + j < e.z, in = (unsigned)id < (unsigned)v.vocab;
+            bad_next |= live && !in;
+            const float *row = v.table + (size_t)(in ? id : 0) * 2 * di + c;
+            const float a = row[0], b = row[di];
+            nx[j] = live && in ? a : 0.f;
+            nz[j] = live && in ? b : 0.f;
+        }
+    };
+    // state and sums of the prompt, or (known false) of its part in this run, with the part's decay product and G
+    float h[4], P[4], Gs[4], pooled = 0.f, pooled_d = 0.f;
+    bool known = true;
+    int closed = 1, closed_bad = 0, prompt = -1, at = 0, len = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h[k] = Gs[k] = px[k] = nx[k] = nz[k] = 0.f, P[k] = 1.f;
+
+    for (int w0 = run0; w0 < run1; w0 += CQ_WIN) {
+        const int nw = min(CQ_WIN, run1 - w0);
+        lds_sync(); // (the window before is done with)
+        for (int p = p_lo, q = first; p < p_hi && q < w0 + nw; ++p) {
+            const int L = cls_len(lens, p, max_len), nc = cls_chunks(L);
+            for (int k = max(q, w0); k < min(q + nc, w0 + nw); ++k) s_chunk[k - w0] = make_int4(p, (k - q) * CQ_TC, L, 0);
+            q += nc;
+        }
+        lds_sync();
+        load_ids(0);
+        if (w0 == run0 && s_chunk[0].y > 0) { // the run starts inside a prompt: the convolution's history of the four tokens before
+            const int4 e = s_chunk[0];
+            known = false;
+            closed = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int id = tokens[(size_t)e.x * max_len + e.y - 4 + j];
+                const bool in = (unsigned)id < (unsigned)v.vocab;
+                const float a = v.table[(size_t)(in ? id : 0) * 2 * di + c];
+                px[j] = in ? a : 0.f;
+            }
+        }
+        gather(0);
+        if (nw > 1) load_ids(1);
+        for (int kc = 0; kc < nw; ++kc) {
+            const int4 e = s_chunk[kc];
+            prompt = __builtin_amdgcn_readfirstlane(e.x);
+            at = __builtin_amdgcn_readfirstlane(e.y);
+            len = __builtin_amdgcn_readfirstlane(e.z);
+            const int nt = min(CQ_TC, len - at);
+            if (at == 0) {
+                known = true;
+                bad = false;
+                pooled = pooled_d = 0.f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) h[k] = px[k] = 0.f;
+            }
+            bad |= bad_next;
+            // (1) causal depthwise convolution and SiLU
+            float z[4], raw[CLS_MAX_CONV + 3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) raw[j] = __shfl(tq == 3 ? px[j + 1] : nx[j + 1], (lane + 48) & 63, 64);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) raw[3 + j] = px[j] = nx[j];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float pre = cb;
+#pragma unroll
+                for (int j = 0; j < CLS_MAX_CONV; ++j) pre = fmaf(cw[j], raw[t + j], pre);
+                z[t] = nz[t] * __builtin_amdgcn_rcpf(1.f + __expf(-nz[t]));
+                s_x[(4 * tq + t) * sx + c] = pre * __builtin_amdgcn_rcpf(1.f + __expf(-pre));
+            }
+            if (kc + 1 < nw) gather(kc + 1); // the next chunk's rows fly while this one is worked on
+            if (kc + 2 < nw) load_ids(kc + 2);
+            lds_sync();
+            // (2) lane (token l % 16, channel l / 16 of four) against (channel, output l % 16); the result leaves tokens
+            // 4 (l / 16) .. + 3 of output l % 16
+            if (proj) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+                const float *xs = s_x + l16 * sx + tq + 4 * k_lo;
+#pragma unroll
+                for (int k = 0; k < per; k += 2) { // (two chains)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k], bw[k], acc, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k + 4], bw[k + 1], acc2, 0, 0, 0);
+                }
+                float *dst = s_part + kq * CQ_TC * CQ_OUT + tq * 4 * CQ_OUT + tile * 16 + l16;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dst[r * CQ_OUT] = acc[r] + acc2[r];
+            }
+            lds_sync();
+            for (int q = tid; q < CQ_TC * CQ_OUT; q += T) {
+                float p = 0.f;
+#pragma unroll
+                for (int w = 0; w < nkq; ++w) p += s_part[w * CQ_TC * CQ_OUT + q];
+                s_dbc[q / CQ_OUT * CQ_ROW + q % CQ_OUT] = p;
+            }
+            lds_sync();
+            // (2), (1) step sizes
+            f32x4 dt4 = {bdt, bdt, bdt, bdt};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dt4 = __builtin_amdgcn_mfma_f32_16x16x4f32(s_dbc[l16 * CQ_ROW + 4 * k + tq], bd[k], dt4, 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int row = 4 * tq + t;
+                const float dt = dt4[t];
+                // softplus = log1p(e^dt): log(u) e / (u - 1) with u = 1 + e undoes the rounding of u (steps are ~1e-3..0.1)
+                const float ex = __expf(dt), u = 1.f + ex;
+                const float delta = dt > 20.f ? dt : (u == 1.f ? ex : logf(u) * ex * __builtin_amdgcn_rcpf(u - 1.f));
+                s_delta[row * sx + c] = delta;
+                const float x = s_x[row * sx + c];
+                s_dz[row * sx + c] = make_float2(delta * x, z[t]);
+                if (row < nt) pooled_d = fmaf(x * D, z[t], pooled_d);
+            }
+            lds_sync();
+            // (3) the state update, token by token, in this thread's registers
+            const float *sd = s_delta + cs;
+            const float2 *sz = s_dz + cs;
+            const float *sb = s_dbc + 16 + sub * 4;
+            auto token = [&](int t, auto with_g) {
+                const float delta = sd[t * sx];
+                const float2 dz = sz[t * sx];
+                const float4 B = *(const float4 *)(sb + t * CQ_ROW), C = *(const float4 *)(sb + t * CQ_ROW + 16);
+                float a[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) a[k] = __builtin_amdgcn_exp2f(delta * A[k]);
+                h[0] = fmaf(a[0], h[0], dz.x * B.x);
+                h[1] = fmaf(a[1], h[1], dz.x * B.y);
+                h[2] = fmaf(a[2], h[2], dz.x * B.z);
+                h[3] = fmaf(a[3], h[3], dz.x * B.w);
+                const float acc = fmaf(C.w, h[3], fmaf(C.z, h[2], fmaf(C.y, h[1], C.x * h[0])));
+                pooled = fmaf(acc, dz.y, pooled);
+                if constexpr (decltype(with_g)::value) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) P[k] *= a[k];
+                    Gs[0] = fmaf(C.x * dz.y, P[0], Gs[0]);
+                    Gs[1] = fmaf(C.y * dz.y, P[1], Gs[1]);
+                    Gs[2] = fmaf(C.z * dz.y, P[2], Gs[2]);
+                    Gs[3] = fmaf(C.w * dz.y, P[3], Gs[3]);
+                }
+            };
+            auto update = [&](auto with_g) {
+                int t = 0;
+                for (; t + 4 <= nt; t += 4) { // (four tokens' operands in flight)
+                    token(t, with_g);
+                    token(t + 1, with_g);
+                    token(t + 2, with_g);
+                    token(t + 3, with_g);
+                }
+                for (; t < nt; ++t) token(t, with_g);
+            };
+            if (known) update(std::false_type{}); // (uniform)
+            else update(std::true_type{});
+            if (at + CQ_TC >= len) { // the prompt ends
+                const bool any_bad = __any(bad); // (every wave sees all token ids)
+                if (known) classifier_finish<DI>(v, prompt, len, pooled, pooled_d, any_bad, s_pool, s_mean, s_logit, logits, draft_id);
+                else {
+                    closed = 1;
+                    closed_bad = any_bad;
+                    cq_record(ws + cq_rec_at(blockIdx.x, T) + tid, T, Gs, P, h, pooled, pooled_d);
+                }
+                prompt = -1;
+            }
+        }
+    }
+    const bool any_bad = __any(bad), open = prompt >= 0 && known;
+    if (prompt >= 0 && !known) { // the whole run lies inside one prompt
+        closed_bad = any_bad;
+        cq_record(ws + cq_rec_at(blockIdx.x, T) + tid, T, Gs, P, h, pooled, pooled_d);
+    }
+    if (open) {
+        float *o = ws + cq_open_at(nb, blockIdx.x, T) + tid;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k * T] = h[k];
+        o[4 * T] = pooled;
+        o[5 * T] = pooled_d;
+    }
+    if (tid == 0) {
+        int *note = (int *)(ws + cq_note_at(nb, blockIdx.x, T));
+        note[CQ_N_CLOSED] = closed;
+        note[CQ_N_BAD] = closed_bad;
+        note[CQ_N_OPEN] = open ? prompt : -1;
+        note[CQ_N_OPEN_BAD] = any_bad;
+    }
+}
+
+// Block b joins the prompt that block b of classifier_run_kernel left open with the records of the blocks behind it.
+template <int DI>
+__global__ void __launch_bounds__(4 * DI, DI / 64)
+classifier_join_kernel(ClsView v, const int32_t *__restrict__ lens, int max_len, float *__restrict__ logits, int32_t *__restrict__ draft_id,
+                       const float *__restrict__ ws)
+{
+    __shared__ float s_pool[4 * DI], s_mean[DI], s_logit[CLS_MAX_CLASSES];
+    constexpr int T = 4 * DI;
+    const int nb = gridDim.x, tid = threadIdx.x;
+    const int *note = (const int *)(ws + cq_note_at(nb, blockIdx.x, T));
+    const int i = note[CQ_N_OPEN];
+    if (i < 0) return;
+    bool bad = note[CQ_N_OPEN_BAD] != 0;
+    float h[4], pooled, pooled_d;
+    const float *o = ws + cq_open_at(nb, blockIdx.x, T) + tid;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h[k] = o[k * T];
+    pooled = o[4 * T];
+    pooled_d = o[5 * T];
+    for (int b = blockIdx.x + 1; b < nb; ++b) { // (an open prompt goes on in the next block's run and ends in one of them)
+        const int *nt = (const int *)(ws + cq_note_at(nb, b, T));
+        const float *rec = ws + cq_rec_at(b, T) + tid;
+        float G[4], P[4], S[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) G[k] = rec[k * T], P[k] = rec[(4 + k) * T], S[k] = rec[(8 + k) * T];
+        pooled += fmaf(G[3], h[3], fmaf(G[2], h[2], fmaf(G[1], h[1], fmaf(G[0], h[0], rec[12 * T]))));
+        pooled_d += rec[13 * T];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) h[k] = fmaf(P[k], h[k], S[k]);
+        bad |= nt[CQ_N_BAD] != 0;
+        if (nt[CQ_N_CLOSED]) break;
+    }
+    classifier_finish<DI>(v, i, cls_len(lens, i, max_len), pooled, pooled_d, bad, s_pool, s_mean, s_logit, logits, draft_id);
+}
+
 // ---------------------------------------------------------------- C ABI
 
 extern "C" int sd_classifier_create(const sd_classifier_shape *s, const sd_classifier_weights *w, sd_classifier **out)
@@ -503,10 +930,10 @@ extern "C" int sd_classifier_create(const sd_classifier_shape *s, const sd_class
     if (lds_bytes > CLS_LDS_LIMIT)
         return sd_fail(SD_EINVAL, "sd_classifier_create: d_inner * (dt_rank + 2 d_state) does not fit the 64 KB of LDS "
                                   "the per-token projection is staged in");
-    // slot 0 holds the table emb W_in; slot 1 is unused once the table is built (emb and W_in go to a
-    // temporary allocation), the rest are copies of the caller's arrays.
+    // slot 0 holds the table emb W_in, slot 1 the head W_out W_fc (emb and W_in go to a temporary allocation), the rest are
+    // copies of the caller's arrays.
     const size_t cols = 2 * (size_t)s->d_inner;
-    const size_t count[12] = {(size_t)s->vocab * cols, 0,
+    const size_t count[12] = {(size_t)s->vocab * cols, (size_t)s->n_classes * s->d_inner,
                               (size_t)s->d_inner * s->d_conv, (size_t)s->d_inner, (size_t)s->d_inner * J,
                               (size_t)s->dt_rank * s->d_inner, (size_t)s->d_inner, (size_t)s->d_inner * s->d_state,
                               (size_t)s->d_inner, (size_t)s->d_inner * s->d_model, (size_t)s->n_classes * s->d_model,
@@ -525,10 +952,9 @@ extern "C" int sd_classifier_create(const sd_classifier_shape *s, const sd_class
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = hipMalloc(&c->mem, total);
     if (e == hipSuccess) e = hipMalloc(&tmp, emb_slot + win_bytes);
-    const float **dst[12] = {&c->v.table, nullptr, &c->v.conv_w, &c->v.conv_b, &c->v.w_x, &c->v.w_dt, &c->v.b_dt,
+    const float **dst[12] = {&c->v.table, &c->v.w_head, &c->v.conv_w, &c->v.conv_b, &c->v.w_x, &c->v.w_dt, &c->v.b_dt,
                              &c->v.a_log, &c->v.d, &c->v.w_out, &c->v.w_fc, &c->v.b_fc};
     for (int k = 0; k < 12 && e == hipSuccess; ++k) {
-        if (!dst[k]) continue;
         *dst[k] = (const float *)((char *)c->mem + off[k]);
         if (k >= 2) e = hipMemcpy((char *)c->mem + off[k], src[k], count[k] * sizeof(float), hipMemcpyHostToDevice);
     }
@@ -537,6 +963,8 @@ extern "C" int sd_classifier_create(const sd_classifier_shape *s, const sd_class
     if (e == hipSuccess) {
         hipLaunchKernelGGL(classifier_table_kernel, dim3(s->vocab), dim3(256), 0, (hipStream_t)0, (const float *)tmp,
                            (const float *)((char *)tmp + emb_slot), s->d_model, (int)cols, (float *)c->mem);
+        hipLaunchKernelGGL(classifier_head_kernel, dim3(s->n_classes), dim3(256), 0, (hipStream_t)0, c->v.w_out, c->v.w_fc, s->d_inner,
+                           s->d_model, (float *)c->v.w_head);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -557,28 +985,66 @@ extern "C" void sd_classifier_destroy(sd_classifier *c)
     delete c;
 }
 
-extern "C" int sd_route_classifier(const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
-                                   int32_t max_len, float *logits, int32_t *draft_id, void *stream)
+// Blocks of classifier_run_kernel for a call with a workspace (0: the kernel has no form for the classifier).
+static int cq_blocks(const sd_classifier *c, int32_t n, int32_t max_len)
 {
-    if (!c || !tokens || !lens || !draft_id) return sd_fail(SD_EINVAL, "sd_route_classifier: null argument");
-    if (n < 1 || max_len < 1) return sd_fail(SD_EINVAL, "sd_route_classifier: non-positive size");
+    if (c->v.d_inner > 192 || (max_len <= CQ_TC && n <= CQ_BLOCKS)) return 0; // (nothing to deal out)
+    return (int)std::min<int64_t>(CQ_BLOCKS, (int64_t)n * ((max_len + CQ_TC - 1) / CQ_TC));
+}
+
+extern "C" int64_t sd_classifier_workspace(const sd_classifier *c, int32_t n, int32_t max_len)
+{
+    if (!c || n < 1 || max_len < 1) return sd_fail(SD_EINVAL, "sd_classifier_workspace: null classifier or non-positive size");
+    const int nb = cq_blocks(c, n, max_len);
+    return nb ? (int64_t)cq_note_at(nb, nb, 4 * c->v.d_inner) * (int64_t)sizeof(float) : 0;
+}
+
+static int route_classifier(const char *who, const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
+                            int32_t max_len, float *logits, int32_t *draft_id, float *ws, void *stream)
+{
+    if (!c || !tokens || !lens || !draft_id) return sd_fail(SD_EINVAL, std::string(who) + ": null argument");
+    if (n < 1 || max_len < 1) return sd_fail(SD_EINVAL, std::string(who) + ": non-positive size");
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev != c->device)
-        return sd_fail(SD_EINVAL, "sd_route_classifier: the classifier was created on another device");
+        return sd_fail(SD_EINVAL, std::string(who) + ": the classifier was created on another device");
+    const int nb = ws ? cq_blocks(c, n, max_len) : 0;
     // Up to 192 channels the four-threads-per-channel kernel is ahead at every batch and prompt length measured (thread per
     // channel -> this, us): 192 channels, one prompt of 128 tokens 124 -> 44, 4096 ragged ones 378 -> 298, 4096 of 16 tokens
     // 191 -> 168, 2000 of 512 tokens 1772 -> 1213; 64 channels 127 -> 30, 198 -> 92, 71 -> 45, 586 -> 381.  At 256 channels
     // its 16 waves no longer share the projection out evenly, above that its block would exceed 1024 threads.
-#define SD_QUAD(DI)                                                                                                          \
-    hipLaunchKernelGGL(classifier_quad_kernel<DI>, dim3(n), dim3(4 * DI), cq_lds_floats(DI, c->v.d_model) * sizeof(float), \
-                       (hipStream_t)stream, c->v, tokens, lens, max_len, logits, draft_id)
+#define SD_QUAD(DI)                                                                                                           \
+    do {                                                                                                                      \
+        if (!nb)                                                                                                              \
+            hipLaunchKernelGGL(classifier_quad_kernel<DI>, dim3(n), dim3(4 * DI), cq_lds_floats(DI, c->v.d_model) * sizeof(float), \
+                               (hipStream_t)stream, c->v, tokens, lens, max_len, logits, draft_id);                           \
+        else {                                                                                                                \
+            hipLaunchKernelGGL(classifier_run_kernel<DI>, dim3(nb), dim3(4 * DI), 0, (hipStream_t)stream, c->v, tokens, lens, \
+                               n, max_len, logits, draft_id, ws);                                                             \
+            if (join)                                                                                                         \
+                hipLaunchKernelGGL(classifier_join_kernel<DI>, dim3(nb), dim3(4 * DI), 0, (hipStream_t)stream, c->v, lens,    \
+                                   max_len, logits, draft_id, ws);                                                            \
+        }                                                                                                                     \
+    } while (0)
+    const bool join = max_len > CQ_TC; // (no run starts inside a prompt of one chunk)
     if (c->v.d_inner == 64) SD_QUAD(64);
     else if (c->v.d_inner == 128) SD_QUAD(128);
     else if (c->v.d_inner == 192) SD_QUAD(192);
     else
         hipLaunchKernelGGL(classifier_kernel, dim3(n), dim3(c->v.d_inner), c->lds_bytes, (hipStream_t)stream, c->v, tokens,
                            lens, max_len, logits, draft_id);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return sd_fail(SD_EHIP, std::string("sd_route_classifier: ") + hipGetErrorString(e));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return sd_fail(SD_EHIP, std::string(who) + ": " + hipGetErrorString(e));
     return SD_OK;
+}
+
+extern "C" int sd_route_classifier(const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
+                                   int32_t max_len, float *logits, int32_t *draft_id, void *stream)
+{
+    return route_classifier("sd_route_classifier", c, tokens, lens, n, max_len, logits, draft_id, nullptr, stream);
+}
+
+extern "C" int sd_route_classifier_ws(const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
+                                      int32_t max_len, float *logits, int32_t *draft_id, float *workspace, void *stream)
+{
+    return route_classifier("sd_route_classifier_ws", c, tokens, lens, n, max_len, logits, draft_id, workspace, stream);
 }

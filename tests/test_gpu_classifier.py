@@ -98,6 +98,49 @@ def test_padding_is_ignored_and_batch_position_does_not_matter():
     assert np.array_equal(ids[perm], ids2) and np.array_equal(logits[perm], logits2)
 
 
+@pytest.mark.parametrize("d_inner,n,max_len", [(192, 1, 700), (192, 400, 128), (128, 300, 60), (64, 40, 200), (192, 30, 33), (192, 6000, 80), (192, 520, 16), (64, 3, 2000)])
+def test_runs_of_chunks_that_cut_prompts(d_inner, n, max_len):
+    """Batches dealt out in runs of chunks that start inside prompts: one prompt over many workgroups, runs of one, several and
+    many chunks (more than are laid out at a time), prompts of one chunk; a sample of the batch against the oracle, in the batch,
+    alone and in the batch permuted; the entry without a workspace; an id out of range in the last token of a prompt."""
+    print(f"classifier batches d_inner={d_inner} n={n} max_len={max_len}", flush=True)
+    shape = dg.ClassifierShape("classifier_cut", vocab=97, d_model=24, d_inner=d_inner, d_state=16, dt_rank=6, d_conv=4, n_classes=5)
+    w = dg.make_classifier(shape, 41)
+    rng = dg._rng(41, 53)
+    tokens = rng.integers(0, shape.vocab, size=(n, max_len), dtype=np.int32)
+    lens = rng.integers(0, max_len + 1, size=n).astype(np.int32)
+    edge = [max_len, 0, 33, 32, 16, 17, 64, 65, 31]
+    lens[:len(edge)] = edge[:n]
+    lens = np.minimum(lens, max_len).astype(np.int32)
+    bad = min(6, n - 1)
+    if n > 1:
+        tokens[bad, lens[bad] - 1] = shape.vocab   # in the last of its segments
+    ids, logits = _run(shape, w, tokens, lens)
+    perm = np.random.default_rng(1).permutation(n)
+    ids2, logits2 = _run(shape, w, tokens[perm], lens[perm])
+    assert np.abs(logits[perm] - logits2).max() <= LOGIT_RTOL * np.abs(logits).max()
+    some = [0] + list(range(1, min(n, 12))) + [n - 1]
+    for i in some:
+        one, lone = _run(shape, w, tokens[i:i + 1], lens[i:i + 1])
+        assert np.abs(lone[0] - logits[i]).max() <= LOGIT_RTOL * np.abs(logits[i]).max(), i
+        assert (one[0] == -1) == (ids[i] == -1)
+    if n > 1:
+        assert ids[bad] == -1
+    keep = [i for i in some if n == 1 or i != bad]
+    _check(shape, w, tokens[keep], lens[keep], ids[keep], logits[keep])
+    cls = api.Classifier(shape, w)   # the entry without a workspace
+    t, l = torch.from_numpy(tokens).cuda(), torch.from_numpy(lens).cuda()
+    ids3 = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    logits3 = torch.full((n, 5), float("nan"), device="cuda")
+    assert api.lib().sd_route_classifier(cls.h, t.data_ptr(), l.data_ptr(), n, max_len, logits3.data_ptr(), ids3.data_ptr(), None) == api.SD_OK
+    torch.cuda.synchronize()
+    cls.close()
+    ids3, logits3 = ids3.cpu().numpy(), logits3.cpu().numpy()
+    assert (ids3[bad] == -1) == (n > 1)
+    _check(shape, w, tokens[keep], lens[keep], ids3[keep], logits3[keep])
+    assert np.abs(logits3 - logits).max() <= LOGIT_RTOL * np.abs(logits).max()   # (both paths within the bar of the oracle)
+
+
 def test_out_of_range_token_is_flagged_not_read():
     shape = dg.CLASSIFIER_TINY
     w = dg.make_classifier(shape, 6)
