@@ -362,6 +362,9 @@ int sd_ctx_truncate(sd_ctx *c, sd_model *m, int32_t seq, int32_t len);
 /* Copy the fp32 logits [rows][vocab] of model m's last forward into out (dev,
  * room for max_rows rows); *rows = rows copied. */
 int sd_last_logits(sd_model *m, float *out, int32_t max_rows, int32_t *rows);
+/* The same as a copy enqueued on `stream`, without synchronising: the caller orders it behind the model's last forward
+ * and in front of its next one (the same stream does both). */
+int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, int32_t *rows, void *stream);
 /* Copy one activation buffer of model m's last forward to out (HOST, fp32): name is
  * "x" (residual [rows][d_model]), "qkv" ([rows][3*d_model]), "q", "o", "a"
  * ([rows][d_model]) or "act" ([rows][d_ffn]); "seq_order" / "seq_len" give, for the

@@ -22,7 +22,7 @@ SD_FP32, SD_BF16 = 0, 1
 
 EXPORTS = ["sd_load_model", "sd_free_model", "sd_ctx_create", "sd_ctx_free", "sd_ctx_attach", "sd_ctx_set_tokens",
            "sd_prefill", "sd_draft", "sd_verify", "sd_commit", "sd_route", "sd_ctx_sync", "sd_ctx_get_tokens",
-           "sd_ctx_set_kv", "sd_ctx_truncate", "sd_debug_read", "sd_debug_layout_index", "sd_last_logits", "sd_set_option", "sd_profile_read", "sd_last_error",
+           "sd_ctx_set_kv", "sd_ctx_truncate", "sd_debug_read", "sd_debug_layout_index", "sd_last_logits", "sd_last_logits_async", "sd_set_option", "sd_profile_read", "sd_last_error",
            "sd_eq1_speedup", "sd_choose_gamma", "sd_alpha_hat", "sd_model_set_lora", "sd_ctx_set_adapters",
            "sd_classifier_create", "sd_classifier_destroy", "sd_route_classifier", "sd_route_classifier_ws",
            "sd_classifier_workspace", "sd_accept",
@@ -100,6 +100,7 @@ def lib():
         L.sd_debug_layout_index.argtypes = [i32, C.c_int64, C.c_int64, C.c_int64, C.c_int64]
         L.sd_debug_layout_index.restype = C.c_int64
         L.sd_last_logits.argtypes = [vp, vp, i32, C.POINTER(i32)]
+        L.sd_last_logits_async.argtypes = [vp, vp, i32, C.POINTER(i32), vp]
         L.sd_set_option.argtypes = [C.c_char_p, i32]
         L.sd_profile_read.argtypes = [i32, C.POINTER(C.c_char_p), C.POINTER(i32), C.POINTER(C.c_float)]
         L.sd_last_error.restype = C.c_char_p
@@ -139,6 +140,18 @@ def _stream() -> C.c_void_p:
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _forward_stream(m: "Model") -> C.c_void_p:
+    """Current stream, noted as the one of model m's last forward (see Model.last_logits)."""
+    s = torch.cuda.current_stream()
+    here = (s.device_index, s.cuda_stream)
+    if torch.cuda.is_current_stream_capturing():
+        m._captured = True
+    elif m._copy_on is not None and m._copy_on != here:
+        torch.cuda.synchronize(m._copy_on[0])  # a copy of the logits this forward overwrites may be pending on another stream
+    m._copy_on, m._forward_on = None, here
+    return C.c_void_p(s.cuda_stream)
+
+
 def _np_i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
@@ -170,6 +183,10 @@ def to_device(a: np.ndarray, device="cuda") -> torch.Tensor:
 class Model:
     """sd_load_model / sd_free_model.  The library copies the weights at load, so the staging
     tensors are released right after."""
+
+    _forward_on = None  # (device, stream) of the last forward
+    _copy_on = None     # (device, stream) of a copy of its logits that may be pending
+    _captured = False   # forwards are in a graph, whose replays this object does not see
 
     def __init__(self, shape, weights: Dict[str, object], max_rows: int, max_pos: int, device="cuda"):
         self.shape = shape
@@ -234,10 +251,18 @@ class Model:
         return out
 
     def last_logits(self) -> torch.Tensor:
-        """Copy of the fp32 logits [rows][vocab] of the last forward (synchronises)."""
+        """Copy of the fp32 logits [rows][vocab] of the last forward.  Called on the stream of that forward the copy is
+        one more operation of the stream (the result is used like that of any torch operation on it); on another
+        stream, or if forwards of this model have been captured into a graph, it synchronises with the device."""
         out = torch.empty((self.max_rows, self.shape.vocab), dtype=torch.float32, device=self.device)
         rows = C.c_int32()
-        _check(lib().sd_last_logits(self.h, _dp(out), self.max_rows, C.byref(rows)))
+        s = torch.cuda.current_stream()
+        here = (s.device_index, s.cuda_stream)
+        if here == self._forward_on and not self._captured and here[0] == out.device.index:
+            _check(lib().sd_last_logits_async(self.h, _dp(out), self.max_rows, C.byref(rows), C.c_void_p(s.cuda_stream)))
+            self._copy_on = here
+        else:
+            _check(lib().sd_last_logits(self.h, _dp(out), self.max_rows, C.byref(rows)))
         return out[:rows.value]
 
 
@@ -351,14 +376,14 @@ def layout_index(kind: int, a: int, b: int, c: int, d: int = 0) -> int:
 
 
 def sd_prefill(m: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, max_new: int) -> None:
-    _check(lib().sd_prefill(m.h, ctx.h, _dp(seq_ids), n_seq, max_new, _stream()))
+    _check(lib().sd_prefill(m.h, ctx.h, _dp(seq_ids), n_seq, max_new, _forward_stream(m)))
 
 
 def sd_draft(draft: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, gamma: int,
              temperature: float, uniforms: Optional[torch.Tensor], cand: torch.Tensor,
              q: Optional[torch.Tensor]) -> None:
     _check(lib().sd_draft(draft.h, ctx.h, _dp(seq_ids), n_seq, gamma, temperature, _dp(uniforms), _dp(cand), _dp(q),
-                          _stream()))
+                          _forward_stream(draft)))
 
 
 def sd_verify(target: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, gamma: int,
@@ -366,7 +391,7 @@ def sd_verify(target: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_se
               uniforms: Optional[torch.Tensor], n_accepted: torch.Tensor, next_token: torch.Tensor,
               commit: bool = True) -> None:
     _check(lib().sd_verify(target.h, ctx.h, _dp(seq_ids), n_seq, gamma, temperature, _dp(cand), _dp(q),
-                           _dp(uniforms), _dp(n_accepted), _dp(next_token), int(commit), _stream()))
+                           _dp(uniforms), _dp(n_accepted), _dp(next_token), int(commit), _forward_stream(target)))
 
 
 def sd_accept(logits: torch.Tensor, gamma: int, temperature: float, cand: Optional[torch.Tensor],

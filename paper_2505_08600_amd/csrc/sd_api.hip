@@ -748,6 +748,16 @@ extern "C" int sd_last_logits(sd_model *m, float *out, int32_t max_rows, int32_t
     return SD_OK;
 }
 
+extern "C" int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, int32_t *rows, void *stream)
+{
+    if (!m || !out || max_rows < 0) return sd_fail(SD_EINVAL, "sd_last_logits_async: bad argument");
+    const int n = std::min(m->last_lm_rows, max_rows);
+    if (n > 0)
+        SD_HIP(hipMemcpyAsync(out, m->logits, (size_t)n * m->cfg.vocab * sizeof(float), hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    if (rows) *rows = n;
+    return SD_OK;
+}
+
 // ---------------------------------------------------------------- one decoder forward
 static hipError_t gemm_generic(sd_model *m, hipStream_t s, int mode, const void *A, ActView a_av, WeightSeg w, int M,
                                int N, int K, float *C, void *Cact, ActView c_av)

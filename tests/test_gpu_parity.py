@@ -1715,3 +1715,67 @@ def test_config3_routed_heterogeneous_drafts_small():
     gt.close()
     for gd in gds:
         gd.close()
+
+
+def test_last_logits_keep_their_place_between_forwards():
+    """Copies taken between forwards without a synchronisation hold their own forward's logits: on the forwards' stream, on
+    another stream (which waits), with the next forward on another stream than a pending copy, and behind a graph capture."""
+    _say("last_logits between forwards")
+    st = dg.SHAPES["tiny_draft"]
+    w = dg.make_weights(st, 6, 20.0)
+    prompt = [int(t) for t in dg.make_prompt(5, 0, 16, st.vocab)]
+    gamma = 3
+    m = api.Model(st, w, 16, 128)
+    ctx = api.Context([64])
+    ctx.attach(m)
+    ctx.set_tokens([prompt])
+    api.sd_prefill(m, ctx, None, 1, len(prompt) - 1)
+    na, nx = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    cands = [torch.randint(0, st.vocab, (1, gamma), dtype=torch.int32, generator=torch.Generator().manual_seed(i)).cuda() for i in range(6)]
+
+    def verify(c):
+        api.sd_verify(m, ctx, None, 1, gamma, 0.0, c, None, None, na, nx, commit=False)
+
+    ref = []
+    for c in cands:
+        verify(c)
+        torch.cuda.synchronize()
+        out = torch.empty((16, st.vocab), device="cuda")
+        rows = api.C.c_int32()
+        assert api.lib().sd_last_logits(m.h, out.data_ptr(), 16, api.C.byref(rows)) == api.SD_OK and rows.value == gamma + 1
+        ref.append(out[:rows.value].clone())
+    torch.cuda.synchronize()
+    assert not torch.equal(ref[0], ref[1])
+    got = []
+    for _ in range(20):
+        for c in cands:
+            verify(c)
+            got.append(m.last_logits())
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, ref[i % len(ref)]) for i, g in enumerate(got))
+    side = torch.cuda.Stream()
+    for i, c in enumerate(cands):   # the copy from another stream; then the next forward there
+        verify(c)
+        with torch.cuda.stream(side):
+            other = m.last_logits()
+        torch.cuda.synchronize()
+        assert torch.equal(other, ref[i])
+        verify(c)
+        here = m.last_logits()
+        with torch.cuda.stream(side):
+            verify(cands[(i + 1) % len(cands)])
+            there = m.last_logits()
+        torch.cuda.synchronize()
+        assert torch.equal(here, ref[i]) and torch.equal(there, ref[(i + 1) % len(cands)])
+    assert not m._captured
+    slot = cands[0].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        verify(slot)
+    assert m._captured
+    for i, c in enumerate(cands):
+        verify(cands[0])
+        slot.copy_(c)
+        graph.replay()
+        assert torch.equal(m.last_logits(), ref[i])
+    m.close()
