@@ -1832,6 +1832,12 @@ __device__ __forceinline__ CandState plan_cand_load(const NextPlan &np, int j)
     }
     return c;
 }
+// What plan_next_cand returns for these arguments, without a store: every thread of a block can work it out for itself.
+__device__ __forceinline__ int next_row_token(const NextPlan &np, int tok, const CandState &cs)
+{
+    const bool fed = cs.in && np.next_idx < cs.g && cs.n >= 1 && max(cs.kv, 0) < cs.cap;
+    return fed && tok >= 0 && tok < np.vocab ? tok : 0;
+}
 __device__ int plan_next_cand(const NextPlan &np, int j, int tok, const CandState &cs)
 {
     const PlanView &pv = np.pv;
@@ -1949,20 +1955,26 @@ struct SplitScratch {
     float red[32];
     float wmax[4];
     float slice[DS_MAX_SLICES];
-    float wtot[2][4];
-    int pick, lastp, tok;
+    float4 wtot[2]; // (component = wave)
+    int pick[4], lastp[4];
 };
 
 __device__ void next_forward_first_step(const NextPlan &next, int j, int tok, const CandState &cs, SplitScratch *ss)
 {
-    // (all threads of the block) thread 0 plans; then the block gathers and norms the row
-    if (threadIdx.x == 0) ss->tok = next.enabled ? plan_next_cand(next, j, tok, cs) : 0;
-    if (!next.enabled || !next.embed) return;
-    lds_barrier(); // (the q slice written before need not have landed)
-    embed_rmsnorm_row((const bf16_t *)next.E, ss->tok, j, next.d, next.x, next.g, next.eps, (bf16_t *)next.out, next.av,
-                      ss->red);
+    // (all threads of the block) thread 0 plans; the block gathers and norms the row
+    if (!next.enabled) return;
+    if (threadIdx.x == 0) plan_next_cand(next, j, tok, cs);
+    if (!next.embed) return;
+    embed_rmsnorm_row((const bf16_t *)next.E, next_row_token(next, tok, cs), j, next.d, next.x, next.g, next.eps,
+                      (bf16_t *)next.out, next.av, ss->red);
 }
 
+// Bound: a chain of dependent steps in one block per slice (the 128 KB of a row are nothing).  Stamped in the kernel at
+// 32000 columns, before / now (us): loads until the local maximum 1.6 / 1.4 - 1.9, slice masses 1.2 / 0.65, slice sums and
+// owner 1.0 / 0.25 (a serial LDS read per slice, twice; now one read and a lane scan), q 0.3, placing the target 2.9 / 1.0 (its
+// "last positive index" was an LDS atomic of every thread), first step of the next forward 2.0; launch 9.0 / 6.2.  The vector
+// loads go out before the sequence state's dependent scalar loads.  NI = slices per wave: 4 serve rows of up to 32768 columns.
+template <int NI>
 __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *logits, const float *stats, int nb, int V,
                                                                   float T, const float *u, int gamma, int idx,
                                                                   int32_t *cand, float *q, NextPlan next)
@@ -1970,12 +1982,6 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
     __shared__ SplitScratch ss;
     const int j = blockIdx.y, k = blockIdx.x, n_slices = gridDim.x;
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
-    const CandState cs = plan_cand_load(next, j);
-    if (!draft_seq_active(next, j, gamma, idx)) { // (uniform over the block) nothing to draw: keep its plan entry empty
-        if (k == 0) next_forward_first_step(next, j, 0, cs, &ss);
-        return;
-    }
-    const float invT = inv_temperature(T), uj = u[j * gamma + idx];
     const float *st = stats + (size_t)j * nb * 3;
     // this block's slice of the logits row: requested first, needed only once the maximum and Z are known
     const float *row = logits + (size_t)j * V;
@@ -1986,47 +1992,41 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
         e[it] = 4 * v < V ? *(const float4 *)(row + 4 * v) : make_float4(-3.0e38f, -3.0e38f, -3.0e38f, -3.0e38f);
     }
     // wave w holds the entries of slices w, w + 4, ...: lane l entry 64 * slice + l
-    float em[DS_MAX_SLICES / 4], es[DS_MAX_SLICES / 4];
-    float mx = -3.0e38f;
+    float em[NI], es[NI];
 #pragma unroll
-    for (int i = 0; i < DS_MAX_SLICES / 4; i++) {
+    for (int i = 0; i < NI; i++) {
         const int b = (4 * i + wv) * 64 + lane;
         const bool in = 4 * i + wv < n_slices && b < nb;
         em[i] = in ? st[3 * b] : -3.0e38f;
         es[i] = in ? st[3 * b + 1] : 0.f;
-        mx = fmaxf(mx, em[i]);
     }
-    mx = wave_max(mx);
+    SD_SCHED_FENCE();
+    const CandState cs = plan_cand_load(next, j);
+    if (!draft_seq_active(next, j, gamma, idx)) { // (uniform over the block) nothing to draw: keep its plan entry empty
+        if (k == 0) next_forward_first_step(next, j, 0, cs, &ss);
+        return;
+    }
+    const float invT = inv_temperature(T), uj = u[j * gamma + idx];
+    float mx = -3.0e38f;
+#pragma unroll
+    for (int i = 0; i < NI; i++) mx = fmaxf(mx, em[i]);
+    mx = wave_max_dpp(mx);
     if (lane == 0) ss.wmax[wv] = mx;
-    if (threadIdx.x == 0) {
-        ss.pick = 0x7fffffff;
-        ss.lastp = -1;
-    }
-    __syncthreads();
+    lds_barrier();
     mx = fmaxf(fmaxf(ss.wmax[0], ss.wmax[1]), fmaxf(ss.wmax[2], ss.wmax[3]));
 #pragma unroll
-    for (int i = 0; i < DS_MAX_SLICES / 4; i++) {
+    for (int i = 0; i < NI; i++) {
         const float mass = wave_sum_dpp(es[i] * expf((em[i] - mx) * invT)); // (entries past the row: 0 * 0)
         if (lane == 0 && 4 * i + wv < n_slices) ss.slice[4 * i + wv] = mass;
     }
-    __syncthreads();
-    float Z = 0.f, base = 0.f;
-    for (int s = 0; s < n_slices; s++) {
-        if (s == k) base = Z;
-        Z += ss.slice[s];
-    }
-    const float target = uj * Z;
-    int owner = -1, last_pos = 0;
-    {
-        float cum = 0.f;
-        for (int s = 0; s < n_slices; s++) {
-            const float m = ss.slice[s];
-            cum += m;
-            if (m > 0.f) last_pos = s;
-            if (owner < 0 && cum > target) owner = s;
-        }
-        if (owner < 0) owner = last_pos;
-    }
+    lds_barrier();
+    // lane s holds slice s; every wave of every block adds the same numbers in the same order.  The owner is the first
+    // slice of positive mass whose running sum exceeds the target, without one the last slice of positive mass.
+    const float sm = lane < n_slices ? ss.slice[lane & (DS_MAX_SLICES - 1)] : 0.f;
+    const float run = wave_incl_scan_dpp(sm, lane);
+    const float Z = lane_f(run, WAVE - 1), base = k ? lane_f(run, k - 1) : 0.f, target = uj * Z;
+    const unsigned long long with_mass = __ballot(sm > 0.f), over = __ballot(sm > 0.f && run > target);
+    const int owner = over ? __ffsll(over) - 1 : with_mass ? WAVE - 1 - __clzll(with_mass) : 0;
     // this block's slice of q
     const float invZ = 1.0f / Z;
     float *qrow = q + ((size_t)j * gamma + idx) * V;
@@ -2051,36 +2051,34 @@ __global__ __launch_bounds__(256) void draft_sample_split_kernel(const float *lo
     int lastp = -1;
 #pragma unroll
     for (int it = 0; it < 2; it++) {
-        const int v = k * (DS_SLICE / 4) + it * 256 + threadIdx.x;
         const float4 f = e[it];
-        if (f.x > 0.f) lastp = 4 * v;
-        if (f.y > 0.f) lastp = 4 * v + 1;
-        if (f.z > 0.f) lastp = 4 * v + 2;
-        if (f.w > 0.f) lastp = 4 * v + 3;
+        lastp = max(lastp, last_positive(f, 4 * (k * (DS_SLICE / 4) + it * 256 + (int)threadIdx.x)));
         l4[it] = ((f.x + f.y) + f.z) + f.w;
         inc[it] = wave_incl_scan_dpp(l4[it], lane);
-        if (lane == WAVE - 1) ss.wtot[it][wv] = inc[it];
+        if (lane == WAVE - 1) ((float *)&ss.wtot[it])[wv] = inc[it];
     }
-    if (lastp >= 0) atomicMax(&ss.lastp, lastp);
     lds_barrier();
     float seg_before = base;
+    int pick = 0x7fffffff;
 #pragma unroll
     for (int it = 0; it < 2; it++) {
-        float before = seg_before;
-        for (int w = 0; w < 4; w++) {
-            if (w < wv) before += ss.wtot[it][w];
-            seg_before += ss.wtot[it][w];
-        }
+        const float4 wt = ss.wtot[it];
+        const float w0 = wt.x, w1 = w0 + wt.y, w2 = w1 + wt.z;
+        const float before = seg_before + (wv == 0 ? 0.f : wv == 1 ? w0 : wv == 2 ? w1 : w2);
+        seg_before += w2 + wt.w;
         const int v = k * (DS_SLICE / 4) + it * 256 + threadIdx.x;
-        const float4 f = e[it];
-        int pk = first_over(before + (inc[it] - l4[it]), f, target, 4 * v);
-        if (pk >= V) pk = 0x7fffffff;
-        pk = wave_min_i(pk);
-        if (lane == 0 && pk != 0x7fffffff) atomicMin(&ss.pick, pk);
+        const int pk = first_over(before + (inc[it] - l4[it]), e[it], target, 4 * v);
+        if (pk < V) pick = min(pick, pk);
+    }
+    pick = wave_min_i(pick);
+    lastp = wave_max_i(lastp);
+    if (lane == 0) {
+        ss.pick[wv] = pick;
+        ss.lastp[wv] = lastp;
     }
     lds_barrier();
-    int pick = ss.pick;
-    if (pick == 0x7fffffff) pick = max(ss.lastp, 0);
+    pick = min(min(ss.pick[0], ss.pick[1]), min(ss.pick[2], ss.pick[3]));
+    if (pick == 0x7fffffff) pick = max(max(max(ss.lastp[0], ss.lastp[1]), max(ss.lastp[2], ss.lastp[3])), 0);
     if (threadIdx.x == 0) cand[j * gamma + idx] = pick;
     next_forward_first_step(next, j, pick, cs, &ss);
 }
@@ -2178,8 +2176,8 @@ hipError_t launch_draft_sample(hipStream_t s, const float *logits, int n_seq, in
     if (stats && stats_nb > 0 && stats_nb * 32 == V && n_slices <= DS_MAX_SLICES && n_seq <= 65535) {
         if (did_embed) *did_embed = next.enabled && next.embed;
         if (T > 0.f)
-            hipLaunchKernelGGL(draft_sample_split_kernel, dim3(n_slices, n_seq), dim3(256), 0, s, logits, stats, stats_nb,
-                               V, T, u, gamma, idx, cand, q, next);
+            hipLaunchKernelGGL(n_slices <= 16 ? draft_sample_split_kernel<4> : draft_sample_split_kernel<DS_MAX_SLICES / 4>,
+                               dim3(n_slices, n_seq), dim3(256), 0, s, logits, stats, stats_nb, V, T, u, gamma, idx, cand, q, next);
         else
             hipLaunchKernelGGL(draft_argmax_split_kernel, dim3(n_seq), dim3(256), 0, s, stats, stats_nb, gamma, idx, cand,
                                next);

@@ -652,6 +652,48 @@ def test_draft_sampler_from_the_lm_heads_partials_matches_the_whole_row_sampler(
     gd.close()
 
 
+@pytest.mark.parametrize("V", [1024, 2048, 2080, 32768, 32800, 65536])
+def test_sliced_draft_sampler_at_the_ends_of_its_slice_counts(V):
+    """One slice, a full one, 32 columns more, 16 slices (the last count that four per wave serve), 17 and 32: the sampler that
+    works from the LM head's partials against the one that reads whole rows - same tokens, q to 1e-6 (two sums of 32-bit
+    exponentials in another order), identical logits of the forward whose first step it runs."""
+    import dataclasses
+    _say(f"small bf16 draft: sliced sampler at V={V}")
+    sd_ = dataclasses.replace(dg.SHAPES["small_draft_bf16"], vocab=V, name=f"small_draft_v{V}")
+    gd = api.Model(sd_, dg.make_weights(sd_, 87, BF16_LM_SCALE), max_rows=16, max_pos=64)
+    B, gamma = 3, 3
+    prompts = [[int(t) for t in dg.make_prompt(87, b, 9 + 5 * b, V)] for b in range(B)]
+    u = np.stack([dg.make_uniforms(87, dg.DRAFT_STREAM, b, 0, gamma) for b in range(B)])
+    u[0, 0], u[1, 0] = 0.0, 1.0 - 2.0 ** -24  # the row's first and last token of positive weight
+    outs = []
+    for force in (0, 4):
+        api.set_option("force_generic", force)
+        try:
+            ctx = api.Context([40] * B)
+            ctx.attach(gd)
+            H.gpu_prefill(ctx, [gd], prompts)
+            cand = torch.full((B, gamma), -1, dtype=torch.int32, device="cuda")
+            q = torch.zeros((B, gamma, V), dtype=torch.float32, device="cuda")
+            api.sd_draft(gd, ctx, None, B, gamma, 0.9, H.dev(u), cand, q)
+            ctx.sync()
+            outs.append((cand.cpu().numpy(), q.cpu().numpy(), gd.last_logits().cpu().numpy()))
+            ctx.close()
+        finally:
+            api.set_option("force_generic", 0)
+    gd.close()
+    (c0, q0, l0), (c1, q1, l1) = outs
+    assert ((0 <= c0) & (c0 < V)).all() and np.abs(q0.sum(-1) - 1.0).max() < 1e-4
+    assert np.abs(q0[:, 0] - q1[:, 0]).max() < 1e-6
+    cdf = np.cumsum(q1.astype(np.float64), -1)
+    for b in range(B):
+        for i in range(gamma):
+            if c0[b, i] != c1[b, i]:  # (only within rounding of the interval's end, and then the later rows differ)
+                assert oracle.cdf_distance(q1[b, i].astype(np.float64), float(u[b, i]), int(c0[b, i])) < 1e-6, (b, i, c0[b], c1[b], cdf[b, i, -1])
+                break
+    if np.array_equal(c0, c1):
+        assert np.array_equal(l0, l1) and np.abs(q0 - q1).max() < 1e-6
+
+
 def test_draft_and_verify_are_graph_capturable_and_replays_match_eager():
     """sd_draft and sd_verify launch kernels only (no allocation, copy, memset or host synchronisation), so a
     caller may capture them into a HIP graph.  Every replay, with eager calls and synchronisations in
