@@ -1635,16 +1635,50 @@ __device__ __forceinline__ float block_sum_rows(float v, FastScratch *fs)
     return sum_waves<RT / WAVE>(fs->red[l & (RT / WAVE - 1)]);
 }
 
+// (V is a multiple of 4.)  The loads are unconditional - vectors past the end re-read the last one, which row_fill replaces
+// where it matters - so that all of them are in flight at once: with a guard each they were a branch each.
 template <int RT, int NSEG>
-__device__ __forceinline__ void row_load(const float *row, int V, float fill, RowRegs<NSEG> &r)
+__device__ __forceinline__ void row_load(const float *row, int V, RowRegs<NSEG> &r)
 {
-    const int nvec = (V + 3) / 4;
+    const int last = V / 4 - 1;
+#pragma unroll
+    for (int it = 0; it < NSEG; it++) r.f[it] = *(const float4 *)(row + 4 * min(it * RT + (int)threadIdx.x, last));
+}
+template <int RT, int NSEG>
+__device__ __forceinline__ void row_fill(int V, float fill, RowRegs<NSEG> &r)
+{
 #pragma unroll
     for (int it = 0; it < NSEG; it++) {
-        const int v = it * RT + threadIdx.x;
-        r.f[it] = v < nvec ? load4_guard(row, v, V, fill) : make_float4(fill, fill, fill, fill);
+        const bool in = it * RT + (int)threadIdx.x < V / 4;
+        r.f[it].x = in ? r.f[it].x : fill;
+        r.f[it].y = in ? r.f[it].y : fill;
+        r.f[it].z = in ? r.f[it].z : fill;
+        r.f[it].w = in ? r.f[it].w : fill;
     }
 }
+
+// e^((x - mx) / T) of a row's elements, x <= mx: 2^n 2^f with n + f = (x - mx) log2(e) / T, n whole, f from one rounding and
+// corrected by what the factor's own rounding takes from the product; nine instructions where expf with the difference and its
+// product takes fifteen.  (-inf and what lies 160 powers of two below the maximum give 0, a NaN stays one.)  Error of the
+// normalised rows against 64 bits, this / expf: N(0, 2), 32000 columns, T = 1: 3.6e-8 / 3.6e-8 (2-norm), T = 0.7: 8.5e-8 / 9.2e-8.
+struct RowExp {
+    float mx, c2, low;
+    __device__ __forceinline__ RowExp(float mx_, float invT) : mx(mx_), c2(fminf(invT * 1.44269504088896f, 3.4e38f))
+    {
+        // (c2 + c2 * low = invT * log2(e); at the ends of the range, where the remainder is not representable, without)
+        const float rest = fmaf(invT, 1.44269504088896f, -c2) + invT * 1.92596299e-8f;
+        low = c2 > 1e-30f && c2 < 1e38f ? rest / c2 : 0.f;
+    }
+    __device__ __forceinline__ float operator()(float x) const
+    {
+        const float d = x - mx, t = fmaxf(d * c2, -160.f), n = rintf(t);
+        return ldexpf(__builtin_amdgcn_exp2f(fmaf(t, low, fmaf(d, c2, -n))), (int)n);
+    }
+    __device__ __forceinline__ float4 operator()(const float4 f) const
+    {
+        return make_float4((*this)(f.x), (*this)(f.y), (*this)(f.z), (*this)(f.w));
+    }
+};
 
 // max, lowest-index argmax (T == 0 only) and (T > 0) z = sum of e(x) = exp((x - max) / T) of the row in r (filled with
 // row_filler past V).  For T > 0 the row is replaced by e(x) (exactly 0 past V), so that the probabilities
@@ -1677,13 +1711,10 @@ __device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, Fas
     z = 1.f;
     if (invT > 0.f) {
         float zl = 0.f;
+        const RowExp ex(mx, invT);
 #pragma unroll
         for (int it = 0; it < NSEG; it++) {
-            float4 f = r.f[it];
-            f.x = expf((f.x - mx) * invT);
-            f.y = expf((f.y - mx) * invT);
-            f.z = expf((f.z - mx) * invT);
-            f.w = expf((f.w - mx) * invT);
+            const float4 f = ex(r.f[it]);
             zl += f.x;
             zl += f.y;
             zl += f.z;
@@ -1694,51 +1725,87 @@ __device__ __forceinline__ void row_stats_regs(RowRegs<NSEG> &r, float invT, Fas
     }
 }
 
+// Sum over the lanes whose number agrees modulo N (N = 1 ... 8), left in all of them: rotations inside the 16-lane rows,
+// then the rows of the wave.
+template <int N>
+__device__ __forceinline__ float stride_sum(float v)
+{
+    v += dpp_f<0x128>(v);
+    if (N <= 4) v += dpp_f<0x124>(v);
+    if (N <= 2) v += dpp_f<0x122>(v);
+    if (N <= 1) v += dpp_f<0x121>(v);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+}
+// Wave totals of N values per lane; lane l gets that of value l % N.  Each exchange halves the values a lane still carries
+// (it keeps those with its own bit and gives the others away): 26 instructions for 8 values where a reduction each takes 88.
+template <int N>
+__device__ __forceinline__ float scatter_sum(const float (&v)[N], int lane)
+{
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "halved in every exchange");
+    float a[4], b[2], c;
+    if constexpr (N == 8) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) a[i] = (lane & 4 ? v[i + 4] : v[i]) + dpp_f<0x141>(lane & 4 ? v[i] : v[i + 4]);
+    } else if constexpr (N == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) a[i] = v[i];
+    }
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < 2; i++) b[i] = (lane & 2 ? a[i + 2] : a[i]) + dpp_f<0x4E>(lane & 2 ? a[i] : a[i + 2]);
+    } else if constexpr (N == 2) {
+        b[0] = v[0];
+        b[1] = v[1];
+    }
+    if constexpr (N >= 2) c = (lane & 1 ? b[1] : b[0]) + dpp_f<0xB1>(lane & 1 ? b[0] : b[1]);
+    else c = v[0];
+    return stride_sum<N>(c);
+}
+
 // Inverse-CDF pick (same rule as block_pick_cdf) over weights held in registers: the whole row, or (pick_regs_range) the
 // float4s v_begin .. v_end of one, for a target that lies `base` or more into the row's sum.  Weights past the end are 0.
 template <bool RANGE, int RT, int NSEG>
 __device__ __forceinline__ int pick_regs_impl(const RowRegs<NSEG> &w, int V, float u, FastScratch *fs, float *total_out, int v_begin, int v_end,
                                               float base, float target)
 {
-    // Index order is (segment it, thread t, component c).  Segment totals are the waves' totals added as a
-    // tree; every thread works out the total Z, the segment holding u * Z and the sum before it for itself
-    // (no single-thread phase), then one block-wide scan of that segment's float4 sums places the element.
+    // Index order is (segment it, thread t, component c).  Segment totals are added as a tree; every wave works out the
+    // total Z, the segment holding u * Z and the sum before it for itself (no single-thread phase), then one block-wide
+    // scan of that segment's float4 sums places the element.
+    constexpr int NW = RT / WAVE;
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
     float loc[NSEG];
 #pragma unroll
-    for (int it = 0; it < NSEG; it++) {
-        const float4 f = w.f[it];
-        loc[it] = wave_sum_dpp(((f.x + f.y) + f.z) + f.w);
-    }
-    lds_barrier(); // the scratch may still be in use by a previous call
-    if (lane == 0) {
-#pragma unroll
-        for (int it = 0; it < NSEG; it++) fs->wsum[wv][it] = loc[it];
-    }
+    for (int it = 0; it < NSEG; it++) loc[it] = ((w.f[it].x + w.f[it].y) + w.f[it].z) + w.f[it].w;
+    float seg = scatter_sum<NSEG>(loc, lane); // of segment lane % NSEG
+    float *wsum = &fs->wsum[0][0];            // [wave][segment], packed
+    lds_barrier();                            // the scratch may still be in use by a previous call
+    if (lane < NSEG) wsum[wv * NSEG + lane] = seg;
     if (threadIdx.x == 0) {
         fs->pick = 0x7fffffff;
         fs->seg_last = -1;
     }
     lds_barrier();
-    const int nseg = (v_end - v_begin + RT - 1) / RT;
-    float seg[NSEG];
+    seg = 0.f;
 #pragma unroll
-    for (int it = 0; it < NSEG; it++) seg[it] = sum_waves<RT / WAVE>(fs->wsum[lane & (RT / WAVE - 1)][it]);
+    for (int e = 0; e < NW * NSEG; e += WAVE) seg += NW * NSEG >= WAVE || lane < NW * NSEG ? wsum[(e + lane) % (NW * NSEG)] : 0.f;
+    seg = stride_sum<NSEG>(seg);
+    // lane it < NSEG: segment it, running sums over the segments (those past the end hold nothing)
+    seg = lane < NSEG ? seg : 0.f;
+    float run = seg;
+    run += dpp_f<0x111>(run);
+    if (NSEG > 2) run += dpp_f<0x112>(run);
+    if (NSEG > 4) run += dpp_f<0x114>(run);
     if (!RANGE) {
-        float Z = 0.f;
-#pragma unroll
-        for (int it = 0; it < NSEG; it++)
-            if (it < nseg) Z += seg[it];
+        const float Z = lane_f(run, NSEG - 1);
         target = u * Z;
         if (total_out) *total_out = Z;
     }
-    int sit = -1;
-#pragma unroll
-    for (int it = 0; it < NSEG; it++)
-        if (it < nseg && sit < 0) {
-            if (base + seg[it] > target) sit = it;
-            else base += seg[it];
-        }
+    const unsigned long long over = __ballot(seg > 0.f && base + run > target);
+    const int sit = over ? __ffsll(over) - 1 : -1;
+    if (sit > 0) base += lane_f(run, sit - 1);
     if (sit >= 0) { // uniform over the block
         float4 f = w.f[0];
 #pragma unroll
@@ -1907,7 +1974,8 @@ __global__ __launch_bounds__(RT) void draft_sample_fast_kernel(const float *logi
         return;
     }
     RowRegs<NSEG> r;
-    row_load<RT>(logits + (size_t)j * V, V, row_filler(T), r);
+    row_load<RT>(logits + (size_t)j * V, V, r);
+    row_fill<RT>(V, row_filler(T), r);
     float mx, z;
     int am;
     row_stats_regs<RT>(r, inv_temperature(T), &fs, mx, am, z);
@@ -2540,6 +2608,9 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
 // under the profiler (before: row statistics in one launch, the decision from a second reading of the deciding row in
 // another): 6 rows 8.1 + 17.9 -> 12.7 + 2.7 us, 192 rows 10.2 + 25.1 -> 18.3 + 4.1; whole call of 6 rows among others 21.4 ->
 // 13.5 us.
+// Stamped in the kernel at 6 rows of 32000 columns, before / now (us): loads until the row is there 1.4 / 0.7 (a branch per
+// vector), maximum, exponentials and sum 4.6 / 3.9 (expf), residual 0.25, pick 3.8 / 2.5 (a reduction over the wave per
+// segment): 11.0 -> 8.1.  What is left of it is instruction issue, four waves on each SIMD of one compute unit.
 // EARLY_Q (up to 256 rows, a block per compute unit): q is requested together with the row, whatever the verdict will be
 // (6 rows: 1.1 us); with more rows than units two blocks share one, q is read only where it is needed.
 // DRAW false (more rows, see launch_verify_tail): the row settles its test only and leaves (max, sum, accepted) for verify_draw_kernel.
@@ -2560,7 +2631,7 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
     float *st = stats + ((size_t)j * (stride_g + 1) + i) * 3;
     if (i > gamma) return; // (uniform) not a live row
     RowRegs<NSEG> r;
-    row_load<RT>(row, V, row_filler(T), r);
+    row_load<RT>(row, V, r);
     const int c = i < gamma ? cand[(size_t)j * stride_g + i] : -1;
     const bool c_in = c >= 0 && c < V;
     float lc = 0.f, qc = 1.f, ui = 0.f, uu = 0.f;
@@ -2573,9 +2644,9 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
             qc = qrow[c];
         }
     }
-    const int nvec = (V + 3) / 4;
     RowRegs<NSEG> qr;
-    if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, 0.f, qr);
+    if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, qr); // (past the end: whatever q is, e(x) is 0 there)
+    row_fill<RT>(V, row_filler(T), r);
     const float invT = inv_temperature(T);
     float mx, z;
     int am;
@@ -2596,9 +2667,8 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
                     float4 w[QH];
 #pragma unroll
                     for (int k = 0; k < QH; k++) {
-                        const int v = (h + k) * RT + threadIdx.x;
                         if (EARLY_Q) w[k] = qr.f[h + k];
-                        else w[k] = v < nvec ? load4_guard(qrow, v, V, 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+                        else w[k] = *(const float4 *)(qrow + 4 * min((h + k) * RT + (int)threadIdx.x, V / 4 - 1));
                     }
 #pragma unroll
                     for (int k = 0; k < QH; k++) {
@@ -2650,16 +2720,13 @@ __global__ __launch_bounds__(RT, 4) void verify_draw_kernel(const float *logits,
     const float uu = u[(size_t)j * (stride_g + 1) + gamma], invT = inv_temperature(T);
     const float mx = st[3 * n_acc], invZ = 1.0f / st[3 * n_acc + 1];
     RowRegs<NSEG> r, w;
-    row_load<RT>(logits + ((size_t)j * (stride_g + 1) + n_acc) * V, V, row_filler(T), r);
-    if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, 0.f, w);
+    row_load<RT>(logits + ((size_t)j * (stride_g + 1) + n_acc) * V, V, r);
+    if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, w); // (past the end e(x) is 0)
+    row_fill<RT>(V, row_filler(T), r);
+    const RowExp ex(mx, invT);
 #pragma unroll
-    for (int it = 0; it < NSEG; it++) {
-        float4 &f = r.f[it];
-        f.x = expf((f.x - mx) * invT) * invZ;
-        f.y = expf((f.y - mx) * invT) * invZ;
-        f.z = expf((f.z - mx) * invT) * invZ;
-        f.w = expf((f.w - mx) * invT) * invZ;
-    }
+    for (int it = 0; it < NSEG; it++) r.f[it] = ex(r.f[it]);
+    row_scale(r, invZ);
     float mass = 0.f;
     int next = 0;
     if (n_acc < gamma) { // (uniform)

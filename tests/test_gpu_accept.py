@@ -319,6 +319,34 @@ def test_infinite_temperature_draws_from_the_uniform_distribution(V):
     assert np.abs(nx.cpu().numpy() - np.floor(u[:, gamma].astype(np.float64) * half)).max() <= 1 + 1e-6 * V
 
 
+@pytest.mark.parametrize("T", [0.05, 0.7, 1.0, 40.0])
+@pytest.mark.parametrize("V", [4, 260, 1028, 4096, 8192, 16384, 32764])
+def test_masked_columns_carry_no_weight(V, T):
+    """Rows in a block's registers whose columns are masked with -inf, the lowest float or -3e38: nothing masked is drawn,
+    accepted or counted, and the draws agree with the oracle's on the same rows."""
+    print(f"masked columns V={V} T={T}", flush=True)
+    B, gamma = 6, 1
+    rng = np.random.default_rng(V)
+    logits = rng.normal(0, 2, (B, gamma + 1, V)).astype(np.float32)
+    keep = rng.random((B, V)) < 0.4
+    keep[:, V // 2] = True
+    for b, mask in enumerate([-np.inf, np.finfo(np.float32).min, -3.0e38] * 2):
+        logits[b, :, ~keep[b]] = mask
+    cand = np.array([[int(np.flatnonzero(~keep[b])[0]) if b % 2 and not keep[b].all() else V // 2] for b in range(B)], np.int32)
+    q = np.full((B, gamma, V), 1.0 / V, np.float32)
+    u = np.stack([dg.make_uniforms(77, dg.VERIFY_STREAM, b, 0, gamma + 1) for b in range(B)])
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_accept(dev(logits), gamma, T, dev(cand), dev(q), dev(u), na, nx, torch.zeros(3 * B * (gamma + 1), device="cuda"))
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    for b in range(B):
+        assert keep[b, nx_h[b]], (b, nx_h[b])
+        assert na_h[b] == 0 or keep[b, cand[b, 0]]
+    low = np.float32(-1.0e30)  # (the oracle's masks: far below everything else, and finite in its differences)
+    assert check_against_oracle(np.maximum(logits, low), q, cand, u, T, na_h, nx_h) <= 1
+
+
 @pytest.mark.parametrize("dtype", [dg.FP32, dg.BF16])
 def test_draft_at_infinite_temperature_is_uniform(dtype):
     """The samplers of the draft phase at T = inf: q = 1 / V and the candidate at u V, in both data types."""
