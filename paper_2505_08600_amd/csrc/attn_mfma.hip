@@ -25,6 +25,7 @@
 // Paper (arXiv 2505.08600): Section 1, Figure 1b (parallel verification of the
 // gamma candidates) and Figure 1a (draft steps).
 #include "sd_internal.h"
+#include <algorithm>
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -479,6 +480,26 @@ __global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t
     }
 }
 
+// A helper block's share of the K / V tiles of one (head, sequence): read into the L2 that the attention block of the pair
+// reads from, tiles dealt out in pieces of one K or V tile per wave.  The last tile is being appended to: left out.
+template <int HD, int WAVES>
+__device__ __forceinline__ void kv_prefetch(const uint16_t *Kl, const uint16_t *Vtl, PlanView pv, CtxView cv, int h, int j,
+                                            int64_t total_cap, int part, int n_help)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_old = pv.seq_nq[j] > 0 ? pv.seq_kv0[j] / AT_TILE : 0;
+    const int first = n_help == 1 ? n_old * 2 / 5 : 0; // (a lone helper leaves the tiles the block starts with to it)
+    const size_t base = ((size_t)h * total_cap + cv.off[pv.seq_b[j]]) * HD + lane * 8;
+    for (int u = 2 * first + wave + part * WAVES; u < 2 * n_old; u += n_help * WAVES) { // tile u / 2, K or V
+        const uint16_t *src = (u & 1 ? Vtl : Kl) + base + (size_t)(u >> 1) * (AT_TILE * HD);
+        bf16x8 v[HD / 16];
+#pragma unroll
+        for (int k = 0; k < HD / 16; k++) v[k] = *(const bf16x8 *)(src + k * 512);
+#pragma unroll
+        for (int k = 0; k < HD / 16; k++) asm volatile("" ::"v"(v[k])); // (the load is all that is wanted)
+    }
+}
+
 // Fused RoPE + cache append + attention for one (sequence, head) per block, no KV split: used when
 // there are enough (sequence, head) pairs to fill the chip or the context is short, where the split
 // kernel plus its combine pass and the separate RoPE kernel are three latency-bound launches.
@@ -499,21 +520,28 @@ struct OProj {
     size_t slab_stride; // rows * d_model
     int32_t d_model;
 };
-template <int HD, int WAVES, bool NT_HINT, bool OPROJ>
+template <int HD, int WAVES, bool NT_HINT, bool OPROJ, bool HELP>
 __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *__restrict__ qkv, int n_slabs,
                                                                    size_t slab_stride, PlanView pv, CtxView cv, int R,
                                                                    int H, const float2 *__restrict__ rope, int max_pos,
                                                                    uint16_t *__restrict__ Kl, uint16_t *__restrict__ Vtl,
                                                                    int64_t total_cap, uint16_t *__restrict__ obuf,
-                                                                   ActView o_av, OProj op)
+                                                                   ActView o_av, OProj op, int n_seq, int n_pad, int n_help)
 {
     constexpr int ND = HD / 16;
     constexpr int HALF = HD / 2;
     __shared__ float sO[WAVES][ND][64][4];
     __shared__ float sM[WAVES][16], sL[WAVES][16];
     __shared__ __attribute__((aligned(16))) uint16_t sQ[2][16][HD];
-    const int h = blockIdx.x;
-    const int j = gridDim.y > 1 ? pv.seq_order[blockIdx.y] : 0; // longest sequences start first
+    // one-dimensional grid: (1 + n_help) times the (sequence, head) pairs padded to a multiple of 8, see launch_attn_fused_bf16
+    const int pair = HELP ? blockIdx.x % n_pad : blockIdx.x;
+    if (HELP && pair >= H * n_seq) return; // (padding)
+    const int h = pair % H;
+    const int j = n_seq > 1 ? pv.seq_order[pair / H] : 0; // longest sequences start first
+    if (HELP && (int)blockIdx.x >= n_pad) {
+        kv_prefetch<HD, WAVES>(Kl, Vtl, pv, cv, h, j, total_cap, blockIdx.x / n_pad - 1, n_help);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int qi = lane & 15, grp = lane >> 4;
     const int nq = pv.seq_nq[j], kv0 = pv.seq_kv0[j];
@@ -679,7 +707,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
 {
     if (oproj_done) *oproj_done = 0;
     if (R < 1 || R > 16 || (hd != 64 && hd != 128) || n_slabs < 1 || n_slabs > 8) return hipErrorNotSupported;
-    if (n_seq > 65535 || H > 65535) return hipErrorNotSupported;
+    if (n_seq > 65535 || H > 65535 || (long)n_seq * H > (1 << 28)) return hipErrorNotSupported;
     const int tiles_upper = (len_upper + AT_TILE - 1) / AT_TILE;
     // one block per (sequence, head): fine when every wave has at most a few tiles anyway, or when those blocks
     // alone fill the chip and the contexts stay below about 2000 tokens - beyond that the split kernel, whose blocks
@@ -692,7 +720,15 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     // per block on, the 8-wave shape streams faster (measured: 4.9 against 4.6 TB/s at 2048 tokens, 5.5
     // against 5.2 at 1024..8192)
     const bool many = g_force_attn_waves ? g_force_attn_waves == 4 : ((long)n_seq * H >= 512 && tiles_upper <= 40);
-    dim3 grid(H, n_seq), block(many ? 256 : 512);
+    const int n_pairs = H * n_seq, n_pad = (n_pairs + 7) / 8 * 8;
+    // Helpers where blocks of one (sequence, head) pair leave half of the 256 units or more idle and have more tiles than
+    // waves: a unit alone draws K and V from HBM at about 50 GB/s however many loads it has in flight, and what its idle
+    // neighbours have read into the die's L2 (blocks go to the dies in turn: a pair's blocks are a multiple of 8 apart) it gets
+    // several times faster.  Head width 128, 7B shape: 32 layers at 32 pairs and 517 tokens 2825 us without, 2835 / 2800 / 2797 /
+    // 2801 with 1 / 2 / 3 / 7 helpers a pair; 2 layers at 128 pairs and 301 to 1500 tokens 327 / 323.7 with one.  At head width 64
+    // (half the bytes per tile, the softmax sets the time) no case moved.
+    const int n_help = hd == 128 && stream_nt && !many && tiles_upper > 8 ? std::min(256 / n_pad - 1, 3) : 0;
+    dim3 grid(n_help > 0 ? n_pad * (1 + n_help) : n_pairs), block(many ? 256 : 512);
     // output projection inside the block: small models in few blocks (each block reads its head's slice of Wo;
     // 8 waves x 8 (head width 64) or 4 (128) column tiles bound d_model), H slabs for the add + norm kernel
     const size_t rows = (size_t)n_seq * R;
@@ -702,31 +738,32 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     const OProj op = {(const uint16_t *)wo_tiled, oslab, rows * (size_t)d_model, d_model};
     if (oproj) {
         if (hd == 128)
-            hipLaunchKernelGGL((attn_fused_kernel<128, 8, false, true>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
-                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op);
+            hipLaunchKernelGGL((attn_fused_kernel<128, 8, false, true, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
+                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);
         else
-            hipLaunchKernelGGL((attn_fused_kernel<64, 8, false, true>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
-                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op);
+            hipLaunchKernelGGL((attn_fused_kernel<64, 8, false, true, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
+                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);
         if (oproj_done) *oproj_done = 1;
         return hipGetLastError();
     }
-#define SD_FUSED(HD_, WAVES_)                                                                                          \
+#define SD_FUSED(HD_, WAVES_, HELP_)                                                                                          \
     do {                                                                                                               \
         if (stream_nt)                                                                                                 \
-            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, true, false>), grid, block, 0, s, qkv, n_slabs,         \
+            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, true, false, HELP_>), grid, block, 0, s, qkv, n_slabs,         \
                                slab_stride, pv, cv, R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap,   \
-                               (uint16_t *)obuf, o_av, op);                                                            \
+                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);                                                            \
         else                                                                                                           \
-            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, false, false>), grid, block, 0, s, qkv, n_slabs,        \
+            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, false, false, false>), grid, block, 0, s, qkv, n_slabs,        \
                                slab_stride, pv, cv, R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap,   \
-                               (uint16_t *)obuf, o_av, op);                                                            \
+                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);                                                            \
     } while (0)
     if (hd == 128) {
-        if (many) SD_FUSED(128, 4);
-        else SD_FUSED(128, 8);
+        if (many) SD_FUSED(128, 4, false);
+        else if (n_help > 0) SD_FUSED(128, 8, true);
+        else SD_FUSED(128, 8, false);
     } else {
-        if (many) SD_FUSED(64, 4);
-        else SD_FUSED(64, 8);
+        if (many) SD_FUSED(64, 4, false);
+        else SD_FUSED(64, 8, false);
     }
 #undef SD_FUSED
     return hipGetLastError();

@@ -652,6 +652,39 @@ def test_draft_sampler_from_the_lm_heads_partials_matches_the_whole_row_sampler(
     gd.close()
 
 
+def test_attention_helpers_change_no_result():
+    """Fused attention at head width 128 whose idle compute units read K and V into the L2 first (three helpers a pair, one at
+    half the units, none beyond; 7 heads: a padded grid) against four-wave blocks without helpers (option attn_waves = 4): the
+    same tiles merged in another order, 2e-4 of the largest logit as for the kernels' other orders."""
+    import dataclasses
+    sh = dataclasses.replace(dg.with_layers(dg.SHAPES["t7b"], 1), n_heads=7, d_model=896, d_ffn=896, vocab=75776, name="helpers")
+    w = dg.make_weights(sh, 88, BF16_LM_SCALE)
+    gt = api.Model(sh, w, max_rows=512, max_pos=900)  # (272 MB of embedding and LM head: weights are streamed)
+    for B, lo, hi in ((1, 520, 520), (1, 250, 251), (3, 33, 700), (12, 100, 300), (18, 270, 340), (20, 257, 300)):
+        _say(f"attention helpers: {B} sequences of {lo} to {hi} tokens")
+        rng = np.random.default_rng(B + hi)
+        prompts = [[int(t) for t in dg.make_prompt(88, b, int(rng.integers(lo, hi + 1)), sh.vocab)] for b in range(B)]
+        cand = H.dev(rng.integers(0, sh.vocab, (B, 2)).astype(np.int32))
+        outs = []
+        for waves in (0, 4):
+            api.set_option("attn_waves", waves)
+            try:
+                ctx = api.Context([len(p) + 16 for p in prompts])
+                ctx.attach(gt)
+                H.gpu_prefill(ctx, [gt], prompts)
+                na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+                api.sd_verify(gt, ctx, None, B, 2, 0.0, cand, None, None, na, nx, commit=False)
+                ctx.sync()
+                outs.append(gt.last_logits().cpu().numpy())
+                ctx.close()
+            finally:
+                api.set_option("attn_waves", 0)
+        assert np.isfinite(outs[0]).all()
+        rel = np.abs(outs[0] - outs[1]).max() / np.abs(outs[1]).max()
+        assert rel < 2e-4, (B, rel)
+    gt.close()
+
+
 @pytest.mark.parametrize("V", [1024, 2048, 2080, 32768, 32800, 65536])
 def test_sliced_draft_sampler_at_the_ends_of_its_slice_counts(V):
     """One slice, a full one, 32 columns more, 16 slices (the last count that four per wave serve), 17 and 32: the sampler that
