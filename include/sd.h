@@ -360,10 +360,12 @@ int sd_ctx_set_kv(sd_ctx *c, sd_model *m, int32_t layer, int32_t seq, const void
  * min(current, len).  Rows beyond stay in memory and are overwritten later. */
 int sd_ctx_truncate(sd_ctx *c, sd_model *m, int32_t seq, int32_t len);
 /* Copy the fp32 logits [rows][vocab] of model m's last forward into out (dev,
- * room for max_rows rows); *rows = rows copied. */
+ * room for max_rows rows); *rows = rows copied.  Waits for the device, then copies on the null
+ * stream; the model's next forward waits for the copy, whatever stream it is enqueued on. */
 int sd_last_logits(sd_model *m, float *out, int32_t max_rows, int32_t *rows);
-/* The same as a copy enqueued on `stream`, without synchronising: the caller orders it behind the model's last forward
- * and in front of its next one (the same stream does both). */
+/* The same as a copy enqueued on `stream`.  On the null stream (NULL) it waits for the device only if the last forward was not
+ * enqueued there too or forwards of the model have been captured, and the next forward waits as above.  On another stream
+ * it never waits: the caller orders that stream behind the model's last forward and in front of its next one. */
 int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, int32_t *rows, void *stream);
 /* Copy one activation buffer of model m's last forward to out (HOST, fp32): name is
  * "x" (residual [rows][d_model]), "qkv" ([rows][3*d_model]), "q", "o", "a"

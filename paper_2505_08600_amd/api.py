@@ -140,18 +140,6 @@ def _stream() -> C.c_void_p:
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
-def _forward_stream(m: "Model") -> C.c_void_p:
-    """Current stream, noted as the one of model m's last forward (see Model.last_logits)."""
-    s = torch.cuda.current_stream()
-    here = (s.device_index, s.cuda_stream)
-    if torch.cuda.is_current_stream_capturing():
-        m._captured = True
-    elif m._copy_on is not None and m._copy_on != here:
-        torch.cuda.synchronize(m._copy_on[0])  # a copy of the logits this forward overwrites may be pending on another stream
-    m._copy_on, m._forward_on = None, here
-    return C.c_void_p(s.cuda_stream)
-
-
 def _np_i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
@@ -183,10 +171,6 @@ def to_device(a: np.ndarray, device="cuda") -> torch.Tensor:
 class Model:
     """sd_load_model / sd_free_model.  The library copies the weights at load, so the staging
     tensors are released right after."""
-
-    _forward_on = None  # (device, stream) of the last forward
-    _copy_on = None     # (device, stream) of a copy of its logits that may be pending
-    _captured = False   # forwards are in a graph, whose replays this object does not see
 
     def __init__(self, shape, weights: Dict[str, object], max_rows: int, max_pos: int, device="cuda"):
         self.shape = shape
@@ -251,18 +235,16 @@ class Model:
         return out
 
     def last_logits(self) -> torch.Tensor:
-        """Copy of the fp32 logits [rows][vocab] of the last forward.  Called on the stream of that forward the copy is
-        one more operation of the stream (the result is used like that of any torch operation on it); on another
-        stream, or if forwards of this model have been captured into a graph, it synchronises with the device."""
+        """Copy of the fp32 logits [rows][vocab] of the last forward.  With the default stream current the copy is in order on that
+        stream, behind the forward wherever it ran; the host waits only if the forward ran on another stream or forwards of
+        this model have been captured into a graph.  With another stream current it is complete on return."""
         out = torch.empty((self.max_rows, self.shape.vocab), dtype=torch.float32, device=self.device)
         rows = C.c_int32()
-        s = torch.cuda.current_stream()
-        here = (s.device_index, s.cuda_stream)
-        if here == self._forward_on and not self._captured and here[0] == out.device.index:
-            _check(lib().sd_last_logits_async(self.h, _dp(out), self.max_rows, C.byref(rows), C.c_void_p(s.cuda_stream)))
-            self._copy_on = here
-        else:
+        if torch.cuda.current_stream().cuda_stream:
             _check(lib().sd_last_logits(self.h, _dp(out), self.max_rows, C.byref(rows)))
+            torch.cuda.default_stream().synchronize()
+        else:
+            _check(lib().sd_last_logits_async(self.h, _dp(out), self.max_rows, C.byref(rows), None))
         return out[:rows.value]
 
 
@@ -376,14 +358,14 @@ def layout_index(kind: int, a: int, b: int, c: int, d: int = 0) -> int:
 
 
 def sd_prefill(m: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, max_new: int) -> None:
-    _check(lib().sd_prefill(m.h, ctx.h, _dp(seq_ids), n_seq, max_new, _forward_stream(m)))
+    _check(lib().sd_prefill(m.h, ctx.h, _dp(seq_ids), n_seq, max_new, _stream()))
 
 
 def sd_draft(draft: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, gamma: int,
              temperature: float, uniforms: Optional[torch.Tensor], cand: torch.Tensor,
              q: Optional[torch.Tensor]) -> None:
     _check(lib().sd_draft(draft.h, ctx.h, _dp(seq_ids), n_seq, gamma, temperature, _dp(uniforms), _dp(cand), _dp(q),
-                          _forward_stream(draft)))
+                          _stream()))
 
 
 def sd_verify(target: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_seq: int, gamma: int,
@@ -391,7 +373,7 @@ def sd_verify(target: Model, ctx: Context, seq_ids: Optional[torch.Tensor], n_se
               uniforms: Optional[torch.Tensor], n_accepted: torch.Tensor, next_token: torch.Tensor,
               commit: bool = True) -> None:
     _check(lib().sd_verify(target.h, ctx.h, _dp(seq_ids), n_seq, gamma, temperature, _dp(cand), _dp(q),
-                           _dp(uniforms), _dp(n_accepted), _dp(next_token), int(commit), _forward_stream(target)))
+                           _dp(uniforms), _dp(n_accepted), _dp(next_token), int(commit), _stream()))
 
 
 def sd_accept(logits: torch.Tensor, gamma: int, temperature: float, cand: Optional[torch.Tensor],

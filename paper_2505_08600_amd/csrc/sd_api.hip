@@ -288,6 +288,9 @@ extern "C" int sd_load_model(const sd_model_config *cfg, const sd_weights *w, sd
         }
     }
     m->last_lm_rows = 0;
+    m->logits_copied = m->logits_captured = false;
+    m->logits_stream = nullptr;
+    m->logits_device = -1;
     m->lm_norm_rows = 0;
     size_t M = c.max_rows, d = c.d_model;
     m->part_floats = attn_part_floats(c);
@@ -743,7 +746,10 @@ extern "C" int sd_last_logits(sd_model *m, float *out, int32_t max_rows, int32_t
     if (!m || !out || max_rows < 0) return sd_fail(SD_EINVAL, "sd_last_logits: bad argument");
     SD_HIP(hipDeviceSynchronize());
     int n = std::min(m->last_lm_rows, max_rows);
-    if (n > 0) SD_HIP(hipMemcpy(out, m->logits, (size_t)n * m->cfg.vocab * sizeof(float), hipMemcpyDeviceToDevice));
+    if (n > 0) {
+        m->logits_copied = true;
+        SD_HIP(hipMemcpy(out, m->logits, (size_t)n * m->cfg.vocab * sizeof(float), hipMemcpyDeviceToDevice));
+    }
     if (rows) *rows = n;
     return SD_OK;
 }
@@ -752,13 +758,45 @@ extern "C" int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, i
 {
     if (!m || !out || max_rows < 0) return sd_fail(SD_EINVAL, "sd_last_logits_async: bad argument");
     const int n = std::min(m->last_lm_rows, max_rows);
-    if (n > 0)
+    if (n > 0) {
+        // The null stream is in order with a forward that was enqueued on it, and it cannot be captured; the handle of another
+        // stream may name a stream that has been destroyed and made again.
+        int dev = -1;
+        SD_HIP(hipGetDevice(&dev));
+        if (!stream && (m->logits_stream || m->logits_device != dev || m->logits_captured)) SD_HIP(hipDeviceSynchronize());
+        m->logits_copied |= !stream;
         SD_HIP(hipMemcpyAsync(out, m->logits, (size_t)n * m->cfg.vocab * sizeof(float), hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    }
     if (rows) *rows = n;
     return SD_OK;
 }
 
 // ---------------------------------------------------------------- one decoder forward
+// Waits on the host for the null stream's work, also from a thread that is capturing another stream.
+static hipError_t wait_null_stream()
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return e;
+    e = hipStreamSynchronize(nullptr);
+    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+    return e != hipSuccess ? e : back;
+}
+
+// Before the logits of model m are written on stream s: no copy of them may be pending elsewhere; notes where they come from.
+static hipError_t logits_written_on(sd_model *m, hipStream_t s)
+{
+    hipError_t e = hipSuccess;
+    if (m->logits_copied && s) e = wait_null_stream(); // (a copy between device buffers need not have ended when hipMemcpy returns)
+    if (e != hipSuccess) return e;
+    m->logits_copied = false;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (s) e = hipStreamIsCapturing(s, &capturing);
+    if (capturing != hipStreamCaptureStatusNone) m->logits_captured = true; // (replays are not seen here)
+    m->logits_stream = s;
+    return e != hipSuccess ? e : hipGetDevice(&m->logits_device);
+}
+
 static hipError_t gemm_generic(sd_model *m, hipStream_t s, int mode, const void *A, ActView a_av, WeightSeg w, int M,
                                int N, int K, float *C, void *Cact, ActView c_av)
 {
@@ -1009,6 +1047,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (!pending) FWD(gemm_generic(m, s, GEMM_RESID, m->act, avf, wd, M, d, F, m->x, nullptr, av0)); }
     }
     if (want_logits) {
+        SD_HIP(logits_written_on(m, s));
         int n_lm = mode == PLAN_VERIFY ? M : n_seq;
         const ActView avlm = fold ? avd : ActView{m->plane_d, n_lm, sm_d}; // (split norm: the rows stay where the last down projection put them)
         m->last_a_rows = fold ? M : n_lm;

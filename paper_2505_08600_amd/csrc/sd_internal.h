@@ -309,6 +309,10 @@ struct sd_model {
     float2 *rope;   // [max_pos][head_dim/2] (cos, sin)
     int32_t *plan_mem;
     PlanView plan;
+    bool logits_copied;        // a copy of the logits may be pending on the null stream
+    bool logits_captured;      // a forward that writes them has been captured into a graph, whose replays are not seen
+    hipStream_t logits_stream; // where the last forward that writes them was enqueued, and the device then current
+    int logits_device;
     int last_lm_rows;
     int last_rows, last_a_rows; // rows of the last forward (layout of the step-major buffers); of abuf
     int lm_norm_rows; // rows of the LM head's input that a norm inside its GEMM kept out of abuf (0: none); sd_debug_read makes them

@@ -70,6 +70,65 @@ def test_argument_errors_do_not_need_a_gpu():
     assert b"null weight" in L.sd_last_error()
 
 
+def test_last_logits_on_another_stream_synchronise_whatever_was_called_there(monkeypatch):
+    """Model.last_logits on a stream of its own waits for the device and for its copy, also where the call before it on that stream
+    was refused or ran no forward; on the default stream the library decides (it knows where the last forward went)."""
+    calls, refuse = [], [False]
+
+    class Lib:
+        def __getattr__(self, name):
+            def call(*args):
+                calls.append(name)
+                return api.SD_EINVAL if refuse[0] and name == "sd_verify" else api.SD_OK
+            return call
+
+        def sd_last_error(self):
+            return b"refused"
+
+    class Stream:
+        device_index = None  # (the device index of a tensor on the CPU)
+
+        def __init__(self, handle):
+            self.cuda_stream = handle
+
+        def synchronize(self):
+            calls.append(f"wait {self.cuda_stream}")
+
+    a, b = Stream(0), Stream(2)
+    current = [a]
+    stub = Lib()
+    monkeypatch.setattr(api, "lib", lambda: stub)
+    monkeypatch.setattr(api, "_dp", lambda t: None)
+    monkeypatch.setattr(api.torch.cuda, "current_stream", lambda *args: current[0])
+    monkeypatch.setattr(api.torch.cuda, "default_stream", lambda *args: a)
+    monkeypatch.setattr(api.torch.cuda, "is_current_stream_capturing", lambda: False)
+    m = api.Model.__new__(api.Model)
+    m.shape, m.device, m.max_rows, m.h = type("S", (), {"vocab": 8})(), "cpu", 2, None
+
+    class Ctx:
+        h = None
+
+    def verify():
+        api.sd_verify(m, Ctx, None, 1, 2, 0.0, None, None, None, None, None)
+
+    def entry():
+        n = len(calls)
+        m.last_logits()
+        return calls[n:]
+
+    verify()
+    assert entry() == ["sd_last_logits_async"]
+    current[0], refuse[0] = b, True
+    with pytest.raises(api.SdError):
+        verify()
+    assert entry() == ["sd_last_logits", "wait 0"]   # refused on b: the last forward is still a's
+    current[0], refuse[0] = a, False
+    verify()
+    current[0] = b
+    api.sd_prefill(m, Ctx, None, 1, 0)   # accepted, no forward
+    assert entry() == ["sd_last_logits", "wait 0"]
+
+
 def test_product_package_does_not_import_the_oracle():
     """The HIP path must not route through the CPU oracle."""
     import glob

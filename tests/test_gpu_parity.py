@@ -1793,8 +1793,9 @@ def test_config3_routed_heterogeneous_drafts_small():
 
 
 def test_last_logits_keep_their_place_between_forwards():
-    """Copies taken between forwards without a synchronisation hold their own forward's logits: on the forwards' stream, on
-    another stream (which waits), with the next forward on another stream than a pending copy, and behind a graph capture."""
+    """Copies taken between forwards hold their own forward's logits: on the default stream without a synchronisation, behind a
+    forward on another stream, on another stream (also behind a refused call or one that runs no forward there), in front of
+    a forward on another stream, in front of and behind a graph capture."""
     _say("last_logits between forwards")
     st = dg.SHAPES["tiny_draft"]
     w = dg.make_weights(st, 6, 20.0)
@@ -1833,21 +1834,35 @@ def test_last_logits_keep_their_place_between_forwards():
         verify(c)
         with torch.cuda.stream(side):
             other = m.last_logits()
-        torch.cuda.synchronize()
+            assert torch.equal(other, ref[i])
+        verify(c)
+        with torch.cuda.stream(side):
+            with pytest.raises(api.SdError):
+                api.sd_verify(m, ctx, None, 1, 99, 0.0, c, None, None, na, nx, commit=False)
+            api.sd_prefill(m, ctx, None, 1, 0)
+            other = m.last_logits()
         assert torch.equal(other, ref[i])
         verify(c)
         here = m.last_logits()
         with torch.cuda.stream(side):
             verify(cands[(i + 1) % len(cands)])
-            there = m.last_logits()
+        there = m.last_logits()
+        with torch.cuda.stream(side):
+            again = m.last_logits()
         torch.cuda.synchronize()
-        assert torch.equal(here, ref[i]) and torch.equal(there, ref[(i + 1) % len(cands)])
-    assert not m._captured
+        assert torch.equal(here, ref[i]) and torch.equal(there, again) and torch.equal(there, ref[(i + 1) % len(cands)])
     slot = cands[0].clone()
+    torch.cuda.synchronize()
+    verify(cands[2])
+    pending = m.last_logits()
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=side):
+    with torch.cuda.stream(side):   # a capture that does not synchronise on entry, with a copy pending
+        graph.capture_begin()
         verify(slot)
-    assert m._captured
+        graph.capture_end()
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(pending, ref[2])
     for i, c in enumerate(cands):
         verify(cands[0])
         slot.copy_(c)
