@@ -2645,7 +2645,7 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
         }
     }
     RowRegs<NSEG> qr;
-    if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, qr); // (past the end: whatever q is, e(x) is 0 there)
+    if (EARLY_Q && T > 0.f && i < gamma) row_load<RT>(qrow, V, qr);
     row_fill<RT>(V, row_filler(T), r);
     const float invT = inv_temperature(T);
     float mx, z;
@@ -2662,13 +2662,18 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
             const float invZ = 1.0f / z;
             row_scale(r, invZ);
             if (i < gamma) {
+                if (EARLY_Q) row_fill<RT>(V, 0.f, qr); // (a q below 0 must leave no weight past the end)
 #pragma unroll
                 for (int h = 0; h < NSEG; h += QH) { // (four segments of q at a time: registers for two blocks per unit)
                     float4 w[QH];
 #pragma unroll
                     for (int k = 0; k < QH; k++) {
                         if (EARLY_Q) w[k] = qr.f[h + k];
-                        else w[k] = *(const float4 *)(qrow + 4 * min((h + k) * RT + (int)threadIdx.x, V / 4 - 1));
+                        else {
+                            const int v = (h + k) * RT + threadIdx.x;
+                            w[k] = *(const float4 *)(qrow + 4 * min(v, V / 4 - 1));
+                            if (v >= V / 4) w[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        }
                     }
 #pragma unroll
                     for (int k = 0; k < QH; k++) {
@@ -2721,8 +2726,9 @@ __global__ __launch_bounds__(RT, 4) void verify_draw_kernel(const float *logits,
     const float mx = st[3 * n_acc], invZ = 1.0f / st[3 * n_acc + 1];
     RowRegs<NSEG> r, w;
     row_load<RT>(logits + ((size_t)j * (stride_g + 1) + n_acc) * V, V, r);
-    if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, w); // (past the end e(x) is 0)
+    if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, w);
     row_fill<RT>(V, row_filler(T), r);
+    if (n_acc < gamma) row_fill<RT>(V, 0.f, w); // (a q below 0 must leave no weight past the end)
     const RowExp ex(mx, invT);
 #pragma unroll
     for (int it = 0; it < NSEG; it++) r.f[it] = ex(r.f[it]);

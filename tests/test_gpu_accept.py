@@ -347,6 +347,29 @@ def test_masked_columns_carry_no_weight(V, T):
     assert check_against_oracle(np.maximum(logits, low), q, cand, u, T, na_h, nx_h) <= 1
 
 
+@pytest.mark.parametrize("V,gamma,B", [(4, 1, 6), (1028, 1, 6), (20000, 1, 6), (1028, 1, 140), (20000, 1, 140), (1028, 2, 100), (20000, 2, 100)])
+def test_a_negative_q_in_the_last_columns_adds_no_weight_past_the_row(V, gamma, B):
+    """q = -0.5 in the last four columns: the token comes from max(0, p - q) over the row alone, in rows that read q early, late
+    and in the draw per sequence, with most of the residual's mass in the row's last vector."""
+    print(f"negative q V={V} gamma={gamma} B={B}", flush=True)
+    rng = np.random.default_rng(V + B)
+    logits = rng.normal(0, 2, (B, gamma + 1, V)).astype(np.float32)
+    q = np.full((B, gamma, V), 1.0 / V, np.float32)
+    q[:, :, V - 4:] = -0.5
+    q[:, :, 0] = 1.0
+    cand = np.zeros((B, gamma), np.int32)
+    u = np.full((B, gamma + 1), 0.9999, np.float32)   # (above p / q of column 0: rejected)
+    u[:, gamma] = rng.random(B).astype(np.float32)
+    u[0, gamma], u[1, gamma] = 1.0 - 2.0 ** -24, 0.0
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    na, nx = (torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_accept(dev(logits), gamma, 1.0, dev(cand), dev(q), dev(u), na, nx, torch.zeros(3 * B * (gamma + 1), device="cuda"))
+    torch.cuda.synchronize()
+    na_h, nx_h = na.cpu().numpy(), nx.cpu().numpy()
+    assert (na_h == 0).all() and ((0 <= nx_h) & (nx_h < V)).all()
+    assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1
+
+
 @pytest.mark.parametrize("dtype", [dg.FP32, dg.BF16])
 def test_draft_at_infinite_temperature_is_uniform(dtype):
     """The samplers of the draft phase at T = inf: q = 1 / V and the candidate at u V, in both data types."""
