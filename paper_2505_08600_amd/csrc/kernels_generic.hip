@@ -1657,6 +1657,17 @@ __device__ __forceinline__ void row_fill(int V, float fill, RowRegs<NSEG> &r)
     }
 }
 
+// p := max(0, p - q); no weight past the end of the row, whatever vector row_load has repeated there (a q below 0 would leave
+// some).  A select on the result: on q itself it makes the late loads of q conditional again (300 rows of 32000 columns: 21.2
+// -> 25.5 us).
+__device__ __forceinline__ void residual(bool in, float4 &p, const float4 q)
+{
+    p.x = in ? fmaxf(p.x - q.x, 0.f) : 0.f;
+    p.y = in ? fmaxf(p.y - q.y, 0.f) : 0.f;
+    p.z = in ? fmaxf(p.z - q.z, 0.f) : 0.f;
+    p.w = in ? fmaxf(p.w - q.w, 0.f) : 0.f;
+}
+
 // e^((x - mx) / T) of a row's elements, x <= mx: 2^n 2^f with n + f = (x - mx) log2(e) / T, n whole, f from one rounding and
 // corrected by what the factor's own rounding takes from the product; nine instructions where expf with the difference and its
 // product takes fifteen.  (-inf and what lies 160 powers of two below the maximum give 0, a NaN stays one.)  Error of the
@@ -2662,26 +2673,16 @@ __global__ __launch_bounds__(RT, EARLY_Q ? 4 : 8) void verify_rows_kernel(const 
             const float invZ = 1.0f / z;
             row_scale(r, invZ);
             if (i < gamma) {
-                if (EARLY_Q) row_fill<RT>(V, 0.f, qr); // (a q below 0 must leave no weight past the end)
 #pragma unroll
                 for (int h = 0; h < NSEG; h += QH) { // (four segments of q at a time: registers for two blocks per unit)
                     float4 w[QH];
 #pragma unroll
                     for (int k = 0; k < QH; k++) {
                         if (EARLY_Q) w[k] = qr.f[h + k];
-                        else {
-                            const int v = (h + k) * RT + threadIdx.x;
-                            w[k] = *(const float4 *)(qrow + 4 * min(v, V / 4 - 1));
-                            if (v >= V / 4) w[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        }
+                        else w[k] = *(const float4 *)(qrow + 4 * min((h + k) * RT + (int)threadIdx.x, V / 4 - 1));
                     }
 #pragma unroll
-                    for (int k = 0; k < QH; k++) {
-                        r.f[h + k].x = fmaxf(r.f[h + k].x - w[k].x, 0.f);
-                        r.f[h + k].y = fmaxf(r.f[h + k].y - w[k].y, 0.f);
-                        r.f[h + k].z = fmaxf(r.f[h + k].z - w[k].z, 0.f);
-                        r.f[h + k].w = fmaxf(r.f[h + k].w - w[k].w, 0.f);
-                    }
+                    for (int k = 0; k < QH; k++) residual((h + k) * RT + (int)threadIdx.x < V / 4, r.f[h + k], w[k]);
                     if (!EARLY_Q) SD_SCHED_FENCE();
                 }
             }
@@ -2728,7 +2729,6 @@ __global__ __launch_bounds__(RT, 4) void verify_draw_kernel(const float *logits,
     row_load<RT>(logits + ((size_t)j * (stride_g + 1) + n_acc) * V, V, r);
     if (n_acc < gamma) row_load<RT>(q + ((size_t)j * stride_g + n_acc) * V, V, w);
     row_fill<RT>(V, row_filler(T), r);
-    if (n_acc < gamma) row_fill<RT>(V, 0.f, w); // (a q below 0 must leave no weight past the end)
     const RowExp ex(mx, invT);
 #pragma unroll
     for (int it = 0; it < NSEG; it++) r.f[it] = ex(r.f[it]);
@@ -2738,11 +2738,9 @@ __global__ __launch_bounds__(RT, 4) void verify_draw_kernel(const float *logits,
     if (n_acc < gamma) { // (uniform)
 #pragma unroll
         for (int it = 0; it < NSEG; it++) {
-            float4 &f = w.f[it];
-            f.x = fmaxf(r.f[it].x - f.x, 0.f);
-            f.y = fmaxf(r.f[it].y - f.y, 0.f);
-            f.z = fmaxf(r.f[it].z - f.z, 0.f);
-            f.w = fmaxf(r.f[it].w - f.w, 0.f);
+            float4 f = r.f[it];
+            residual(it * RT + (int)threadIdx.x < V / 4, f, w.f[it]);
+            w.f[it] = f;
         }
         next = pick_regs<RT>(w, V, uu, &fs, &mass);
     }
