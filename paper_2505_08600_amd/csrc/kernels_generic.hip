@@ -2378,16 +2378,35 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // argmax entries, which sampling does not use.  A block keeps two batches of 4 float4 per thread, one in flight while the
 // other is summed.
 // The statistics pass is bound by instruction issue as much as by memory: with expf (13 instructions an element beside the
-// subtraction and the maximum) 576 rows of 128000 columns take 64 us, with the hardware's 2^x on the difference times
-// log2(e) / T 55, and then the nontemporal hint pays (48 us, 6.1 TB/s).  The sum's error against 64 bits is the same either
-// way, that of adding 32-bit numbers in this order (rows of N(0, 2) at T = 0.7 and 1, 33000 to 262144 columns: 5e-8 to 1.3e-7
-// rms; peaked rows 1e-8 and less); the probability an acceptance test or a draw uses keeps expf.
+// subtraction and the maximum) 576 rows of 128000 columns take 64 us, with three (WideExp) 56, and then the nontemporal
+// hint pays (49 us, 6.0 TB/s).
 // The hint and block shape, whole call: 576 x 128000 84.5 us (512 threads) / 77.4 (512, hint) / 75.2 (1024, hint); 360 x 128000
 // 58.5 without, 55.1 with the hint; 144 x 128000 34.5 / 35.8; 540 x 33000 31.3 / 32.7 / 34.2; 100 x 128000, gamma 0, where the
 // pick reads the row again, 64.5 / 73.0: the hint above 128 MB of logits, 512 threads below that where there are rows
 // enough to put two blocks on every compute unit.
 // Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 75 us (101 with expf, the acceptance test in the
 // second launch and a pick that read its slice twice).
+// e^(d / T), d <= 0, as 2^(c d + r d): c = log2(e) / T rounded down, r >= 0 what that leaves of it (the two-constant reduction
+// of Cody and Waite, in base 2).  r > 0 and bounded by c: -inf stays -inf through both products and gives 0, d = 0 gives 1
+// at any T.  Error of a row's sum against 64 bits, rms over 300 rows of N(0, 2), 128000 columns, T = 1 / 1.1 / 1.3 / 2: expf
+// 6.3e-8 / 8.9e-8 / 9.9e-8 / 6.0e-8, this 6.2e-8 / 8.9e-8 / 9.6e-8 / 6.1e-8 (from 1.1 on mostly what 1 / T loses in 32 bits);
+// without r, whose lack has the same sign in every column, 6.2e-8 / 1.5e-7 / 1.3e-7 / 6.6e-8, 0.8 us faster at 576 rows.
+// The probability an acceptance test or a draw uses is expf's.
+struct WideExp {
+    float c, r;
+    __device__ __forceinline__ WideExp(float invT)
+    {
+        const float lo = invT * 1.92596299e-8f; // (log2(e) minus its nearest float)
+        c = fminf(invT * 1.44269504088896f, 3.4e38f);
+        r = fmaf(invT, 1.44269504088896f, -c) + lo;
+        if (r < 0.f && c > 1e-30f) {
+            c = __uint_as_float(__float_as_uint(c) - 1u);
+            r = fmaf(invT, 1.44269504088896f, -c) + lo;
+        }
+        r = fmaxf(fminf(r, c * 2.4e-7f), 1.4e-45f);
+    }
+    __device__ __forceinline__ float operator()(float d) const { return __builtin_amdgcn_exp2f(fmaf(d, c, d * r)); }
+};
 #define WIDE_U 4
 template <int THREADS, bool NT>
 __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float *logits, int gamma, int V, float T, const int32_t *cand,
@@ -2397,7 +2416,8 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
     __shared__ int redi[32];
     const float4 *row = (const float4 *)(logits + (size_t)blockIdx.x * V);
     const int nvec = V / 4; // (V is a multiple of 4)
-    const float invT = inv_temperature(T), c2 = fminf(invT * 1.44269504088896f, 3.4e38f); // e^(d / T) = 2^(c2 d); 0 * c2 stays 0
+    const float invT = inv_temperature(T);
+    const WideExp ex(invT);
     // the row's acceptance test: what it needs beside the row's sums is requested first
     const int j = blockIdx.x / (gamma + 1), i = blockIdx.x % (gamma + 1);
     int c = -1;
@@ -2433,10 +2453,9 @@ __global__ __launch_bounds__(THREADS) void verify_stats_wide_kernel(const float 
             for (int k = 0; k < WIDE_U; k++) m = fmaxf(m, fmaxf(fmaxf(f[k].x, f[k].y), fmaxf(f[k].z, f[k].w)));
 #pragma unroll
             for (int k = 0; k < WIDE_U; k++) {
-                s += (__builtin_amdgcn_exp2f((f[k].x - m) * c2) + __builtin_amdgcn_exp2f((f[k].y - m) * c2)) +
-                     (__builtin_amdgcn_exp2f((f[k].z - m) * c2) + __builtin_amdgcn_exp2f((f[k].w - m) * c2));
+                s += (ex(f[k].x - m) + ex(f[k].y - m)) + (ex(f[k].z - m) + ex(f[k].w - m));
             }
-            z = m > m_old ? z * __builtin_amdgcn_exp2f((m_old - m) * c2) + s : z + s;
+            z = m > m_old ? z * ex(m_old - m) + s : z + s;
         } else {
 #pragma unroll
             for (int k = 0; k < WIDE_U; k++) {
