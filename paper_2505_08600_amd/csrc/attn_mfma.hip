@@ -533,11 +533,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
     __shared__ float sO[WAVES][ND][64][4];
     __shared__ float sM[WAVES][16], sL[WAVES][16];
     __shared__ __attribute__((aligned(16))) uint16_t sQ[2][16][HD];
-    // one-dimensional grid: (1 + n_help) times the (sequence, head) pairs padded to a multiple of 8, see launch_attn_fused_bf16
-    const int pair = HELP ? blockIdx.x % n_pad : blockIdx.x;
+    // grid (H, n_seq), or with helpers (1 + n_help) times the (sequence, head) pairs padded to a multiple of 8
+    const int pair = blockIdx.x % n_pad;
     if (HELP && pair >= H * n_seq) return; // (padding)
-    const int h = pair % H;
-    const int j = n_seq > 1 ? pv.seq_order[pair / H] : 0; // longest sequences start first
+    const int h = HELP ? pair % H : blockIdx.x, js = HELP ? pair / H : blockIdx.y;
+    const int j = n_seq > 1 ? pv.seq_order[js] : 0; // longest sequences start first
     if (HELP && (int)blockIdx.x >= n_pad) {
         kv_prefetch<HD, WAVES>(Kl, Vtl, pv, cv, h, j, total_cap, blockIdx.x / n_pad - 1, n_help);
         return;
@@ -707,7 +707,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
 {
     if (oproj_done) *oproj_done = 0;
     if (R < 1 || R > 16 || (hd != 64 && hd != 128) || n_slabs < 1 || n_slabs > 8) return hipErrorNotSupported;
-    if (n_seq > 65535 || H > 65535 || (long)n_seq * H > (1 << 28)) return hipErrorNotSupported;
+    if (n_seq > 65535 || H > 65535) return hipErrorNotSupported;
     const int tiles_upper = (len_upper + AT_TILE - 1) / AT_TILE;
     // one block per (sequence, head): fine when every wave has at most a few tiles anyway, or when those blocks
     // alone fill the chip and the contexts stay below about 2000 tokens - beyond that the split kernel, whose blocks
@@ -720,15 +720,17 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     // per block on, the 8-wave shape streams faster (measured: 4.9 against 4.6 TB/s at 2048 tokens, 5.5
     // against 5.2 at 1024..8192)
     const bool many = g_force_attn_waves ? g_force_attn_waves == 4 : ((long)n_seq * H >= 512 && tiles_upper <= 40);
-    const int n_pairs = H * n_seq, n_pad = (n_pairs + 7) / 8 * 8;
+    const int n_pad = (int)std::min<long>(((long)n_seq * H + 7) / 8 * 8, 512); // (helpers: up to 128 pairs)
     // Helpers where blocks of one (sequence, head) pair leave half of the 256 units or more idle and have more tiles than
     // waves: a unit alone draws K and V from HBM at about 50 GB/s however many loads it has in flight, and what its idle
     // neighbours have read into the die's L2 (blocks go to the dies in turn: a pair's blocks are a multiple of 8 apart) it gets
     // several times faster.  Head width 128, 7B shape: 32 layers at 32 pairs and 517 tokens 2825 us without, 2835 / 2800 / 2797 /
     // 2801 with 1 / 2 / 3 / 7 helpers a pair; 2 layers at 128 pairs and 301 to 1500 tokens 327 / 323.7 with one.  At head width 64
     // (half the bytes per tile, the softmax sets the time) no case moved.
-    const int n_help = hd == 128 && stream_nt && !many && tiles_upper > 8 ? std::min(256 / n_pad - 1, 3) : 0;
-    dim3 grid(n_help > 0 ? n_pad * (1 + n_help) : n_pairs), block(many ? 256 : 512);
+    // A forced shape runs without.
+    const int n_help = hd == 128 && stream_nt && !many && !g_force_attn_waves && tiles_upper > 8 ? std::min(256 / n_pad - 1, 3) : 0;
+    const dim3 grid = n_help > 0 ? dim3(n_pad * (1 + n_help)) : dim3(H, n_seq), block(many ? 256 : 512);
+    static_assert(65535ull * 512 < (1ull << 32), "threads of a grid dimension fit 32 bits");
     // output projection inside the block: small models in few blocks (each block reads its head's slice of Wo;
     // 8 waves x 8 (head width 64) or 4 (128) column tiles bound d_model), H slabs for the add + norm kernel
     const size_t rows = (size_t)n_seq * R;

@@ -654,8 +654,9 @@ def test_draft_sampler_from_the_lm_heads_partials_matches_the_whole_row_sampler(
 
 def test_attention_helpers_change_no_result():
     """Fused attention at head width 128 whose idle compute units read K and V into the L2 first (three helpers a pair, one at
-    half the units, none beyond; 7 heads: a padded grid) against four-wave blocks without helpers (option attn_waves = 4): the
-    same tiles merged in another order, 2e-4 of the largest logit as for the kernels' other orders."""
+    half the units, none beyond; 7 heads: a padded grid) against the same eight-wave blocks without helpers (option attn_waves
+    = 8): the same bits; and against four-wave blocks (attn_waves = 4): the same tiles merged in another order, 2e-4 of the
+    largest logit as for the kernels' other orders."""
     import dataclasses
     sh = dataclasses.replace(dg.with_layers(dg.SHAPES["t7b"], 1), n_heads=7, d_model=896, d_ffn=896, vocab=75776, name="helpers")
     w = dg.make_weights(sh, 88, BF16_LM_SCALE)
@@ -666,7 +667,7 @@ def test_attention_helpers_change_no_result():
         prompts = [[int(t) for t in dg.make_prompt(88, b, int(rng.integers(lo, hi + 1)), sh.vocab)] for b in range(B)]
         cand = H.dev(rng.integers(0, sh.vocab, (B, 2)).astype(np.int32))
         outs = []
-        for waves in (0, 4):
+        for waves in (0, 4, 8):
             api.set_option("attn_waves", waves)
             try:
                 ctx = api.Context([len(p) + 16 for p in prompts])
@@ -682,6 +683,7 @@ def test_attention_helpers_change_no_result():
         assert np.isfinite(outs[0]).all()
         rel = np.abs(outs[0] - outs[1]).max() / np.abs(outs[1]).max()
         assert rel < 2e-4, (B, rel)
+        assert np.array_equal(outs[0], outs[2]), B
     gt.close()
 
 
