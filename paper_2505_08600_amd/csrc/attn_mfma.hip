@@ -488,9 +488,8 @@ __device__ __forceinline__ void kv_prefetch(const uint16_t *Kl, const uint16_t *
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_old = pv.seq_nq[j] > 0 ? pv.seq_kv0[j] / AT_TILE : 0;
-    const int first = n_help == 1 ? n_old * 2 / 5 : 0; // (a lone helper leaves the tiles the block starts with to it)
     const size_t base = ((size_t)h * total_cap + cv.off[pv.seq_b[j]]) * HD + lane * 8;
-    for (int u = 2 * first + wave + part * WAVES; u < 2 * n_old; u += n_help * WAVES) { // tile u / 2, K or V
+    for (int u = wave + part * WAVES; u < 2 * n_old; u += n_help * WAVES) { // tile u / 2, K or V
         const uint16_t *src = (u & 1 ? Vtl : Kl) + base + (size_t)(u >> 1) * (AT_TILE * HD);
         bf16x8 v[HD / 16];
 #pragma unroll
@@ -725,8 +724,10 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     // waves: a unit alone draws K and V from HBM at about 50 GB/s however many loads it has in flight, and what its idle
     // neighbours have read into the die's L2 (blocks go to the dies in turn: a pair's blocks are a multiple of 8 apart) it gets
     // several times faster.  Head width 128, 7B shape: 32 layers at 32 pairs and 517 tokens 2825 us without, 2835 / 2800 / 2797 /
-    // 2801 with 1 / 2 / 3 / 7 helpers a pair; 2 layers at 128 pairs and 301 to 1500 tokens 327 / 323.7 with one.  At head width 64
-    // (half the bytes per tile, the softmax sets the time) no case moved.
+    // 2801 with 1 / 2 / 3 / 7 helpers a pair.  One helper (86 to 128 pairs), 2 layers, without / helper that leaves the first two
+    // fifths of the tiles to the block / helper from the first tile on: 4 sequences of 301 to 1500 tokens 319.7 / 318.3 / 315.8, 3
+    // of 400 to 600 284.5 / 283.4 / 279.1, 4 of 1200 to 1400 310.2 / 312.3 / 307.0.  At head width 64 (half the bytes per tile,
+    // the softmax sets the time) no case moved.
     // A forced shape runs without.
     const int n_help = hd == 128 && stream_nt && !many && !g_force_attn_waves && tiles_upper > 8 ? std::min(256 / n_pad - 1, 3) : 0;
     const dim3 grid = n_help > 0 ? dim3(n_pad * (1 + n_help)) : dim3(H, n_seq), block(many ? 256 : 512);
