@@ -2380,11 +2380,15 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // The statistics pass is bound by instruction issue as much as by memory: with expf (13 instructions an element beside the
 // subtraction and the maximum) 576 rows of 128000 columns take 64 us, with three (WideExp) 56, and then the nontemporal
 // hint pays (49 us, 6.0 TB/s).
-// The hint and block shape, whole call: 576 x 128000 84.5 us (512 threads) / 77.4 (512, hint) / 75.2 (1024, hint); 360 x 128000
-// 58.5 without, 55.1 with the hint; 144 x 128000 34.5 / 35.8; 540 x 33000 31.3 / 32.7 / 34.2; 100 x 128000, gamma 0, where the
-// pick reads the row again, 64.5 / 73.0: the hint above 128 MB of logits, 512 threads below that where there are rows
-// enough to put two blocks on every compute unit.
-// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 75 us (101 with expf, the acceptance test in the
+// The hint, whole call at T = 1 without / with it (1024 threads), the same logits in every call | three sets of logits in turn:
+// 270 rows of 128000 columns, gamma 8 50.0 / 53.4 | 55.7 / 53.7; 360 rows 52.5 / 57.9 | 61.8 / 58.5; 576 rows 79.5 / 77.6 | 87.8 / 77.6;
+// 1350 rows of 33000 50.5 / 54.7 | 56.5 / 54.8: what the memory-side cache (256 MB) still holds from the call before it gives
+// faster without, what it does not with; above 128 MB of logits the hint (at gamma 1 the same: 280 rows 85.1 / 91.2 | 94.4 / 93.0).  At gamma
+// 0, where the pick reads the rows again: 270 rows 127 / 133 | 135 / 147; 400 rows 134 / 148 | 147 / 154; 520 rows 201 / 205 | 209 / 221;
+// 2000 rows of 33000 189 / 206 | 198 / 212; 600 rows of 128000 (307 MB) 220.6 / 218.7 | 229.1 / 228.2: the hint above 256
+// MB.  512 threads without it where there are rows enough to put two blocks on every compute unit (540 x 33000: 31.3, 1024
+// threads with the hint 34.2).
+// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 76 us (101 with expf, the acceptance test in the
 // second launch and a pick that read its slice twice).
 // e^(d / T), d <= 0, as 2^(c d + r d): c = log2(e) / T rounded down, r >= 0 what that leaves of it (the two-constant reduction
 // of Cody and Waite, in base 2).  r > 0 and bounded by c: -inf stays -inf through both products and gives 0, d = 0 gives 1
@@ -2837,7 +2841,8 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
     }
 #define SD_STATS_WIDE(RT, NT)                                                                                             \
     hipLaunchKernelGGL((verify_stats_wide_kernel<RT, NT>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, q, u, stats)
-    if ((size_t)n_rows * V > ((size_t)1 << 25)) SD_STATS_WIDE(1024, true); // (128 MB of logits)
+    // (128 MB of logits; 256 MB where they are read again)
+    if ((size_t)n_rows * V > ((size_t)1 << (T > 0.f && gamma == 0 ? 26 : 25))) SD_STATS_WIDE(1024, true);
     else if (n_rows >= 512) SD_STATS_WIDE(512, false);
     else SD_STATS_WIDE(1024, false);
     if (T > 0.f) {
