@@ -443,10 +443,13 @@ class Classifier:
     def route(self, tokens: torch.Tensor, lens: torch.Tensor, draft_id: torch.Tensor,
               logits: Optional[torch.Tensor] = None) -> None:
         """sd_route_classifier_ws on the current stream; tokens int32 [n][max_len], lens int32 [n].  The workspace is the caching
-        allocator's, in order with that stream."""
+        allocator's, in order with that stream; without memory for it the call runs as sd_route_classifier."""
         with torch.cuda.device(self.device):
             need = lib().sd_classifier_workspace(self.h, tokens.shape[0], tokens.shape[1])
-            ws = torch.empty(need, dtype=torch.uint8, device=tokens.device) if need > 0 else None
+            try:
+                ws = torch.empty(need, dtype=torch.uint8, device=tokens.device) if need > 0 else None
+            except torch.OutOfMemoryError:  # (a block per prompt needs none)
+                ws = None
             _check(lib().sd_route_classifier_ws(self.h, _dp(tokens), _dp(lens), tokens.shape[0], tokens.shape[1],
                                                 _dp(logits), _dp(draft_id), _dp(ws), _stream()))
 

@@ -129,6 +129,36 @@ def test_last_logits_on_another_stream_synchronise_whatever_was_called_there(mon
     assert entry() == ["sd_last_logits", "wait 0"]
 
 
+def test_routing_without_memory_for_a_workspace_runs_without_one(monkeypatch):
+    """Classifier.route when the allocator has nothing left: the library gets no workspace (and runs a block per prompt)."""
+    import contextlib
+    import torch
+    seen = []
+
+    class Lib:
+        def sd_classifier_workspace(self, h, n, max_len):
+            return 4096
+
+        def sd_route_classifier_ws(self, *args):
+            seen.append(args[-2])
+            return api.SD_OK
+
+    def empty(*args, **kw):
+        raise torch.OutOfMemoryError("out of memory")
+
+    monkeypatch.setattr(api, "lib", Lib)
+    monkeypatch.setattr(api, "_dp", lambda t: t)
+    monkeypatch.setattr(api, "_stream", lambda: None)
+    monkeypatch.setattr(api.torch.cuda, "device", lambda d: contextlib.nullcontext())
+    c = api.Classifier.__new__(api.Classifier)
+    c.h, c.device = None, 0
+    tokens, lens = torch.zeros((3, 20), dtype=torch.int32), torch.zeros(3, dtype=torch.int32)
+    c.route(tokens, lens, lens)
+    monkeypatch.setattr(api.torch, "empty", empty)
+    c.route(tokens, lens, lens)
+    assert seen[0] is not None and seen[1] is None
+
+
 def test_product_package_does_not_import_the_oracle():
     """The HIP path must not route through the CPU oracle."""
     import glob
