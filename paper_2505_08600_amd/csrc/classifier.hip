@@ -985,11 +985,13 @@ extern "C" void sd_classifier_destroy(sd_classifier *c)
     delete c;
 }
 
-// Blocks of classifier_run_kernel for a call with a workspace (0: the kernel has no form for the classifier).
+// Blocks of classifier_run_kernel for a call with a workspace (0: the call has no use for it).
 static int cq_blocks(const sd_classifier *c, int32_t n, int32_t max_len)
 {
-    if (c->v.d_inner > 192 || (max_len <= CQ_TC && n <= CQ_BLOCKS)) return 0; // (nothing to deal out)
-    return (int)std::min<int64_t>(CQ_BLOCKS, (int64_t)n * ((max_len + CQ_TC - 1) / CQ_TC));
+    if (c->v.d_inner > 192 || (max_len <= CQ_TC && n <= CQ_BLOCKS)) return 0; // (no form for it; nothing to deal out)
+    const int64_t chunks = (int64_t)n * ((max_len + (int64_t)CQ_TC - 1) / CQ_TC);
+    if (chunks > 1 << 30) return 0; // (chunk numbers are 32 bits)
+    return (int)std::min<int64_t>(CQ_BLOCKS, chunks);
 }
 
 extern "C" int64_t sd_classifier_workspace(const sd_classifier *c, int32_t n, int32_t max_len)

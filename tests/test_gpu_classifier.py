@@ -141,6 +141,16 @@ def test_runs_of_chunks_that_cut_prompts(d_inner, n, max_len):
     assert np.abs(logits3 - logits).max() <= LOGIT_RTOL * np.abs(logits).max()   # (both paths within the bar of the oracle)
 
 
+def test_more_chunks_than_32_bits_number_take_no_workspace():
+    """Up to 2^30 chunks of 16 tokens are dealt out; more could wrap the numbers the blocks count them with: a block per prompt."""
+    shape = dg.CLASSIFIER_TINY
+    cls = api.Classifier(shape, dg.make_classifier(shape, 6))
+    need = lambda n, max_len: api.lib().sd_classifier_workspace(cls.h, n, max_len)
+    assert need(2 ** 31 - 1, 17) == 0 and need(2 ** 31 - 1, 2 ** 31 - 1) == 0
+    assert need(2 ** 30, 16) > 0 and need(2 ** 29, 32) > 0 and need(2 ** 29 + 1, 32) == 0
+    cls.close()
+
+
 def test_out_of_range_token_is_flagged_not_read():
     shape = dg.CLASSIFIER_TINY
     w = dg.make_classifier(shape, 6)
