@@ -119,6 +119,14 @@ def test_runs_of_chunks_that_cut_prompts(d_inner, n, max_len):
     perm = np.random.default_rng(1).permutation(n)
     ids2, logits2 = _run(shape, w, tokens[perm], lens[perm])
     assert np.abs(logits[perm] - logits2).max() <= LOGIT_RTOL * np.abs(logits).max()
+    top = np.sort(logits, 1)
+    clear = top[:, -1] - top[:, -2] > 2 * LOGIT_RTOL * np.abs(logits).max()   # (elsewhere two classes tie to rounding)
+
+    def same_ids(a, b):
+        assert np.array_equal(a == -1, b == -1) and np.array_equal(a[clear], b[clear])
+
+    assert np.array_equal(np.flatnonzero(ids == -1), [bad] if n > 1 else [])
+    same_ids(ids, ids2[np.argsort(perm)])
     some = [0] + list(range(1, min(n, 12))) + [n - 1]
     for i in some:
         one, lone = _run(shape, w, tokens[i:i + 1], lens[i:i + 1])
@@ -136,9 +144,94 @@ def test_runs_of_chunks_that_cut_prompts(d_inner, n, max_len):
     torch.cuda.synchronize()
     cls.close()
     ids3, logits3 = ids3.cpu().numpy(), logits3.cpu().numpy()
-    assert (ids3[bad] == -1) == (n > 1)
+    same_ids(ids, ids3)
     _check(shape, w, tokens[keep], lens[keep], ids3[keep], logits3[keep])
     assert np.abs(logits3 - logits).max() <= LOGIT_RTOL * np.abs(logits).max()   # (both paths within the bar of the oracle)
+
+
+@pytest.mark.parametrize("d_inner", [64, 192])
+def test_an_invalid_id_in_any_part_of_a_cut_prompt_is_flagged(d_inner):
+    """Three prompts of 1300 to 2000 tokens over some 200 workgroups (runs of two chunks): an id out of range in the part a prompt
+    starts in, in runs that lie inside it, in its last chunk and behind its end; exactly the prompts that hold one get -1, and
+    the others keep their logits."""
+    shape = dg.ClassifierShape("classifier_parts", vocab=97, d_model=24, d_inner=d_inner, d_state=16, dt_rank=6, d_conv=4, n_classes=5)
+    w = dg.make_classifier(shape, 43)
+    rng = dg._rng(43, 59)
+    tokens = rng.integers(0, shape.vocab, size=(3, 2000), dtype=np.int32)
+    lens = np.array([1777, 2000, 1300], np.int32)
+    ids, logits = _run(shape, w, tokens, lens)
+    assert (ids >= 0).all()
+    for i in range(3):
+        L = int(lens[i])
+        for at in (0, 15, 16, 40, L // 2, L - 40, L - 17, L - 1, L):
+            if at == tokens.shape[1]:
+                continue
+            print(f"invalid id d_inner={d_inner} prompt {i} token {at}", flush=True)
+            t = tokens.copy()
+            t[i, at] = (-1, shape.vocab, 2 ** 31 - 1)[at % 3]
+            got, lg = _run(shape, w, t, lens)
+            want = ids.copy()
+            if at < L:
+                want[i] = -1
+            assert np.array_equal(got, want), (i, at, got)
+            others = [k for k in range(3) if k != i or at >= L]
+            assert np.array_equal(lg[others], logits[others])
+
+
+def test_workspaces_hold_anything_and_calls_on_several_streams_keep_apart():
+    """The same batch with workspaces of zeros, ones, NaN, of a call of another batch and at an address that is no multiple of 8, on
+    four streams at once: the same bits in every call; and captured into a graph whose replays see other lengths and ids."""
+    shape = dg.ClassifierShape("classifier_streams", vocab=97, d_model=24, d_inner=128, d_state=16, dt_rank=6, d_conv=4, n_classes=5)
+    w = dg.make_classifier(shape, 47)
+    rng = dg._rng(47, 61)
+    n, max_len, L = 37, 300, api.lib()
+    cls = api.Classifier(shape, w)
+    batches = []
+    for k in range(4):
+        t = torch.from_numpy(rng.integers(0, shape.vocab, size=(n, max_len), dtype=np.int32)).cuda()
+        l = torch.from_numpy((rng.integers(0, max_len + 1, size=n) if k else np.full(n, max_len)).astype(np.int32)).cuda()
+        batches.append((t, l))
+    need = L.sd_classifier_workspace(cls.h, n, max_len)
+
+    def call(t, l, ws):
+        ids = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        lg = torch.full((n, 5), float("nan"), device="cuda")
+        api._check(L.sd_route_classifier_ws(cls.h, t.data_ptr(), l.data_ptr(), n, max_len, lg.data_ptr(), ids.data_ptr(), ws.data_ptr(), api._stream()))
+        return ids, lg
+
+    ref = [call(t, l, torch.zeros(need, dtype=torch.uint8, device="cuda")) for t, l in batches]
+    torch.cuda.synchronize()
+    for fill in (0, 1, 255):
+        ws = torch.full((need + 8,), fill, dtype=torch.uint8, device="cuda")
+        for k, (t, l) in enumerate(batches):   # (the second call finds the first one's workspace)
+            for at in (0, 4):
+                ids, lg = call(t, l, ws[at:])
+                assert torch.equal(ids, ref[k][0]) and torch.equal(lg, ref[k][1])
+    streams = [torch.cuda.Stream() for _ in batches]
+    spaces = [torch.full((need,), 255, dtype=torch.uint8, device="cuda") for _ in batches]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(25):
+        for k, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got.append((k,) + call(*batches[k], spaces[k]))
+    torch.cuda.synchronize()
+    assert all(torch.equal(ids, ref[k][0]) and torch.equal(lg, ref[k][1]) for k, ids, lg in got)
+    t, l = (x.clone() for x in batches[0])
+    ids, lg = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty((n, 5), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        cls.route(t, l, ids, lg)
+    for rep in range(3):
+        for k in (1, 0, 2, 3):
+            t.copy_(batches[k][0])
+            l.copy_(batches[k][1])
+            graph.replay()
+            assert torch.equal(ids, ref[k][0]) and torch.equal(lg, ref[k][1]), (rep, k)
+            cls.route(*batches[(k + 1) % 4], torch.empty_like(ids))   # the program's own calls in between
+            torch.cuda.synchronize()
+    cls.close()
 
 
 def test_more_chunks_than_32_bits_number_take_no_workspace():
