@@ -293,9 +293,9 @@ void sd_classifier_destroy(sd_classifier *c); /* NULL is a no-op; synchronise th
  * SD_EINVAL for a null pointer, n or max_len below 1, or a current device other than the classifier's. */
 int sd_route_classifier(const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
                         int32_t max_len, float *logits, int32_t *draft_id, void *stream);
-/* The same with a workspace (dev, 4-byte aligned, sd_classifier_workspace(c, n, max_len) bytes, this call's alone until its
- * kernels have run): up to 192 inner channels the batch's tokens are then dealt out evenly over the workgroups and a second
- * kernel on `stream` joins the parts of prompts that were shared.  NULL: as sd_route_classifier.  Results agree with
+/* The same with a workspace (dev, 4-byte aligned, sd_classifier_workspace(c, n, max_len) bytes of any contents, this call's alone
+ * until its kernel has run): up to 192 inner channels the batch's tokens are then dealt out evenly over the workgroups, and
+ * the last workgroup of a prompt that was shared joins its parts.  NULL: as sd_route_classifier.  Results agree with
  * sd_route_classifier's to rounding; where a prompt is cut follows from the lengths in the batch. */
 int sd_route_classifier_ws(const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
                            int32_t max_len, float *logits, int32_t *draft_id, float *workspace, void *stream);

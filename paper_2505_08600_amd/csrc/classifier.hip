@@ -1,7 +1,7 @@
 // Prompt classifier (Sections 2.4, 3.3.3): embedding -> one selective state-space layer ->
 // average pooling over the prompt -> linear layer -> arg max, as the second backend of routing.
 //
-// One workgroup per prompt.  The recurrence over tokens is sequential, so everything a channel
+// One workgroup per prompt or (classifier_run_kernel) per run of tokens.  The recurrence over tokens is sequential, so everything a channel
 // needs between tokens (its state row, its weights) stays in registers; only the small per-token
 // projection (dt_rank + 2 d_state outputs) crosses threads, through LDS.  Everything without a
 // dependence between tokens is done for a chunk of tokens at a time.  Pooling and the output
@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <string>
@@ -504,27 +506,47 @@ classifier_quad_kernel(ClsView v, const int32_t *__restrict__ tokens, const int3
 // are loaded once per run, and the head is one matrix.  A run that starts inside a prompt works from a zero state; with P
 // the product of its decays and G the sum of C P silu(z) over its tokens, the state before it enters the pooled sum as G . h and the
 // state behind it as P h.  So the block leaves the record (G, P, state, sums) of that prompt's part in the workspace, the block a
-// prompt starts in leaves what it has, and classifier_join_kernel joins them in order.
-// Bound: vector issue and barriers of 4.3 - 4.5 us a chunk, 4.4 us from the start of a block to its first chunk, 4.7 us for the
-// second launch.
-// Measured, 192 channels, a block per prompt / runs (us): 8 prompts of up to 64 tokens 21.0 / 16.4, 40 of up to 128 27.7 / 19.3, 100 of
-// up to 40 19.6 / 19.3, 200 of up to 200 52.1 / 25.4, 400 of up to 128 50.2 / 35.0, 1000 93 / 60, 4000 293 / 191; 3000 of up to 16 125 / 76;
-// all of one length: 400 x 128 90 / 88, 200 x 128 44 / 51, 100 x 200 65 / 48, 2000 x 200 516 / 532, 20 of 900 - 1000 288 / 49.
-#define CQ_WIN 64 // chunks whose places are laid out at a time
+// prompt starts in leaves what it has, and whichever of the prompt's blocks ends last joins them in order: no block waits for
+// another, and the sums are the same whoever joins.  Where cutting would save a chunk at most, each block has a prompt.
+// Bound: vector issue and barriers, 4.3 - 4.6 us a chunk, 4.4 us from the start of a block to its first chunk, about 7 us for a cut
+// batch's hand-over (the stores' arrival, one write-back of the die's L2 and an atomic per block, the join's loads; fences of all
+// twelve waves instead of one cost 70).  A second launch for the joins cost 5 - 8 us, and 2 where nothing was cut.
+// Measured, 192 channels, a block per prompt / runs (us): 8 prompts of up to 64 tokens 24.9 / 17.3, 40 of up to 128 28.7 / 18.0, 100 of
+// up to 40 19.7 / 17.2, 200 of up to 200 32.6 / 24.7, 400 of up to 128 55.6 / 34.0, 1000 87 / 58, 4000 284 / 185, 100000 of up to 40
+// 5920 / 3784; 3000 of up to 16 124 / 73; all of one length: 200 x 128 44.1 / 43.8, 100 x 200 64 / 44, 400 x 128 86.5 / 80.7, 2000 x 200
+// 515 / 494, 250 x 512 153 / 156, 20 of 900 - 1000 285 / 48.
 #define CQ_BLOCKS 256 // blocks at most: one per compute unit
 __host__ __device__ static constexpr size_t cq_run_lds_floats(int di)
 {
     // x [TC][di + 4] | delta [TC][di + 4] (the projection's partial sums before that) | (delta x, silu(z)) [TC][di + 4] | r, B, C [TC][52]
     return 4 * (size_t)CQ_TC * (di + 4) + CQ_TC * CQ_ROW;
 }
-// Workspace of nb blocks of t threads, in floats: records [nb][14][t] | open prompts [nb][6][t] | notes [nb][8]
-__host__ __device__ static inline size_t cq_rec_at(size_t b, int t) { return b * 14 * (size_t)t; }
-__host__ __device__ static inline size_t cq_open_at(size_t nb, size_t b, int t) { return (nb * 14 + b * 6) * (size_t)t; }
-__host__ __device__ static inline size_t cq_note_at(size_t nb, size_t b, int t) { return nb * 20 * (size_t)t + b * 8; }
-// does the prompt the run starts in end in it (a prompt that ended before: 1 as well), its flag; prompt that starts here and is left open or -1, its flag
-enum CqNote { CQ_N_CLOSED, CQ_N_BAD, CQ_N_OPEN, CQ_N_OPEN_BAD };
+// Workspace of nb blocks of t threads, in floats: arrivals [nb] (64 bits each) | records [nb][14][t] | open prompts [nb][6][t] |
+// invalid ids seen in a block's record, in its open prompt [nb][2]
+__host__ __device__ static inline size_t cq_rec_at(size_t nb, size_t b, int t) { return 2 * nb + b * 14 * (size_t)t; }
+__host__ __device__ static inline size_t cq_open_at(size_t nb, size_t b, int t) { return 2 * nb + (nb * 14 + b * 6) * (size_t)t; }
+__host__ __device__ static inline size_t cq_bad_at(size_t nb, size_t b, int t) { return 2 * nb + nb * 20 * (size_t)t + b * 2; }
+
+// What blocks hand to each other goes past the caches that only one die sees.
+__device__ __forceinline__ void put(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// One of `parts` arrivals at *word; true for the last.  The word counts for this call only where its upper 48 bits are the call's
+// tag, so the workspace may hold anything; the last arrival leaves 0 (a replay of a captured call has the same tag).
+__device__ __forceinline__ bool cq_arrive(unsigned long long *word, unsigned long long tag, int parts)
+{
+    unsigned long long old = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) { // (repeated only when another part has arrived in between)
+        const unsigned long long seen = (old & ~0xffffull) == tag ? old & 0xffff : 0;
+        const bool last = (int)seen + 1 == parts;
+        if (__hip_atomic_compare_exchange_strong(word, &old, last ? 0 : tag | (seen + 1), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return last;
+    }
+}
 
 __device__ __forceinline__ int cls_len(const int32_t *lens, int i, int max_len) { return min(max(lens[i], 0), max_len); }
+struct CqChunk {
+    int p, at, len; // prompt, first token, the prompt's length
+};
 __device__ __forceinline__ int cls_chunks(int L) { return max(1, (L + CQ_TC - 1) / CQ_TC); } // (an empty prompt has one, of no tokens)
 
 // Mean over tokens, head, arg max of a prompt whose sums are complete: pooled per (channel, quarter) thread, pooled_d per
@@ -568,21 +590,47 @@ __device__ __forceinline__ void classifier_finish(const ClsView &v, int i, int L
 __device__ __forceinline__ void cq_record(float *rec, int T, const float *G, const float *P, const float *h, float pooled, float pooled_d)
 {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) rec[k * T] = G[k], rec[(4 + k) * T] = P[k], rec[(8 + k) * T] = h[k];
-    rec[12 * T] = pooled;
-    rec[13 * T] = pooled_d;
+    for (int k = 0; k < 4; ++k) put(rec + k * T, G[k]), put(rec + (4 + k) * T, P[k]), put(rec + (8 + k) * T, h[k]);
+    put(rec + 12 * T, pooled);
+    put(rec + 13 * T, pooled_d);
+}
+
+// Joins prompt i, which block b0 left open, with the records of blocks b0 + 1 .. b1.
+template <int DI>
+__device__ __forceinline__ void cq_join(const ClsView &v, int i, int L, int b0, int b1, int nb, const float *ws, float *s_pool, float *s_mean,
+                                        float *s_logit, float *logits, int32_t *draft_id)
+{
+    constexpr int T = 4 * DI;
+    const int tid = threadIdx.x;
+    const float *o = ws + cq_open_at(nb, b0, T) + tid;
+    bool bad = get(ws + cq_bad_at(nb, b0, T) + 1) != 0.f;
+    float h[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h[k] = get(o + k * T);
+    float pooled = get(o + 4 * T), pooled_d = get(o + 5 * T);
+    for (int b = b0 + 1; b <= b1; ++b) {
+        const float *rec = ws + cq_rec_at(nb, b, T) + tid;
+        float r[14];
+#pragma unroll
+        for (int k = 0; k < 14; ++k) r[k] = get(rec + k * T);
+        bad |= get(ws + cq_bad_at(nb, b, T)) != 0.f;
+        pooled += fmaf(r[3], h[3], fmaf(r[2], h[2], fmaf(r[1], h[1], fmaf(r[0], h[0], r[12]))));
+        pooled_d += r[13];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) h[k] = fmaf(r[4 + k], h[k], r[8 + k]);
+    }
+    classifier_finish<DI>(v, i, L, pooled, pooled_d, bad, s_pool, s_mean, s_logit, logits, draft_id);
 }
 
 template <int DI> // d_inner: 64, 128 or 192
 __global__ void __launch_bounds__(4 * DI, DI / 64)
 classifier_run_kernel(ClsView v, const int32_t *__restrict__ tokens, const int32_t *__restrict__ lens, int n, int max_len,
-                       float *__restrict__ logits, int32_t *__restrict__ draft_id, float *__restrict__ ws)
+                      float *__restrict__ logits, int32_t *__restrict__ draft_id, float *ws, unsigned long long tag)
 {
     typedef __attribute__((ext_vector_type(4))) float f32x4;
     __shared__ __align__(16) float lds[cq_run_lds_floats(DI)];
     __shared__ float s_pool[4 * DI], s_mean[DI], s_logit[CLS_MAX_CLASSES];
-    __shared__ int4 s_chunk[CQ_WIN]; // (prompt, first token, length)
-    __shared__ int s_sum[16], s_max[16], s_run[2];
+    __shared__ int s_sum[16], s_max[16], s_start[3], s_last[2];
     constexpr int di = DI, sx = DI + 4, T = 4 * DI; // (rows 4 banks apart)
     constexpr int waves = DI / 16, nkq = waves / 3, per = DI / 4 / nkq; // (2): a wave's share is `per` instructions
     static_assert(nkq * per * 4 == DI, "shares of whole instructions");
@@ -593,6 +641,9 @@ classifier_run_kernel(ClsView v, const int32_t *__restrict__ tokens, const int32
     const int l16 = lane & 15, tq = lane >> 4, c = wave * 16 + l16; // (1): channel, group of four tokens
     const int cs = tid >> 2, sub = tid & 3;                         // (3): channel, quarter of the states
 
+    // (for a batch in which nothing is cut: this block's prompt)
+    const int own = min((int)blockIdx.x, n - 1), own_len = cls_len(lens, own, max_len);
+    const int own_id = l16 < max_len ? tokens[(size_t)own * max_len + l16] : 0;
     // chunks of the prompts this thread looks after (pp in a row), and of those before them
     const int pp = (n + T - 1) / T, p_lo = min(n, tid * pp), p_hi = min(n, p_lo + pp);
     int mine = 0, longest = 0;
@@ -661,251 +712,256 @@ classifier_run_kernel(ClsView v, const int32_t *__restrict__ tokens, const int32
     total = __builtin_amdgcn_readfirstlane(total); // (the loops below are uniform: keep their bounds in scalar registers)
     longest = __builtin_amdgcn_readfirstlane(longest);
     const int nb = gridDim.x, run = (total + nb - 1) / nb;
-    int run0 = (int)min((int64_t)total, (int64_t)blockIdx.x * run), run1 = min(total, run0 + run);
-    if (n <= nb && longest <= run + 1) { // cutting would save a chunk at most: a block per prompt (200 prompts of 128 tokens: 51 us, 54 cut)
-        if (tid == 0) s_run[0] = s_run[1] = total;
-        lds_sync();
-        for (int p = p_lo, q = first; p < p_hi; ++p) {
-            const int nc = cls_chunks(cls_len(lens, p, max_len));
-            if (p == (int)blockIdx.x) {
-                s_run[0] = q;
-                s_run[1] = q + nc;
+    // cutting would save a chunk at most: a block per prompt
+    const bool whole = n <= nb && longest <= run + 1;
+    int run0, run1;
+    CqChunk cur = {own, 0, own_len};
+    if (whole) {
+        run0 = 0;
+        run1 = (int)blockIdx.x < n ? cls_chunks(own_len) : 0;
+    } else {
+        run0 = (int)min((int64_t)total, (int64_t)blockIdx.x * run), run1 = min(total, run0 + run);
+        if (run0 < run1 && first <= run0 && run0 < first + mine) { // (one thread's prompts hold chunk run0)
+            int p = p_lo, q = first, L = cls_len(lens, p, max_len);
+            while (q + cls_chunks(L) <= run0) {
+                q += cls_chunks(L);
+                L = cls_len(lens, ++p, max_len);
             }
-            q += nc;
+            s_start[0] = p;
+            s_start[1] = (run0 - q) * CQ_TC;
+            s_start[2] = L;
         }
         lds_sync();
-        run0 = __builtin_amdgcn_readfirstlane(s_run[0]);
-        run1 = __builtin_amdgcn_readfirstlane(s_run[1]);
+        cur.p = __builtin_amdgcn_readfirstlane(s_start[0]);
+        cur.at = __builtin_amdgcn_readfirstlane(s_start[1]);
+        cur.len = __builtin_amdgcn_readfirstlane(s_start[2]);
     }
+    if (run0 >= run1) return; // (uniform)
+    // The chunks behind this one: the same prompt's, or the first of the next prompt, whose length was requested two prompts
+    // before.
+    CqChunk ahead = cur;
+    int len1 = 0, len2 = 0; // of prompts ahead.p + 1, ahead.p + 2
+    if (!whole) {
+        len1 = cls_len(lens, min(cur.p + 1, n - 1), max_len);
+        len2 = cls_len(lens, min(cur.p + 2, n - 1), max_len);
+    }
+    auto advance = [&]() {
+        if (ahead.at + CQ_TC < ahead.len) ahead.at += CQ_TC;
+        else {
+            ahead = {ahead.p + 1, 0, len1};
+            len1 = len2;
+            if (!whole) len2 = cls_len(lens, min(ahead.p + 2, n - 1), max_len);
+        }
+        return ahead;
+    };
 
     // The table rows of this lane's four tokens.  Ids run one chunk ahead of the rows (lane t of every wave holds the id of
     // token t), the rows one chunk ahead of their use; the convolution's history is the neighbouring token group's.
+    // (Every chunk gathers, past the run's end row 0: in a branch the rows would be waited for where it ends, 0.4 us a chunk.)
     float nx[4], nz[4], px[4]; // next rows; this lane's inputs of the chunk before (the last three count)
-    bool bad = false, bad_next = false;
+    bool take[4], bad = false, bad_next = false; // rows of valid tokens
     int idv = 0;
-    auto load_ids = [&](int k) {
-        const int4 e = s_chunk[k];
-        idv = e.y + l16 < e.z ? tokens[(size_t)e.x * max_len + e.y + l16] : 0;
-    };
-    auto gather = [&](int k) {
-        const int4 e = s_chunk[k];
+    auto load_ids = [&](const CqChunk &e) { idv = e.at + l16 < e.len ? tokens[(size_t)e.p * max_len + e.at + l16] : 0; };
+    auto gather = [&](const CqChunk &e) {
         bad_next = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int id = __shfl(idv, 4 * tq + j, 64);
-            const bool live = e.y + 4 * tq + j < e.z, in = (unsigned)id < (unsigned)v.vocab;
+            const bool live = e.at + 4 * tq + j < e.len, in = (unsigned)id < (unsigned)v.vocab;
             bad_next |= live && !in;
+            take[j] = live && in;
             const float *row = v.table + (size_t)(in ? id : 0) * 2 * di + c;
-            const float a = row[0], b = row[di];
-            nx[j] = live && in ? a : 0.f;
-            nz[j] = live && in ? b : 0.f;
+            nx[j] = row[0];
+            nz[j] = row[di];
         }
     };
-    // state and sums of the prompt, or (known false) of its part in this run, with the part's decay product and G
-    float h[4], P[4], Gs[4], pooled = 0.f, pooled_d = 0.f;
-    bool known = true;
-    int closed = 1, closed_bad = 0, prompt = -1, at = 0, len = 0;
+    // state and sums of the prompt, or of the part of the prompt the run starts inside, with its decay product and G
+    float h[4], pooled = 0.f, pooled_d = 0.f;
+    const CqChunk start = cur;
+    const bool head_part = start.at > 0;
+    bool part_bad = false; // an invalid id in the part of the prompt the run starts inside
 #pragma unroll
-    for (int k = 0; k < 4; ++k) h[k] = Gs[k] = px[k] = nx[k] = nz[k] = 0.f, P[k] = 1.f;
-
-    for (int w0 = run0; w0 < run1; w0 += CQ_WIN) {
-        const int nw = min(CQ_WIN, run1 - w0);
-        lds_sync(); // (the window before is done with)
-        for (int p = p_lo, q = first; p < p_hi && q < w0 + nw; ++p) {
-            const int L = cls_len(lens, p, max_len), nc = cls_chunks(L);
-            for (int k = max(q, w0); k < min(q + nc, w0 + nw); ++k) s_chunk[k - w0] = make_int4(p, (k - q) * CQ_TC, L, 0);
-            q += nc;
+    for (int k = 0; k < 4; ++k) h[k] = px[k] = 0.f;
+    if (whole) idv = l16 < cur.len ? own_id : 0;
+    else load_ids(cur);
+    if (head_part) { // the convolution's history of the four tokens before
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int id = tokens[(size_t)cur.p * max_len + cur.at - 4 + j];
+            const bool in = (unsigned)id < (unsigned)v.vocab;
+            const float a = v.table[(size_t)(in ? id : 0) * 2 * di + c];
+            px[j] = in ? a : 0.f;
+        }
+    }
+    gather(cur);
+    const CqChunk none = {0, 0, 0};
+    CqChunk next = run0 + 1 < run1 ? advance() : none, next2 = run0 + 2 < run1 ? advance() : none;
+    load_ids(next);
+    int kc = run0;
+    // One chunk; `each` looks at the decays, delta x silu(z) and C of a token's states after their update.
+    auto chunk = [&](auto each) {
+        const int nt = min(CQ_TC, cur.len - cur.at);
+        bad |= bad_next;
+        // (1) causal depthwise convolution and SiLU
+        float z[4], raw[CLS_MAX_CONV + 3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) nx[j] = take[j] ? nx[j] : 0.f, nz[j] = take[j] ? nz[j] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) raw[j] = __shfl(tq == 3 ? px[j + 1] : nx[j + 1], (lane + 48) & 63, 64);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) raw[3 + j] = px[j] = nx[j];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float pre = cb;
+#pragma unroll
+            for (int j = 0; j < CLS_MAX_CONV; ++j) pre = fmaf(cw[j], raw[t + j], pre);
+            z[t] = nz[t] * __builtin_amdgcn_rcpf(1.f + __expf(-nz[t]));
+            s_x[(4 * tq + t) * sx + c] = pre * __builtin_amdgcn_rcpf(1.f + __expf(-pre));
+        }
+        gather(next); // the next chunk's rows fly while this one is worked on
+        load_ids(next2);
+        lds_sync();
+        // (2) lane (token l % 16, channel l / 16 of four) against (channel, output l % 16); the result leaves tokens
+        // 4 (l / 16) .. + 3 of output l % 16
+        if (proj) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+            const float *xs = s_x + l16 * sx + tq + 4 * k_lo;
+#pragma unroll
+            for (int k = 0; k < per; k += 2) { // (two chains)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k], bw[k], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k + 4], bw[k + 1], acc2, 0, 0, 0);
+            }
+            float *dst = s_part + kq * CQ_TC * CQ_OUT + tq * 4 * CQ_OUT + tile * 16 + l16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[r * CQ_OUT] = acc[r] + acc2[r];
         }
         lds_sync();
-        load_ids(0);
-        if (w0 == run0 && s_chunk[0].y > 0) { // the run starts inside a prompt: the convolution's history of the four tokens before
-            const int4 e = s_chunk[0];
-            known = false;
-            closed = 0;
+        for (int q = tid; q < CQ_TC * CQ_OUT; q += T) {
+            float p = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int id = tokens[(size_t)e.x * max_len + e.y - 4 + j];
-                const bool in = (unsigned)id < (unsigned)v.vocab;
-                const float a = v.table[(size_t)(in ? id : 0) * 2 * di + c];
-                px[j] = in ? a : 0.f;
-            }
+            for (int w = 0; w < nkq; ++w) p += s_part[w * CQ_TC * CQ_OUT + q];
+            s_dbc[q / CQ_OUT * CQ_ROW + q % CQ_OUT] = p;
         }
-        gather(0);
-        if (nw > 1) load_ids(1);
-        for (int kc = 0; kc < nw; ++kc) {
-            const int4 e = s_chunk[kc];
-            prompt = __builtin_amdgcn_readfirstlane(e.x);
-            at = __builtin_amdgcn_readfirstlane(e.y);
-            len = __builtin_amdgcn_readfirstlane(e.z);
-            const int nt = min(CQ_TC, len - at);
-            if (at == 0) {
-                known = true;
-                bad = false;
-                pooled = pooled_d = 0.f;
+        lds_sync();
+        // (2), (1) step sizes
+        f32x4 dt4 = {bdt, bdt, bdt, bdt};
 #pragma unroll
-                for (int k = 0; k < 4; ++k) h[k] = px[k] = 0.f;
-            }
-            bad |= bad_next;
-            // (1) causal depthwise convolution and SiLU
-            float z[4], raw[CLS_MAX_CONV + 3];
+        for (int k = 0; k < 4; ++k) dt4 = __builtin_amdgcn_mfma_f32_16x16x4f32(s_dbc[l16 * CQ_ROW + 4 * k + tq], bd[k], dt4, 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) raw[j] = __shfl(tq == 3 ? px[j + 1] : nx[j + 1], (lane + 48) & 63, 64);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) raw[3 + j] = px[j] = nx[j];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                float pre = cb;
-#pragma unroll
-                for (int j = 0; j < CLS_MAX_CONV; ++j) pre = fmaf(cw[j], raw[t + j], pre);
-                z[t] = nz[t] * __builtin_amdgcn_rcpf(1.f + __expf(-nz[t]));
-                s_x[(4 * tq + t) * sx + c] = pre * __builtin_amdgcn_rcpf(1.f + __expf(-pre));
-            }
-            if (kc + 1 < nw) gather(kc + 1); // the next chunk's rows fly while this one is worked on
-            if (kc + 2 < nw) load_ids(kc + 2);
-            lds_sync();
-            // (2) lane (token l % 16, channel l / 16 of four) against (channel, output l % 16); the result leaves tokens
-            // 4 (l / 16) .. + 3 of output l % 16
-            if (proj) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
-                const float *xs = s_x + l16 * sx + tq + 4 * k_lo;
-#pragma unroll
-                for (int k = 0; k < per; k += 2) { // (two chains)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k], bw[k], acc, 0, 0, 0);
-                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[4 * k + 4], bw[k + 1], acc2, 0, 0, 0);
-                }
-                float *dst = s_part + kq * CQ_TC * CQ_OUT + tq * 4 * CQ_OUT + tile * 16 + l16;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[r * CQ_OUT] = acc[r] + acc2[r];
-            }
-            lds_sync();
-            for (int q = tid; q < CQ_TC * CQ_OUT; q += T) {
-                float p = 0.f;
-#pragma unroll
-                for (int w = 0; w < nkq; ++w) p += s_part[w * CQ_TC * CQ_OUT + q];
-                s_dbc[q / CQ_OUT * CQ_ROW + q % CQ_OUT] = p;
-            }
-            lds_sync();
-            // (2), (1) step sizes
-            f32x4 dt4 = {bdt, bdt, bdt, bdt};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) dt4 = __builtin_amdgcn_mfma_f32_16x16x4f32(s_dbc[l16 * CQ_ROW + 4 * k + tq], bd[k], dt4, 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int row = 4 * tq + t;
-                const float dt = dt4[t];
-                // softplus = log1p(e^dt): log(u) e / (u - 1) with u = 1 + e undoes the rounding of u (steps are ~1e-3..0.1)
-                const float ex = __expf(dt), u = 1.f + ex;
-                const float delta = dt > 20.f ? dt : (u == 1.f ? ex : logf(u) * ex * __builtin_amdgcn_rcpf(u - 1.f));
-                s_delta[row * sx + c] = delta;
-                const float x = s_x[row * sx + c];
-                s_dz[row * sx + c] = make_float2(delta * x, z[t]);
-                if (row < nt) pooled_d = fmaf(x * D, z[t], pooled_d);
-            }
-            lds_sync();
-            // (3) the state update, token by token, in this thread's registers
-            const float *sd = s_delta + cs;
-            const float2 *sz = s_dz + cs;
-            const float *sb = s_dbc + 16 + sub * 4;
-            auto token = [&](int t, auto with_g) {
-                const float delta = sd[t * sx];
-                const float2 dz = sz[t * sx];
-                const float4 B = *(const float4 *)(sb + t * CQ_ROW), C = *(const float4 *)(sb + t * CQ_ROW + 16);
-                float a[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) a[k] = __builtin_amdgcn_exp2f(delta * A[k]);
-                h[0] = fmaf(a[0], h[0], dz.x * B.x);
-                h[1] = fmaf(a[1], h[1], dz.x * B.y);
-                h[2] = fmaf(a[2], h[2], dz.x * B.z);
-                h[3] = fmaf(a[3], h[3], dz.x * B.w);
-                const float acc = fmaf(C.w, h[3], fmaf(C.z, h[2], fmaf(C.y, h[1], C.x * h[0])));
-                pooled = fmaf(acc, dz.y, pooled);
-                if constexpr (decltype(with_g)::value) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) P[k] *= a[k];
-                    Gs[0] = fmaf(C.x * dz.y, P[0], Gs[0]);
-                    Gs[1] = fmaf(C.y * dz.y, P[1], Gs[1]);
-                    Gs[2] = fmaf(C.z * dz.y, P[2], Gs[2]);
-                    Gs[3] = fmaf(C.w * dz.y, P[3], Gs[3]);
-                }
-            };
-            auto update = [&](auto with_g) {
-                int t = 0;
-                for (; t + 4 <= nt; t += 4) { // (four tokens' operands in flight)
-                    token(t, with_g);
-                    token(t + 1, with_g);
-                    token(t + 2, with_g);
-                    token(t + 3, with_g);
-                }
-                for (; t < nt; ++t) token(t, with_g);
-            };
-            if (known) update(std::false_type{}); // (uniform)
-            else update(std::true_type{});
-            if (at + CQ_TC >= len) { // the prompt ends
-                const bool any_bad = __any(bad); // (every wave sees all token ids)
-                if (known) classifier_finish<DI>(v, prompt, len, pooled, pooled_d, any_bad, s_pool, s_mean, s_logit, logits, draft_id);
-                else {
-                    closed = 1;
-                    closed_bad = any_bad;
-                    cq_record(ws + cq_rec_at(blockIdx.x, T) + tid, T, Gs, P, h, pooled, pooled_d);
-                }
-                prompt = -1;
-            }
+        for (int t = 0; t < 4; ++t) {
+            const int row = 4 * tq + t;
+            const float dt = dt4[t];
+            // softplus = log1p(e^dt): log(u) e / (u - 1) with u = 1 + e undoes the rounding of u (steps are ~1e-3..0.1)
+            const float ex = __expf(dt), u = 1.f + ex;
+            const float delta = dt > 20.f ? dt : (u == 1.f ? ex : logf(u) * ex * __builtin_amdgcn_rcpf(u - 1.f));
+            s_delta[row * sx + c] = delta;
+            const float x = s_x[row * sx + c];
+            s_dz[row * sx + c] = make_float2(delta * x, z[t]);
+            if (row < nt) pooled_d = fmaf(x * D, z[t], pooled_d);
         }
+        lds_sync();
+        // (3) the state update, token by token, in this thread's registers
+        const float *sd = s_delta + cs;
+        const float2 *sz = s_dz + cs;
+        const float *sb = s_dbc + 16 + sub * 4;
+        auto token = [&](int t) {
+            const float delta = sd[t * sx];
+            const float2 dz = sz[t * sx];
+            const float4 B = *(const float4 *)(sb + t * CQ_ROW), C = *(const float4 *)(sb + t * CQ_ROW + 16);
+            float a[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[k] = __builtin_amdgcn_exp2f(delta * A[k]);
+            h[0] = fmaf(a[0], h[0], dz.x * B.x);
+            h[1] = fmaf(a[1], h[1], dz.x * B.y);
+            h[2] = fmaf(a[2], h[2], dz.x * B.z);
+            h[3] = fmaf(a[3], h[3], dz.x * B.w);
+            const float acc = fmaf(C.w, h[3], fmaf(C.z, h[2], fmaf(C.y, h[1], C.x * h[0])));
+            pooled = fmaf(acc, dz.y, pooled);
+            each(a, C, dz.y);
+        };
+        int t = 0;
+        for (; t + 4 <= nt; t += 4) { // (four tokens' operands in flight)
+            token(t);
+            token(t + 1);
+            token(t + 2);
+            token(t + 3);
+        }
+        for (; t < nt; ++t) token(t);
+    };
+    auto step = [&]() {
+        ++kc;
+        cur = next;
+        next = next2;
+        next2 = kc + 2 < run1 ? advance() : none;
+    };
+    // The part of a prompt that started in an earlier run (a loop of its own: in one with the other chunks, choosing the update
+    // by a uniform test costs 60 register copies a chunk).
+    if (head_part) {
+        float P[4], G[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) P[k] = 1.f, G[k] = 0.f;
+        bool more = true;
+        while (more) {
+            chunk([&](const float *a, const float4 &C, float z) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) P[k] *= a[k];
+                G[0] = fmaf(C.x * z, P[0], G[0]);
+                G[1] = fmaf(C.y * z, P[1], G[1]);
+                G[2] = fmaf(C.z * z, P[2], G[2]);
+                G[3] = fmaf(C.w * z, P[3], G[3]);
+            });
+            more = cur.at + CQ_TC < cur.len && kc + 1 < run1;
+            step();
+        }
+        part_bad = __any(bad); // (every wave sees all token ids)
+        cq_record(ws + cq_rec_at(nb, blockIdx.x, T) + tid, T, G, P, h, pooled, pooled_d);
     }
-    const bool any_bad = __any(bad), open = prompt >= 0 && known;
-    if (prompt >= 0 && !known) { // the whole run lies inside one prompt
-        closed_bad = any_bad;
-        cq_record(ws + cq_rec_at(blockIdx.x, T) + tid, T, Gs, P, h, pooled, pooled_d);
+    // prompts from their start
+    CqChunk last = start;
+    bool open = false;
+    while (kc < run1) {
+        if (cur.at == 0) {
+            bad = false;
+            pooled = pooled_d = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) h[k] = px[k] = 0.f;
+        }
+        chunk([](const float *, const float4 &, float) {});
+        last = cur;
+        open = cur.at + CQ_TC < cur.len;
+        if (!open) classifier_finish<DI>(v, cur.p, cur.len, pooled, pooled_d, __any(bad), s_pool, s_mean, s_logit, logits, draft_id);
+        step();
     }
+    // parts of cut prompts: the one the run starts inside, and the one it ends in
+    if (!head_part && !open) return; // (uniform)
     if (open) {
         float *o = ws + cq_open_at(nb, blockIdx.x, T) + tid;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o[k * T] = h[k];
-        o[4 * T] = pooled;
-        o[5 * T] = pooled_d;
+        for (int k = 0; k < 4; ++k) put(o + k * T, h[k]);
+        put(o + 4 * T, pooled);
+        put(o + 5 * T, pooled_d);
     }
+    const bool open_bad = __any(bad);
     if (tid == 0) {
-        int *note = (int *)(ws + cq_note_at(nb, blockIdx.x, T));
-        note[CQ_N_CLOSED] = closed;
-        note[CQ_N_BAD] = closed_bad;
-        note[CQ_N_OPEN] = open ? prompt : -1;
-        note[CQ_N_OPEN_BAD] = any_bad;
+        put(ws + cq_bad_at(nb, blockIdx.x, T), part_bad ? 1.f : 0.f);
+        put(ws + cq_bad_at(nb, blockIdx.x, T) + 1, open_bad ? 1.f : 0.f);
     }
-}
-
-// Block b joins the prompt that block b of classifier_run_kernel left open with the records of the blocks behind it.
-template <int DI>
-__global__ void __launch_bounds__(4 * DI, DI / 64)
-classifier_join_kernel(ClsView v, const int32_t *__restrict__ lens, int max_len, float *__restrict__ logits, int32_t *__restrict__ draft_id,
-                       const float *__restrict__ ws)
-{
-    __shared__ float s_pool[4 * DI], s_mean[DI], s_logit[CLS_MAX_CLASSES];
-    constexpr int T = 4 * DI;
-    const int nb = gridDim.x, tid = threadIdx.x;
-    const int *note = (const int *)(ws + cq_note_at(nb, blockIdx.x, T));
-    const int i = note[CQ_N_OPEN];
-    if (i < 0) return;
-    bool bad = note[CQ_N_OPEN_BAD] != 0;
-    float h[4], pooled, pooled_d;
-    const float *o = ws + cq_open_at(nb, blockIdx.x, T) + tid;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) h[k] = o[k * T];
-    pooled = o[4 * T];
-    pooled_d = o[5 * T];
-    for (int b = blockIdx.x + 1; b < nb; ++b) { // (an open prompt goes on in the next block's run and ends in one of them)
-        const int *nt = (const int *)(ws + cq_note_at(nb, b, T));
-        const float *rec = ws + cq_rec_at(b, T) + tid;
-        float G[4], P[4], S[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) G[k] = rec[k * T], P[k] = rec[(4 + k) * T], S[k] = rec[(8 + k) * T];
-        pooled += fmaf(G[3], h[3], fmaf(G[2], h[2], fmaf(G[1], h[1], fmaf(G[0], h[0], rec[12 * T]))));
-        pooled_d += rec[13 * T];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) h[k] = fmaf(P[k], h[k], S[k]);
-        bad |= nt[CQ_N_BAD] != 0;
-        if (nt[CQ_N_CLOSED]) break;
+    // (first and last blocks of the prompts: chunk numbers over the run's length)
+    const int head_chunk = run0 - start.at / CQ_TC, tail_chunk = run1 - 1 - last.at / CQ_TC;
+    const int head_b0 = head_chunk / run, head_b1 = (head_chunk + cls_chunks(start.len) - 1) / run;
+    const int tail_b1 = (tail_chunk + cls_chunks(last.len) - 1) / run;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every wave's stores have arrived
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long *arrivals = (unsigned long long *)ws;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        s_last[0] = head_part && cq_arrive(arrivals + head_b0, tag, head_b1 - head_b0 + 1);
+        s_last[1] = open && cq_arrive(arrivals + blockIdx.x, tag, tail_b1 - (int)blockIdx.x + 1);
+        if (s_last[0] || s_last[1]) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    classifier_finish<DI>(v, i, cls_len(lens, i, max_len), pooled, pooled_d, bad, s_pool, s_mean, s_logit, logits, draft_id);
+    __syncthreads();
+    if (s_last[0]) cq_join<DI>(v, start.p, start.len, head_b0, head_b1, nb, ws, s_pool, s_mean, s_logit, logits, draft_id);
+    if (s_last[1]) cq_join<DI>(v, last.p, last.len, blockIdx.x, tail_b1, nb, ws, s_pool, s_mean, s_logit, logits, draft_id);
 }
 
 // ---------------------------------------------------------------- C ABI
@@ -998,7 +1054,19 @@ extern "C" int64_t sd_classifier_workspace(const sd_classifier *c, int32_t n, in
 {
     if (!c || n < 1 || max_len < 1) return sd_fail(SD_EINVAL, "sd_classifier_workspace: null classifier or non-positive size");
     const int nb = cq_blocks(c, n, max_len);
-    return nb ? (int64_t)cq_note_at(nb, nb, 4 * c->v.d_inner) * (int64_t)sizeof(float) : 0;
+    return nb ? (int64_t)cq_bad_at(nb, nb, 4 * c->v.d_inner) * (int64_t)sizeof(float) + 4 : 0; // (4: to align the arrivals)
+}
+
+// A number of 48 bits (in the upper ones) that no other call's has but by chance: the workspace of a call may hold what any
+// other has left there.
+static unsigned long long cq_call_tag()
+{
+    static std::atomic<unsigned long long> calls{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
+    unsigned long long x = calls.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull; // (Weyl sequence, mixed as in splitmix64)
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    x = (x ^ (x >> 31)) & ~0xffffull;
+    return x ? x : 1ull << 63;
 }
 
 static int route_classifier(const char *who, const sd_classifier *c, const int32_t *tokens, const int32_t *lens, int32_t n,
@@ -1021,13 +1089,11 @@ static int route_classifier(const char *who, const sd_classifier *c, const int32
                                (hipStream_t)stream, c->v, tokens, lens, max_len, logits, draft_id);                           \
         else {                                                                                                                \
             hipLaunchKernelGGL(classifier_run_kernel<DI>, dim3(nb), dim3(4 * DI), 0, (hipStream_t)stream, c->v, tokens, lens, \
-                               n, max_len, logits, draft_id, ws);                                                             \
-            if (join)                                                                                                         \
-                hipLaunchKernelGGL(classifier_join_kernel<DI>, dim3(nb), dim3(4 * DI), 0, (hipStream_t)stream, c->v, lens,    \
-                                   max_len, logits, draft_id, ws);                                                            \
+                               n, max_len, logits, draft_id, ws, tag);                                                        \
         }                                                                                                                     \
     } while (0)
-    const bool join = max_len > CQ_TC; // (no run starts inside a prompt of one chunk)
+    ws = (float *)(((uintptr_t)ws + 7) & ~(uintptr_t)7);
+    const unsigned long long tag = nb ? cq_call_tag() : 0;
     if (c->v.d_inner == 64) SD_QUAD(64);
     else if (c->v.d_inner == 128) SD_QUAD(128);
     else if (c->v.d_inner == 192) SD_QUAD(192);

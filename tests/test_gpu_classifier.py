@@ -149,6 +149,27 @@ def test_runs_of_chunks_that_cut_prompts(d_inner, n, max_len):
     assert np.abs(logits3 - logits).max() <= LOGIT_RTOL * np.abs(logits).max()   # (both paths within the bar of the oracle)
 
 
+@pytest.mark.parametrize("d_inner,n,lo,hi", [(192, 250, 50, 70), (128, 200, 60, 64), (64, 256, 1, 17), (192, 31, 33, 40)])
+def test_batches_of_nearly_equal_lengths_are_not_cut(d_inner, n, lo, hi):
+    """Lengths within a chunk of each other on up to 256 workgroups: a workgroup per prompt in the call with a workspace too, so the
+    logits do not depend on the batch bit for bit; an empty prompt and an invalid last id among them."""
+    print(f"classifier uncut d_inner={d_inner} n={n} of {lo} to {hi}", flush=True)
+    shape = dg.ClassifierShape("classifier_uncut", vocab=97, d_model=24, d_inner=d_inner, d_state=16, dt_rank=6, d_conv=4, n_classes=5)
+    w = dg.make_classifier(shape, 45)
+    rng = dg._rng(45, 67)
+    tokens = rng.integers(0, shape.vocab, size=(n, hi), dtype=np.int32)
+    lens = rng.integers(lo, hi + 1, size=n).astype(np.int32)
+    lens[3], lens[4], lens[n - 1] = 0, hi, hi
+    tokens[4, hi - 1] = -5
+    ids, logits = _run(shape, w, tokens, lens)
+    assert np.flatnonzero(ids == -1).tolist() == [4]
+    some = [0, 1, 2, 3, 5, n // 2, n - 1]
+    _check(shape, w, tokens[some], lens[some], ids[some], logits[some])
+    perm = np.random.default_rng(2).permutation(n)
+    ids2, logits2 = _run(shape, w, tokens[perm], lens[perm])
+    assert np.array_equal(ids[perm], ids2) and np.array_equal(logits[perm], logits2)
+
+
 @pytest.mark.parametrize("d_inner", [64, 192])
 def test_an_invalid_id_in_any_part_of_a_cut_prompt_is_flagged(d_inner):
     """Three prompts of 1300 to 2000 tokens over some 200 workgroups (runs of two chunks): an id out of range in the part a prompt
