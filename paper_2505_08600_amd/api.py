@@ -441,11 +441,13 @@ class Classifier:
         self.h = h
 
     def route(self, tokens: torch.Tensor, lens: torch.Tensor, draft_id: torch.Tensor,
-              logits: Optional[torch.Tensor] = None) -> None:
-        """sd_route_classifier_ws on the current stream; tokens int32 [n][max_len], lens int32 [n].  The workspace is the caching
-        allocator's, in order with that stream; without memory for it the call runs as sd_route_classifier."""
+              logits: Optional[torch.Tensor] = None, batch_invariant: bool = False) -> None:
+        """sd_route_classifier_ws on the current stream; tokens int32 [n][max_len], lens int32 [n].  The workspace (up to 15.7 MB) is
+        the caching allocator's, in order with that stream; without memory for it the call runs as sd_route_classifier.
+        Where the tokens are dealt out, a prompt's logits depend on the lengths of the others in the batch by rounding, and a tie
+        within that can go either way; batch_invariant=True runs sd_route_classifier, whose logits are the same bits in any batch."""
         with torch.cuda.device(self.device):
-            need = lib().sd_classifier_workspace(self.h, tokens.shape[0], tokens.shape[1])
+            need = 0 if batch_invariant else lib().sd_classifier_workspace(self.h, tokens.shape[0], tokens.shape[1])
             try:
                 ws = torch.empty(need, dtype=torch.uint8, device=tokens.device) if need > 0 else None
             except torch.OutOfMemoryError:  # (a block per prompt needs none)

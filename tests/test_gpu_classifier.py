@@ -22,14 +22,14 @@ ONE_TAP = dataclasses.replace(dg.CLASSIFIER_TINY, name="classifier_one_tap", d_c
                               n_classes=1)
 
 
-def _run(shape, weights, tokens, lens, want_logits=True):
+def _run(shape, weights, tokens, lens, want_logits=True, **options):
     cls = api.Classifier(shape, weights)
     n = tokens.shape[0]
     t = torch.from_numpy(tokens).cuda()
     l = torch.from_numpy(lens).cuda()
     ids = torch.full((n,), -7, dtype=torch.int32, device="cuda")
     logits = torch.full((n, shape.n_classes), float("nan"), device="cuda") if want_logits else None
-    cls.route(t, l, ids, logits)
+    cls.route(t, l, ids, logits, **options)
     torch.cuda.synchronize()
     cls.close()
     return ids.cpu().numpy(), (logits.cpu().numpy() if want_logits else None)
@@ -96,6 +96,27 @@ def test_padding_is_ignored_and_batch_position_does_not_matter():
     perm = np.random.default_rng(0).permutation(16)
     ids2, logits2 = _run(shape, w, junk[perm], lens[perm])
     assert np.array_equal(ids[perm], ids2) and np.array_equal(logits[perm], logits2)
+
+
+@pytest.mark.parametrize("d_inner", [64, 192])
+def test_batch_invariant_logits_are_the_same_bits_in_any_batch(d_inner):
+    """60 prompts of up to 300 tokens, which the default call cuts: with batch_invariant a prompt's logits do not change with the
+    order of the batch or with who else is in it; without it they agree to the stated bar."""
+    shape = dg.ClassifierShape("classifier_invariant", vocab=97, d_model=24, d_inner=d_inner, d_state=16, dt_rank=6, d_conv=4, n_classes=5)
+    w = dg.make_classifier(shape, 49)
+    rng = dg._rng(49, 71)
+    n, max_len = 60, 300
+    tokens = rng.integers(0, shape.vocab, size=(n, max_len), dtype=np.int32)
+    lens = rng.integers(0, max_len + 1, size=n).astype(np.int32)
+    ids, logits = _run(shape, w, tokens, lens, batch_invariant=True)
+    perm = np.random.default_rng(3).permutation(n)
+    ids2, logits2 = _run(shape, w, tokens[perm], lens[perm], batch_invariant=True)
+    assert np.array_equal(ids[perm], ids2) and np.array_equal(logits[perm], logits2)
+    for part in (slice(0, 1), slice(7, 9), slice(20, 60)):
+        ids3, logits3 = _run(shape, w, tokens[part], lens[part], batch_invariant=True)
+        assert np.array_equal(ids[part], ids3) and np.array_equal(logits[part], logits3)
+    _, cut = _run(shape, w, tokens, lens)
+    assert np.abs(cut - logits).max() <= LOGIT_RTOL * np.abs(logits).max()
 
 
 @pytest.mark.parametrize("d_inner,n,max_len", [(192, 1, 700), (192, 400, 128), (128, 300, 60), (64, 40, 200), (192, 30, 33), (192, 6000, 80), (192, 520, 16), (64, 3, 2000)])
