@@ -2022,7 +2022,7 @@ __global__ __launch_bounds__(RT) void draft_sample_fast_kernel(const float *logi
 // A row's vocabulary is cut into slices of DS_SLICE columns, one 256-thread block each.  Every block reads all
 // the row's partials (a few KB) and derives from them, in the same order and therefore to the same bits as
 // every other block of the row: the row maximum, the mass of every slice (one wave-wide sum of the slice's 64
-// entries), the normaliser Z (the slice masses added in order) and the slice in which the running sum first
+// entries), the normaliser Z (a lane scan of the slice masses) and the slice in which the running sum first
 // exceeds u * Z.  It then writes its own slice of q = exp((x - max) / T) / Z, and the one block that owns the
 // slice holding u * Z places the candidate inside it with a block-wide scan (same rule as block_pick_cdf:
 // first index whose inclusive sum exceeds the target, else the last index of positive weight).  No block waits
@@ -2378,8 +2378,8 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // argmax entries, which sampling does not use.  A block keeps two batches of 4 float4 per thread, one in flight while the
 // other is summed.
 // The statistics pass is bound by instruction issue as much as by memory: with expf (13 instructions an element beside the
-// subtraction and the maximum) 576 rows of 128000 columns take 64 us, with three (WideExp) 56, and then the nontemporal
-// hint pays (49 us, 6.0 TB/s).
+// subtraction and the maximum) 576 rows of 128000 columns take 64 us, with three (WideExp) and the nontemporal hint, which
+// then pays, 54 (5.5 TB/s; under the profiler).
 // The hint, whole call at T = 1 without / with it (1024 threads), the same logits in every call | three sets of logits in turn:
 // 270 rows of 128000 columns, gamma 8 50.0 / 53.4 | 55.7 / 53.7; 360 rows 52.5 / 57.9 | 61.8 / 58.5; 576 rows 79.5 / 77.6 | 87.8 / 77.6;
 // 1350 rows of 33000 50.5 / 54.7 | 56.5 / 54.8: what the memory-side cache (256 MB) still holds from the call before it gives
