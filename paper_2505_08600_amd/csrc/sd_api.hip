@@ -865,6 +865,11 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     // (1 / temperature, 0 for greedy) for the sampler that follows, where the LM-head kernel can.  more: another forward of
     // the same call follows (nothing can look at this one's buffers).
     const sd_model_config &cf = m->cfg;
+    // A forward without logits is there for its cache rows: of its last layer nothing behind the cache append is read by
+    // anyone, so attention, projections and FFN of that layer are left out - one layer in n_layers of a prefill, less its
+    // QKV projection (two layers of the 7B shape, 8192 tokens at 1024 rows: 15.06 -> 9.5 ms, 32 layers: a 34th of the whole).
+    // The last forward of a call keeps them for fp32 models, whose buffers sd_debug_read promises.
+    const bool cache_only = !want_logits && (more || cf.dtype == SD_BF16);
     const int n_slots = n_seq * G; // plan slots: what the attention kernels see as sequences
     const int M = n_slots * R, d = cf.d_model, H = cf.n_heads, hd = cf.head_dim, F = cf.d_ffn, V = cf.vocab;
     if (G < 1 || (G > 1 && mode != PLAN_CATCHUP)) return sd_fail(SD_EINVAL, "forward: row groups are for prefill only");
@@ -949,6 +954,11 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             FWD(launch_lora_delta(s, cf.dtype, m->abuf, avd, M, d, d, 3, pv, cv.adapter + (size_t)slot * cv.B, m->lora_n,
                                   m->lora_rank, m->lora_scale, A3, B3, dst, qkv_in_place ? 1 : 0));
             if (!qkv_in_place) nq_slabs++;
+        }
+        if (cache_only && l + 1 == cf.n_layers) { ProfScope ps(T_ROPE, s);
+            FWD(launch_rope_append(s, cf.dtype, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, M, R, H, hd, m->rope,
+                                   cf.max_pos, m->qbuf, avd, Kl, Vtl, c->total_cap));
+            break;
         }
         hipError_t ea = hipErrorNotSupported;
         int oproj_done = 0; // the attention blocks applied the output projection themselves: H slabs in gpart_r

@@ -1871,3 +1871,32 @@ def test_last_logits_keep_their_place_between_forwards():
         graph.replay()
         assert torch.equal(m.last_logits(), ref[i])
     m.close()
+
+
+@pytest.mark.parametrize("shape_name,tol", [("tiny_target", 1e-4), ("small_target_bf16", 2e-2), ("small_draft_bf16", 2e-2)])
+@pytest.mark.parametrize("layers", [1, 2])
+@pytest.mark.parametrize("max_rows,lens", [(8, [37]), (24, [50, 9]), (32, [16, 33]), (64, [70, 18]), (16, [2])])
+def test_prefill_that_stops_at_the_last_layers_cache_matches_oracle(shape_name, tol, layers, max_rows, lens):
+    """A prefill leaves out what follows the cache append in its last layer - the only layer, or the second of two: rows of
+    a few sequences per slot (8 rows: the split norm's GEMMs; 12 rows), one 16-row group per sequence, two groups, a single
+    row.  The caches must give the oracle's logits in the verify pass that follows."""
+    _say(f"prefill up to the last cache append, {shape_name}, {layers} layers, workspace {max_rows} rows, prompts {lens}")
+    st_ = dg.with_layers(dg.SHAPES[shape_name], layers)
+    w = dg.make_weights(st_, 83, BF16_LM_SCALE if st_.dtype == dg.BF16 else 1.0)
+    om, gm = oracle.OracleModel(st_, w), api.Model(st_, w, max_rows=max_rows, max_pos=max(lens) + 64)
+    B, gamma, V = len(lens), 2, st_.vocab
+    prompts = [[int(t) for t in dg.make_prompt(83, b, n, V)] for b, n in enumerate(lens)]
+    ctx = api.Context([n + 16 for n in lens])
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    cand = dg.make_prompt(84, 0, B * gamma, V).reshape(B, gamma).astype(np.int32)
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_verify(gm, ctx, None, B, gamma, 0.0, H.dev(cand), None, None, na, nx, commit=False)
+    lg = gm.last_logits().cpu().numpy().reshape(B, gamma + 1, V)
+    for b in range(B):
+        seq = om.new_seq(lens[b] + 16)
+        oracle.prefill(seq, prompts[b])
+        r_lg = seq.verify(prompts[b], gamma, 0.0, cand[b], None, np.zeros(gamma + 1, np.float32), want_logits=True)[3]
+        assert np.abs(lg[b] - r_lg).max() < tol * np.abs(r_lg).max(), b
+    ctx.close()
+    gm.close()
