@@ -2388,8 +2388,8 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // 2000 rows of 33000 189 / 206 | 198 / 212; 600 rows of 128000 (307 MB) 220.6 / 218.7 | 229.1 / 228.2: the hint above 256
 // MB.  512 threads without it where there are rows enough to put two blocks on every compute unit (540 x 33000: 31.3, 1024
 // threads with the hint 34.2).
-// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 76 us (101 with expf, the acceptance test in the
-// second launch and a pick that read its slice twice).
+// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 71 us (76 in blocks of 1024 threads, 101 with expf,
+// the acceptance test in the second launch and a pick that read its slice twice).
 // e^(d / T), d <= 0, as 2^(c d + r d): c = log2(e) / T rounded down, r >= 0 what that leaves of it (the two-constant reduction
 // of Cody and Waite, in base 2).  r > 0 and bounded by c: -inf stays -inf through both products and gives 0, d = 0 gives 1
 // at any T.  Error of a row's sum against 64 bits, rms over 300 rows of N(0, 2), 128000 columns, T = 1 / 1.1 / 1.3 / 2: expf
@@ -2842,8 +2842,16 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
 #define SD_STATS_WIDE(RT, NT)                                                                                             \
     hipLaunchKernelGGL((verify_stats_wide_kernel<RT, NT>), dim3(n_rows), dim3(RT), 0, s, logits, gamma, V, T, cand, q, u, stats)
     // (128 MB of logits; 256 MB where they are read again)
-    if ((size_t)n_rows * V > ((size_t)1 << (T > 0.f && gamma == 0 ? 26 : 25))) SD_STATS_WIDE(1024, true);
-    else if (n_rows >= 512) SD_STATS_WIDE(512, false);
+    // Blocks of 1024 threads put two rows on a compute unit, so a little more than one row or two rows a unit leaves most of
+    // the chip waiting for the few units with another: 257 to 511 rows go in blocks of 512 threads, 513 to 767 in blocks of
+    // 256, all resident at once.  Whole call, T = 0.7, 1024 / 512 / 256 threads (us): 270 rows of 128000 columns 53.2 / 48.8 /
+    // 57.7, of 262144 91.5 / 81.1 / 95.7; 360 rows of 262144 94.9 / 90.0 / 99.5; 576 rows of 128000 74.4 / 77.2 / 70.7, of 262144 133 /
+    // 136 / 122; 800 rows of 128000 104.3 / 103.9 / 104.2; 1350 rows of 128000 139 / 138 / 144.
+    if ((size_t)n_rows * V > ((size_t)1 << (T > 0.f && gamma == 0 ? 26 : 25))) {
+        if (n_rows > 256 && n_rows < 512) SD_STATS_WIDE(512, true);
+        else if (n_rows > 512 && n_rows < 768) SD_STATS_WIDE(256, true);
+        else SD_STATS_WIDE(1024, true);
+    } else if (n_rows >= 512) SD_STATS_WIDE(512, false);
     else SD_STATS_WIDE(1024, false);
     if (T > 0.f) {
         if (gamma > 0)

@@ -484,3 +484,22 @@ def test_stream_read_probe_reads_every_word_exactly_once(nt):
             assert int(word.item()) == 0
     finally:
         api.set_option("stream_read_nt", 1)
+
+
+@pytest.mark.parametrize("rows,V", [(257, 131076), (511, 66004), (512, 66004), (513, 66004), (767, 44004), (768, 44004)])
+def test_wide_greedy_rows_at_the_edges_of_each_block_shape(rows, V):
+    """More than 128 MB of logits, row counts on both sides of the block shapes' limits: the first of equal maxima is taken, also
+    where they lie in different threads, waves and loads of a row, in its first and its last vector."""
+    print(f"wide greedy rows={rows} V={V}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn((rows, 1, V), device="cuda", generator=g)
+    at = torch.randint(0, V, (rows, 3), device="cuda", generator=g)
+    at[0, 0], at[1, :], at[2, 0] = 0, V - 1, 1023
+    x[:, 0].scatter_(1, at, 9.0)
+    x[3, 0] = -1.0e30
+    na, nx = (torch.full((rows,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.full((3 * rows,), float("nan"), device="cuda")
+    api.sd_accept(x, 0, 0.0, None, None, None, na, nx, ws)
+    expect = at.min(dim=1).values
+    expect[3] = 0
+    assert (na == 0).all() and (nx.long() == expect).all()
