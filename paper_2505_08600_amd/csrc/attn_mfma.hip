@@ -519,14 +519,38 @@ struct OProj {
     size_t slab_stride; // rows * d_model
     int32_t d_model;
 };
-template <int HD, int WAVES, bool NT_HINT, bool OPROJ, bool HELP>
-__global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *__restrict__ qkv, int n_slabs,
+// SPLIT (long contexts, few pairs): S blocks per pair, each with T consecutive tiles of it (a shorter sequence's last blocks have
+// none and leave at once).  A block rotates the query rows for itself, appends the new rows that fall into its tiles - so no
+// block reads cache rows another one writes - and leaves (O, max, sum) of its tiles in `part`; the block of a pair that
+// arrives last, by a counter, merges the parts in order.  No block waits for another.  The parts cross the dies' L2s: they
+// are written and read with agent-scope accesses, and a block counts itself only after its stores have been acknowledged
+// (a release fence would write back everything that is dirty in the die's L2, several microseconds).  The last block clears the
+// counter, so a launch finds it as it was at the start.
+struct AttnSplit {
+    float *part;       // [pair][S][16 * (HD + 2)]: O [q][HD], then (max, sum) [q]
+    int32_t *arrivals; // [pair], 0 between launches
+    int32_t S, T;
+};
+__device__ __forceinline__ void store_agent(float *p, float a, float b)
+{
+    const uint64_t v = (uint64_t)__float_as_uint(b) << 32 | __float_as_uint(a);
+    __hip_atomic_store((uint64_t *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_agent(const float *p)
+{
+    const uint64_t v = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+template <int HD, int WAVES, bool NT_HINT, bool OPROJ, bool HELP, bool SPLIT>
+__global__ __launch_bounds__(WAVES * 64, SPLIT && HD == 64 ? 4 : 2) void attn_fused_kernel(const float *__restrict__ qkv, int n_slabs,
                                                                    size_t slab_stride, PlanView pv, CtxView cv, int R,
                                                                    int H, const float2 *__restrict__ rope, int max_pos,
                                                                    uint16_t *__restrict__ Kl, uint16_t *__restrict__ Vtl,
                                                                    int64_t total_cap, uint16_t *__restrict__ obuf,
-                                                                   ActView o_av, OProj op, int n_seq, int n_pad, int n_help)
+                                                                   ActView o_av, OProj op, int n_seq, int n_pad, int n_help,
+                                                                   AttnSplit sp)
 {
+    static_assert(!SPLIT || (!OPROJ && !HELP), "a pair's blocks share nothing but its counter");
     constexpr int ND = HD / 16;
     constexpr int HALF = HD / 2;
     __shared__ float sO[WAVES][ND][64][4];
@@ -547,6 +571,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
     const int Lk = kv0 + nq;
     const int64_t off = cv.off[pv.seq_b[j]];
     const int HDm = H * HD;
+    const int n_tiles = nq > 0 ? (Lk + AT_TILE - 1) / AT_TILE : 0;
+    // (T follows from the longest sequence the host knows of; one that a replayed graph has let grow beyond it takes more)
+    const int T = SPLIT ? max(sp.T, (n_tiles + sp.S - 1) / sp.S) : 1, split = SPLIT ? (int)blockIdx.z : 0;
+    const int n_split = SPLIT ? max(1, (n_tiles + T - 1) / T) : 1;
+    if (SPLIT && split >= n_split) return; // (uniform)
+    const int t_begin = SPLIT ? split * T : 0, t_end = SPLIT ? min(n_tiles, t_begin + T) : n_tiles;
     uint16_t *K = Kl + ((size_t)h * total_cap + off) * HD;
     uint16_t *Vt = Vtl + ((size_t)h * total_cap + off) * HD; // this sequence's first 32-token tile
     // ---- prologue: slabs -> q, k, v of this head; RoPE; append
@@ -556,6 +586,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
             const int row = j * R + (r < R ? r : 0);
             const int pos = kv0 + r;
             bool valid = r < nq && pos < max_pos;
+            const bool mine = !SPLIT || ((pos >> 5) >= t_begin && (pos >> 5) < t_end); // this block appends the row
             if (r < nq && pos >= max_pos && e == 0) atomicOr(cv.status, 8);
             float q0 = 0.f, q1 = 0.f, k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
             if (valid) {
@@ -567,30 +598,36 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
                         const float *rs = base + (size_t)sl * slab_stride;
                         ld[sl][0] = rs[0];
                         ld[sl][1] = rs[HALF];
-                        ld[sl][2] = rs[HDm];
-                        ld[sl][3] = rs[HDm + HALF];
-                        ld[sl][4] = rs[2 * HDm];
-                        ld[sl][5] = rs[2 * HDm + HALF];
+                        if (!SPLIT || mine) {
+                            ld[sl][2] = rs[HDm];
+                            ld[sl][3] = rs[HDm + HALF];
+                            ld[sl][4] = rs[2 * HDm];
+                            ld[sl][5] = rs[2 * HDm + HALF];
+                        }
                     }
 #pragma unroll
                 for (int sl = 0; sl < 8; sl++)
                     if (sl < n_slabs) {
                         q0 += ld[sl][0];
                         q1 += ld[sl][1];
-                        k0 += ld[sl][2];
-                        k1 += ld[sl][3];
-                        v0 += ld[sl][4];
-                        v1 += ld[sl][5];
+                        if (!SPLIT || mine) {
+                            k0 += ld[sl][2];
+                            k1 += ld[sl][3];
+                            v0 += ld[sl][4];
+                            v1 += ld[sl][5];
+                        }
                     }
                 const float2 cs = rope[(size_t)pos * HALF + e];
                 const float qa = q0 * cs.x - q1 * cs.y, qb = q1 * cs.x + q0 * cs.y;
                 const float ka = k0 * cs.x - k1 * cs.y, kb = k1 * cs.x + k0 * cs.y;
                 q0 = qa;
                 q1 = qb;
-                K[kt_offset(HD, pos, e)] = bf16_bits_rne(ka);
-                K[kt_offset(HD, pos, e + HALF)] = bf16_bits_rne(kb);
-                Vt[vt_offset(HD, pos, e)] = bf16_bits_rne(v0);
-                Vt[vt_offset(HD, pos, e + HALF)] = bf16_bits_rne(v1);
+                if (mine) {
+                    K[kt_offset(HD, pos, e)] = bf16_bits_rne(ka);
+                    K[kt_offset(HD, pos, e + HALF)] = bf16_bits_rne(kb);
+                    Vt[vt_offset(HD, pos, e)] = bf16_bits_rne(v0);
+                    Vt[vt_offset(HD, pos, e + HALF)] = bf16_bits_rne(v1);
+                }
             }
             const uint16_t h0 = bf16_bits_rne(q0), h1 = bf16_bits_rne(q1);
             sQ[0][r][e] = h0;
@@ -603,13 +640,12 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
     // the Q^T operand stays in LDS: lane (q, grp) reads Q[q][32*c + 8*grp .. +8] per tile
     const bf16x8 *qv = (const bf16x8 *)(&sQ[0][qi][grp * 8]);
     const bf16x8 *ql = (const bf16x8 *)(&sQ[1][qi][grp * 8]);
-    const int n_tiles = nq > 0 ? (Lk + AT_TILE - 1) / AT_TILE : 0;
     const int vis = kv0 + qi;
     float m_run = AT_NEG, l_run = 0.f;
     f32x4 o[ND];
 #pragma unroll
     for (int d = 0; d < ND; d++) o[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    attn_tiles<HD, NT_HINT, true>(K, Vt, total_cap, qv, ql, vis, wave, n_tiles, WAVES, m_run, l_run, o);
+    attn_tiles<HD, NT_HINT, true>(K, Vt, total_cap, qv, ql, vis, t_begin + wave, t_end, WAVES, m_run, l_run, o);
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
     // OPROJ: this wave's 16-column tiles of the projection are wave, wave + WAVES, ...; their weight fragments
@@ -657,6 +693,15 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
             O += p * f;
             L += sL[w][q] * f;
         }
+        if (SPLIT && n_split > 1) { // (uniform)
+            if (q < nq) {
+                float *pp = sp.part + ((size_t)(j * H + h) * sp.S + split) * 16 * (HD + 2);
+                store_agent(pp + q * HD + dim, O[0], O[1]);
+                store_agent(pp + q * HD + dim + 2, O[2], O[3]);
+                if (dim == 0) store_agent(pp + 16 * HD + 2 * q, M, L);
+            }
+            continue;
+        }
         const bool live = q < nq && L > 0.f;
         float out[4];
 #pragma unroll
@@ -669,6 +714,61 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
             *(uint2 *)&sQ[1][q][dim] = make_uint2(l0, l1);
         } else {
             const size_t oi = act_index(o_av, j * R + q, h * HD + dim, HDm); // 4 columns inside one K step
+            *(uint2 *)(obuf + oi) = make_uint2(h0, h1);
+            *(uint2 *)(obuf + oi + o_av.plane) = make_uint2(l0, l1);
+        }
+    }
+    if (SPLIT && n_split > 1) { // (uniform)
+        __shared__ int s_last;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70); // this wave's parts have reached memory ...
+        __syncthreads();                    // ... and every wave's
+        if (threadIdx.x == 0) {
+            const int n = __hip_atomic_fetch_add(sp.arrivals + j * H + h, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = n == n_split - 1;
+            if (n == n_split - 1) __hip_atomic_store(sp.arrivals + j * H + h, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (!s_last) return;
+        constexpr int MB = 4; // parts requested at a time
+        const float *base = sp.part + (size_t)(j * H + h) * sp.S * 16 * (HD + 2);
+        for (int e = threadIdx.x; e < R * (HD / 4); e += WAVES * 64) {
+            const int q = e / (HD / 4), dim = e % (HD / 4) * 4;
+            float M = AT_NEG, L = 0.f;
+            f32x4 O = {0.f, 0.f, 0.f, 0.f};
+            if (q < nq) {
+                for (int s0 = 0; s0 < n_split; s0 += MB) {
+                    float2 a[MB], b[MB], ml[MB];
+#pragma unroll
+                    for (int k = 0; k < MB; k++) {
+                        const float *pp = base + (size_t)min(s0 + k, n_split - 1) * 16 * (HD + 2);
+                        a[k] = load_agent(pp + q * HD + dim);
+                        b[k] = load_agent(pp + q * HD + dim + 2);
+                        ml[k] = load_agent(pp + 16 * HD + 2 * q);
+                    }
+                    float m_new = M;
+#pragma unroll
+                    for (int k = 0; k < MB; k++) m_new = fmaxf(m_new, ml[k].x); // (a part read twice changes no maximum)
+                    const float corr = __builtin_amdgcn_exp2f(M - m_new);
+                    O *= corr;
+                    L *= corr;
+                    M = m_new;
+#pragma unroll
+                    for (int k = 0; k < MB; k++) {
+                        const float f = s0 + k < n_split ? __builtin_amdgcn_exp2f(ml[k].x - M) : 0.f;
+                        O += (f32x4){a[k].x, a[k].y, b[k].x, b[k].y} * f;
+                        L += ml[k].y * f;
+                    }
+                }
+            }
+            const bool live = q < nq && L > 0.f;
+            float out[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) out[r] = live ? O[r] / L : 0.f;
+            uint32_t h0, l0, h1, l1;
+            bf16x2_split(out[0], out[1], h0, l0);
+            bf16x2_split(out[2], out[3], h1, l1);
+            const size_t oi = act_index(o_av, j * R + q, h * HD + dim, HDm);
             *(uint2 *)(obuf + oi) = make_uint2(h0, h1);
             *(uint2 *)(obuf + oi + o_av.plane) = make_uint2(l0, l1);
         }
@@ -696,13 +796,14 @@ __global__ __launch_bounds__(WAVES * 64, 2) void attn_fused_kernel(const float *
 }
 
 int g_force_attn_waves = 0;
+int g_force_attn_split = 0;
 
 // Returns hipErrorNotSupported when the split path (RoPE kernel + split attention + combine) should run.
 hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                                   CtxView cv, int R, int n_seq, int H, int hd, const float2 *rope, int max_pos,
                                   void *Kl, void *Vtl, int64_t total_cap, int len_upper, void *obuf, ActView o_av,
-                                  int stream_nt, const void *wo_tiled, int d_model, float *oslab, size_t oslab_floats,
-                                  int *oproj_done)
+                                  int stream_nt, float *part, size_t part_floats, int32_t *arrivals, const void *wo_tiled,
+                                  int d_model, float *oslab, size_t oslab_floats, int *oproj_done)
 {
     if (oproj_done) *oproj_done = 0;
     if (R < 1 || R > 16 || (hd != 64 && hd != 128) || n_slabs < 1 || n_slabs > 8) return hipErrorNotSupported;
@@ -713,6 +814,29 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     // only stream, is faster even with its RoPE and combine launches (32 x 2048 tokens, 40 heads: 20.1 against
     // 20.4 ms for the whole verify pass; 64 sequences of 1024 - 8192 tokens: 38.0 against 38.6; at 32 sequences of
     // up to 1024 tokens the fused kernel wins, 8.26 against 8.50 ms)
+    const AttnSplit none = {nullptr, nullptr, 1, 1};
+    {
+        const long pairs = (long)n_seq * H;
+        const int fit = (int)std::max(1L, std::min(8L, 256 / pairs));
+        int S = 1;
+        if (g_force_attn_split) S = g_force_attn_split;
+        else if (g_force_attn_waves) S = 1;
+        else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
+        else if (tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
+        if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {
+            const AttnSplit sp = {part, arrivals, S, (tiles_upper + S - 1) / S};
+#define SD_FUSED_SPLIT(HD_, NT_)                                                                                              \
+    hipLaunchKernelGGL((attn_fused_kernel<HD_, 8, NT_, false, false, true>), dim3(H, n_seq, S), dim3(512), 0, s, qkv, n_slabs, \
+                       slab_stride, pv, cv, R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, \
+                       o_av, OProj{nullptr, nullptr, 0, 0}, n_seq, 1, 0, sp)
+            if (hd == 128 && stream_nt) SD_FUSED_SPLIT(128, true);
+            else if (hd == 128) SD_FUSED_SPLIT(128, false);
+            else if (stream_nt) SD_FUSED_SPLIT(64, true);
+            else SD_FUSED_SPLIT(64, false);
+#undef SD_FUSED_SPLIT
+            return hipGetLastError();
+        }
+    }
     if (!(tiles_upper <= 48 || ((long)n_seq * H >= 512 && tiles_upper < 64))) return hipErrorNotSupported;
     // with more than two blocks per compute unit and short contexts the 4-wave shape (two resident blocks
     // per unit) hides each block's prologue and merge behind its neighbour's streaming; from about 40 tiles
@@ -741,24 +865,24 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     const OProj op = {(const uint16_t *)wo_tiled, oslab, rows * (size_t)d_model, d_model};
     if (oproj) {
         if (hd == 128)
-            hipLaunchKernelGGL((attn_fused_kernel<128, 8, false, true, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
-                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);
+            hipLaunchKernelGGL((attn_fused_kernel<128, 8, false, true, false, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
+                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help, none);
         else
-            hipLaunchKernelGGL((attn_fused_kernel<64, 8, false, true, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
-                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);
+            hipLaunchKernelGGL((attn_fused_kernel<64, 8, false, true, false, false>), grid, block, 0, s, qkv, n_slabs, slab_stride, pv, cv,
+                               R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap, (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help, none);
         if (oproj_done) *oproj_done = 1;
         return hipGetLastError();
     }
 #define SD_FUSED(HD_, WAVES_, HELP_)                                                                                          \
     do {                                                                                                               \
         if (stream_nt)                                                                                                 \
-            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, true, false, HELP_>), grid, block, 0, s, qkv, n_slabs,         \
+            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, true, false, HELP_, false>), grid, block, 0, s, qkv, n_slabs,         \
                                slab_stride, pv, cv, R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap,   \
-                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);                                                            \
+                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help, none);                                                            \
         else                                                                                                           \
-            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, false, false, false>), grid, block, 0, s, qkv, n_slabs,        \
+            hipLaunchKernelGGL((attn_fused_kernel<HD_, WAVES_, false, false, false, false>), grid, block, 0, s, qkv, n_slabs,        \
                                slab_stride, pv, cv, R, H, rope, max_pos, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap,   \
-                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help);                                                            \
+                               (uint16_t *)obuf, o_av, op, n_seq, n_pad, n_help, none);                                                            \
     } while (0)
     if (hd == 128) {
         if (many) SD_FUSED(128, 4, false);

@@ -141,6 +141,11 @@ extern "C" int sd_set_option(const char *name, int32_t value)
         g_force_attn_waves = value;
         return SD_OK;
     }
+    if (!strcmp(name, "attn_split")) { // blocks per (sequence, head) of the fused attention kernel: 1 .. 32, or 0 = automatic
+        if (value < 0 || value > SD_ATTN_MAX_SPLITS) return sd_fail(SD_EINVAL, "sd_set_option: attn_split is 0 .. 32");
+        g_force_attn_split = value;
+        return SD_OK;
+    }
     if (!strcmp(name, "stream_read_nt")) { // pattern of sd_debug_stream_read: 1 = contiguous ranges, nontemporal hint (default);
                                            // 0 = grid-strided; + 2 = checking mode (XOR of every word read is folded into the scratch word)
         if (value < 0 || value > 3) return sd_fail(SD_EINVAL, "sd_set_option: stream_read_nt is 0..3");
@@ -325,6 +330,8 @@ extern "C" int sd_load_model(const sd_model_config *cfg, const sd_weights *w, sd
     alloc((void **)&m->gpart_r, m->gpart_r_floats * 4);
     alloc((void **)&m->rope, (size_t)c.max_pos * (c.head_dim / 2) * sizeof(float2));
     alloc((void **)&m->plan_mem, (5 * M + 4 * M) * sizeof(int32_t));
+    alloc((void **)&m->arrivals, SD_ATTN_MAX_PAIRS * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(m->arrivals, 0, SD_ATTN_MAX_PAIRS * sizeof(int32_t));
     if (e != hipSuccess) {
         sd_free_model(m);
         return sd_fail(SD_EHIP, std::string("sd_load_model: hipMalloc: ") + hipGetErrorString(e));
@@ -373,6 +380,7 @@ extern "C" int sd_free_model(sd_model *m)
     (void)hipFree(m->gpart_r);
     (void)hipFree(m->rope);
     (void)hipFree(m->plan_mem);
+    (void)hipFree(m->arrivals);
     (void)hipFree(m->wmem);
     (void)hipFree(m->lora_mem);
     delete m;
@@ -968,8 +976,8 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             ProfScope ps(T_ATTN, s);
             const bool try_oproj = !fold && !lora_o && m->tiled_dd && !(g_force_generic & (1 | 8));
             ea = launch_attn_fused_bf16(s, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, R, n_seq, H, hd, m->rope,
-                                        cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt,
-                                        try_oproj ? m->wo[l] : nullptr, d, m->gpart_r, m->gpart_r_floats, &oproj_done);
+                                        cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt, m->part,
+                                        m->part_floats, m->arrivals, try_oproj ? m->wo[l] : nullptr, d, m->gpart_r, m->gpart_r_floats, &oproj_done);
             if (ea == hipErrorNotSupported) ps.drop();
         }
         if (cf.dtype == SD_FP32 && G == 1 && nq_slabs == 1 && !(g_force_generic & (1 | 2))) {

@@ -11,6 +11,7 @@
 #define SD_MAX_SLOTS 8
 #define SD_MAX_GAMMA 15
 #define SD_ATTN_MAX_SPLITS 32
+#define SD_ATTN_MAX_PAIRS 1024 // (sequence, head) pairs whose blocks may meet over a counter
 #define SD_MIN_INV_T 1.4e-45f // 1 / T at T = inf (see inv_temperature)
 
 // ---------------------------------------------------------------- element types
@@ -303,6 +304,7 @@ struct sd_model {
     float *lm_stats; // [max_rows][vocab / 32][3] per-block softmax partials of the last LM head (see LmStats)
     int lm_stats_nb; // blocks per row the last forward's LM head left there (0: none)
     float *part;    // split-KV partial results of the attention kernel
+    int32_t *arrivals; // [SD_ATTN_MAX_PAIRS] blocks of a (sequence, head) pair that have left their part (0 between launches)
     float *gpart_q, *gpart_r; // split-K partial slabs of the weight-streaming GEMMs (QKV; O / down)
     size_t gpart_q_floats, gpart_r_floats;
     size_t part_floats;
@@ -366,6 +368,7 @@ extern int g_force_tile_cols;  // 96-row GEMM block width forced by option "gemm
 extern int g_rope_group;       // option "rope_group": RoPE + cache append one block per (head, row group) for bf16 models (1, default)
 extern int g_prefill_attn;     // option "prefill_attn": the prefill attention kernel (1, default) or the split kernel per group (0)
 extern int g_force_attn_waves; // fused attention block shape forced by option "attn_waves" (0 = automatic)
+extern int g_force_attn_split; // option "attn_split": blocks per (sequence, head) of the fused attention kernel (0 = automatic, 1 = one)
 extern int g_stream_read_nt;   // sd_debug_stream_read: 1 = contiguous ranges with the nontemporal hint, 0 = grid-strided ordinary loads
 extern int g_force_splits[3]; // per GEMM mode: K splits forced by option "gemm_splits" (0 = automatic)
 
@@ -448,7 +451,8 @@ hipError_t launch_add_rmsnorm(hipStream_t s, int dtype, float *x, const float *p
 hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                                   CtxView cv, int R, int n_seq, int H, int hd, const float2 *rope, int max_pos,
                                   void *Kl, void *Vtl, int64_t total_cap, int len_upper, void *obuf, ActView o_av,
-                                  int stream_nt, const void *wo_tiled = nullptr, int d_model = 0, float *oslab = nullptr,
+                                  int stream_nt, float *part, size_t part_floats, int32_t *arrivals,
+                                  const void *wo_tiled = nullptr, int d_model = 0, float *oslab = nullptr,
                                   size_t oslab_floats = 0, int *oproj_done = nullptr);
 hipError_t launch_attn_mfma_bf16(hipStream_t s, const void *qbuf, ActView q_av, const void *Kl, const void *Vtl,
                                  PlanView pv, CtxView cv, int R, int n_seq, int H, int hd, int64_t total_cap,

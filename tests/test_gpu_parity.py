@@ -1900,3 +1900,72 @@ def test_prefill_that_stops_at_the_last_layers_cache_matches_oracle(shape_name, 
         assert np.abs(lg[b] - r_lg).max() < tol * np.abs(r_lg).max(), b
     ctx.close()
     gm.close()
+
+
+@pytest.mark.parametrize("shape_name", ["small_target_bf16", "small_draft_bf16"])
+@pytest.mark.parametrize("S", [2, 3, 8, 32])
+def test_attention_split_over_blocks_matches_one_block_per_pair(shape_name, S):
+    """Option attn_split: S blocks per (sequence, head) whose last one merges the parts, against one block (attn_split = 1): two
+    committing passes over ragged sequences - one token, new rows that start and end on both sides of a tile and of a
+    block's share, fewer tiles than blocks - the same decisions and logits to 2e-4 as for the kernels' other orders; the
+    same bits in a second run (parts are merged in order, the counters are back at 0).  Then a captured pass, replayed on
+    sequences that have outgrown what the host knew at the capture."""
+    _say(f"{shape_name}: attention split over {S} blocks")
+    st_ = dg.SHAPES[shape_name]
+    w = dg.make_weights(st_, 91, BF16_LM_SCALE)
+    lens, gamma, V = [1, 30, 33, 64, 96, 127, 290, 701], 4, st_.vocab
+    B = len(lens)
+    gm = api.Model(st_, w, max_rows=128, max_pos=800)
+    prompts = [[int(t) for t in dg.make_prompt(91, b, n, V)] for b, n in enumerate(lens)]
+    cand = [H.dev(dg.make_prompt(92 + k, 0, B * gamma, V).reshape(B, gamma).astype(np.int32)) for k in range(2)]
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+
+    def passes(split):
+        api.set_option("attn_split", split)
+        try:
+            ctx = api.Context([n + 16 for n in lens])
+            ctx.attach(gm)
+            H.gpu_prefill(ctx, [gm], prompts)
+            out = []
+            for k in range(2):
+                api.sd_verify(gm, ctx, None, B, gamma, 0.0, cand[k], None, None, na, nx, commit=True)
+                out += [gm.last_logits().cpu().numpy(), na.cpu().numpy().copy(), nx.cpu().numpy().copy()]
+            ctx.sync()
+            ctx.close()
+            return out
+        finally:
+            api.set_option("attn_split", 0)
+
+    one, got, again = passes(1), passes(S), passes(S)
+    for k in (0, 3):
+        assert np.isfinite(got[k]).all() and np.abs(got[k] - one[k]).max() < 2e-4 * np.abs(one[k]).max()
+        assert all(np.array_equal(got[k + i], one[k + i]) for i in (1, 2))
+    assert all(np.array_equal(a, b) for a, b in zip(got, again))
+
+    def verify(ctx):
+        api.sd_verify(gm, ctx, None, 1, gamma, 0.0, cand[0], None, None, na, nx, commit=False)
+
+    ctx = api.Context([720])
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], [prompts[1]])
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    api.set_option("attn_split", S)
+    try:
+        with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+            verify(ctx)
+        H.gpu_prefill(ctx, [gm], [prompts[7]])
+        api.set_option("attn_split", 1)
+        verify(ctx)
+        ref = gm.last_logits().cpu().numpy()
+        for _ in range(3):
+            ctx.truncate(gm, 0, lens[7] - 1)
+            graph.replay()
+            torch.cuda.synchronize()
+            lg = gm.last_logits().cpu().numpy()
+            assert np.abs(lg - ref).max() < 2e-4 * np.abs(ref).max()
+    finally:
+        api.set_option("attn_split", 0)
+    ctx.sync()
+    ctx.close()
+    gm.close()
