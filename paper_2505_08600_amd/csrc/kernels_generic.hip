@@ -2897,6 +2897,25 @@ hipError_t launch_route(hipStream_t s, const float *W, const float *b, int n_dra
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- new sequences
+__global__ __launch_bounds__(256) void set_tokens_kernel(CtxView cv, const int32_t *staged, int n)
+{
+    const int32_t *entry = staged + 3 * (size_t)blockIdx.x;
+    const int b = entry[0], len = entry[1];
+    const int32_t *src = staged + 3 * (size_t)n + entry[2];
+    int32_t *dst = cv.tokens + cv.off[b];
+    for (int i = threadIdx.x; i < len; i += 256) dst[i] = src[i];
+    if (threadIdx.x < SD_MAX_SLOTS) cv.kvlen[(size_t)threadIdx.x * cv.B + b] = 0;
+    if (threadIdx.x < 2) cv.pol[(size_t)threadIdx.x * cv.B + b] = 0; // a new sequence starts without acceptance history
+    if (threadIdx.x == 0) cv.ntok[b] = len;
+}
+
+hipError_t launch_set_tokens(hipStream_t s, CtxView cv, const int32_t *staged, int n)
+{
+    hipLaunchKernelGGL(set_tokens_kernel, dim3(n), dim3(256), 0, s, cv, staged, n);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- synthetic cache load
 template <typename T>
 __global__ void set_kv_kernel(const T *k_rows, const T *v_rows, int len, int H, int hd, int64_t seq_off,

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -328,6 +329,8 @@ struct sd_ctx {
     int64_t *d_off;
     int32_t *d_cap, *d_tokens, *d_ntok, *d_kvlen, *d_status, *d_adapter;
     int32_t *d_gamma, *d_policy; // per-sequence candidate counts [B] (used when use_gamma) and accepted / examined [2][B]
+    int32_t *d_staging; // [total_cap + 3 B] where sd_ctx_set_tokens uploads to
+    std::mutex staging_lock;
     int use_gamma;
     int n_slots;
     sd_model *models[SD_MAX_SLOTS];
@@ -421,6 +424,9 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
                          const int32_t *cand, const int32_t *n_acc, const int32_t *next_tok);
 hipError_t launch_route(hipStream_t s, const float *W, const float *b, int n_drafts, int emb, const float *e, int n,
                         int32_t *id);
+// Replaces the tokens of n sequences and forgets their caches and acceptance history: staged = n entries (sequence, length, offset of its
+// tokens behind the entries), then the tokens.
+hipError_t launch_set_tokens(hipStream_t s, CtxView cv, const int32_t *staged, int n);
 hipError_t launch_set_kv(hipStream_t s, int dtype, const void *k_rows, const void *v_rows, int len, int H, int hd,
                          int64_t seq_off, int64_t total_cap, void *Kl, void *Vtl);
 

@@ -1969,3 +1969,30 @@ def test_attention_split_over_blocks_matches_one_block_per_pair(shape_name, S):
     ctx.sync()
     ctx.close()
     gm.close()
+
+
+def test_set_tokens_sets_what_is_named_and_nothing_else():
+    """Sequences of 1 token, a whole capacity, 255 to 257 tokens, out of order and named twice (the last one counts); one that
+    is refused ends the call behind those in front of it; the others keep their tokens."""
+    _say("set_tokens")
+    rng = np.random.default_rng(3)
+    seq = lambda n: rng.integers(0, 1 << 30, n).astype(np.int32)
+    ctx = api.Context([64, 128, 320, 320, 320, 64])
+    want = [seq(n) for n in (1, 128, 255, 256, 257, 64)]
+    ctx.set_tokens(want)
+    ids, new = [4, 0, 2, 4], [seq(320), seq(64), seq(1), seq(3)]
+    ctx.set_tokens(new, ids)
+    for b, t in zip(ids, new):
+        want[b] = t
+    new = [seq(9), seq(7), seq(11), seq(2)]
+    for ids in ([3, 6, 1, 0], [3, -1, 1, 0]):
+        with pytest.raises(api.SdError):
+            ctx.set_tokens(new, ids)
+    want[3] = new[0]
+    with pytest.raises(api.SdError):
+        ctx.set_tokens([seq(4), seq(65)], [1, 5])
+    n, _ = ctx.sync()
+    assert n.tolist() == [len(t) for t in want[:1]] + [4] + [len(t) for t in want[2:]]
+    for b in (0, 2, 3, 4, 5):
+        assert np.array_equal(ctx.get_tokens(b), want[b]), b
+    ctx.close()
