@@ -26,6 +26,7 @@
 //
 // Paper (arXiv 2505.08600): Section 1, Figure 1 (draft steps and the parallel
 // verify pass whose linear layers these are); Section 3.1 (LLaMA blocks).
+#include "lora.h"
 #include "sd_internal.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -529,15 +530,22 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_ksplit_kernel(const uint16_t 
 // used.  Measured at M = 24, 7B shape, weights from HBM (before: gemm_ksplit_kernel; us): QKV 27.3 -> 20.3, O 11.1 -> 9,
 // gate/up 50.0 -> 36.3, down 24.3 -> 19.0, LM head 66.3 -> 46.7; at M = 64 (before: gemm_tile_kernel in 48-row blocks)
 // 36.4 -> 29.4, 15.1 -> 12.7, 61.2 -> 53.1, 28.5 -> 25.5, 67.4 -> 63.7, and a 768-wide QKV 10.5 -> 5.0.
+// LORA: the blocks behind the first n_cols columns of the grid take the low-rank update of the same rows (a block per row,
+// projection and part), which would otherwise be a launch of 4.7 us between this one and its consumer.
 #define WIDE_WAVES 4
-template <int NMAT, int MT, int NW, bool NT_HINT>
+template <int NMAT, int MT, int NW, bool NT_HINT, bool LORA>
 __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16_t *__restrict__ A, ActView a_av, WeightSeg w, int M,
                                                                int N, int K, int steps_per_split, float *__restrict__ C,
                                                                size_t c_split_stride, uint16_t *__restrict__ Cact, ActView c_av,
-                                                               LmStats ls)
+                                                               LmStats ls, int n_cols, LoraArgs la)
 {
     constexpr int WAVES = WIDE_WAVES;
     static_assert(NW % 2 == 0, "tiles are finished in pairs");
+    if (LORA && (int)blockIdx.x >= n_cols) { // (uniform)
+        const int id = ((int)blockIdx.x - n_cols) * gridDim.y + blockIdx.y, r = id % M, p = id / M % la.n_proj, part = id / M / la.n_proj;
+        if (part * lora_part(WAVES) < la.N) lora_block<bf16_t, -1, WAVES>((const bf16_t *)A, a_av, K, la, r, p, part);
+        return;
+    }
     __shared__ f32x4 red[WAVES][NW][MT][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
@@ -830,11 +838,24 @@ static hipError_t tile_launch(hipStream_t s, const uint16_t *a, ActView a_av, We
 
 template <int NMAT, int MT, bool NT>
 static void wide_launch_nw(hipStream_t s, WidePlan p, const uint16_t *a, ActView a_av, WeightSeg w, int M, int N, int K, int sps,
-                           float *C, size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls)
+                           float *C, size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls, const LoraArgs *la)
 {
-    const dim3 grid(p.ncol, p.ks), block(WIDE_WAVES * 64);
+    dim3 grid(p.ncol, p.ks);
+    const dim3 block(WIDE_WAVES * 64);
+    if constexpr (NMAT == 1 && !NT) {
+        if (la) {
+            const int parts = (la->N + lora_part(WIDE_WAVES) - 1) / lora_part(WIDE_WAVES);
+            grid.x += (M * la->n_proj * parts + p.ks - 1) / p.ks;
+#define SD_WIDE_LORA(NW_)                                                                                                     \
+    hipLaunchKernelGGL((gemm_wide_kernel<NMAT, MT, NW_, NT, true>), grid, block, 0, s, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls, p.ncol, *la)
+            if (p.nw == 2) SD_WIDE_LORA(2);
+            else SD_WIDE_LORA(4);
+#undef SD_WIDE_LORA
+            return;
+        }
+    }
 #define SD_WIDE(NW_)                                                                                                          \
-    hipLaunchKernelGGL((gemm_wide_kernel<NMAT, MT, NW_, NT>), grid, block, 0, s, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls)
+    hipLaunchKernelGGL((gemm_wide_kernel<NMAT, MT, NW_, NT, false>), grid, block, 0, s, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls, p.ncol, LoraArgs{})
     if (p.nw == 2) SD_WIDE(2);
     else if (p.nw == 4) SD_WIDE(4);
     else if (p.nw == 6) SD_WIDE(6);
@@ -843,15 +864,15 @@ static void wide_launch_nw(hipStream_t s, WidePlan p, const uint16_t *a, ActView
 }
 template <int NMAT>
 static hipError_t wide_launch(hipStream_t s, WidePlan p, const uint16_t *a, ActView a_av, WeightSeg w, int M, int N, int K, float *C,
-                              size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls)
+                              size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls, const LoraArgs *la = nullptr)
 {
     int kps, ny;
     split_geometry(K, p.ks, &kps, &ny);
     const int mt = (M + 15) / 16, sps = kps / 128;
 #define SD_WIDE_MT(MT_)                                                                                                   \
     do {                                                                                                                  \
-        if (w.nt) wide_launch_nw<NMAT, MT_, true>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls);        \
-        else wide_launch_nw<NMAT, MT_, false>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls);            \
+        if (w.nt) wide_launch_nw<NMAT, MT_, true>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls, la);        \
+        else wide_launch_nw<NMAT, MT_, false>(s, p, a, a_av, w, M, N, K, sps, C, c_split_stride, ca, c_av, ls, la);            \
     } while (0)
     if (mt == 1) SD_WIDE_MT(1);
     else if (mt == 2) SD_WIDE_MT(2);
@@ -925,9 +946,10 @@ int gemm_normfold_blocks(int N) { return N % 32 == 0 && N / 32 >= 256 ? N / 32 :
 // store into partial slabs followed by the fused add + norm kernel.
 hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActView a_av, WeightSeg w, int M, int N,
                                    int K, float *C, size_t c_split_stride, int splits, void *Cact, ActView c_av,
-                                   LmStats ls, int *ls_done, NormFold nf)
+                                   LmStats ls, int *ls_done, NormFold nf, const LoraArgs *lora, int *lora_done)
 {
     if (ls_done) *ls_done = 0;
+    if (lora_done) *lora_done = 0;
     const LmStats no_ls = {nullptr, 0.f};
     const bool folded = nf.ss_in || nf.x || nf.row_map;
     if (folded && (M > 32 || nf.ss_nb > SD_NORMFOLD_MAX_BLOCKS)) return hipErrorNotSupported;
@@ -948,7 +970,10 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
             const LmStats lsk = mode == GEMM_STORE && wp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
             if (ls_done && lsk.p) *ls_done = 1;
             if (mode == GEMM_SWIGLU) return wide_launch<2>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
-            return wide_launch<1>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
+            // (weights that stay cached - the instances of the kernel that carry an update are for those - in blocks of two or four tiles, as the projections of small models run)
+            const bool carry = lora && lora_done && !w.nt && wp.nw <= 4 && lora_valid(M, K, *lora);
+            if (carry) *lora_done = 1;
+            return wide_launch<1>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk, carry ? lora : nullptr);
         }
     }
     if (M > 32) { // row-blocked

@@ -5,6 +5,7 @@
 //
 // Paper (arXiv 2505.08600): Section 1 / Figure 1 (draft rows, verify rows),
 // Section 3.1 (LLaMA blocks; speculative-sampling verification, greedy limit).
+#include "lora.h"
 #include "sd_internal.h"
 #include <algorithm>
 
@@ -881,122 +882,39 @@ hipError_t launch_add_rmsnorm(hipStream_t s, int dtype, float *x, const float *p
 }
 
 // ---------------------------------------------------------------- low-rank adapters
-// Block (row, projection, part of LORA_PART outputs).  Bound: latency - a row reads 2 * rank * (K + N) floats of factors
-// per projection (49 KB at rank 8, width 768) and multiplies each once - so the block is laid out to have everything in
-// flight at once: the rows of B that its threads will need go out first, then wave w takes the dot products
-// w, w + LORA_WAVES, ... with A, row of X and row of A straight into registers, and one barrier later every thread
-// finishes its outputs from registers.  A grid dimension per projection puts three times the blocks on the chip.
-// RQ = rank / 4 reads the rows of B (rank contiguous floats) as 16-byte vectors; 0 takes any rank, element by element.
 // Measured at width 768, rank 8: 4.6 us for 32 or 64 rows and one or three projections (18.9 us with one block of 256
 // threads per row, all projections in it, the factors fetched after the dot products); below that the launch itself remains.
-#define LORA_MAX_RANK 16
-#define LORA_MAX_K 8192
-#define LORA_WAVES 8
-#define LORA_OUT 2 // outputs per thread
-#define LORA_PART (LORA_OUT * LORA_WAVES * 64)
-struct LoraPtrs {
-    const float *a[3], *b[3];
-};
-__device__ __forceinline__ float4 load_act4(const float *b, size_t i, size_t) { return *(const float4 *)(b + i); }
-__device__ __forceinline__ float4 load_act4(const bf16_t *b, size_t i, size_t plane)
-{
-    const uint2 h = *(const uint2 *)(b + i), l = *(const uint2 *)(b + i + plane);
-    return make_float4(__uint_as_float(h.x << 16) + __uint_as_float(l.x << 16),
-                       __uint_as_float(h.x & 0xffff0000u) + __uint_as_float(l.x & 0xffff0000u),
-                       __uint_as_float(h.y << 16) + __uint_as_float(l.y << 16),
-                       __uint_as_float(h.y & 0xffff0000u) + __uint_as_float(l.y & 0xffff0000u));
-}
 template <typename T, int RQ>
-__global__ __launch_bounds__(LORA_WAVES * 64) void lora_delta_kernel(const T *X, ActView x_av, int K, int N, int n_proj, PlanView pv,
-                                                                     const int32_t *adapter, int n_adapters, int rank, float scale,
-                                                                     LoraPtrs lp, float *out, int accumulate)
+__global__ __launch_bounds__(LORA_WAVES * 64) void lora_delta_kernel(const T *X, ActView x_av, int K, LoraArgs la)
 {
-    constexpr int THREADS = LORA_WAVES * 64, NB = RQ > 0 ? RQ * 4 : LORA_MAX_RANK;
-    __shared__ float st[LORA_MAX_RANK];
-    const int r = blockIdx.x, p = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float *Ap = p == 0 ? lp.a[0] : p == 1 ? lp.a[1] : lp.a[2], *Bp = p == 0 ? lp.b[0] : p == 1 ? lp.b[1] : lp.b[2];
-    const int valid = pv.row_valid[r];
-    int a = adapter[pv.row_b[r]]; // (row_b of an unused row is in range too)
-    if (!valid || a >= n_adapters) a = -1;
-    float *orow = out + (size_t)r * n_proj * N + (size_t)p * N;
-    const int n0 = blockIdx.z * LORA_PART + threadIdx.x;
-    if (a < 0 || !Ap || !Bp) { // (uniform) no update for this row and projection
-        if (!accumulate) {
-#pragma unroll
-            for (int o = 0; o < LORA_OUT; o++)
-                if (n0 + o * THREADS < N) orow[n0 + o * THREADS] = 0.f;
-        }
-        return;
-    }
-    float bv[LORA_OUT][NB], old[LORA_OUT];
-#pragma unroll
-    for (int o = 0; o < LORA_OUT; o++) {
-        const int n = min(n0 + o * THREADS, N - 1); // (outputs past the end re-read the last one; never stored)
-        old[o] = accumulate ? orow[n] : 0.f;
-        const float *brow = Bp + ((size_t)a * N + n) * rank;
-        if (RQ > 0) {
-#pragma unroll
-            for (int i = 0; i < RQ; i++) {
-                const float4 v = *(const float4 *)(brow + 4 * i);
-                bv[o][4 * i] = v.x, bv[o][4 * i + 1] = v.y, bv[o][4 * i + 2] = v.z, bv[o][4 * i + 3] = v.w;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NB; i++) bv[o][i] = i < rank ? brow[i] : 0.f;
-        }
-    }
-    for (int j = wave; j < rank; j += LORA_WAVES) {
-        const float *arow = Ap + ((size_t)a * rank + j) * K;
-        float acc = 0.f;
-#pragma unroll 4
-        for (int k = 4 * lane; k < K; k += 256) { // 16 bytes per lane and load (K is a multiple of 4)
-            const float4 xv = load_act4(X, act_index(x_av, r, k, K), x_av.plane), av = *(const float4 *)(arow + k);
-            acc += av.x * xv.x + av.y * xv.y + av.z * xv.z + av.w * xv.w;
-        }
-        acc = wave_sum_dpp(acc);
-        if (lane == 0) st[j] = acc;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int o = 0; o < LORA_OUT; o++) {
-        float acc = 0.f;
-#pragma unroll
-        for (int i = 0; i < NB; i++)
-            if (RQ > 0 || i < rank) acc += bv[o][i] * st[i];
-        if (n0 + o * THREADS < N) orow[n0 + o * THREADS] = old[o] + scale * acc;
-    }
+    lora_block<T, RQ, LORA_WAVES>(X, x_av, K, la, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <typename T>
-static hipError_t lora_launch(hipStream_t s, const T *X, ActView x_av, int M, int K, int N, int n_proj, PlanView pv, const int32_t *adapter,
-                              int n_adapters, int rank, float scale, LoraPtrs lp, float *out, int accumulate)
+static hipError_t lora_launch(hipStream_t s, const T *X, ActView x_av, int M, int K, const LoraArgs &la)
 {
-    bool vec = rank % 4 == 0;
-    for (int p = 0; p < n_proj; p++)
-        if ((uintptr_t)lp.b[p] & 15) vec = false;
-    const dim3 grid(M, n_proj, (N + LORA_PART - 1) / LORA_PART), block(LORA_WAVES * 64);
-#define SD_LORA(RQ_) \
-    hipLaunchKernelGGL((lora_delta_kernel<T, RQ_>), grid, block, 0, s, X, x_av, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate)
+    const bool vec = la.rank % 4 == 0 && !(((uintptr_t)la.b0 | (uintptr_t)la.b1 | (uintptr_t)la.b2) & 15);
+    const dim3 grid(M, la.n_proj, (la.N + lora_part(LORA_WAVES) - 1) / lora_part(LORA_WAVES)), block(LORA_WAVES * 64);
+#define SD_LORA(RQ_) hipLaunchKernelGGL((lora_delta_kernel<T, RQ_>), grid, block, 0, s, X, x_av, K, la)
     if (!vec) SD_LORA(0);
-    else if (rank == 4) SD_LORA(1);
-    else if (rank == 8) SD_LORA(2);
-    else if (rank == 12) SD_LORA(3);
+    else if (la.rank == 4) SD_LORA(1);
+    else if (la.rank == 8) SD_LORA(2);
+    else if (la.rank == 12) SD_LORA(3);
     else SD_LORA(4);
 #undef SD_LORA
     return hipGetLastError();
 }
 
-hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_av, int M, int K, int N, int n_proj,
-                             PlanView pv, const int32_t *adapter, int n_adapters, int rank, float scale,
-                             const float *const *A, const float *const *B, float *out, int accumulate)
+bool lora_valid(int M, int K, const LoraArgs &la)
 {
-    if (M < 1 || K < 4 || (K & 3) || K > LORA_MAX_K || n_proj < 1 || n_proj > 3 || rank < 1 || rank > LORA_MAX_RANK || !adapter)
-        return hipErrorInvalidValue;
-    LoraPtrs lp;
-    for (int p = 0; p < 3; p++) lp.a[p] = p < n_proj ? A[p] : nullptr, lp.b[p] = p < n_proj ? B[p] : nullptr;
-    if (dtype == SD_BF16)
-        return lora_launch(s, (const bf16_t *)X, x_av, M, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate);
-    return lora_launch(s, (const float *)X, x_av, M, K, N, n_proj, pv, adapter, n_adapters, rank, scale, lp, out, accumulate);
+    return M >= 1 && K >= 4 && !(K & 3) && K <= LORA_MAX_K && la.n_proj >= 1 && la.n_proj <= 3 && la.rank >= 1 && la.rank <= LORA_MAX_RANK &&
+           la.adapter;
+}
+hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_av, int M, int K, const LoraArgs &la)
+{
+    if (!lora_valid(M, K, la)) return hipErrorInvalidValue;
+    if (dtype == SD_BF16) return lora_launch(s, (const bf16_t *)X, x_av, M, K, la);
+    return lora_launch(s, (const float *)X, x_av, M, K, la);
 }
 
 template <typename T>

@@ -850,17 +850,21 @@ extern "C" int32_t sd_debug_gemm_splits(int32_t m, int32_t n, int32_t k, int32_t
 static const NormFold kNoFold = {nullptr, 0, 0.f, nullptr, nullptr, nullptr, nullptr};
 static int stream_gemm(sd_model *m, hipStream_t s, const void *A, ActView a_av, WeightSeg w, int M, int N, int K,
                        float *slabs, size_t slabs_floats, int force_splits, hipError_t *err, int extra_slabs = 0,
-                       LmStats ls = {nullptr, 0.f}, int *ls_done = nullptr, NormFold nf = kNoFold)
+                       LmStats ls = {nullptr, 0.f}, int *ls_done = nullptr, NormFold nf = kNoFold, LoraArgs *lora = nullptr,
+                       int *lora_done = nullptr)
 {
+    // (lora: its update becomes the slab behind the product's)
     if (ls_done) *ls_done = 0;
+    if (lora_done) *lora_done = 0;
     *err = hipSuccess;
     if (m->cfg.dtype != SD_BF16 || (g_force_generic & 1)) return 0;
     int ns = force_splits > 0 ? force_splits : stream_splits(M, N, K, w.n_per_seg, nf.ss_in || nf.x || nf.row_map, extra_slabs);
     if ((size_t)(ns + extra_slabs) * M * N > slabs_floats) ns = 1;
     if ((size_t)(ns + extra_slabs) * M * N > slabs_floats) return 0;
     const ActView none = {0, 0, 0};
+    if (lora) lora->out = slabs + (size_t)ns * M * N, lora->accumulate = 0;
     hipError_t e = launch_gemm_skinny_bf16(s, GEMM_STORE, A, a_av, w, M, N, K, slabs, (size_t)M * N, ns, nullptr, none,
-                                           ls, ls_done, nf);
+                                           ls, ls_done, nf, lora, lora_done);
     if (e == hipErrorNotSupported) return 0;
     *err = e;
     return ns;
@@ -959,14 +963,25 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         // slab for the consumer to add - or is added in place where the GEMM left a single full result
         const bool lora_qkv = m->lora_n > 0 && (m->lora_a[0][l] || m->lora_a[1][l] || m->lora_a[2][l]);
         const bool lora_o = m->lora_n > 0 && m->lora_a[3][l];
+        auto lora_args = [&](int first, int n) { // the update of n projections of this layer
+            LoraArgs la = {};
+            la.a0 = m->lora_a[first][l], la.b0 = m->lora_b[first][l];
+            if (n == 3) la.a1 = m->lora_a[first + 1][l], la.b1 = m->lora_b[first + 1][l], la.a2 = m->lora_a[first + 2][l], la.b2 = m->lora_b[first + 2][l];
+            la.row_valid = pv.row_valid, la.row_b = pv.row_b, la.adapter = cv.adapter + (size_t)slot * cv.B;
+            la.N = d, la.n_proj = n, la.n_adapters = m->lora_n, la.rank = m->lora_rank, la.scale = m->lora_scale;
+            return la;
+        };
+        LoraArgs la_qkv = lora_qkv ? lora_args(0, 3) : LoraArgs{}, la_o = lora_o ? lora_args(3, 1) : LoraArgs{};
+        int lora_done = 0;
         bool qkv_in_place = qkv_done;
         if (qkv_done) {
             nq_slabs = 1;
             qkv_src = m->qkv;
         } else { ProfScope ps(T_QKV, s);
         nq_slabs = stream_gemm(m, s, m->abuf, avd, wqkv, M, 3 * d, d, m->gpart_q, m->gpart_q_floats, 0, &ge, lora_qkv ? 1 : 0,
-                               LmStats{nullptr, 0.f}, nullptr, a_scaled ? nf_consume : kNoFold);
+                               LmStats{nullptr, 0.f}, nullptr, a_scaled ? nf_consume : kNoFold, lora_qkv ? &la_qkv : nullptr, &lora_done);
         FWD(ge);
+        if (lora_done) nq_slabs++;
         qkv_src = m->gpart_q;
         if (!nq_slabs && fold) return sd_fail(SD_EHIP, "forward: QKV shape left the few-row kernels under the split norm");
         if (!nq_slabs) {
@@ -975,12 +990,10 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             qkv_src = m->qkv;
             qkv_in_place = true;
         } }
-        if (lora_qkv) { ProfScope ps(T_LORA, s);
-            const float *A3[3] = {m->lora_a[0][l], m->lora_a[1][l], m->lora_a[2][l]};
-            const float *B3[3] = {m->lora_b[0][l], m->lora_b[1][l], m->lora_b[2][l]};
-            float *dst = qkv_in_place ? m->qkv : m->gpart_q + (size_t)nq_slabs * M * 3 * d;
-            FWD(launch_lora_delta(s, cf.dtype, m->abuf, avd, M, d, d, 3, pv, cv.adapter + (size_t)slot * cv.B, m->lora_n,
-                                  m->lora_rank, m->lora_scale, A3, B3, dst, qkv_in_place ? 1 : 0));
+        if (lora_qkv && !lora_done) { ProfScope ps(T_LORA, s);
+            la_qkv.out = qkv_in_place ? m->qkv : m->gpart_q + (size_t)nq_slabs * M * 3 * d;
+            la_qkv.accumulate = qkv_in_place;
+            FWD(launch_lora_delta(s, cf.dtype, m->abuf, avd, M, d, la_qkv));
             if (!qkv_in_place) nq_slabs++;
         }
         if (cache_only && l + 1 == cf.n_layers) { ProfScope ps(T_ROPE, s);
@@ -1035,14 +1048,15 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             FWD(eo);
             a_scaled = true;
         } else if (!oproj_done) { ProfScope ps(T_OPROJ, s);
-        no_slabs = stream_gemm(m, s, m->obuf, avd, wo, M, d, d, m->gpart_r, m->gpart_r_floats, 0, &ge, lora_o ? 1 : 0);
+        no_slabs = stream_gemm(m, s, m->obuf, avd, wo, M, d, d, m->gpart_r, m->gpart_r_floats, 0, &ge, lora_o ? 1 : 0,
+                               LmStats{nullptr, 0.f}, nullptr, kNoFold, lora_o ? &la_o : nullptr, &lora_done);
         FWD(ge);
+        if (lora_done) no_slabs++;
         if (!no_slabs) FWD(gemm_generic(m, s, GEMM_RESID, m->obuf, avd, wo, M, d, d, m->x, nullptr, av0)); }
-        if (lora_o) { ProfScope ps(T_LORA, s); // (without slabs the projection was added to x directly: so is its update)
-            const float *A1[1] = {m->lora_a[3][l]}, *B1[1] = {m->lora_b[3][l]};
-            float *dst = no_slabs ? m->gpart_r + (size_t)no_slabs * M * d : m->x;
-            FWD(launch_lora_delta(s, cf.dtype, m->obuf, avd, M, d, d, 1, pv, cv.adapter + (size_t)slot * cv.B, m->lora_n,
-                                  m->lora_rank, m->lora_scale, A1, B1, dst, no_slabs ? 0 : 1));
+        if (lora_o && !lora_done) { ProfScope ps(T_LORA, s); // (without slabs the projection was added to x directly: so is its update)
+            la_o.out = no_slabs ? m->gpart_r + (size_t)no_slabs * M * d : m->x;
+            la_o.accumulate = no_slabs ? 0 : 1;
+            FWD(launch_lora_delta(s, cf.dtype, m->obuf, avd, M, d, la_o));
             if (no_slabs) no_slabs++;
         }
         WeightSeg wgu = {{m->wgate[l], m->wup[l], nullptr}, F, m->tiled_fd, m->stream_nt};

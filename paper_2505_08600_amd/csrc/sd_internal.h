@@ -274,6 +274,17 @@ struct LmStats {
     float invT; // 1 / temperature, or 0
 };
 
+// Low-rank update of n_proj (<= 3) projections that share the input rows X: for row r of a sequence with
+// adapter a >= 0, out[r][p * N + n] (+)= scale * sum_j B[p][a][n][j] * (sum_k A[p][a][j][k] * X[r][k]); rows
+// without an adapter (and projections whose factors are NULL) get 0 (or are left alone when accumulating).
+struct LoraArgs {
+    const float *a0, *a1, *a2, *b0, *b1, *b2; // (names, not arrays: an element picked by a variable index would put the struct in scratch memory)
+    const int32_t *row_valid, *row_b, *adapter; // of the plan; [B] adapter of each sequence
+    int32_t N, n_proj, n_adapters, rank, accumulate;
+    float scale;
+    float *out;
+};
+
 // ---------------------------------------------------------------- host-side objects
 struct sd_model {
     sd_model_config cfg;
@@ -377,12 +388,8 @@ extern int g_force_splits[3]; // per GEMM mode: K splits forced by option "gemm_
 
 // ---------------------------------------------------------------- kernel launchers
 // (each returns a hipError_t from hipGetLastError after the launch)
-// Low-rank update of n_proj (<= 3) projections that share the input rows X: for row r of a sequence with
-// adapter a >= 0, out[r][p * N + n] (+)= scale * sum_j B[p][a][n][j] * (sum_k A[p][a][j][k] * X[r][k]); rows
-// without an adapter (and projections whose factors are NULL) get 0 (or are left alone when accumulating).
-hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_av, int M, int K, int N, int n_proj,
-                             PlanView pv, const int32_t *adapter, int n_adapters, int rank, float scale,
-                             const float *const *A, const float *const *B, float *out, int accumulate);
+hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_av, int M, int K, const LoraArgs &la);
+bool lora_valid(int M, int K, const LoraArgs &la);
 hipError_t launch_plan(hipStream_t s, int mode, int R, int n_seq, const int32_t *seq_ids, CtxView cv, int slot,
                        int upto_off, const int32_t *cand, int gamma, int cand_idx, int vocab, PlanView pv);
 hipError_t launch_plan_prefill(hipStream_t s, int R, int G, int n_seq, const int32_t *seq_ids, CtxView cv, int slot,
@@ -443,10 +450,12 @@ int gemm_tile_plan(int mode, int M, int N, int K, int n_per_seg, int plan[6]); /
 // kernel chosen for the shape wrote them.
 // nf: norm split between producer and consumer (few-row kernels only: the launcher returns
 // hipErrorNotSupported for a shape it would send to the row-blocked kernel).
+// lora: low-rank update of the same rows A, wanted beside the product; *lora_done tells whether the launch carried it.
 hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActView a_av, WeightSeg w, int M, int N,
                                    int K, float *C, size_t c_split_stride, int splits, void *Cact, ActView c_av,
                                    LmStats ls = {nullptr, 0.f}, int *ls_done = nullptr,
-                                   NormFold nf = {nullptr, 0, 0.f, nullptr, nullptr, nullptr, nullptr});
+                                   NormFold nf = {nullptr, 0, 0.f, nullptr, nullptr, nullptr, nullptr},
+                                   const LoraArgs *lora = nullptr, int *lora_done = nullptr);
 hipError_t launch_add_rmsnorm(hipStream_t s, int dtype, float *x, const float *part, int n_slabs, size_t slab_stride,
                               const float *g, const int32_t *row_map, int n_rows, int d, float eps, void *out,
                               ActView out_av);

@@ -1996,3 +1996,37 @@ def test_set_tokens_sets_what_is_named_and_nothing_else():
     for b in (0, 2, 3, 4, 5):
         assert np.array_equal(ctx.get_tokens(b), want[b]), b
     ctx.close()
+
+
+@pytest.mark.parametrize("d,heads,rank", [(768, 12, 8), (768, 12, 1), (1024, 16, 3), (1024, 16, 16), (128, 2, 12), (896, 14, 13)])
+def test_low_rank_update_carried_by_the_gemm_launch_matches_reference_kernels(d, heads, rank):
+    """9 to 64 rows: the low-rank update runs as extra blocks of the QKV and O launches (one part of 768 outputs, a partial one, two
+    parts, ranks that are and are not multiples of four), sequences with different adapters and without, against the separate
+    launches of the reference path."""
+    import dataclasses
+    _say(f"carried low-rank update d={d} rank={rank}")
+    st_ = dataclasses.replace(dg.SHAPES["small_draft_bf16"], n_layers=2, d_model=d, n_heads=heads, d_ffn=512, name=f"lora_{d}")
+    gm = api.Model(st_, dg.make_weights(st_, 95, BF16_LM_SCALE), max_rows=64, max_pos=128)
+    gm.set_lora(dg.make_lora(st_, 96, 3, rank, 0.05, 0.05), 2.0)
+    for B, gamma in ((3, 2), (12, 1), (16, 3), (9, 6)):
+        lens = dg.make_prompt_lengths(95, B, 5, 60)
+        prompts = [[int(t) for t in dg.make_prompt(95, b, int(lens[b]), st_.vocab)] for b in range(B)]
+        cand = H.dev(dg.make_prompt(97, 0, B * gamma, st_.vocab).reshape(B, gamma).astype(np.int32))
+        na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+        ctx = api.Context([80] * B)
+        ctx.attach(gm)
+        ctx.set_adapters(gm, [b % 4 - 1 for b in range(B)])
+        H.gpu_prefill(ctx, [gm], prompts)
+        outs = []
+        for force in (0, 1):
+            api.set_option("force_generic", force)
+            try:
+                api.sd_verify(gm, ctx, None, B, gamma, 0.0, cand, None, None, na, nx, commit=False)
+            finally:
+                api.set_option("force_generic", 0)
+            outs.append(gm.last_logits().cpu().numpy())
+            for b in range(B):
+                ctx.truncate(gm, b, int(lens[b]) - 1)
+        assert np.isfinite(outs[0]).all() and np.abs(outs[0] - outs[1]).max() < 5e-4 * np.abs(outs[1]).max(), (B, gamma)
+        ctx.close()
+    gm.close()
