@@ -1308,7 +1308,7 @@ struct PickScratch {
 // vectors, then a scan of the one that holds the target.  Without a crossing: the chosen segment's last index of
 // positive weight, or the range's if no segment was chosen.  At most 64 segments.
 template <typename F>
-__device__ int block_pick_range(F wfun, int v_begin, int v_end, int V, float base, float target, PickScratch *ps)
+__device__ __forceinline__ int block_pick_range(F wfun, int v_begin, int v_end, int V, float base, float target, PickScratch *ps)
 {
     const int T = blockDim.x;
     const int nseg = (v_end - v_begin + T - 1) / T;
@@ -1356,7 +1356,7 @@ __device__ int block_pick_range(F wfun, int v_begin, int v_end, int V, float bas
 }
 
 template <typename F>
-__device__ int block_pick_cdf(F wfun, int V, float u, PickScratch *ps, float *total_out)
+__device__ __forceinline__ int block_pick_cdf(F wfun, int V, float u, PickScratch *ps, float *total_out)
 {
     const int T = blockDim.x;
     int nvec = (V + 3) / 4;
@@ -2306,8 +2306,8 @@ hipError_t launch_commit(hipStream_t s, CtxView cv, const int32_t *seq_ids, int 
 // 2000 rows of 33000 189 / 206 | 198 / 212; 600 rows of 128000 (307 MB) 220.6 / 218.7 | 229.1 / 228.2: the hint above 256
 // MB.  512 threads without it where there are rows enough to put two blocks on every compute unit (540 x 33000: 31.3, 1024
 // threads with the hint 34.2).
-// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 71 us (76 in blocks of 1024 threads, 101 with expf,
-// the acceptance test in the second launch and a pick that read its slice twice).
+// Whole call at 64 sequences, gamma 8, 128000 columns (295 MB of logits): 69 us (71 with scratch memory and flat loads in the pick, 76 in
+// blocks of 1024 threads, 101 with expf, the acceptance test in the second launch and a pick that read its slice twice).
 // e^(d / T), d <= 0, as 2^(c d + r d): c = log2(e) / T rounded down, r >= 0 what that leaves of it (the two-constant reduction
 // of Cody and Waite, in base 2).  r > 0 and bounded by c: -inf stays -inf through both products and gives 0, d = 0 gives 1
 // at any T.  Error of a row's sum against 64 bits, rms over 300 rows of N(0, 2), 128000 columns, T = 1 / 1.1 / 1.3 / 2: expf
@@ -2490,7 +2490,7 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
     const float *st = stats + (size_t)j * (stride_g + 1) * 3;
     const int n_acc = accepted_prefix(st, gamma);
     const float uu = u[(size_t)j * (stride_g + 1) + gamma];
-    DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
+    const DrawWeights w = {(const float4 *)(rows + (size_t)n_acc * V),
                      n_acc < gamma ? (const float4 *)(q + ((size_t)j * stride_g + n_acc) * V) : nullptr, st[3 * n_acc],
                      inv_temperature(T), 1.0f / fabsf(st[3 * n_acc + 1])};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
@@ -2498,10 +2498,10 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
     if (stride_g)
         for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
     int next;
-    if (!stride_g) next = block_pick_cdf(w, V, uu, &ps, nullptr);
-    else if (w.q && !(Z > 0.f)) { // numerically empty residual: draw from p
-        w.q = nullptr;
-        next = block_pick_cdf(w, V, uu, &ps, nullptr);
+    const bool whole = NSEG == 0 && !stride_g, empty = w.q && !(Z > 0.f);
+    if (whole || empty) { // (whole: w.q is null anyway) numerically empty residual: draw from p
+        const DrawWeights p = {w.row, nullptr, w.mx, w.invT, w.invZ};
+        next = block_pick_cdf(p, V, uu, &ps, nullptr);
     } else {
         // every thread walks the slice masses in the same order: first slice whose running sum exceeds the target, else
         // (rounding) the last slice of positive mass
@@ -2530,9 +2530,12 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
             const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int it = 0; it < NSEG; it++) {
-                const int v = v_begin + it * 1024 + threadIdx.x;
-                f.f[it] = v < v_end ? w.row[v] : zero;
-                r.f[it] = w.q && v < v_end ? w.q[v] : zero;
+                // (unconditional loads: a choice between a vector of the row and a zero one would be made of their addresses, with
+                // the zero in scratch memory and flat loads)
+                const int v = min(v_begin + it * 1024 + (int)threadIdx.x, v_end - 1);
+                f.f[it] = w.row[v];
+                r.f[it] = zero;
+                if (w.q) r.f[it] = w.q[v]; // (uniform)
             }
 #pragma unroll
             for (int it = 0; it < NSEG; it++) f.f[it] = v_begin + it * 1024 + (int)threadIdx.x < v_end ? w.of(f.f[it], r.f[it]) : zero;
