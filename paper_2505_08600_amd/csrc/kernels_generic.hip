@@ -518,7 +518,9 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const T *A, ActView a
 // NORM: A is the residual stream, its RMSNorm is part of the launch: every wave multiplies the rows by the gains as it
 // reads them, adds up their squares beside the products and scales its sums by 1 / rms (row_map: source row of output
 // row m).  A norm launch costs the small shapes as much as the GEMM behind it; above 16 rows the waves would repeat too
-// much of it (launch_gemm_f32_norm).  Whole step of the tiny pair, 12 norm launches of 67 fewer: 277 -> 233 us.
+// much of it (launch_gemm_f32_norm).  Whole step of the tiny pair, 12 norm launches of 67 fewer: 277 -> 233 us; the first
+// layer's reads the embedding rows themselves and the projection behind its attention adds to them, five launches of 49
+// fewer: 205 -> 190 us.
 template <int MODE, int MR, bool NORM>
 __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const float *__restrict__ A, WeightSeg w, int M, int N, int K, float *C,
                                                                       float *__restrict__ Cact, const float *__restrict__ gain,
@@ -543,7 +545,8 @@ __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const floa
     }
     const size_t o = (size_t)(m0 + lane) * N + n; // lane m finishes row m
     const bool live = lane < MR && m0 + lane < M;
-    const float resid = MODE == GEMM_RESID && live ? C[o] : 0.f;
+    float resid = 0.f; // GEMM_RESID with a row map: the residual rows are rows of `gain`, an embedding table
+    if (MODE == GEMM_RESID && live) resid = row_map ? gain[(size_t)row_map[m0 + lane] * N + n] : C[o];
     float acc[NM][MR], ss[MR];
 #pragma unroll
     for (int m = 0; m < MR; m++) {
@@ -638,6 +641,16 @@ hipError_t launch_gemm_f32_norm(hipStream_t s, int mode, const float *x, const f
     if (M > 16 || K % 4 != 0 || (addr & 15) || w.tiled || (mode != GEMM_STORE && mode != GEMM_SWIGLU)) return hipErrorNotSupported;
     if (mode == GEMM_STORE) gemm_f32_rows<GEMM_STORE, true>(s, x, w, M, N, K, C, nullptr, gain, row_map, eps);
     else gemm_f32_rows<GEMM_SWIGLU, true>(s, x, w, M, N, K, nullptr, Cact, gain, row_map, eps);
+    return hipGetLastError();
+}
+
+// C = the embedding rows of the tokens + A . W^T: a projection onto residual rows that no launch has gathered.
+hipError_t launch_gemm_f32_embed_resid(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, const float *E,
+                                       const int32_t *row_tok)
+{
+    const uintptr_t addr = (uintptr_t)A | (uintptr_t)w.p[0];
+    if (M > 16 || K % 4 != 0 || (addr & 15) || w.tiled) return hipErrorNotSupported;
+    gemm_f32_rows<GEMM_RESID, false>(s, A, w, M, N, K, C, nullptr, E, row_tok, 0.f);
     return hipGetLastError();
 }
 

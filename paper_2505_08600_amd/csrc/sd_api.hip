@@ -931,20 +931,30 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     if (!plan_ready) { ProfScope ps(T_PLAN, s); // (the draft sampler lays out the single-row forwards that follow it)
     if (G > 1) FWD(launch_plan_prefill(s, R, G, n_seq, seq_ids, cv, slot, upto_off, V, pv));
     else FWD(launch_plan(s, mode, R, n_seq, seq_ids, cv, slot, upto_off, cand, gamma, cand_idx, V, pv)); }
-    if (!embed_ready) { ProfScope ps(T_EMBED, s); // embedding gather + the first layer's norm in one launch
-    FWD(launch_embed_rmsnorm(s, cf.dtype, m->embed, pv.row_tok, M, d, m->x, m->norm_attn[0], cf.rms_eps, m->abuf, avd)); }
     int pending = 0; // split-K slabs of the previous down projection not yet added to x
     // fp32 models at few rows: the norms are part of the GEMMs that read them (low-rank updates read the normed rows too)
     const bool norm32 = cf.dtype == SD_FP32 && M <= 16 && !(g_force_generic & (1 | 16)) && m->lora_n == 0;
-    auto norm_gemm32 = [&](int mode_g, const float *gain, const int32_t *row_map, WeightSeg wg, int rows, int N, float *C, void *Cact) {
-        return norm32 ? launch_gemm_f32_norm(s, mode_g, m->x, gain, row_map, cf.rms_eps, wg, rows, N, d, C, (float *)Cact) : hipErrorNotSupported;
+    auto norm_gemm32 = [&](int mode_g, const float *gain, const int32_t *row_map, WeightSeg wg, int rows, int N, float *C, void *Cact,
+                           const float *x) {
+        return norm32 ? launch_gemm_f32_norm(s, mode_g, x, gain, row_map, cf.rms_eps, wg, rows, N, d, C, (float *)Cact) : hipErrorNotSupported;
     };
+    bool x_is_embed = false; // (norm32) nothing has gathered the embedding rows: the first layer reads them in the table
+    if (!embed_ready && norm32) {
+        ProfScope pe(T_EMBED, s), ps(T_QKV, s); // (the profile counts the stage inside the launch as well)
+        const WeightSeg wqkv = {{m->wq[0], m->wk[0], m->wv[0]}, d, m->tiled_dd, m->stream_nt};
+        const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[0], pv.row_tok, wqkv, M, 3 * d, m->qkv, nullptr, (const float *)m->embed);
+        if (en != hipErrorNotSupported) FWD(en);
+        else pe.drop(), ps.drop();
+        x_is_embed = en == hipSuccess;
+    }
+    if (!embed_ready && !x_is_embed) { ProfScope ps(T_EMBED, s); // embedding gather + the first layer's norm in one launch
+    FWD(launch_embed_rmsnorm(s, cf.dtype, m->embed, pv.row_tok, M, d, m->x, m->norm_attn[0], cf.rms_eps, m->abuf, avd)); }
     for (int l = 0; l < cf.n_layers; l++) {
         void *Kl = (char *)c->kcache[slot] + l * lstride, *Vtl = (char *)c->vcache[slot] + l * lstride;
         WeightSeg wqkv = {{m->wq[l], m->wk[l], m->wv[l]}, d, m->tiled_dd, m->stream_nt};
-        bool qkv_done = false;
+        bool qkv_done = l == 0 && x_is_embed;
         if (l > 0 && norm32) { ProfScope ps(T_QKV, s);
-            const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[l], nullptr, wqkv, M, 3 * d, m->qkv, nullptr);
+            const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[l], nullptr, wqkv, M, 3 * d, m->qkv, nullptr, m->x);
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
             qkv_done = en == hipSuccess;
@@ -1052,7 +1062,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
                                LmStats{nullptr, 0.f}, nullptr, kNoFold, lora_o ? &la_o : nullptr, &lora_done);
         FWD(ge);
         if (lora_done) no_slabs++;
-        if (!no_slabs) FWD(gemm_generic(m, s, GEMM_RESID, m->obuf, avd, wo, M, d, d, m->x, nullptr, av0)); }
+        if (!no_slabs && l == 0 && x_is_embed)
+            FWD(launch_gemm_f32_embed_resid(s, (const float *)m->obuf, wo, M, d, d, m->x, (const float *)m->embed, pv.row_tok));
+        else if (!no_slabs) FWD(gemm_generic(m, s, GEMM_RESID, m->obuf, avd, wo, M, d, d, m->x, nullptr, av0)); }
         if (lora_o && !lora_done) { ProfScope ps(T_LORA, s); // (without slabs the projection was added to x directly: so is its update)
             la_o.out = no_slabs ? m->gpart_r + (size_t)no_slabs * M * d : m->x;
             la_o.accumulate = no_slabs ? 0 : 1;
@@ -1063,7 +1075,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         bool gu_done = false;
         // (without logits this norm is the call's last: a launch of its own leaves it in abuf for sd_debug_read)
         if (norm32 && !no_slabs && (want_logits || more || l + 1 < cf.n_layers)) { ProfScope ps(T_GATEUP, s);
-            const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act);
+            const hipError_t en = norm_gemm32(GEMM_SWIGLU, m->norm_ffn[l], nullptr, wgu, M, F, nullptr, m->act, m->x);
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
             gu_done = en == hipSuccess;
@@ -1106,7 +1118,7 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         WeightSeg wl = {{m->lm_head, nullptr, nullptr}, V, m->tiled_lm, m->stream_nt};
         bool lm_done = false;
         if (norm32 && !pending) { ProfScope ps(T_LMHEAD, s);
-            const hipError_t en = norm_gemm32(GEMM_STORE, m->final_norm, pv.lm_row, wl, n_lm, V, m->logits, nullptr);
+            const hipError_t en = norm_gemm32(GEMM_STORE, m->final_norm, pv.lm_row, wl, n_lm, V, m->logits, nullptr, m->x);
             if (en != hipErrorNotSupported) FWD(en);
             else ps.drop();
             lm_done = en == hipSuccess;

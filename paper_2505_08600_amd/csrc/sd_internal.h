@@ -407,6 +407,8 @@ hipError_t launch_gemm_generic(hipStream_t s, int dtype, int mode, const void *A
 // hipErrorNotSupported where the caller should run the two itself
 hipError_t launch_gemm_f32_norm(hipStream_t s, int mode, const float *x, const float *gain, const int32_t *row_map, float eps, WeightSeg w,
                                 int M, int N, int K, float *C, float *Cact);
+hipError_t launch_gemm_f32_embed_resid(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, const float *E,
+                                       const int32_t *row_tok);
 // (R: rows per plan slot; the rows of a slot hold consecutive positions of one sequence)
 hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                               CtxView cv, int M, int R, int H,
