@@ -376,8 +376,8 @@ int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, int32_t *row
  * fused kernel skipped hold older data: "qkv" and "q" whenever attention consumes the
  * QKV GEMM's partial sums directly, "o" when a small model's attention blocks apply the
  * output projection themselves (option "force_generic" selects the unfused kernels); and a
- * prefill, which leaves out what follows the cache append in its last layer, leaves every
- * buffer but "q" as the layer before had it. */
+ * prefill, which leaves out what the cache append of its last layer does not need, leaves
+ * the buffers as the layer before had them. */
 int sd_debug_read(sd_model *m, const char *name, float *out, int32_t rows);
 /* Host-only (no GPU call): element offset that the library's internal layouts assign.
  * kind 0: tiled bf16 weight [N][K], a = row n, b = column k, c = K  (16-row x 128-column

@@ -930,7 +930,8 @@ hipError_t launch_lora_delta(hipStream_t s, int dtype, const void *X, ActView x_
     return lora_launch(s, (const float *)X, x_av, M, K, la);
 }
 
-template <typename T>
+// KV: the rows of `qkv` hold keys and values only, and no queries are wanted (the last layer of a prefill).
+template <typename T, bool KV>
 __global__ void rope_append_kernel(const float *qkv, int n_slabs, size_t slab_stride, PlanView pv, CtxView cv, int H,
                                    int hd, const float2 *rope,
                                    int max_pos, T *qbuf, ActView q_av, T *Kl, T *Vtl, int64_t total_cap)
@@ -943,11 +944,12 @@ __global__ void rope_append_kernel(const float *qkv, int n_slabs, size_t slab_st
         if (threadIdx.x == 0 && valid) atomicOr(cv.status, 8);
         valid = 0;
     }
-    const float *row = qkv + (size_t)r * 3 * HD;
+    const float *row = qkv + (size_t)r * (KV ? 2 : 3) * HD - (KV ? HD : 0);
     int64_t off = cv.off[pv.row_b[r]];
     for (int i = threadIdx.x; i < H * half; i += blockDim.x) {
         int h = i / half, e = i % half;
         if (!valid) {
+            if (KV) continue;
             store_act(qbuf, act_index(q_av, r, h * hd + e, HD), q_av.plane, 0.f);
             store_act(qbuf, act_index(q_av, r, h * hd + e + half, HD), q_av.plane, 0.f);
             continue;
@@ -959,8 +961,8 @@ __global__ void rope_append_kernel(const float *qkv, int n_slabs, size_t slab_st
         for (int sl = 0; sl < ROPE_MAX_SLABS; sl++) // split-K slabs of the QKV GEMM: all loads go out first
             if (sl < n_slabs) {
                 const float *rs = row + (size_t)sl * slab_stride;
-                ld[sl][0] = rs[h * hd + e];
-                ld[sl][1] = rs[h * hd + e + half];
+                ld[sl][0] = KV ? 0.f : rs[h * hd + e];
+                ld[sl][1] = KV ? 0.f : rs[h * hd + e + half];
                 ld[sl][2] = rs[HD + h * hd + e];
                 ld[sl][3] = rs[HD + h * hd + e + half];
                 ld[sl][4] = rs[2 * HD + h * hd + e];
@@ -976,8 +978,10 @@ __global__ void rope_append_kernel(const float *qkv, int n_slabs, size_t slab_st
                 v0 += ld[sl][4];
                 v1 += ld[sl][5];
             }
-        store_act(qbuf, act_index(q_av, r, h * hd + e, HD), q_av.plane, q0 * cs.x - q1 * cs.y);
-        store_act(qbuf, act_index(q_av, r, h * hd + e + half, HD), q_av.plane, q1 * cs.x + q0 * cs.y);
+        if (!KV) {
+            store_act(qbuf, act_index(q_av, r, h * hd + e, HD), q_av.plane, q0 * cs.x - q1 * cs.y);
+            store_act(qbuf, act_index(q_av, r, h * hd + e + half, HD), q_av.plane, q1 * cs.x + q0 * cs.y);
+        }
         T *kh = Kl + (size_t)h * total_cap * hd;
         kh[kt_offset(hd, off + pos, e)] = from_float<T>(k0 * cs.x - k1 * cs.y);
         kh[kt_offset(hd, off + pos, e + half)] = from_float<T>(k1 * cs.x + k0 * cs.y);
@@ -995,7 +999,7 @@ __global__ void rope_append_kernel(const float *qkv, int n_slabs, size_t slab_st
 // of the K pieces (8 consecutive dimensions of a token are one piece of the operand-order tile); the V values go
 // through LDS so that a thread can write the 16 tokens of one dimension as 32 contiguous bytes when the group is
 // full and starts at a multiple of 16 (every prefill group of a fresh prompt), and token by token otherwise.
-template <int HD>
+template <int HD, bool KV>
 __global__ __launch_bounds__(HD) void rope_append_group_kernel(const float *__restrict__ qkv, int n_slabs, size_t slab_stride,
                                                                PlanView pv, CtxView cv, int R, int H,
                                                                const float2 *__restrict__ rope, int max_pos,
@@ -1022,12 +1026,12 @@ __global__ __launch_bounds__(HD) void rope_append_group_kernel(const float *__re
 #pragma unroll
     for (int e = 0; e < 16; e++) q[e] = k[e] = v[e] = 0.f;
     if (valid) {
-        const float *base = qkv + (size_t)r * 3 * HDm + h * HD;
+        const float *base = qkv + (size_t)r * (KV ? 2 : 3) * HDm - (KV ? HDm : 0) + h * HD;
         for (int sl = 0; sl < n_slabs; sl++) { // split-K slabs of the QKV GEMM, added in slab order
             const float *rs = base + (size_t)sl * slab_stride;
             float4 ld[12];
 #pragma unroll
-            for (int m = 0; m < 3; m++) {
+            for (int m = KV ? 1 : 0; m < 3; m++) {
                 ld[4 * m + 0] = *(const float4 *)(rs + m * HDm + d0);
                 ld[4 * m + 1] = *(const float4 *)(rs + m * HDm + d0 + 4);
                 ld[4 * m + 2] = *(const float4 *)(rs + m * HDm + d1);
@@ -1035,8 +1039,8 @@ __global__ __launch_bounds__(HD) void rope_append_group_kernel(const float *__re
             }
 #pragma unroll
             for (int c = 0; c < 4; c++) {
-                const float4 a = ld[c], b = ld[4 + c], w = ld[8 + c];
-                q[4 * c + 0] += a.x, q[4 * c + 1] += a.y, q[4 * c + 2] += a.z, q[4 * c + 3] += a.w;
+                const float4 a = ld[KV ? 4 + c : c], b = ld[4 + c], w = ld[8 + c];
+                if (!KV) q[4 * c + 0] += a.x, q[4 * c + 1] += a.y, q[4 * c + 2] += a.z, q[4 * c + 3] += a.w;
                 k[4 * c + 0] += b.x, k[4 * c + 1] += b.y, k[4 * c + 2] += b.z, k[4 * c + 3] += b.w;
                 v[4 * c + 0] += w.x, v[4 * c + 1] += w.y, v[4 * c + 2] += w.z, v[4 * c + 3] += w.w;
             }
@@ -1050,7 +1054,7 @@ __global__ __launch_bounds__(HD) void rope_append_group_kernel(const float *__re
             q[e] = qa, q[8 + e] = qb, k[e] = ka, k[8 + e] = kb;
         }
     }
-    if (i < R) { // q planes (zeros for rows without a token), 8 consecutive columns inside one K step
+    if (!KV && i < R) { // q planes (zeros for rows without a token), 8 consecutive columns inside one K step
 #pragma unroll
         for (int hf = 0; hf < 2; hf++) {
             uint32_t hi[4], lo[4];
@@ -1100,26 +1104,30 @@ __global__ __launch_bounds__(HD) void rope_append_group_kernel(const float *__re
 int g_rope_group = 1; // option "rope_group": 0 keeps the row-per-block kernel for bf16 models too
 hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                               CtxView cv, int M, int R, int H, int hd, const float2 *rope, int max_pos, void *qbuf,
-                              ActView q_av, void *Kl, void *Vtl, int64_t total_cap)
+                              ActView q_av, void *Kl, void *Vtl, int64_t total_cap, bool kv_only)
 {
     if (n_slabs > ROPE_MAX_SLABS) return hipErrorInvalidValue;
     if (dtype == SD_BF16 && g_rope_group && R >= 1 && R <= 16 && M % R == 0 && (hd == 64 || hd == 128) && H <= 65535 &&
         M / R <= 65535 && (q_av.plane & 7) == 0 && ((uintptr_t)qbuf & 15) == 0 && ((uintptr_t)Kl & 15) == 0 &&
         ((uintptr_t)Vtl & 15) == 0 && ((uintptr_t)qkv & 15) == 0 && (slab_stride & 3) == 0 && total_cap % 64 == 0) {
-        if (hd == 128)
-            hipLaunchKernelGGL(rope_append_group_kernel<128>, dim3(H, M / R), dim3(128), 0, s, qkv, n_slabs, slab_stride, pv,
-                               cv, R, H, rope, max_pos, (uint16_t *)qbuf, q_av, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap);
-        else
-            hipLaunchKernelGGL(rope_append_group_kernel<64>, dim3(H, M / R), dim3(64), 0, s, qkv, n_slabs, slab_stride, pv, cv,
-                               R, H, rope, max_pos, (uint16_t *)qbuf, q_av, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap);
+#define SD_ROPE_GROUP(HD_, KV_)                                                                                               \
+    hipLaunchKernelGGL((rope_append_group_kernel<HD_, KV_>), dim3(H, M / R), dim3(HD_), 0, s, qkv, n_slabs, slab_stride, pv, cv, R, H, \
+                       rope, max_pos, (uint16_t *)qbuf, q_av, (uint16_t *)Kl, (uint16_t *)Vtl, total_cap)
+        if (hd == 128 && kv_only) SD_ROPE_GROUP(128, true);
+        else if (hd == 128) SD_ROPE_GROUP(128, false);
+        else if (kv_only) SD_ROPE_GROUP(64, true);
+        else SD_ROPE_GROUP(64, false);
+#undef SD_ROPE_GROUP
         return hipGetLastError();
     }
-    if (dtype == SD_BF16)
-        hipLaunchKernelGGL(rope_append_kernel<bf16_t>, dim3(M), dim3(1024), 0, s, qkv, n_slabs, slab_stride, pv, cv, H,
-                           hd, rope, max_pos, (bf16_t *)qbuf, q_av, (bf16_t *)Kl, (bf16_t *)Vtl, total_cap);
-    else
-        hipLaunchKernelGGL(rope_append_kernel<float>, dim3(M), dim3(1024), 0, s, qkv, n_slabs, slab_stride, pv, cv, H,
-                           hd, rope, max_pos, (float *)qbuf, q_av, (float *)Kl, (float *)Vtl, total_cap);
+#define SD_ROPE_ROWS(T_, KV_)                                                                                                 \
+    hipLaunchKernelGGL((rope_append_kernel<T_, KV_>), dim3(M), dim3(1024), 0, s, qkv, n_slabs, slab_stride, pv, cv, H, hd, rope, max_pos, \
+                       (T_ *)qbuf, q_av, (T_ *)Kl, (T_ *)Vtl, total_cap)
+    if (dtype == SD_BF16 && kv_only) SD_ROPE_ROWS(bf16_t, true);
+    else if (dtype == SD_BF16) SD_ROPE_ROWS(bf16_t, false);
+    else if (kv_only) return hipErrorInvalidValue; // (fp32 models keep the queries of a call's last forward)
+    else SD_ROPE_ROWS(float, false);
+#undef SD_ROPE_ROWS
     return hipGetLastError();
 }
 

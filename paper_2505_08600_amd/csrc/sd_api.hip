@@ -898,8 +898,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     // the same call follows (nothing can look at this one's buffers).
     const sd_model_config &cf = m->cfg;
     // A forward without logits is there for its cache rows: of its last layer nothing behind the cache append is read by
-    // anyone, so attention, projections and FFN of that layer are left out - one layer in n_layers of a prefill, less its
-    // QKV projection (two layers of the 7B shape, 8192 tokens at 1024 rows: 15.06 -> 9.5 ms, 32 layers: a 34th of the whole).
+    // anyone, so queries, attention, projections and FFN of that layer are left out - one layer in n_layers of a prefill, less
+    // its key and value projections (two layers of the 7B shape, 8192 tokens at 1024 rows: 15.05 -> 9.33 ms, 8.68 without the
+    // queries; 32 layers: a 33rd of the whole).
     // The last forward of a call keeps them for fp32 models, whose buffers sd_debug_read promises.
     const bool cache_only = !want_logits && (more || cf.dtype == SD_BF16);
     const int n_slots = n_seq * G; // plan slots: what the attention kernels see as sequences
@@ -952,6 +953,10 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     for (int l = 0; l < cf.n_layers; l++) {
         void *Kl = (char *)c->kcache[slot] + l * lstride, *Vtl = (char *)c->vcache[slot] + l * lstride;
         WeightSeg wqkv = {{m->wq[l], m->wk[l], m->wv[l]}, d, m->tiled_dd, m->stream_nt};
+        const bool last_cache = cache_only && l + 1 == cf.n_layers;
+        const bool kv_only = last_cache && cf.dtype == SD_BF16 && m->lora_n == 0; // cache rows only: no queries either
+        const int n_qkv = (kv_only ? 2 : 3) * d;
+        if (kv_only) wqkv = WeightSeg{{m->wk[l], m->wv[l], nullptr}, d, m->tiled_dd, m->stream_nt};
         bool qkv_done = l == 0 && x_is_embed;
         if (l > 0 && norm32) { ProfScope ps(T_QKV, s);
             const hipError_t en = norm_gemm32(GEMM_STORE, m->norm_attn[l], nullptr, wqkv, M, 3 * d, m->qkv, nullptr, m->x);
@@ -988,14 +993,14 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             nq_slabs = 1;
             qkv_src = m->qkv;
         } else { ProfScope ps(T_QKV, s);
-        nq_slabs = stream_gemm(m, s, m->abuf, avd, wqkv, M, 3 * d, d, m->gpart_q, m->gpart_q_floats, 0, &ge, lora_qkv ? 1 : 0,
+        nq_slabs = stream_gemm(m, s, m->abuf, avd, wqkv, M, n_qkv, d, m->gpart_q, m->gpart_q_floats, 0, &ge, lora_qkv ? 1 : 0,
                                LmStats{nullptr, 0.f}, nullptr, a_scaled ? nf_consume : kNoFold, lora_qkv ? &la_qkv : nullptr, &lora_done);
         FWD(ge);
         if (lora_done) nq_slabs++;
         qkv_src = m->gpart_q;
         if (!nq_slabs && fold) return sd_fail(SD_EHIP, "forward: QKV shape left the few-row kernels under the split norm");
         if (!nq_slabs) {
-            FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, 3 * d, d, m->qkv, nullptr, av0));
+            FWD(gemm_generic(m, s, GEMM_STORE, m->abuf, avd, wqkv, M, n_qkv, d, m->qkv, nullptr, av0));
             nq_slabs = 1;
             qkv_src = m->qkv;
             qkv_in_place = true;
@@ -1006,9 +1011,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
             FWD(launch_lora_delta(s, cf.dtype, m->abuf, avd, M, d, la_qkv));
             if (!qkv_in_place) nq_slabs++;
         }
-        if (cache_only && l + 1 == cf.n_layers) { ProfScope ps(T_ROPE, s);
-            FWD(launch_rope_append(s, cf.dtype, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, M, R, H, hd, m->rope,
-                                   cf.max_pos, m->qbuf, avd, Kl, Vtl, c->total_cap));
+        if (last_cache) { ProfScope ps(T_ROPE, s);
+            FWD(launch_rope_append(s, cf.dtype, qkv_src, nq_slabs, (size_t)M * n_qkv, pv, cv, M, R, H, hd, m->rope,
+                                   cf.max_pos, m->qbuf, avd, Kl, Vtl, c->total_cap, kv_only));
             break;
         }
         hipError_t ea = hipErrorNotSupported;

@@ -410,10 +410,11 @@ hipError_t launch_gemm_f32_norm(hipStream_t s, int mode, const float *x, const f
 hipError_t launch_gemm_f32_embed_resid(hipStream_t s, const float *A, WeightSeg w, int M, int N, int K, float *C, const float *E,
                                        const int32_t *row_tok);
 // (R: rows per plan slot; the rows of a slot hold consecutive positions of one sequence)
+// (kv_only: rows of keys and values without queries, bf16 models)
 hipError_t launch_rope_append(hipStream_t s, int dtype, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                               CtxView cv, int M, int R, int H,
                               int hd, const float2 *rope, int max_pos, void *qbuf, ActView q_av, void *Kl, void *Vtl,
-                              int64_t total_cap);
+                              int64_t total_cap, bool kv_only = false);
 hipError_t launch_attn_generic(hipStream_t s, int dtype, void *qbuf, ActView q_av, void *Kl, void *Vtl, PlanView pv, CtxView cv, int R,
                                int n_seq, int H, int hd, int64_t total_cap, int len_upper, void *obuf, ActView o_av);
 hipError_t launch_attn_f32_fused(hipStream_t s, const float *qkv, const float2 *rope, int max_pos, float *Kl, float *Vtl, PlanView pv, CtxView cv,
