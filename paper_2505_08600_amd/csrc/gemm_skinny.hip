@@ -16,8 +16,9 @@
 //    the lo rows, and the epilogue adds the two halves; for larger M every weight
 //    fragment is multiplied twice;
 //  * few rows (gemm_ksplit_kernel up to 8 rows or where the norm is split, gemm_wide_kernel
-//    from 9 to 64): the waves of a block split K, fetch their activation fragments straight
-//    from L2 and meet in LDS - no barrier in the K loop;
+//    from 9 to 16, and to 64 in layers narrower than 4096): the waves of a block split K, fetch their
+//    activation fragments straight from L2 and meet in LDS - no barrier in the K loop;
+//    17 to 64 rows of wide layers (gemm_lds_kernel): weights and rows staged through LDS;
 //    more rows (gemm_tile_kernel): row blocks share a staged activation chunk in LDS;
 //  * results leave either directly (store; SwiGLU: silu(gate)*up split to bf16
 //    hi/lo) or as fp32 partial sums per K split, which the consuming kernel adds in
@@ -521,7 +522,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_ksplit_kernel(const uint16_t 
     }
 }
 
-// Wide few-row GEMM (9 to 64 rows): like gemm_ksplit_kernel the waves of a block share out the K steps and meet in LDS,
+// Wide few-row GEMM (9 to 16 rows, to 64 where gemm_lds_kernel does not take the shape): like gemm_ksplit_kernel the waves of a block share out the K steps and meet in LDS,
 // but a block owns NW weight tiles instead of one or two.
 // Bound: bytes through L2 into the compute units (about 8.5 TB/s on this part for 16-byte loads), of which HBM only
 // supplies the weights: a block re-reads the activation rows of its K range, 4 M bytes per K element against 32 NW of
@@ -671,6 +672,174 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16
     }
 }
 
+// Few-row GEMM of wide layers (17 to 64 rows, 4096 elements of K and more): a block of WR x WC waves, each with one 32 x 32
+// tile of the result (v_mfma_f32_32x32x16_bf16, weights as the first operand), and one block per compute unit.
+// Bound: what a compute unit pulls through L2 (50 - 60 GB/s), of which HBM only supplies the weights.  gemm_wide_kernel reads
+// the activation rows once per wave and K step into registers, as many bytes of rows as of weights at M = 32; here both operands go to LDS
+// (global_load_lds, 16 bytes a lane, no registers in between), so a block pulls its rows once for all of its weight
+// tiles, and NB - 1 chunks of 64 elements are in flight while one is multiplied, whatever the registers hold.
+// One barrier per chunk, in front of its last MFMA group: behind it the next chunk's fragments are read and the buffer
+// just emptied is refilled.  Weight tiles lie in LDS as in memory (operand order, conflict free); rows of 128 bytes have their eight 16-byte
+// pieces exchanged by (row / 2) % 8, so that the 32 rows of an operand fall into all banks.
+// Measured alone, the slabs' reader included (gemm_wide_kernel before -> now, us): 4096 wide, M = 24: gate/up 34.6 -> 31.5, QKV 19.4 ->
+// 19.6, O 8.4 -> 8.6, down 18.5 -> 17.8; M = 64: gate/up 53.0 -> 42.9, QKV 30.7 -> 24.7, O 14.4 -> 13.1, down 27.5 -> 24.2, LM
+// head 63.7 -> 49.0; 5120 wide, M = 24: gate/up 52.2 -> 45.8, QKV 28.5 -> 27.3, down 27.3 -> 24.4; M = 64: gate/up 73.8 -> 57.1, QKV
+// 42.5 -> 34.2, down 40.0 -> 32.7.  Deeper rings (5 stages of 64 x 96, 7 of 32 x 96) change nothing.  Verify pass of two 4096-wide
+// layers: 301 -> 293 at 18 rows, 307 -> 295 at 24, 340 -> 312 at 30, 410 -> 369 at 48, 488 -> 430 at 64.
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void global_cvoid;
+template <int MODE, int WR, int WC, int NB, bool NT_HINT>
+__global__ __launch_bounds__(WR *WC * 64) void gemm_lds_kernel(const uint16_t *__restrict__ A, ActView a_av, WeightSeg w, int M, int N, int K,
+                                                            int k_per_split, float *__restrict__ C, size_t c_split_stride, uint16_t *__restrict__ Cact, ActView c_av, LmStats ls)
+{
+    constexpr bool SW = MODE == GEMM_SWIGLU; // weight tiles of the block: gate and up alternate
+    constexpr int WAVES = WR * WC, BM = 32 * WR, BN = 32 * WC, COLS = SW ? BN / 2 : BN;
+    constexpr int KC = 64;                             // elements per chunk
+    constexpr int NA = 2 * BM / 8, NW = BN / 16 * 2;   // loads of 1 KiB per chunk: 8 rows of a plane, 32 elements of a weight tile
+    constexpr int PA = (NA + WAVES - 1) / WAVES, PB = (NW + WAVES - 1) / WAVES, PD = PA + PB; // per wave (some load a piece twice where the waves don't divide)
+    constexpr int STAGE = (NA + NW) * 1024;
+    static_assert(NB * STAGE <= 160 * 1024 && (NB - 2) * PD < 64, "LDS, vmcnt");
+    __shared__ __attribute__((aligned(1024))) char lds[NB * STAGE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave / WC, wc = wave % WC;
+    const int n0 = blockIdx.x * COLS;
+    const int kb = blockIdx.y * k_per_split, ke = min(K, kb + k_per_split);
+    const int nchunks = (ke - kb) / KC;
+    const size_t tile_elems = (size_t)(K >> 7) * 2048;
+    const uint16_t *Wp[PB]; // (uniform) tiles past the end (last block) re-read the last one
+    {
+        const int seg_tiles = w.n_per_seg / 16, last = N / 16 - 1;
+#pragma unroll
+        for (int j = 0; j < PB; j++) {
+            const int id = min(j * WAVES + wave, NW - 1), q = id / 2;
+            const int t = min(n0 / 16 + (SW ? q >> 1 : q), last), seg = SW ? q & 1 : t / seg_tiles;
+            const uint16_t *base = (const uint16_t *)(seg == 0 ? w.p[0] : seg == 1 ? w.p[1] : w.p[2]);
+            Wp[j] = base + (size_t)(SW ? t : t - seg * seg_tiles) * tile_elems + (size_t)(kb >> 7) * 2048 + id % 2 * 512;
+        }
+    }
+    uint32_t a_off[PA]; // rows past M re-read the last one; they only reach result rows that are never stored
+#pragma unroll
+    for (int j = 0; j < PA; j++) {
+        const int id = min(j * WAVES + wave, NA - 1), plane = id / (BM / 8), r = id % (BM / 8) * 8 + lane / 8;
+        a_off[j] = (uint32_t)((plane ? a_av.plane : 0) + (size_t)min(r, M - 1) * 128 + ((lane & 7) ^ (r >> 1 & 7)) * 8);
+    }
+    const size_t step_stride = (size_t)a_av.rows * 128;
+    const uint16_t *Ab = A + (size_t)(kb >> 7) * step_stride;
+    auto dma = [&](int ch, int buf) { // chunks past the end re-read the last one (the count of loads in flight stays the same)
+        const int cc = min(ch, nchunks - 1);
+        const uint16_t *ab = Ab + (size_t)(cc >> 1) * step_stride + (cc & 1) * KC;
+        char *st = lds + buf * STAGE;
+#pragma unroll
+        for (int j = 0; j < PA; j++)
+            __builtin_amdgcn_global_load_lds((global_cvoid *)(ab + a_off[j]), (lds_void *)(st + min(j * WAVES + wave, NA - 1) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int j = 0; j < PB; j++)
+            __builtin_amdgcn_global_load_lds((global_cvoid *)(Wp[j] + (size_t)cc * (KC * 16) + lane * 8),
+                                             (lds_void *)(st + (NA + min(j * WAVES + wave, NW - 1)) * 1024), 16, 0, NT_HINT ? 2 : 0);
+    };
+    const int lr = lane & 31, lg = lane >> 5;
+    uint32_t fa[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) fa[kk] = (wr * 32 + lr) * 128 + (((2 * kk + lg) ^ (lr >> 1 & 7)) << 4);
+    const uint32_t fb = NA * 1024 + (wc * 2 + (lr >> 4)) * 2048 + lg * 256 + (lr & 15) * 16;
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[e] = 0.f;
+    bf16x8 ah[2], al[2], bw[2];
+    auto frags = [&](int buf, int kk, int s) { // 16 of the chunk's elements
+        const char *b = lds + buf * STAGE;
+        bw[s] = *(const bf16x8 *)(b + fb + (kk >> 1) * 1024 + (kk & 1) * 512);
+        ah[s] = *(const bf16x8 *)(b + fa[kk]);
+        al[s] = *(const bf16x8 *)(b + fa[kk] + BM * 128);
+    };
+    auto mfmas = [&](int s) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw[s], ah[s], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw[s], al[s], acc, 0, 0, 0);
+    };
+    constexpr int VM = (NB - 2) * PD, VMCNT = (VM & 15) | (VM >> 4 << 14); // this wave's part of the next chunk has landed
+#pragma unroll
+    for (int b = 0; b < NB - 1; b++) dma(b, b);
+    __builtin_amdgcn_s_waitcnt(0x0f70 | VMCNT);
+    __builtin_amdgcn_s_barrier();
+    SD_ORDER();
+    dma(NB - 1, NB - 1);
+    frags(0, 0, 0);
+    // chunk ch in buffer b; at entry the fragments of its group 0 are requested and the loads of chunks up to ch + NB - 1 issued
+    auto chunk = [&](int ch, int b) {
+#pragma unroll
+        for (int kk = 0; kk < 3; kk++) {
+            frags(b, kk + 1, (kk + 1) & 1);
+            mfmas(kk & 1);
+            SD_ORDER();
+        }
+        // everything of this chunk is in registers; the next one has landed once all waves are past the barrier
+        __builtin_amdgcn_s_waitcnt(0x0070 | VMCNT);
+        __builtin_amdgcn_s_barrier();
+        SD_ORDER();
+        frags((b + 1) % NB, 0, 0);
+        SD_ORDER();
+        dma(ch + NB, b);
+        mfmas(1);
+        SD_ORDER();
+    };
+    const int n_main = nchunks / NB * NB;
+    for (int c0 = 0; c0 < n_main; c0 += NB) {
+#pragma unroll
+        for (int b = 0; b < NB; b++) chunk(c0 + b, b);
+    }
+#pragma unroll
+    for (int b = 0; b < NB - 1; b++)
+        if (n_main + b < nchunks) chunk(n_main + b, b);
+    __builtin_amdgcn_s_waitcnt(0x0f70); // nothing may land in LDS after the block has ended
+    // lane (m' = lane % 32, g = lane / 32) holds columns 8 i + 4 g + 0 .. 3, i = 0 .. 3, of row m'
+    const int m = wr * 32 + lr;
+    if (SW) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int n = n0 + wc * 16 + 8 * h + 4 * lg;
+            if (m >= M || n >= N) continue;
+            float y[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) y[r] = acc[4 * h + r] / (1.0f + expf(-acc[4 * h + r])) * acc[8 + 4 * h + r];
+            uint32_t h0, l0, h1, l1;
+            bf16x2_split(y[0], y[1], h0, l0);
+            bf16x2_split(y[2], y[3], h1, l1);
+            const size_t o = act_index(c_av, m, n, N); // 4 columns inside one K step
+            *(uint2 *)(Cact + o) = make_uint2(h0, h1);
+            *(uint2 *)(Cact + c_av.plane + o) = make_uint2(l0, l1);
+        }
+    } else {
+        const int nb = n0 + wc * 32 + 4 * lg;
+        float *dst = C + (size_t)blockIdx.y * c_split_stride + (size_t)m * N + nb;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (m < M && nb + 8 * i < N) *(f32x4 *)(dst + 8 * i) = (f32x4){acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]};
+        if (ls.p && n0 + wc * 32 < N) { // (uniform; N is a multiple of 32) partials of the wave's 32 columns
+            float mx = acc[0];
+            int ai = nb;
+#pragma unroll
+            for (int e = 1; e < 16; e++)
+                if (acc[e] > mx) mx = acc[e], ai = nb + e / 4 * 8 + e % 4;
+            const float ov = __shfl_xor(mx, 32, 64);
+            const int oi = __shfl_xor(ai, 32, 64);
+            if (ov > mx || (ov == mx && oi < ai)) mx = ov, ai = oi;
+            float ex = 0.f;
+            if (ls.invT > 0.f) {
+#pragma unroll
+                for (int e = 0; e < 16; e++) ex += expf((acc[e] - mx) * ls.invT);
+            }
+            ex += __shfl_xor(ex, 32, 64);
+            if (lg == 0 && m < M) {
+                float *sp = ls.p + ((size_t)m * (N / 32) + n0 / 32 + wc) * 3;
+                sp[0] = mx;
+                sp[1] = ex;
+                sp[2] = __int_as_float(ai);
+            }
+        }
+    }
+}
+
 // Block shape of the wide kernel: NW weight tiles per block and the K splits (nw = 0: not a shape of it).  The estimate
 // is what the busiest compute unit pulls in, in KiB: rounds of blocks over 256 units x K steps per split x (4 NW for the
 // weights + M / 2 for the rows), plus the splits' fp32 slabs, written here and read by the consumer (32 bytes per element
@@ -684,8 +853,8 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
     WidePlan best = {0, 0, 1};
     if (M < 9 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || K < 128) return best;
     // 41 to 48 rows fit one 48-row block of the row-blocked kernel, which stages them once for 128 weight rows: where
-    // its unsplit grid fills the chip it is ahead (gate/up at M = 48: 44.7 against 45.9 us at 4096 / 11008, 55.5 against 65.2
-    // at 5120 / 13824; the 32000-column head 52.8 against 55.0)
+    // its unsplit grid fills the chip it is ahead of this one (gate/up at M = 48: 44.7 against 45.9 us at 4096 / 11008, 55.5 against 65.2
+    // at 5120 / 13824; the 32000-column head 52.8 against 55.0; from a K of 4096 on gemm_lds_kernel has these shapes)
     const int nmat = mode == GEMM_SWIGLU ? 2 : 1, rows_w = N * nmat, steps = K / 128;
     if (M > 40 && M <= 48 && steps >= 16 && rows_w % 128 == 0 && n_per_seg % 128 == 0 && N == n_per_seg && rows_w / 128 >= 160) return best;
     float best_cost = 0.f;
@@ -759,6 +928,39 @@ static int tile_splits(int ncol, int nmb, int slots, int steps)
     }
     return best;
 }
+// Block shape and K splits of gemm_lds_kernel (cols = 0: not a shape of it).  Blocks of 32 rows up to M = 32, of 64 above; 96 or 128
+// weight rows; the estimate is rounds of blocks over 256 units x (K steps per split + 2), a step of 128 weight rows
+// 1.05 of one of 96, plus the splits' fp32 slabs; no split of fewer than four steps.  Over QKV / O / gate-up / down / LM head of the
+// 4096- and 5120-wide models at 20 to 64 rows its choice is the fastest of the sweep (both widths, 1 to 8 splits) or within 3 %
+// but for one (O at M = 48: 13.0 against 11.7).
+// Up to 16 rows gemm_wide_kernel is ahead (QKV 17.3 against 19.0, O 7.1 against 7.9 at M = 16), and so it is on narrower
+// models (2048 wide, M = 32: gate/up 15.6 against 16.4, down 7.6 against 9.3), whose few K steps don't repay filling the ring.
+struct LdsPlan {
+    int cols, ncol, ks;
+};
+static LdsPlan lds_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks, int max_ks = 8)
+{
+    LdsPlan best = {0, 0, 1};
+    const int rows_w = N * (mode == GEMM_SWIGLU ? 2 : 1), steps = K / 128;
+    if (M < 17 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || steps < 32 || rows_w < 4096) return best;
+    float best_cost = 0.f;
+    for (int cols = 96; cols <= 128; cols += 32) {
+        const int ncol = (rows_w + cols - 1) / cols;
+        for (int ks = force_ks > 0 ? force_ks : 1; ks <= (force_ks > 0 ? force_ks : mode == GEMM_SWIGLU ? 1 : max_ks); ks++) {
+            int kps, ny;
+            split_geometry(K, ks, &kps, &ny);
+            if (force_ks <= 0 && ks > 1 && (ny != ks || steps / ks < 4)) continue;
+            const float cost = (float)((ncol * ny + 255) / 256) * (float)(kps / 128 + 2) * (cols == 128 ? 1.05f : 1.f) +
+                               (ny > 1 ? 0.2f * 4e-6f * (float)ny * M * N : 0.f);
+            if (best.cols == 0 || cost < best_cost) {
+                best = {cols, ncol, ny};
+                best_cost = cost;
+            }
+        }
+    }
+    return best;
+}
+
 int g_force_tile_cols = 0; // weight rows per 96-row block forced by option "gemm_tile_cols" (0 = automatic)
 static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K)
 {
@@ -882,6 +1084,21 @@ static hipError_t wide_launch(hipStream_t s, WidePlan p, const uint16_t *a, ActV
     return hipGetLastError();
 }
 
+template <int MODE, bool NT>
+static hipError_t lds_launch(hipStream_t s, LdsPlan p, const uint16_t *a, ActView a_av, WeightSeg w, int M, int N, int K, float *C,
+                             size_t c_split_stride, uint16_t *ca, ActView c_av, LmStats ls)
+{
+    int kps, ny;
+    split_geometry(K, p.ks, &kps, &ny);
+#define SD_LDS(WR, WC, NB)                                                                                                           hipLaunchKernelGGL((gemm_lds_kernel<MODE, WR, WC, NB, NT>), dim3(p.ncol, ny), dim3(WR * WC * 64), 0, s, a, a_av, w, M, N, K,                        kps, C, c_split_stride, ca, c_av, ls)
+    if (M <= 32 && p.cols == 96) SD_LDS(1, 3, 5);
+    else if (M <= 32) SD_LDS(1, 4, 4);
+    else if (p.cols == 96) SD_LDS(2, 3, 3);
+    else SD_LDS(2, 4, 4);
+#undef SD_LDS
+    return hipGetLastError();
+}
+
 int g_force_splits[3] = {0, 0, 0}; // [mode] -> K splits (0 = automatic); a tuning knob for sweeps
 
 // K splits of the row-blocked kernel.  Measured at M = 192: a block costs about five K steps of fixed time, so one round
@@ -908,6 +1125,8 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded
     const int steps = K / 128;
     int ks;
     if (!folded) {
+        const LdsPlan lp = lds_plan(mode, M, N, K, n_per_seg, 0, max_ks);
+        if (lp.cols) return lp.ks;
         const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0, max_ks);
         if (wp.nw) return wp.ks;
     }
@@ -965,6 +1184,16 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
     const uint16_t *a = (const uint16_t *)A;
     uint16_t *ca = (uint16_t *)Cact;
     if (M > 8 && !folded) {
+        const LdsPlan lp = lds_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
+        if (lp.cols) {
+            const LmStats lsk = mode == GEMM_STORE && lp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
+            if (ls_done && lsk.p) *ls_done = 1;
+            if (mode == GEMM_SWIGLU)
+                return w.nt ? lds_launch<GEMM_SWIGLU, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
+                            : lds_launch<GEMM_SWIGLU, false>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
+            return w.nt ? lds_launch<GEMM_STORE, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
+                        : lds_launch<GEMM_STORE, false>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
+        }
         const WidePlan wp = wide_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
         if (wp.nw) {
             const LmStats lsk = mode == GEMM_STORE && wp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)

@@ -325,6 +325,65 @@ def test_wide_few_row_gemm_matches_reference_kernels(d, F, V):
     gt.close()
 
 
+@pytest.mark.parametrize("F,V", [(2048, 4128), (4352, 4112), (4224, 8224)])
+def test_few_row_gemm_of_wide_layers_matches_reference_kernels(F, V):
+    """17 to 64 rows of layers 4096 wide take the few-row GEMM that stages both operands: the edges of its 32- and 64-row
+    blocks, K ranges that its splits and its ring of chunks don't divide (33 and 34 steps), numbers of weight rows that no
+    block divides (8704, 4112, 8224), a model small enough for cached weights (the first) and the LM head's softmax partials
+    (4128, 8224).  Same caches on both sides; fp32 sums in another order, single cache elements one bf16 step."""
+    import dataclasses
+    st_ = dataclasses.replace(dg.SHAPES["small_target_bf16"], n_layers=1, d_model=4096, n_heads=32, d_ffn=F, vocab=V, name=f"rows_{F}")
+    gt = api.Model(st_, dg.make_weights(st_, 97, BF16_LM_SCALE), max_rows=64, max_pos=128)
+    try:
+        for B, gamma in ((16, 0), (17, 0), (8, 3), (11, 2), (8, 5), (8, 7)):
+            M = B * (gamma + 1)
+            _say(f"few rows of wide layers, F={F} V={V} rows={M}")
+            lens = dg.make_prompt_lengths(97 + M, B, 3, 20)
+            prompts = [[int(t) for t in dg.make_prompt(97, b, int(lens[b]), V)] for b in range(B)]
+            ctx = api.Context([int(l) + 16 for l in lens])
+            ctx.attach(gt)
+            H.gpu_prefill(ctx, [gt], prompts)
+            cand = H.dev(dg.make_prompt(98, B, max(1, B * gamma), V)[:B * gamma].reshape(B, gamma).astype(np.int32))
+            na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+            outs = []
+            for force in (0, 1):
+                api.set_option("force_generic", force)
+                api.sd_verify(gt, ctx, None, B, gamma, 0.0, cand if gamma else None, None, None, na, nx, commit=False)
+                torch.cuda.synchronize()
+                outs.append((gt.last_logits().cpu().numpy(), gt.debug_read("act", M), na.cpu().numpy(), nx.cpu().numpy()))
+                api.set_option("force_generic", 0)
+                for b in range(B):
+                    ctx.truncate(gt, b, int(lens[b]) - 1)
+            ctx.close()
+            for got, ref in zip(outs[0][:2], outs[1][:2]):
+                assert np.isfinite(got).all() and np.abs(got - ref).max() < 5e-4 * np.abs(ref).max(), (M, np.abs(got - ref).max() / np.abs(ref).max())
+            for b in range(B):   # the first rejected row's greedy token, from the partials or the whole row of this pass's own logits
+                rows = outs[0][0].reshape(B, gamma + 1, V)[b].argmax(-1)
+                want = next((i for i in range(gamma) if rows[i] != int(cand[b, i])), gamma)
+                assert outs[0][2][b] == want and outs[0][3][b] == rows[want]
+        if V % 32 == 0:   # the softmax partials at a temperature, against the sampler that reads the whole row
+            B, gamma = 20, 2
+            prompts = [[int(t) for t in dg.make_prompt(99, b, 9 + b, V)] for b in range(B)]
+            u = H.dev(np.stack([dg.make_uniforms(99, dg.DRAFT_STREAM, b, 0, gamma) for b in range(B)]))
+            outs = []
+            for force in (0, 4):
+                api.set_option("force_generic", force)
+                ctx = api.Context([64] * B)
+                ctx.attach(gt)
+                H.gpu_prefill(ctx, [gt], prompts)
+                cand = torch.zeros((B, gamma), dtype=torch.int32, device="cuda")
+                q = torch.zeros((B, gamma, V), device="cuda")
+                api.sd_draft(gt, ctx, None, B, gamma, 0.8, u, cand, q)
+                ctx.sync()
+                outs.append((cand.cpu().numpy(), q.cpu().numpy()))
+                ctx.close()
+                api.set_option("force_generic", 0)
+            assert np.array_equal(outs[0][0], outs[1][0]) and np.abs(outs[0][1] - outs[1][1]).max() < 1e-6
+    finally:
+        api.set_option("force_generic", 0)
+    gt.close()
+
+
 def test_48_row_blocks_match_reference_kernels():
     """41 to 48 rows of a gate/up pair or logits matrix of 20480 weight rows and more, K of 2048 and more, run on the
     48-row blocks of the row-blocked kernel; 40 and 49 rows of the same shapes on the wide few-row kernel.  Logits and SwiGLU
