@@ -884,7 +884,7 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
 // 9; 768 wide 81.6 / 78.8 at 9, 89.0 / 82.5 at 16, 120 / 96 at 32.
 bool gemm_normfold_pays(int M, int d) { return M <= 8 || (M <= 10 && gemm_normfold_blocks(d) == 256); }
 
-// Block shapes of the row-blocked kernel.  More than 64 rows: 96 rows x 256 columns (4 waves x 4 tiles; chunks
+// Block shapes of the row-blocked kernel (unsplit: the launch has one K split).  More than 64 rows: 96 rows x 256 columns (4 waves x 4 tiles; chunks
 // of half a K step) - the bytes a block pulls through L2 per MFMA halve against 48 x 128, which is what
 // bounds these GEMMs - or x 192 columns (3 tiles per wave) where that fills the 256 compute units better
 // (QKV at M = 192: 128 blocks x 2 K splits instead of 96 x 2); 64-row blocks of the same widths where they
@@ -962,7 +962,7 @@ static LdsPlan lds_plan(int mode, int M, int N, int K, int n_per_seg, int force_
 }
 
 int g_force_tile_cols = 0; // weight rows per 96-row block forced by option "gemm_tile_cols" (0 = automatic)
-static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K)
+static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K, bool unsplit)
 {
     const int out_per_col = mode == GEMM_SWIGLU ? 2 : 1; // weight rows per output column
     const int rows_w = N * out_per_col;                  // weight rows streamed
@@ -1000,12 +1000,15 @@ static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K)
         if (g_force_tile_cols == 192 && ok192) cols = 192;
         if (g_force_tile_cols == 128 && ok128) cols = 128;
         if (cols) {
-            // 64-row blocks when they pad M less (M = 128: 2 x 64 instead of 96 + 32) and do not cost more rounds
+            // 64-row blocks when they pad M less (M = 128: 2 x 64 instead of 96 + 32) and do not cost more rounds; from 65 to 96
+            // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (115 and 125
+            // blocks at 4096 wide), and two of 64 rows pull little more than one of 96 (weights outweigh rows in every block).
+            // Verify pass of two 4096-wide layers 518 -> 500 us at 72 rows, 544 -> 525 at 96; one 5120-wide layer 392 -> 385, 409 -> 402
             const int ncol = (rows_w + cols - 1) / cols, nmb64 = (M + 63) / 64;
             auto rounds = [&](int rb) {
                 return die_rounds(ncol, rb, mode == GEMM_SWIGLU ? 1 : one_round_splits(ncol, rb, 256, steps), 256);
             };
-            const bool use64 = nmb64 * 64 < nmb * 96 && rounds(nmb64) * 64 <= rounds(nmb) * 96;
+            const bool use64 = (nmb64 * 64 < nmb * 96 || (unsplit && M <= 96)) && rounds(nmb64) * 64 <= rounds(nmb) * 96;
             return use64 ? TileShape{cols, 64, ncol, nmb64, 256} : TileShape{cols, 96, ncol, nmb, 256};
         }
     }
@@ -1020,7 +1023,7 @@ static hipError_t tile_launch(hipStream_t s, const uint16_t *a, ActView a_av, We
 {
     int kps, ny;
     split_geometry(K, ks, &kps, &ny);
-    const TileShape t = tile_shape(MODE, M, N, w.n_per_seg, K);
+    const TileShape t = tile_shape(MODE, M, N, w.n_per_seg, K, ks == 1);
     if (!t.cols) return hipErrorNotSupported;
     constexpr int OUT_PER_COL = MODE == GEMM_SWIGLU ? 2 : 1;
     const int ntiles = (N * OUT_PER_COL + t.cols - 1) / t.cols, nmb = (M + t.bm - 1) / t.bm;
@@ -1106,7 +1109,7 @@ int g_force_splits[3] = {0, 0, 0}; // [mode] -> K splits (0 = automatic); a tuni
 static int tile_ks(int mode, int M, int N, int K, int n_per_seg)
 {
     if (mode == GEMM_SWIGLU) return 1;
-    const TileShape t = tile_shape(mode, M, N, n_per_seg, K);
+    const TileShape t = tile_shape(mode, M, N, n_per_seg, K, false);
     int kps, ny;
     split_geometry(K, g_force_splits[mode] > 0 ? g_force_splits[mode] : t.cols ? tile_splits(t.ncol, t.nmb, t.slots, K / 128) : 1, &kps, &ny);
     return ny;
@@ -1145,9 +1148,9 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded
 int gemm_tile_plan(int mode, int M, int N, int K, int n_per_seg, int plan[6])
 {
     if (M <= 32 || K < 128 || K % 128 != 0 || (mode != GEMM_STORE && mode != GEMM_SWIGLU)) return -1;
-    const TileShape t = tile_shape(mode, M, N, n_per_seg, K);
-    if (!t.cols) return -1;
     const int ks = tile_ks(mode, M, N, K, n_per_seg);
+    const TileShape t = tile_shape(mode, M, N, n_per_seg, K, ks == 1);
+    if (!t.cols) return -1;
     plan[0] = t.cols;
     plan[1] = t.bm;
     plan[2] = t.ncol;

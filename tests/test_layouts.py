@@ -108,6 +108,16 @@ def test_row_blocked_gemm_plans_fit_the_busiest_die_in_one_round():
     assert api.gemm_plan(0, 768, 12288, 4096, 4096)[4] == 1 and api.gemm_plan(0, 1024, 12288, 4096, 4096)[4] == 1   # whole rounds: no split
 
 
+def test_unsplit_row_blocked_gemms_of_65_to_96_rows_run_as_two_row_blocks():
+    """Gate/up pairs and logits of 65 to 96 rows: two 64-row blocks per column tile while that is one round on the busiest
+    die, as at 97 to 128 rows; projections that split K, and grids that would run a second round, keep one 96-row block."""
+    for m in (65, 72, 96, 97, 128):
+        assert api.gemm_plan(2, m, 11008, 4096) == (192, 64, 115, 2, 1, 30)
+    for m in (65, 72, 96):
+        assert api.gemm_plan(2, m, 13824, 5120)[:4] == (192, 96, 144, 1)        # 288 blocks of 64 rows: two rounds
+        assert api.gemm_plan(0, m, 12288, 4096, 4096)[1] == 96 and api.gemm_plan(0, m, 4096, 11008)[1] == 96
+
+
 def test_k_splits_follow_the_kernel_that_runs_and_the_slabs_there_is_room_for():
     """K splits of the few-row GEMMs (host logic only).  A launch that is part of a split norm runs on the K-split kernel,
     whose four waves share a split's K steps: none may be left without one, and the plan of the wide kernel, which
