@@ -851,7 +851,7 @@ struct WidePlan {
 static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks, int max_ks = 8)
 {
     WidePlan best = {0, 0, 1};
-    if (M < 9 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || K < 128) return best;
+    if (M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || K < 128) return best;
     // 41 to 48 rows fit one 48-row block of the row-blocked kernel, which stages them once for 128 weight rows: where
     // its unsplit grid fills the chip it is ahead of this one (gate/up at M = 48: 44.7 against 45.9 us at 4096 / 11008, 55.5 against 65.2
     // at 5120 / 13824; the 32000-column head 52.8 against 55.0; from a K of 4096 on gemm_lds_kernel has these shapes)
@@ -1127,7 +1127,7 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded
     }
     const int steps = K / 128;
     int ks;
-    if (!folded) {
+    if (M > 8 && !folded) {
         const LdsPlan lp = lds_plan(mode, M, N, K, n_per_seg, 0, max_ks);
         if (lp.cols) return lp.ks;
         const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0, max_ks);
@@ -1186,7 +1186,10 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
     if (mode == GEMM_SWIGLU && (!c_av.sm || (c_av.plane & 7) || N % 128 != 0 || ((uintptr_t)Cact & 15))) return hipErrorNotSupported;
     const uint16_t *a = (const uint16_t *)A;
     uint16_t *ca = (uint16_t *)Cact;
-    if (M > 8 && !folded) {
+    // (weights that stay cached - the instances of the wide kernel that carry an update are for those - in blocks of two or four
+    // tiles, as the projections of small models run; with an update to carry, 8 rows and fewer run on it too)
+    const bool can_carry = mode == GEMM_STORE && lora && lora_done && !w.nt && lora_valid(M, K, *lora);
+    if ((M > 8 || can_carry) && !folded) {
         const LdsPlan lp = lds_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
         if (lp.cols) {
             const LmStats lsk = mode == GEMM_STORE && lp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
@@ -1198,12 +1201,11 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
                         : lds_launch<GEMM_STORE, false>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
         }
         const WidePlan wp = wide_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
-        if (wp.nw) {
+        if (wp.nw && (M > 8 || wp.nw <= 4)) {
             const LmStats lsk = mode == GEMM_STORE && wp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
             if (ls_done && lsk.p) *ls_done = 1;
             if (mode == GEMM_SWIGLU) return wide_launch<2>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
-            // (weights that stay cached - the instances of the kernel that carry an update are for those - in blocks of two or four tiles, as the projections of small models run)
-            const bool carry = lora && lora_done && !w.nt && wp.nw <= 4 && lora_valid(M, K, *lora);
+            const bool carry = can_carry && wp.nw <= 4;
             if (carry) *lora_done = 1;
             return wide_launch<1>(s, wp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk, carry ? lora : nullptr);
         }

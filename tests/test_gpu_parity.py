@@ -2059,7 +2059,7 @@ def test_set_tokens_sets_what_is_named_and_nothing_else():
 
 @pytest.mark.parametrize("d,heads,rank", [(768, 12, 8), (768, 12, 1), (1024, 16, 3), (1024, 16, 16), (128, 2, 12), (896, 14, 13)])
 def test_low_rank_update_carried_by_the_gemm_launch_matches_reference_kernels(d, heads, rank):
-    """9 to 64 rows: the low-rank update runs as extra blocks of the QKV and O launches (one part of 768 outputs, a partial one, two
+    """1 to 64 rows: the low-rank update runs as extra blocks of the QKV and O launches (one part of 768 outputs, a partial one, two
     parts, ranks that are and are not multiples of four), sequences with different adapters and without, against the separate
     launches of the reference path."""
     import dataclasses
@@ -2067,7 +2067,7 @@ def test_low_rank_update_carried_by_the_gemm_launch_matches_reference_kernels(d,
     st_ = dataclasses.replace(dg.SHAPES["small_draft_bf16"], n_layers=2, d_model=d, n_heads=heads, d_ffn=512, name=f"lora_{d}")
     gm = api.Model(st_, dg.make_weights(st_, 95, BF16_LM_SCALE), max_rows=64, max_pos=128)
     gm.set_lora(dg.make_lora(st_, 96, 3, rank, 0.05, 0.05), 2.0)
-    for B, gamma in ((3, 2), (12, 1), (16, 3), (9, 6)):
+    for B, gamma in ((1, 1), (2, 3), (3, 2), (12, 1), (16, 3), (9, 6)):
         lens = dg.make_prompt_lengths(95, B, 5, 60)
         prompts = [[int(t) for t in dg.make_prompt(95, b, int(lens[b]), st_.vocab)] for b in range(B)]
         cand = H.dev(dg.make_prompt(97, 0, B * gamma, st_.vocab).reshape(B, gamma).astype(np.int32))
