@@ -430,7 +430,9 @@ int sd_debug_stream_read(const void *buf, size_t bytes, uint32_t *scratch_word, 
  * blocks of its own (the split kernel of the decode path).
  * option "attn_waves" = 4 or 8 forces the block shape of the fused attention kernel, without helper
  * blocks (0 = automatic: 4-wave blocks when (sequence, head) pairs oversubscribe the chip and
- * contexts are short).
+ * contexts are short; four-wave blocks also keep every pair in one block).
+ * option "attn_split" = 1 .. 32 forces the number of blocks that share one (sequence, head) pair's context in the
+ * fused attention kernel (0 = automatic: more than one where pairs leave compute units idle and contexts are long).
  * option "stream_read_nt" = 0 makes sd_debug_stream_read a grid-strided read with ordinary loads;
  * 1 (the default) gives every block one contiguous range and reads it with the nontemporal hint,
  * the fastest pattern measured on this part; adding 2 to either turns on a checking mode in which the XOR

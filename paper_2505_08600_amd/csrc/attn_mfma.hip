@@ -519,7 +519,7 @@ struct OProj {
     size_t slab_stride; // rows * d_model
     int32_t d_model;
 };
-// SPLIT (long contexts, few pairs): S blocks per pair, each with T consecutive tiles of it (a shorter sequence's last blocks have
+// SPLIT (few pairs, contexts of some 500 tokens and more): S blocks per pair, each with T consecutive tiles of it (a shorter sequence's last blocks have
 // none and leave at once).  A block rotates the query rows for itself, appends the new rows that fall into its tiles - so no
 // block reads cache rows another one writes - and leaves (O, max, sum) of its tiles in `part`; the block of a pair that
 // arrives last, by a counter, merges the parts in order.  No block waits for another.  The parts cross the dies' L2s: they
@@ -809,20 +809,30 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     if (R < 1 || R > 16 || (hd != 64 && hd != 128) || n_slabs < 1 || n_slabs > 8) return hipErrorNotSupported;
     if (n_seq > 65535 || H > 65535) return hipErrorNotSupported;
     const int tiles_upper = (len_upper + AT_TILE - 1) / AT_TILE;
-    // one block per (sequence, head): fine when every wave has at most a few tiles anyway, or when those blocks
-    // alone fill the chip and the contexts stay below about 2000 tokens - beyond that the split kernel, whose blocks
-    // only stream, is faster even with its RoPE and combine launches (32 x 2048 tokens, 40 heads: 20.1 against
-    // 20.4 ms for the whole verify pass; 64 sequences of 1024 - 8192 tokens: 38.0 against 38.6; at 32 sequences of
-    // up to 1024 tokens the fused kernel wins, 8.26 against 8.50 ms)
     const AttnSplit none = {nullptr, nullptr, 1, 1};
+    const bool can_oproj = wo_tiled && oslab && stream_nt == 0 && d_model % 128 == 0 && d_model == H * hd &&
+                           d_model <= 16 * 8 * (hd == 64 ? 8 : 4) && H <= SD_OPROJ_MAX_HEADS && ((uintptr_t)wo_tiled & 15) == 0;
     {
+        // Blocks per (sequence, head): one draws K and V at 50 - 60 GB/s however long the context, so where pairs leave units
+        // idle the context is split over S blocks that meet over a counter - which costs the pair some 2 us and, at head
+        // width 128, the helpers below.  Whole passes, one block -> S blocks a pair (us; 7B shape unless said otherwise):
+        //  * room for six blocks a pair and more (32 pairs): eight layers 737 -> 735 at 384 tokens, 746 -> 740 at 512, 755 -> 741
+        //    at 640 with S = 4, 732 and 737 at 128 and 256 (720 and 729 without); a draft model with 32 pairs 961 ->
+        //    948 at 384, 972 -> 962, 997 -> 965, 1003 -> 967 at 760 (S = 8: 992).  A model whose blocks apply the output
+        //    projection as well loses that launch again: 318 -> 324 at 256 tokens, 324 -> 328 at 512, 329 -> 326 at 640, 334 -> 328 at 760;
+        //  * room for three to five (64 pairs, four layers): 477 -> 477 at 512, 482 -> 479 at 640, 477 -> 470 at 800, 526 -> 484 at 1480;
+        //  * room for two (128 pairs, where one block has one helper): 501 -> 518 at 800, 517 -> 523 at 1000, 540 -> 526 at 1250,
+        //    583 -> 533 at 1480; 96 pairs 499 -> 508, 502 -> 515 at 1250, 573 -> 520 at 1480;
+        //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are): 160 pairs 622 -> 589 at
+        //    1480, 256 pairs 728 -> 699; from 512 pairs on the three launches, whose blocks only stream, are ahead.
         const long pairs = (long)n_seq * H;
         const int fit = (int)std::max(1L, std::min(8L, 256 / pairs));
         int S = 1;
         if (g_force_attn_split) S = g_force_attn_split;
-        else if (g_force_attn_waves) S = 1;
+        else if (g_force_attn_waves == 4) S = 1;
         else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
-        else if (tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
+        else if (tiles_upper > (fit >= 3 ? 24 : 40)) S = std::min(fit, tiles_upper / 4);
+        else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 14)) S = 4;
         if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {
             const AttnSplit sp = {part, arrivals, S, (tiles_upper + S - 1) / S};
 #define SD_FUSED_SPLIT(HD_, NT_)                                                                                              \
@@ -837,6 +847,10 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
             return hipGetLastError();
         }
     }
+    // one block per pair where those blocks alone fill the chip, up to about 2000 tokens - beyond that the split kernel, whose
+    // blocks only stream, is faster even with its RoPE and combine launches (32 x 2048 tokens, 40 heads: 20.1 against
+    // 20.4 ms for the whole verify pass; 64 sequences of 1024 - 8192 tokens: 38.0 against 38.6; at 32 sequences of
+    // up to 1024 tokens the fused kernel wins, 8.26 against 8.50 ms)
     if (!(tiles_upper <= 48 || ((long)n_seq * H >= 512 && tiles_upper < 64))) return hipErrorNotSupported;
     // with more than two blocks per compute unit and short contexts the 4-wave shape (two resident blocks
     // per unit) hides each block's prologue and merge behind its neighbour's streaming; from about 40 tiles
@@ -859,9 +873,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
     // output projection inside the block: small models in few blocks (each block reads its head's slice of Wo;
     // 8 waves x 8 (head width 64) or 4 (128) column tiles bound d_model), H slabs for the add + norm kernel
     const size_t rows = (size_t)n_seq * R;
-    const bool oproj = wo_tiled && oslab && !many && stream_nt == 0 && d_model % 128 == 0 && d_model == H * hd &&
-                       d_model <= 16 * 8 * (hd == 64 ? 8 : 4) && H <= SD_OPROJ_MAX_HEADS && (long)n_seq * H < 512 &&
-                       (size_t)H * rows * d_model <= oslab_floats && ((uintptr_t)wo_tiled & 15) == 0;
+    const bool oproj = can_oproj && !many && (long)n_seq * H < 512 && (size_t)H * rows * d_model <= oslab_floats;
     const OProj op = {(const uint16_t *)wo_tiled, oslab, rows * (size_t)d_model, d_model};
     if (oproj) {
         if (hd == 128)
