@@ -31,6 +31,15 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8; // explicit LDS address space: ds_read, not flat loads
 
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void global_cvoid;
+// Pins the program order of the memory operations around it, for the optimiser and the scheduler alike.
+#define SD_ORDER()                          \
+    do {                                    \
+        asm volatile("" ::: "memory");       \
+        __builtin_amdgcn_sched_barrier(0);  \
+    } while (0)
+
 #define AT_WAVES 4
 #define AT_TILE 32
 #define AT_NEG (-1.0e30f)
@@ -74,19 +83,19 @@ __device__ __forceinline__ float tile_softmax(const f32x4 &sa, const f32x4 &sb, 
     float mx = AT_NEG;
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-        float v = (e < 4 ? sa[e] : sb[e - 4]) * sl2;
+        float v = e < 4 ? sa[e] : sb[e - 4];
         if (MASKED) v = tok0 + e <= vis ? v : AT_NEG;
         sc[e] = v;
         mx = fmaxf(mx, v);
     }
-    mx = rows_max(mx);
+    mx = rows_max(mx) * sl2;
     const float m_new = fmaxf(m_run, mx);
     const float corr = __builtin_amdgcn_exp2f(m_run - m_new); // 1 when nothing changed, 0 from the initial state
     float psum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-        float p0 = __builtin_amdgcn_exp2f(sc[e] - m_new), p1 = __builtin_amdgcn_exp2f(sc[e + 1] - m_new);
-        if (MASKED) { // (a row that has seen nothing yet has m_new = AT_NEG: its differences are 0, not -inf)
+        float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, -m_new)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], sl2, -m_new));
+        if (MASKED) { // (of a row that has seen nothing yet the difference is one of two large numbers)
             p0 = sc[e] > 0.5f * AT_NEG ? p0 : 0.f;
             p1 = sc[e + 1] > 0.5f * AT_NEG ? p1 : 0.f;
         }
@@ -307,18 +316,22 @@ __global__ void attn_combine_kernel(const float *__restrict__ part, PlanView pv,
 }
 
 // Causal attention of a prompt (prefill): WG consecutive 16-row groups of ONE sequence and head per block, one
-// group per wave.  With a block per group every group streams the whole prefix through L2 again (an 8192-token
-// prompt at head width 128: 1.1 TB per 32 layers, the ceiling of what the L2s deliver); here the block stages
-// each 32-token K / V tile in LDS once - double buffered, the loads of the next tile in flight while the
-// current one is consumed - and every wave takes its operands from there, at the offsets it would have used in
-// global memory (the tiles are stored in operand order, so the LDS reads are lane-linear), which divides the L2
-// traffic by WG and leaves a wave ~100 registers, so that several blocks share a compute unit and cover each
-// other's softmax and dependent MFMA chains.  The rows of all groups are in the cache before the launch
-// (rope_append_kernel); wave w sees tokens <= kv0_w + row.  No merge between waves: each owns its rows.  With
-// S > 1 the tile range is split over grid.z and attn_combine_kernel merges the partials (same layout as the
+// group per wave of each of the block's WS sets of waves.  With a block per group every group streams the whole prefix
+// through L2 again (an 8192-token prompt at head width 128: 1.1 TB per 32 layers, the ceiling of what the L2s deliver);
+// here the block stages each 32-token K / V tile in LDS once, straight from memory, and every wave of a set takes its
+// operands from there, at the offsets it would have used in global memory, which divides the L2 traffic by WG.
+// Bound: the matrix units and the softmax beside them at the clock the power budget leaves (257 TFLOP of products in 240 us for
+// 1024 rows behind 7168 tokens, 1.07 PFLOP/s, what the GEMMs of this shape issue) - if four waves a SIMD cover each other's
+// chains of LDS reads, score products, softmax and output products.  1024 rows of 32 heads are only two blocks of WG waves per
+// compute unit, so a block's tiles are dealt out to WS sets of waves, each with a running softmax and staging buffers of
+// its own, which meet in LDS at the end.  8192 tokens at 1024 rows, 32 heads of 128, all forwards of a layer: 1291 us with one set
+// and tiles staged through registers, 1202 staged directly (any ring depth), 1090 with two sets; two groups of rows per wave,
+// which halve the LDS reads and the waves, 1202.
+// The rows of all groups are in the cache before the launch (rope_append_kernel); wave w sees tokens <= kv0_w + row.  With
+// S > 1 the tile range is split over grid.z as well and attn_combine_kernel merges the partials (same layout as the
 // split kernel's).  Blocks start with the longest prefixes first.
-template <int HD, int WG>
-__global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t *__restrict__ qbuf, ActView q_av,
+template <int HD, int WG, int WS>
+__global__ __launch_bounds__(WG * WS * 64, 4) void attn_prefill_kernel(const uint16_t *__restrict__ qbuf, ActView q_av,
                                                                const uint16_t *__restrict__ Kl,
                                                                const uint16_t *__restrict__ Vtl, PlanView pv, CtxView cv,
                                                                int R, int H, int G, int n_seq, int64_t total_cap, int S,
@@ -328,13 +341,15 @@ __global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t
     constexpr int NC = HD / 32, ND = HD / 16;
     constexpr int TILE = AT_TILE * HD;                   // elements of one K (or V) tile
     constexpr int NLD = (2 * TILE * 2) / (16 * WG * 64); // 16-byte pieces per thread and tile (K and V together)
-    static_assert(NLD >= 1 && NLD * 16 * WG * 64 == 2 * TILE * 2, "tile does not divide over the block");
-    __shared__ __attribute__((aligned(16))) uint16_t sKV[2][2 * TILE]; // [buffer][K tile, then V tile]
+    static_assert(NLD >= 1 && NLD * 16 * WG * 64 == 2 * TILE * 2, "tile does not divide over a set");
+    static_assert(WS == 2 && WG * (ND * 4 + 2) * 256 <= 2 * WS * 2 * TILE * 2, "the second set's results fit the staging buffers");
+    __shared__ __attribute__((aligned(16))) uint16_t sKV[2][WS][2 * TILE]; // [buffer][set][K tile, then V tile]
     const int h = blockIdx.x;
     const int n_gb = (G + WG - 1) / WG;
     const int seq = blockIdx.y % n_seq, gb = n_gb - 1 - blockIdx.y / n_seq; // later groups (longer prefixes) first
     const int s = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % WG;
+    const int set = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / WG, tid = threadIdx.x & (WG * 64 - 1);
     const int qi = lane & 15, grp = lane >> 4;
     const int j0 = seq * G + gb * WG;
     const bool w_valid = gb * WG + wave < G;
@@ -371,34 +386,29 @@ __global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t
     f32x4 o[ND];
 #pragma unroll
     for (int d = 0; d < ND; d++) o[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // staging: piece c = threadIdx.x + k * threads of the tile pair; pieces 0 .. TILE/8-1 are K, the rest V.  Two
-    // register sets: the loads of tiles t + 1 and t + 2 are in flight while tile t is consumed (one tile ahead left
-    // every iteration waiting for most of a memory round trip)
-    bf16x8 st0[NLD], st1[NLD];
-    // The K tile is stored in operand order already: piece c goes to LDS position c and a fragment read is
+    // Staging: piece c = tid + k * threads of a set's tile pair (pieces 0 .. TILE/8-1 are K, the rest V) goes to LDS position c;
+    // the set's next tile is in flight while the current one is consumed.
+    // The K tile is stored in operand order already: a fragment read is
     // lane-linear.  The V^T tile is [dim][32 tokens] (64-byte rows), and lane (qi, grp) of a fragment read wants piece
     // grp of row 16 d + qi: read from a row-major copy, such reads hit the banks unevenly (80 % of the LDS cycles were
     // conflict cycles).  So the thread that fills LDS position 64 d + l of the V part fetches the piece lane l of
     // fragment d will want - row 16 d + l % 16, piece l / 16.  The lanes of a wave still cover the same contiguous
     // KiB of global memory, only in another order, and both the LDS writes and the fragment reads are linear.
-    auto fetch = [&](int t, bf16x8 *st) {
+    auto fetch = [&](int t, int b) {
+        const int tt = min(t, t_end - 1); // (a set without a tile left re-reads the last one and leaves it)
 #pragma unroll
         for (int k = 0; k < NLD; k++) {
-            const int c = threadIdx.x + k * (WG * 64);
+            const int c = tid + k * (WG * 64);
             const int cv = c - TILE / 8, l = cv & 63;
-            const uint16_t *src = c < TILE / 8 ? K + (size_t)t * TILE + c * 8
-                                               : Vt + (size_t)t * TILE + ((((cv >> 6) * 16 + (l & 15)) << 2) + (l >> 4)) * 8;
-            st[k] = *(const bf16x8 *)src;
+            const uint16_t *src = c < TILE / 8 ? K + (size_t)tt * TILE + c * 8
+                                               : Vt + (size_t)tt * TILE + ((((cv >> 6) * 16 + (l & 15)) << 2) + (l >> 4)) * 8;
+            __builtin_amdgcn_global_load_lds((global_cvoid *)src, (lds_void *)&sKV[b][set][(wave * 64 + k * (WG * 64)) * 8], 16, 0, 0);
         }
     };
-    auto stash = [&](int b, const bf16x8 *st) {
-#pragma unroll
-        for (int k = 0; k < NLD; k++) *(lds_bf16x8 *)(lds_bf16x8 *)&sKV[b][(threadIdx.x + k * (WG * 64)) * 8] = st[k];
-    };
     auto consume = [&](int t, int b) {
-    if (t * AT_TILE <= vis_wave) { // (uniform over the wave) tiles past the wave's last row hold nothing it sees
-        const uint16_t *kp = &sKV[b][lane * 8];
-        const uint16_t *vp = &sKV[b][TILE + lane * 8]; // (fragment d: + 512 d elements)
+    if (t < t_end && t * AT_TILE <= vis_wave) { // (uniform over the wave) tiles past the wave's last row hold nothing it sees
+        const uint16_t *kp = &sKV[b][set][lane * 8];
+        const uint16_t *vp = &sKV[b][set][TILE + lane * 8]; // (fragment d: + 512 d elements)
         // all K fragments are requested before the first product, and half of the V fragments behind the score
         // products (into the registers the K fragments leave), so that the LDS round trips run under the MFMAs and
         // the softmax instead of in front of every pair of products
@@ -414,7 +424,7 @@ __global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t
             sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * c + 1], ql[c], sb, 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int NVH = ND / 2; // (all of them would not fit three waves per SIMD without spilling)
+        constexpr int NVH = ND / 2; // (all of them would not fit four waves per SIMD without spilling)
         bf16x8 vf[NVH];
 #pragma unroll
         for (int d = 0; d < NVH; d++) vf[d] = *(const lds_bf16x8 *)(const lds_bf16x8 *)(vp + d * 512);
@@ -433,24 +443,36 @@ __global__ __launch_bounds__(WG * 64, 3) void attn_prefill_kernel(const uint16_t
         }
     }
     };
-    // one step: tile t sits in LDS buffer b; `nxt` holds tile t + 1 (requested earlier), `far` is free for tile t + 2
-    auto step = [&](int t, int b, bf16x8 *nxt, bf16x8 *far) {
-        fetch(min(t + 2, t_end - 1), far); // (always issued, so that the wait for `nxt` below counts exactly)
-        consume(t, b);
-        if (t + 1 < t_end) stash(b ^ 1, nxt);
-        __syncthreads(); // tile t + 1 is staged, and nobody reads buffer b any more
-    };
-    if (t_begin < t_end) {
-        fetch(t_begin, st0);
-        if (t_begin + 1 < t_end) fetch(t_begin + 1, st1);
-        stash(0, st0);
+    if (t_begin < t_end) { // (uniform over the block)
+        fetch(t_begin + set, 0);
+        for (int u = t_begin, b = 0; u < t_end; u += WS, b ^= 1) {
+            __builtin_amdgcn_s_waitcnt(0x0f70); // this thread's part of the set's tile has landed ...
+            __builtin_amdgcn_s_barrier();       // ... everyone's has, and nobody reads the other buffer any more
+            SD_ORDER();
+            if (u + WS < t_end) fetch(u + WS + set, b ^ 1);
+            consume(u + set, b);
+            SD_ORDER();
+        }
+    }
+    // the second set leaves its part of every row, the first one adds it
+    __syncthreads();
+    float *mg = (float *)sKV + wave * (ND * 4 + 2) * 64;
+    if (set == 1) {
+#pragma unroll
+        for (int d = 0; d < ND; d++) *(f32x4 *)(mg + (d * 64 + lane) * 4) = o[d];
+        mg[ND * 256 + lane] = m_run;
+        mg[ND * 256 + 64 + lane] = l_run;
     }
     __syncthreads();
-    for (int t = t_begin; t < t_end; t += 2) {
-        step(t, 0, st1, st0);
-        if (t + 1 < t_end) step(t + 1, 1, st0, st1);
+    if (set == 1 || !w_valid) return;
+    {
+        const float m1 = mg[ND * 256 + lane], l1 = mg[ND * 256 + 64 + lane], m = fmaxf(m_run, m1);
+        const float f0 = __builtin_amdgcn_exp2f(m_run - m), f1 = __builtin_amdgcn_exp2f(m1 - m); // (nothing seen on either side: 1 and sums of 0)
+#pragma unroll
+        for (int d = 0; d < ND; d++) o[d] = o[d] * f0 + *(const f32x4 *)(mg + (d * 64 + lane) * 4) * f1;
+        l_run = l_run * f0 + l1 * f1;
+        m_run = m;
     }
-    if (!w_valid) return;
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
     // lane (q = qi, grp) holds O^T[dim = 16 d + 4 grp + r][q] in o[d][r]
@@ -953,24 +975,25 @@ hipError_t launch_attn_prefill_bf16(hipStream_t s, const void *qbuf, ActView q_a
                                     int len_upper, float *part, size_t part_floats, void *obuf, ActView o_av)
 {
     if (!g_prefill_attn || R != 16 || G < 2 || (hd != 64 && hd != 128)) return hipErrorNotSupported;
-    constexpr int WG = 4;
-    const int n_gb = (G + WG - 1) / WG, n_slots = n_seq * G;
+    constexpr int WG = 4, WS = 2;
+    const int n_slots = n_seq * G;
+    const int n_gb = (G + WG - 1) / WG;
     if ((long)n_seq * n_gb > 65535 || H > 65535) return hipErrorNotSupported;
     const int tiles_upper = (len_upper + AT_TILE - 1) / AT_TILE;
-    // as many splits as keep all blocks resident at once (three per compute unit at head width 128), at least 8
-    // tiles per split, and partials that fit
-    int S = 768 / (H * n_seq * n_gb);
+    // as many splits as keep all blocks resident at once (two per compute unit), at least 8 tiles per split, and
+    // partials that fit
+    int S = 512 / (H * n_seq * n_gb);
     if (S > tiles_upper / 8) S = tiles_upper / 8;
     if (S > SD_ATTN_MAX_SPLITS) S = SD_ATTN_MAX_SPLITS;
     while (S > 1 && (size_t)n_slots * H * S * 16 * (hd + 2) > part_floats) S--;
     if (S < 1) S = 1;
-    dim3 grid(H, n_seq * n_gb, S), block(WG * 64);
+    dim3 grid(H, n_seq * n_gb, S), block(WG * WS * 64);
     if (hd == 128)
-        hipLaunchKernelGGL((attn_prefill_kernel<128, WG>), grid, block, 0, s, (const uint16_t *)qbuf, q_av,
+        hipLaunchKernelGGL((attn_prefill_kernel<128, WG, WS>), grid, block, 0, s, (const uint16_t *)qbuf, q_av,
                            (const uint16_t *)Kl, (const uint16_t *)Vtl, pv, cv, R, H, G, n_seq, total_cap, S, part,
                            (uint16_t *)obuf, o_av);
     else
-        hipLaunchKernelGGL((attn_prefill_kernel<64, WG>), grid, block, 0, s, (const uint16_t *)qbuf, q_av,
+        hipLaunchKernelGGL((attn_prefill_kernel<64, WG, WS>), grid, block, 0, s, (const uint16_t *)qbuf, q_av,
                            (const uint16_t *)Kl, (const uint16_t *)Vtl, pv, cv, R, H, G, n_seq, total_cap, S, part,
                            (uint16_t *)obuf, o_av);
     hipError_t e = hipGetLastError();
