@@ -18,7 +18,7 @@
 //  * few rows (gemm_ksplit_kernel up to 8 rows or where the norm is split, gemm_wide_kernel
 //    from 9 to 16, and to 64 in layers narrower than 4096): the waves of a block split K, fetch their
 //    activation fragments straight from L2 and meet in LDS - no barrier in the K loop;
-//    17 to 64 rows of wide layers (gemm_lds_kernel): weights and rows staged through LDS;
+//    17 to 96 rows of wide layers (gemm_lds_kernel): weights and rows staged through LDS;
 //    more rows (gemm_tile_kernel): row blocks share a staged activation chunk in LDS;
 //  * results leave either directly (store; SwiGLU: silu(gate)*up split to bf16
 //    hi/lo) or as fp32 partial sums per K split, which the consuming kernel adds in
@@ -672,7 +672,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16
     }
 }
 
-// Few-row GEMM of wide layers (17 to 64 rows, 4096 elements of K and more): a block of WR x WC waves, each with one 32 x 32
+// Few-row GEMM of wide layers (17 to 96 rows, 4096 elements of K and more): a block of WR x WC waves, each with one 32 x 32
 // tile of the result (v_mfma_f32_32x32x16_bf16, weights as the first operand), and one block per compute unit.
 // Bound: what a compute unit pulls through L2 (50 - 60 GB/s), of which HBM only supplies the weights.  gemm_wide_kernel reads
 // the activation rows once per wave and K step into registers, as many bytes of rows as of weights at M = 32; here both operands go to LDS
@@ -684,7 +684,8 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16
 // Measured alone, the slabs' reader included (gemm_wide_kernel before -> now, us): 4096 wide, M = 24: gate/up 34.6 -> 31.5, QKV 19.4 ->
 // 19.6, O 8.4 -> 8.6, down 18.5 -> 17.8; M = 64: gate/up 53.0 -> 42.9, QKV 30.7 -> 24.7, O 14.4 -> 13.1, down 27.5 -> 24.2, LM
 // head 63.7 -> 49.0; 5120 wide, M = 24: gate/up 52.2 -> 45.8, QKV 28.5 -> 27.3, down 27.3 -> 24.4; M = 64: gate/up 73.8 -> 57.1, QKV
-// 42.5 -> 34.2, down 40.0 -> 32.7.  Deeper rings (5 stages of 64 x 96, 7 of 32 x 96) change nothing.  Verify pass of two 4096-wide
+// 42.5 -> 34.2, down 40.0 -> 32.7; M = 80 (gemm_tile_kernel before, weights cold): gate/up 59.0 -> 53.5, QKV 35.6 -> 30.6, O 15.7 ->
+// 16.0, down 27.0 -> 26.9, LM head 60.1 -> 53.1, at 5120 wide 79.9 -> 68.8, 44.8 -> 40.6, 20.3 -> 19.9, 38.4 -> 39.2.  Deeper rings (5 stages of 64 x 96, 7 of 32 x 96) change nothing.  Verify pass of two 4096-wide
 // layers: 301 -> 293 at 18 rows, 307 -> 295 at 24, 340 -> 312 at 30, 410 -> 369 at 48, 488 -> 430 at 64.
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) void lds_void;
@@ -928,13 +929,15 @@ static int tile_splits(int ncol, int nmb, int slots, int steps)
     }
     return best;
 }
-// Block shape and K splits of gemm_lds_kernel (cols = 0: not a shape of it).  Blocks of 32 rows up to M = 32, of 64 above; 96 or 128
+// Block shape and K splits of gemm_lds_kernel (cols = 0: not a shape of it).  Blocks of 32, 64 or 96 rows, all of the launch's; 96 or 128
 // weight rows; the estimate is rounds of blocks over 256 units x (K steps per split + 2), a step of 128 weight rows
 // 1.05 of one of 96, plus the splits' fp32 slabs; no split of fewer than four steps.  Over QKV / O / gate-up / down / LM head of the
 // 4096- and 5120-wide models at 20 to 64 rows its choice is the fastest of the sweep (both widths, 1 to 8 splits) or within 3 %
 // but for one (O at M = 48: 13.0 against 11.7).
 // Up to 16 rows gemm_wide_kernel is ahead (QKV 17.3 against 19.0, O 7.1 against 7.9 at M = 16), and so it is on narrower
 // models (2048 wide, M = 32: gate/up 15.6 against 16.4, down 7.6 against 9.3), whose few K steps don't repay filling the ring.
+// Above 96 rows one block takes too much LDS for a ring, and two row blocks per column tile are slower than gemm_tile_kernel (gate/up
+// at M = 128: 84 against 59).
 struct LdsPlan {
     int cols, ncol, ks;
 };
@@ -942,7 +945,7 @@ static LdsPlan lds_plan(int mode, int M, int N, int K, int n_per_seg, int force_
 {
     LdsPlan best = {0, 0, 1};
     const int rows_w = N * (mode == GEMM_SWIGLU ? 2 : 1), steps = K / 128;
-    if (M < 17 || M > 64 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || steps < 32 || rows_w < 4096) return best;
+    if (M < 17 || M > 96 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || steps < 32 || rows_w < 4096) return best;
     float best_cost = 0.f;
     for (int cols = 96; cols <= 128; cols += 32) {
         const int ncol = (rows_w + cols - 1) / cols;
@@ -1001,9 +1004,10 @@ static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K, bool u
         if (g_force_tile_cols == 128 && ok128) cols = 128;
         if (cols) {
             // 64-row blocks when they pad M less (M = 128: 2 x 64 instead of 96 + 32) and do not cost more rounds; from 65 to 96
-            // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (115 and 125
-            // blocks at 4096 wide), and two of 64 rows pull little more than one of 96 (weights outweigh rows in every block).
-            // Verify pass of two 4096-wide layers 518 -> 500 us at 72 rows, 544 -> 525 at 96; one 5120-wide layer 392 -> 385, 409 -> 402
+            // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (58 and 125
+            // blocks at 2048 wide), and two of 64 rows pull little more than one of 96 (weights outweigh rows in every block):
+            // gate/up at 2048 / 5504 40 -> 25 us, a verify pass of two 4096-wide layers 518 -> 500 at 72 rows, 544 -> 525 at 96
+            // (from a K of 4096 on gemm_lds_kernel has these rows)
             const int ncol = (rows_w + cols - 1) / cols, nmb64 = (M + 63) / 64;
             auto rounds = [&](int rb) {
                 return die_rounds(ncol, rb, mode == GEMM_SWIGLU ? 1 : one_round_splits(ncol, rb, 256, steps), 256);
@@ -1094,6 +1098,13 @@ static hipError_t lds_launch(hipStream_t s, LdsPlan p, const uint16_t *a, ActVie
     int kps, ny;
     split_geometry(K, p.ks, &kps, &ny);
 #define SD_LDS(WR, WC, NB)                                                                                                           hipLaunchKernelGGL((gemm_lds_kernel<MODE, WR, WC, NB, NT>), dim3(p.ncol, ny), dim3(WR * WC * 64), 0, s, a, a_av, w, M, N, K,                        kps, C, c_split_stride, ca, c_av, ls)
+    if constexpr (!NT) {
+        if (M > 64) {
+            if (p.cols == 96) SD_LDS(3, 3, 4);
+            else SD_LDS(3, 4, 3);
+            return hipGetLastError();
+        }
+    }
     if (M <= 32 && p.cols == 96) SD_LDS(1, 3, 5);
     else if (M <= 32) SD_LDS(1, 4, 4);
     else if (p.cols == 96) SD_LDS(2, 3, 3);
@@ -1194,10 +1205,11 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
         if (lp.cols) {
             const LmStats lsk = mode == GEMM_STORE && lp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
             if (ls_done && lsk.p) *ls_done = 1;
+            const bool nt = w.nt && M <= 64; // (80 rows, 4096 wide: the LM head 61.3 us with the hint, 53.1 without; at 64 and fewer even or ahead with it)
             if (mode == GEMM_SWIGLU)
-                return w.nt ? lds_launch<GEMM_SWIGLU, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
+                return nt ? lds_launch<GEMM_SWIGLU, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
                             : lds_launch<GEMM_SWIGLU, false>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
-            return w.nt ? lds_launch<GEMM_STORE, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
+            return nt ? lds_launch<GEMM_STORE, true>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk)
                         : lds_launch<GEMM_STORE, false>(s, lp, a, a_av, w, M, N, K, C, c_split_stride, ca, c_av, lsk);
         }
         const WidePlan wp = wide_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);

@@ -327,15 +327,15 @@ def test_wide_few_row_gemm_matches_reference_kernels(d, F, V):
 
 @pytest.mark.parametrize("F,V", [(2048, 4128), (4352, 4112), (4224, 8224)])
 def test_few_row_gemm_of_wide_layers_matches_reference_kernels(F, V):
-    """17 to 64 rows of layers 4096 wide take the few-row GEMM that stages both operands: the edges of its 32- and 64-row
+    """17 to 96 rows of layers 4096 wide take the few-row GEMM that stages both operands: the edges of its 32-, 64- and 96-row
     blocks, K ranges that its splits and its ring of chunks don't divide (33 and 34 steps), numbers of weight rows that no
     block divides (8704, 4112, 8224), a model small enough for cached weights (the first) and the LM head's softmax partials
     (4128, 8224).  Same caches on both sides; fp32 sums in another order, single cache elements one bf16 step."""
     import dataclasses
     st_ = dataclasses.replace(dg.SHAPES["small_target_bf16"], n_layers=1, d_model=4096, n_heads=32, d_ffn=F, vocab=V, name=f"rows_{F}")
-    gt = api.Model(st_, dg.make_weights(st_, 97, BF16_LM_SCALE), max_rows=64, max_pos=128)
+    gt = api.Model(st_, dg.make_weights(st_, 97, BF16_LM_SCALE), max_rows=97, max_pos=128)
     try:
-        for B, gamma in ((16, 0), (17, 0), (8, 3), (11, 2), (8, 5), (8, 7)):
+        for B, gamma in ((16, 0), (17, 0), (8, 3), (11, 2), (8, 5), (8, 7), (13, 4), (12, 7), (97, 0)):
             M = B * (gamma + 1)
             _say(f"few rows of wide layers, F={F} V={V} rows={M}")
             lens = dg.make_prompt_lengths(97 + M, B, 3, 20)
