@@ -603,59 +603,65 @@ __global__ __launch_bounds__(WAVES * 64, SPLIT && HD == 64 ? 4 : 2) void attn_fu
     uint16_t *Vt = Vtl + ((size_t)h * total_cap + off) * HD; // this sequence's first 32-token tile
     // ---- prologue: slabs -> q, k, v of this head; RoPE; append
     {
-        for (int idx = threadIdx.x; idx < 16 * HALF; idx += WAVES * 64) {
-            const int r = idx / HALF, e = idx % HALF;
+        // A thread takes two neighbouring dimensions of each half of a row (8-byte loads): 8 rows of head width 128 are one round
+        // of a four-wave block.  (One dimension of each half: 4 rows, and the second round's loads wait behind the first's.)
+        for (int idx = threadIdx.x; idx < 16 * (HALF / 2); idx += WAVES * 64) {
+            const int r = idx / (HALF / 2), e = idx % (HALF / 2) * 2;
             const int row = j * R + (r < R ? r : 0);
             const int pos = kv0 + r;
             bool valid = r < nq && pos < max_pos;
             const bool mine = !SPLIT || ((pos >> 5) >= t_begin && (pos >> 5) < t_end); // this block appends the row
             if (r < nq && pos >= max_pos && e == 0) atomicOr(cv.status, 8);
-            float q0 = 0.f, q1 = 0.f, k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
+            float2 q0 = {0.f, 0.f}, q1 = {0.f, 0.f}, k0 = {0.f, 0.f}, k1 = {0.f, 0.f}, v0 = {0.f, 0.f}, v1 = {0.f, 0.f};
             if (valid) {
                 const float *base = qkv + (size_t)row * 3 * HDm + h * HD + e;
-                float ld[8][6];
+                const float4 cs = *(const float4 *)(rope + (size_t)pos * HALF + e); // (cos, sin) of both dimensions
+                float2 ld[8][6];
 #pragma unroll
                 for (int sl = 0; sl < 8; sl++)
                     if (sl < n_slabs) {
                         const float *rs = base + (size_t)sl * slab_stride;
-                        ld[sl][0] = rs[0];
-                        ld[sl][1] = rs[HALF];
+                        ld[sl][0] = *(const float2 *)rs;
+                        ld[sl][1] = *(const float2 *)(rs + HALF);
                         if (!SPLIT || mine) {
-                            ld[sl][2] = rs[HDm];
-                            ld[sl][3] = rs[HDm + HALF];
-                            ld[sl][4] = rs[2 * HDm];
-                            ld[sl][5] = rs[2 * HDm + HALF];
+                            ld[sl][2] = *(const float2 *)(rs + HDm);
+                            ld[sl][3] = *(const float2 *)(rs + HDm + HALF);
+                            ld[sl][4] = *(const float2 *)(rs + 2 * HDm);
+                            ld[sl][5] = *(const float2 *)(rs + 2 * HDm + HALF);
                         }
                     }
 #pragma unroll
                 for (int sl = 0; sl < 8; sl++)
                     if (sl < n_slabs) {
-                        q0 += ld[sl][0];
-                        q1 += ld[sl][1];
+                        q0.x += ld[sl][0].x, q0.y += ld[sl][0].y;
+                        q1.x += ld[sl][1].x, q1.y += ld[sl][1].y;
                         if (!SPLIT || mine) {
-                            k0 += ld[sl][2];
-                            k1 += ld[sl][3];
-                            v0 += ld[sl][4];
-                            v1 += ld[sl][5];
+                            k0.x += ld[sl][2].x, k0.y += ld[sl][2].y;
+                            k1.x += ld[sl][3].x, k1.y += ld[sl][3].y;
+                            v0.x += ld[sl][4].x, v0.y += ld[sl][4].y;
+                            v1.x += ld[sl][5].x, v1.y += ld[sl][5].y;
                         }
                     }
-                const float2 cs = rope[(size_t)pos * HALF + e];
-                const float qa = q0 * cs.x - q1 * cs.y, qb = q1 * cs.x + q0 * cs.y;
-                const float ka = k0 * cs.x - k1 * cs.y, kb = k1 * cs.x + k0 * cs.y;
+                const float2 qa = {q0.x * cs.x - q1.x * cs.y, q0.y * cs.z - q1.y * cs.w}, qb = {q1.x * cs.x + q0.x * cs.y, q1.y * cs.z + q0.y * cs.w};
+                const float2 ka = {k0.x * cs.x - k1.x * cs.y, k0.y * cs.z - k1.y * cs.w}, kb = {k1.x * cs.x + k0.x * cs.y, k1.y * cs.z + k0.y * cs.w};
                 q0 = qa;
                 q1 = qb;
-                if (mine) {
-                    K[kt_offset(HD, pos, e)] = bf16_bits_rne(ka);
-                    K[kt_offset(HD, pos, e + HALF)] = bf16_bits_rne(kb);
-                    Vt[vt_offset(HD, pos, e)] = bf16_bits_rne(v0);
-                    Vt[vt_offset(HD, pos, e + HALF)] = bf16_bits_rne(v1);
+                if (mine) { // (two dimensions of a key lie side by side, those of a value a row of 32 tokens apart)
+                    *(uint32_t *)(K + kt_offset(HD, pos, e)) = (uint32_t)bf16_bits_rne(ka.y) << 16 | bf16_bits_rne(ka.x);
+                    *(uint32_t *)(K + kt_offset(HD, pos, e + HALF)) = (uint32_t)bf16_bits_rne(kb.y) << 16 | bf16_bits_rne(kb.x);
+                    Vt[vt_offset(HD, pos, e)] = bf16_bits_rne(v0.x);
+                    Vt[vt_offset(HD, pos, e + 1)] = bf16_bits_rne(v0.y);
+                    Vt[vt_offset(HD, pos, e + HALF)] = bf16_bits_rne(v1.x);
+                    Vt[vt_offset(HD, pos, e + HALF + 1)] = bf16_bits_rne(v1.y);
                 }
             }
-            const uint16_t h0 = bf16_bits_rne(q0), h1 = bf16_bits_rne(q1);
-            sQ[0][r][e] = h0;
-            sQ[0][r][e + HALF] = h1;
-            sQ[1][r][e] = bf16_bits_rne(q0 - __uint_as_float((uint32_t)h0 << 16));
-            sQ[1][r][e + HALF] = bf16_bits_rne(q1 - __uint_as_float((uint32_t)h1 << 16));
+            uint32_t h0, l0, h1, l1;
+            bf16x2_split(q0.x, q0.y, h0, l0);
+            bf16x2_split(q1.x, q1.y, h1, l1);
+            *(uint32_t *)&sQ[0][r][e] = h0;
+            *(uint32_t *)&sQ[0][r][e + HALF] = h1;
+            *(uint32_t *)&sQ[1][r][e] = l0;
+            *(uint32_t *)&sQ[1][r][e + HALF] = l1;
         }
     }
     __syncthreads(); // q in LDS; the new cache rows are visible to this block's later loads

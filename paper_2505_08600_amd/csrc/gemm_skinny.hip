@@ -1004,7 +1004,7 @@ static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K, bool u
         if (g_force_tile_cols == 128 && ok128) cols = 128;
         if (cols) {
             // 64-row blocks when they pad M less (M = 128: 2 x 64 instead of 96 + 32) and do not cost more rounds; from 65 to 96
-            // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (58 and 125
+            // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (43 and 125
             // blocks at 2048 wide), and two of 64 rows pull little more than one of 96 (weights outweigh rows in every block):
             // gate/up at 2048 / 5504 40 -> 25 us, a verify pass of two 4096-wide layers 518 -> 500 at 72 rows, 544 -> 525 at 96
             // (from a K of 4096 on gemm_lds_kernel has these rows)
