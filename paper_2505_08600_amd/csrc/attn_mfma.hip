@@ -860,7 +860,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         else if (g_force_attn_waves == 4) S = 1;
         else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
         else if (tiles_upper > (fit >= 3 ? 24 : 40)) S = std::min(fit, tiles_upper / 4);
-        else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 14)) S = 4;
+        else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 16)) S = 4; // (the bound is the longest sequence's; shorter ones gain less)
         if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {
             const AttnSplit sp = {part, arrivals, S, (tiles_upper + S - 1) / S};
 #define SD_FUSED_SPLIT(HD_, NT_)                                                                                              \
