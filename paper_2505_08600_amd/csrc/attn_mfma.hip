@@ -849,9 +849,9 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         //    948 at 384, 972 -> 962, 997 -> 965, 1003 -> 967 at 760 (S = 8: 992).  A model whose blocks apply the output
         //    projection as well loses that launch again: 318 -> 324 at 256 tokens, 324 -> 328 at 512, 329 -> 326 at 640, 334 -> 328 at 760;
         //  * room for three to five (64 pairs, four layers): 477 -> 477 at 512, 482 -> 479 at 640, 477 -> 470 at 800, 526 -> 484 at 1480;
-        //  * room for two (128 pairs, where one block has one helper): 501 -> 518 at 800, 517 -> 523 at 1000, 540 -> 526 at 1250,
-        //    583 -> 533 at 1480; 96 pairs 499 -> 508, 502 -> 515 at 1250, 573 -> 520 at 1480;
-        //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are): 160 pairs 622 -> 589 at
+        //  * room for two (where one block has one helper), two layers: 128 pairs 298 -> 304 at 1150, 300 -> 307 at 1300, 306 -> 308
+        //    at 1400; 96 pairs 285 -> 292, 288 -> 294, 290 -> 295: one block;
+        //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are): 128 pairs 583 -> 533 at 1480, 160 pairs 622 -> 589 at
         //    1480, 256 pairs 728 -> 699; from 512 pairs on the three launches, whose blocks only stream, are ahead.
         const long pairs = (long)n_seq * H;
         const int fit = (int)std::max(1L, std::min(8L, 256 / pairs));
@@ -859,7 +859,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         if (g_force_attn_split) S = g_force_attn_split;
         else if (g_force_attn_waves == 4) S = 1;
         else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
-        else if (tiles_upper > (fit >= 3 ? 24 : 40)) S = std::min(fit, tiles_upper / 4);
+        else if (fit >= 3 && tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
         else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 16)) S = 4; // (the bound is the longest sequence's; shorter ones gain less)
         if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {
             const AttnSplit sp = {part, arrivals, S, (tiles_upper + S - 1) / S};
