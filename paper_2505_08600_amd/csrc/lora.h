@@ -64,16 +64,37 @@ __device__ __forceinline__ void lora_block(const T *X, ActView x_av, int K, cons
             for (int i = 0; i < NB; i++) bv[o][i] = i < rank ? brow[i] : 0.f;
         }
     }
-    for (int j = wave; j < rank; j += WAVES) {
-        const float *arow = Ap + ((size_t)a * rank + j) * K;
-        float acc = 0.f;
-#pragma unroll 4
-        for (int k = 4 * lane; k < K; k += 256) { // 16 bytes per lane and load (K is a multiple of 4)
-            const float4 xv = load_act4(X, act_index(x_av, r, k, K), x_av.plane), av = *(const float4 *)(arow + k);
-            acc += av.x * xv.x + av.y * xv.y + av.z * xv.z + av.w * xv.w;
+    // Dot products a wave takes at a time: with four waves a rank of 8 is two, with one read of X.  Three draft tokens of the
+    // 768-wide model at rank 8: 32 sequences 321 -> 311 us so, 304 with four pieces of each row requested together (a loop
+    // over K of 768 is three trips, one after the other); 16 sequences 297 -> 279, one 245 -> 233.
+    constexpr int JS = WAVES == 8 ? 1 : 2;
+    for (int j = wave; j < rank; j += JS * WAVES) {
+        const float *arow[JS];
+        float acc[JS];
+#pragma unroll
+        for (int i = 0; i < JS; i++) arow[i] = Ap + ((size_t)a * rank + min(j + i * WAVES, rank - 1)) * K, acc[i] = 0.f; // (past the last: read again, not stored)
+        for (int k0 = 4 * lane; k0 < K; k0 += 1024) { // 16 bytes per lane and load (K is a multiple of 4), four of each row in flight
+            float4 xv[4], av[JS][4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int k = k0 + 256 * u < K ? k0 + 256 * u : k0;
+                xv[u] = load_act4(X, act_index(x_av, r, k, K), x_av.plane);
+#pragma unroll
+                for (int i = 0; i < JS; i++) av[i][u] = *(const float4 *)(arow[i] + k);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int i = 0; i < JS; i++) {
+                    const float t = acc[i] + (av[i][u].x * xv[u].x + av[i][u].y * xv[u].y + av[i][u].z * xv[u].z + av[i][u].w * xv[u].w);
+                    acc[i] = k0 + 256 * u < K ? t : acc[i];
+                }
         }
-        acc = wave_sum_dpp(acc);
-        if (lane == 0) st[j] = acc;
+#pragma unroll
+        for (int i = 0; i < JS; i++) {
+            acc[i] = wave_sum_dpp(acc[i]);
+            if (lane == 0 && j + i * WAVES < rank) st[j + i * WAVES] = acc[i];
+        }
     }
     __syncthreads();
 #pragma unroll
