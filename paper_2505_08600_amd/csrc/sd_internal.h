@@ -328,6 +328,7 @@ struct sd_model {
     hipStream_t logits_stream; // where the last forward that writes them was enqueued, and the device then current
     int logits_device;
     int last_lm_rows;
+    bool stopped_at_cache; // the last forward left out what follows the cache append of its last layer
     int last_rows, last_a_rows; // rows of the last forward (layout of the step-major buffers); of abuf
     int lm_norm_rows; // rows of the LM head's input that a norm inside its GEMM kept out of abuf (0: none); sd_debug_read makes them
 };

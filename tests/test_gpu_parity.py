@@ -2089,3 +2089,60 @@ def test_low_rank_update_carried_by_the_gemm_launch_matches_reference_kernels(d,
         assert np.isfinite(outs[0]).all() and np.abs(outs[0] - outs[1]).max() < 5e-4 * np.abs(outs[1]).max(), (B, gamma)
         ctx.close()
     gm.close()
+
+
+def test_bf16_inspection_buffers_behind_a_prefill():
+    """A one-layer bf16 model, 69 tokens in forwards of 64 rows.  Under force_generic sd_debug_read gives the last forward's q, k | v,
+    attention output, residual, norm and SwiGLU rows, against the same in 64 bits from the weights (cache rows rounded to
+    bf16): activations carry 16 bits through at most five contractions, and a cache value that rounds the other way moves a row of 65
+    tokens and more by 2^-8 / 65 of its size, 1e-3 of the largest.  Without the option the prefill stops at its cache append and
+    the buffers are refused, until a verify pass has filled them."""
+    _say("bf16 inspection buffers behind a prefill")
+    st_ = dg.SHAPES["small_draft_bf16"]
+    w = dg.make_weights(st_, 61, BF16_LM_SCALE)
+    d, H_, hd, rows = st_.d_model, st_.n_heads, st_.head_dim, 5
+    prompt = [int(t) for t in dg.make_prompt(61, 0, 70, st_.vocab)]
+    f64 = lambda a: dg.bf16_bits_to_f32(a).astype(np.float64)
+    bf16 = lambda a: f64(dg.f32_to_bf16_bits(a.astype(np.float32)))
+    norm = lambda x, g: x / np.sqrt((x * x).mean(-1, keepdims=True) + st_.rms_eps) * g
+    x = f64(w["embed"])[prompt[:69]]
+    h = norm(x, w["norm_attn"][0])
+    qkv = h @ np.concatenate([f64(w[n][0]) for n in ("wq", "wk", "wv")]).T
+    ang = np.arange(69)[:, None] * st_.rope_base ** (-2.0 * np.arange(hd // 2) / hd)
+
+    def rope(t):
+        t = t.reshape(69, H_, hd)
+        a, b, c, s = t[..., :hd // 2], t[..., hd // 2:], np.cos(ang)[:, None], np.sin(ang)[:, None]
+        return np.concatenate([a * c - b * s, b * c + a * s], -1)
+
+    q, k, v = rope(qkv[:, :d]), bf16(rope(qkv[:, d:2 * d])), bf16(qkv[:, 2 * d:]).reshape(69, H_, hd)
+    sc = np.einsum("ihc,jhc->hij", q, k) / np.sqrt(hd)
+    sc[:, np.arange(69)[:, None] < np.arange(69)] = -np.inf
+    p = np.exp(sc - sc.max(-1, keepdims=True))
+    o = np.einsum("hij,jhc->ihc", p / p.sum(-1, keepdims=True), v).reshape(69, d)
+    x = x + o @ f64(w["wo"][0]).T
+    a = norm(x, w["norm_ffn"][0])
+    g = a @ f64(w["wgate"][0]).T
+    act = g / (1.0 + np.exp(-g)) * (a @ f64(w["wup"][0]).T)
+    ref = {"q": q.reshape(69, d), "qkv": qkv, "o": o, "a": a, "act": act}
+    gm = api.Model(st_, w, max_rows=64, max_pos=128)
+    ctx = api.Context([80])
+    ctx.attach(gm)
+    try:
+        api.set_option("force_generic", 1)
+        H.gpu_prefill(ctx, [gm], [prompt])
+        for n, r in ref.items():
+            got = gm.debug_read(n, rows)
+            assert np.abs(got - r[64:]).max() < 1e-3 * np.abs(r[64:]).max(), n
+    finally:
+        api.set_option("force_generic", 0)
+    H.gpu_prefill(ctx, [gm], [prompt])
+    for n in ("x", "qkv", "q", "o", "a", "act"):
+        with pytest.raises(api.SdError):
+            gm.debug_read(n, rows)
+    assert gm.debug_read("seq_len", 1)[0, 0] > 0
+    na, nx = (torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2))
+    api.sd_verify(gm, ctx, None, 1, 0, 0.0, None, None, None, na, nx, commit=False)
+    assert np.isfinite(gm.debug_read("act", 1)).all() and np.isfinite(gm.debug_read("x", 1)).all()
+    ctx.close()
+    gm.close()
