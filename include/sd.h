@@ -428,11 +428,12 @@ int sd_debug_stream_read(const void *buf, size_t bytes, uint32_t *scratch_word, 
  * option "prefill_attn": 1 (the default) lets four 16-row groups of a prompt share every K / V tile they
  * read in a prefill forward (one block per four groups and head, tiles staged in LDS); 0 gives every group
  * blocks of its own (the split kernel of the decode path).
- * option "attn_waves" = 4 or 8 forces the block shape of the fused attention kernel, without helper
- * blocks (0 = automatic: 4-wave blocks when (sequence, head) pairs oversubscribe the chip and
- * contexts are short; four-wave blocks also keep every pair in one block).
+ * option "attn_waves" = 4 or 8 forces the block shape of the fused attention kernel, one block per
+ * (sequence, head) pair without helper blocks (0 = automatic: 4-wave blocks when pairs oversubscribe
+ * the chip and contexts are short).
  * option "attn_split" = 1 .. 32 forces the number of blocks that share one (sequence, head) pair's context in the
- * fused attention kernel (0 = automatic: more than one where pairs leave compute units idle and contexts are long).
+ * fused attention kernel, whatever "attn_waves" says (0 = automatic: more than one where pairs leave compute units idle
+ * and contexts are long).
  * option "stream_read_nt" = 0 makes sd_debug_stream_read a grid-strided read with ordinary loads;
  * 1 (the default) gives every block one contiguous range and reads it with the nontemporal hint,
  * the fastest pattern measured on this part; adding 2 to either turns on a checking mode in which the XOR

@@ -857,7 +857,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         const int fit = (int)std::max(1L, std::min(8L, 256 / pairs));
         int S = 1;
         if (g_force_attn_split) S = g_force_attn_split;
-        else if (g_force_attn_waves == 4) S = 1;
+        else if (g_force_attn_waves) S = 1; // (a forced shape keeps every pair in one block, whatever the context)
         else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
         else if (fit >= 3 && tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
         else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 16)) S = 4; // (the bound is the longest sequence's; shorter ones gain less)
