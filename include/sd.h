@@ -377,7 +377,7 @@ int sd_last_logits_async(sd_model *m, float *out, int32_t max_rows, int32_t *row
  * QKV GEMM's partial sums directly, "o" when a small model's attention blocks apply the
  * output projection themselves (option "force_generic" selects the unfused kernels).  A
  * prefill leaves out what the cache append of its last layer does not need: behind one the
- * six activation buffers are SD_EINVAL, unless it ran under "force_generic", which runs it whole. */
+ * six activation buffers are SD_EINVAL, unless it ran under "force_generic" = 1, which runs it whole. */
 int sd_debug_read(sd_model *m, const char *name, float *out, int32_t rows);
 /* Host-only (no GPU call): element offset that the library's internal layouts assign.
  * kind 0: tiled bf16 weight [N][K], a = row n, b = column k, c = K  (16-row x 128-column

@@ -227,8 +227,7 @@ class Model:
 
     def debug_read(self, name: str, rows: int) -> np.ndarray:
         """Host copy (fp32) of a workspace buffer of the last forward: x, qkv, q, o, a, act (not behind a bf16 prefill, unless it
-        ran under option force_generic); or, with
-        rows = number of sequences, the last plan's seq_order / seq_len as one column."""
+        ran under option force_generic = 1); or, with rows = number of sequences, the last plan's seq_order / seq_len as one column."""
         width = {"x": self.shape.d_model, "qkv": 3 * self.shape.d_model, "act": self.shape.d_ffn,
                  "seq_order": 1, "seq_len": 1}.get(name, self.shape.d_model)
         out = np.empty((rows, width), np.float32)

@@ -720,7 +720,7 @@ extern "C" int sd_debug_read(sd_model *m, const char *name, float *out_host, int
     if (!m || !name || !out_host || rows < 0 || rows > m->cfg.max_rows) return sd_fail(SD_EINVAL, "sd_debug_read: bad argument");
     if (m->stopped_at_cache && strcmp(name, "seq_order") && strcmp(name, "seq_len"))
         return sd_fail(SD_EINVAL, "sd_debug_read: the last forward was a prefill, which stops at its last layer's cache append; option "
-                                  "force_generic runs it whole");
+                                  "force_generic = 1 runs it whole");
     SD_HIP(hipDeviceSynchronize());
     const size_t d = m->cfg.d_model, F = m->cfg.d_ffn;
     if (!strcmp(name, "x") || !strcmp(name, "qkv")) {
@@ -905,9 +905,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
     // anyone, so queries, attention, projections and FFN of that layer are left out - one layer in n_layers of a prefill, less
     // its key and value projections (two layers of the 7B shape, 8192 tokens at 1024 rows: 15.05 -> 9.33 ms, 8.68 without the
     // queries; 32 layers: a 33rd of the whole).
-    // The last forward of a call keeps them for fp32 models and under force_generic, whose buffers sd_debug_read promises (it
+    // The last forward of a call keeps them for fp32 models and under force_generic = 1, whose buffers sd_debug_read promises (it
     // refuses those of a forward that has stopped early).
-    const bool cache_only = !want_logits && (more || (cf.dtype == SD_BF16 && !g_force_generic));
+    const bool cache_only = !want_logits && (more || (cf.dtype == SD_BF16 && !(g_force_generic & 1)));
     const int n_slots = n_seq * G; // plan slots: what the attention kernels see as sequences
     const int M = n_slots * R, d = cf.d_model, H = cf.n_heads, hd = cf.head_dim, F = cf.d_ffn, V = cf.vocab;
     if (G < 1 || (G > 1 && mode != PLAN_CATCHUP)) return sd_fail(SD_EINVAL, "forward: row groups are for prefill only");
