@@ -841,6 +841,8 @@ __global__ __launch_bounds__(WR *WC * 64) void gemm_lds_kernel(const uint16_t *_
     }
 }
 
+// fp32 slabs of a K split: written by the launch and read by its consumer, 32 bytes per element spread over the 256 units (KiB each).
+static float slab_kib(int ny, int M, int N) { return ny > 1 ? (float)ny * M * N * (32.f / (256 * 1024)) : 0.f; }
 // Block shape of the wide kernel: NW weight tiles per block and the K splits (nw = 0: not a shape of it).  The estimate
 // is what the busiest compute unit pulls in, in KiB: rounds of blocks over 256 units x K steps per split x (4 NW for the
 // weights + M / 2 for the rows), plus the splits' fp32 slabs, written here and read by the consumer (32 bytes per element
@@ -866,7 +868,7 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
             split_geometry(K, ks, &kps, &ny);
             if (force_ks <= 0 && ks > 1 && (ny != ks || kps < 256)) continue;
             const float rounds = (float)((ncol * ny + 255) / 256);
-            const float cost = rounds * (float)(kps / 128) * (4.f * nw + 0.5f * M) + (ny > 1 ? (float)ny * M * N * (32.f / (256 * 1024)) : 0.f);
+            const float cost = rounds * (float)(kps / 128) * (4.f * nw + 0.5f * M) + slab_kib(ny, M, N);
             if (best.nw == 0 || cost < best_cost) {
                 best = {nw, ncol, ny};
                 best_cost = cost;
@@ -929,34 +931,41 @@ static int tile_splits(int ncol, int nmb, int slots, int steps)
     }
     return best;
 }
-// Block shape and K splits of gemm_lds_kernel (cols = 0: not a shape of it).  Blocks of 32, 64 or 96 rows, all of the launch's; 96 or 128
-// weight rows; the estimate is rounds of blocks over 256 units x (K steps per split + 2), a step of 128 weight rows
-// 1.05 of one of 96, plus the splits' fp32 slabs; no split of fewer than four steps.  Over QKV / O / gate-up / down / LM head of the
-// 4096- and 5120-wide models at 20 to 64 rows its choice is the fastest of the sweep (both widths, 1 to 8 splits) or within 3 %
-// but for one (O at M = 48: 13.0 against 11.7).
-// Up to 16 rows gemm_wide_kernel is ahead (QKV 17.3 against 19.0, O 7.1 against 7.9 at M = 16), and so it is on narrower
-// models (2048 wide, M = 32: gate/up 15.6 against 16.4, down 7.6 against 9.3), whose few K steps don't repay filling the ring.
+// Block shape and K splits of gemm_lds_kernel (cols = 0: not a shape of it).  Blocks of 32, 64 or 96 rows, all of the
+// launch's; 96 or 128 weight rows; the estimate is rounds of blocks over 256 units x (K steps per split + 2), a step of 128
+// weight rows 1.05 of one of 96, plus the splits' fp32 slabs; no split of fewer than four steps, and none in more than one round
+// of blocks (two from 33 rows on): every round fills its ring anew.  QKV, whole passes, us per launch against the present choice:
+// 8192 wide in four splits, three rounds, 13 to 18 behind up to 32 rows, 9 to 15 at 36 to 64; 6144 and 7168 wide in three splits, two rounds,
+// 2 to 6 behind up to 32 rows, at 36 to 64 the unsplit launch is 2 to 4 behind and 3 ahead to 5 behind.  Over QKV / O / gate-up / down / LM head of the 4096- and
+// 5120-wide models at 20 to 64 rows its choice is the fastest of the sweep (both widths, 1 to 8 splits) or within 3 % but for
+// one (O at M = 48: 13.0 against 11.7).
+// Up to 16 rows gemm_wide_kernel is ahead (QKV 17.3 against 19.0, O 7.1 against 7.9 at M = 16), so it is on narrower models (2048
+// wide, M = 32: gate/up 15.6 against 16.4, down 7.6 against 9.3), whose few K steps don't repay filling the ring, and up to 48
+// rows where a unit's share of the launch is fewer than five steps of 128 weight rows (O at 4096 wide, in a whole pass: 2.0 us ahead at 18 and
+// 24 rows, 1.4 at 32, 0.5 at 48, 1.1 behind at 64; at 5120 wide, a share of six, the two are equal).
 // Above 96 rows one block takes too much LDS for a ring, and two row blocks per column tile are slower than gemm_tile_kernel (gate/up
 // at M = 128: 84 against 59).
 struct LdsPlan {
     int cols, ncol, ks;
+    float pull; // what the busiest unit pulls in, KiB
 };
 static LdsPlan lds_plan(int mode, int M, int N, int K, int n_per_seg, int force_ks, int max_ks = 8)
 {
-    LdsPlan best = {0, 0, 1};
+    LdsPlan best = {0, 0, 1, 0.f};
     const int rows_w = N * (mode == GEMM_SWIGLU ? 2 : 1), steps = K / 128;
     if (M < 17 || M > 96 || N % 16 != 0 || n_per_seg % 16 != 0 || K % 128 != 0 || steps < 32 || rows_w < 4096) return best;
+    if (M <= 48 && (long)rows_w * steps < 5L * 256 * 128) return best;
     float best_cost = 0.f;
     for (int cols = 96; cols <= 128; cols += 32) {
         const int ncol = (rows_w + cols - 1) / cols;
         for (int ks = force_ks > 0 ? force_ks : 1; ks <= (force_ks > 0 ? force_ks : mode == GEMM_SWIGLU ? 1 : max_ks); ks++) {
             int kps, ny;
             split_geometry(K, ks, &kps, &ny);
-            if (force_ks <= 0 && ks > 1 && (ny != ks || steps / ks < 4)) continue;
-            const float cost = (float)((ncol * ny + 255) / 256) * (float)(kps / 128 + 2) * (cols == 128 ? 1.05f : 1.f) +
-                               (ny > 1 ? 0.2f * 4e-6f * (float)ny * M * N : 0.f);
+            if (force_ks <= 0 && ks > 1 && (ny != ks || steps / ks < 4 || ncol * ny > (M <= 32 ? 256 : 512))) continue;
+            const float turns = (float)((ncol * ny + 255) / 256) * (float)(kps / 128 + 2);
+            const float cost = turns * (cols == 128 ? 1.05f : 1.f) + (ny > 1 ? 0.2f * 4e-6f * (float)ny * M * N : 0.f);
             if (best.cols == 0 || cost < best_cost) {
-                best = {cols, ncol, ny};
+                best = {cols, ncol, ny, turns * (cols / 4 + (M + 31) / 32 * 16) + slab_kib(ny, M, N)};
                 best_cost = cost;
             }
         }
@@ -1126,6 +1135,28 @@ static int tile_ks(int mode, int M, int N, int K, int n_per_seg)
     return ny;
 }
 
+// Does the launch run on gemm_lds_kernel?  From 65 to 96 rows its 96-row blocks pull two thirds of their bytes for rows, and
+// gemm_tile_kernel, whose blocks have up to 256 columns, pulls less where the matrix fills the chip with those: the kernel
+// whose busiest unit has less to pull, as measured (whole passes at 4096 to 12288 wide and 32000 or 128256 columns, 66 to 96
+// rows, us per launch): gate/up at 4096 / 5120 / 6144 / 7168 / 8192 wide 3.7 to 6.7, 5.7 to 9.7 and 6.3 to 11.7 ahead, 23 to 35 and 27 to 47
+// behind; QKV 3.5 ahead at 4096, equal at 5120, 5 to 8 behind at 6144, 6 to 14 at 7168, 19 to 26 at 8192; down equal up to 5120, 2 to 6
+// behind at 6144, up to 13 at 8192 / 28672; the head 5 to 20 ahead at 32000 columns, 3 to 15 behind at 128256.  The
+// estimates' ratio is 0.92 and less where this kernel is ahead or equal, 1.0 and more where it is behind.
+// splits: those of the launch, or 0 while they are being chosen.
+static LdsPlan lds_choice(int mode, int M, int N, int K, int n_per_seg, int splits, int max_ks = 8)
+{
+    const LdsPlan lp = lds_plan(mode, M, N, K, n_per_seg, splits, max_ks);
+    if (!lp.cols || M <= 64) return lp;
+    const int ks = splits == 1 ? 1 : tile_ks(mode, M, N, K, n_per_seg);
+    const TileShape t = tile_shape(mode, M, N, n_per_seg, K, ks == 1);
+    if (!t.cols) return lp;
+    int kps, ny;
+    split_geometry(K, ks, &kps, &ny);
+    const float pull = (float)(die_rounds(t.ncol, t.nmb, ny, t.slots) * (t.slots / 256)) * (float)(kps / 128 + 5) *
+                           (float)(t.cols / 4 + t.bm / 2) + slab_kib(ny, M, N);
+    return lp.pull <= 0.95f * pull ? lp : LdsPlan{0, 0, 1, 0.f};
+}
+
 // Number of K splits the launcher will use for this shape (the caller sizes and reduces the partials).  folded: the launch is
 // part of a split norm, which stays on the K-split kernel; max_ks: slabs the caller has room for.
 int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded, int max_ks)
@@ -1139,7 +1170,7 @@ int gemm_skinny_splits(int mode, int M, int N, int K, int n_per_seg, bool folded
     const int steps = K / 128;
     int ks;
     if (M > 8 && !folded) {
-        const LdsPlan lp = lds_plan(mode, M, N, K, n_per_seg, 0, max_ks);
+        const LdsPlan lp = lds_choice(mode, M, N, K, n_per_seg, 0, max_ks);
         if (lp.cols) return lp.ks;
         const WidePlan wp = wide_plan(mode, M, N, K, n_per_seg, 0, max_ks);
         if (wp.nw) return wp.ks;
@@ -1201,7 +1232,7 @@ hipError_t launch_gemm_skinny_bf16(hipStream_t s, int mode, const void *A, ActVi
     // tiles, as the projections of small models run; with an update to carry, 8 rows and fewer run on it too)
     const bool can_carry = mode == GEMM_STORE && lora && lora_done && !w.nt && lora_valid(M, K, *lora);
     if ((M > 8 || can_carry) && !folded) {
-        const LdsPlan lp = lds_plan(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
+        const LdsPlan lp = lds_choice(mode, M, N, K, w.n_per_seg, mode == GEMM_SWIGLU ? 1 : splits);
         if (lp.cols) {
             const LmStats lsk = mode == GEMM_STORE && lp.ks == 1 && N % 32 == 0 ? ls : no_ls; // (partial sums of a K split have no softmax)
             if (ls_done && lsk.p) *ls_done = 1;

@@ -384,6 +384,40 @@ def test_few_row_gemm_of_wide_layers_matches_reference_kernels(F, V):
     gt.close()
 
 
+def test_few_row_gemms_of_a_6144_wide_layer_match_reference_kernels():
+    """Row counts whose projections change kernel or splits with the width: 18 rows (QKV unsplit on the staged kernel, 96-column
+    blocks across the borders of q, k and v), 40 (three splits in two rounds), 72 and 96 (QKV and down on the row-blocked kernel, O and
+    gate/up on the staged one).  Tolerance as for the 4096-wide layers."""
+    import dataclasses
+    st_ = dataclasses.replace(dg.SHAPES["small_target_bf16"], n_layers=1, d_model=6144, n_heads=48, d_ffn=4224, vocab=4128, name="w6144")
+    gt = api.Model(st_, dg.make_weights(st_, 93, BF16_LM_SCALE), max_rows=96, max_pos=64)
+    try:
+        for B, gamma in ((6, 2), (8, 4), (9, 7), (12, 7)):
+            M = B * (gamma + 1)
+            _say(f"few rows of a 6144-wide layer, rows={M}")
+            lens = dg.make_prompt_lengths(93 + M, B, 3, 20)
+            prompts = [[int(t) for t in dg.make_prompt(93, b, int(lens[b]), st_.vocab)] for b in range(B)]
+            ctx = api.Context([int(l) + 16 for l in lens])
+            ctx.attach(gt)
+            H.gpu_prefill(ctx, [gt], prompts)
+            cand = H.dev(dg.make_prompt(94, B, B * gamma, st_.vocab).reshape(B, gamma).astype(np.int32))
+            na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+            outs = []
+            for force in (0, 1):
+                api.set_option("force_generic", force)
+                api.sd_verify(gt, ctx, None, B, gamma, 0.0, cand, None, None, na, nx, commit=False)
+                outs.append((gt.last_logits().cpu().numpy(), gt.debug_read("act", M)))
+                for b in range(B):
+                    ctx.truncate(gt, b, int(lens[b]) - 1)
+            api.set_option("force_generic", 0)
+            ctx.close()
+            for got, ref in zip(*outs):
+                assert np.isfinite(got).all() and np.abs(got - ref).max() < 5e-4 * np.abs(ref).max(), (M, np.abs(got - ref).max() / np.abs(ref).max())
+    finally:
+        api.set_option("force_generic", 0)
+    gt.close()
+
+
 def test_48_row_blocks_match_reference_kernels():
     """41 to 48 rows of a gate/up pair or logits matrix of 20480 weight rows and more, K of 2048 and more, run on the
     48-row blocks of the row-blocked kernel; 40 and 49 rows of the same shapes on the wide few-row kernel.  Logits and SwiGLU

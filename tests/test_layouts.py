@@ -118,6 +118,26 @@ def test_unsplit_row_blocked_gemms_of_65_to_96_rows_run_as_two_row_blocks():
         assert api.gemm_plan(0, m, 12288, 4096, 4096)[1] == 96 and api.gemm_plan(0, m, 4096, 11008)[1] == 96
 
 
+def test_wide_layers_of_17_to_96_rows_go_to_the_kernel_that_has_less_to_pull():
+    """K splits tell which few-row kernel has a projection (host logic only).  From 65 to 96 rows, layers from 6144 wide on whose
+    column tiles fill the chip go to the row-blocked kernel and follow its plan (down would have 5, 4 and 4 splits on the
+    staged kernel); 4096 and 5120 wide keep the staged kernel's.  Up to 32 rows no split takes a second round of blocks, and up
+    to 48 rows the 4096-wide output projection keeps the wide kernel's four splits."""
+    for d, f in ((6144, 16384), (7168, 18432), (8192, 28672)):
+        for m in (65, 80, 96):
+            assert api.gemm_splits(m, 3 * d, d, d) == api.gemm_plan(0, m, 3 * d, d, d)[4]
+            assert api.gemm_splits(m, d, f) == api.gemm_plan(0, m, d, f)[4] == 8
+        for m in (17, 24, 32):
+            assert api.gemm_splits(m, 3 * d, d, d) == 1
+    for m in (17, 32, 48):
+        assert api.gemm_splits(m, 4096, 4096) == 4
+    for m in (64, 65, 96):
+        assert api.gemm_splits(m, 4096, 4096) == 8
+    for m in (17, 32, 64, 65, 96):
+        assert api.gemm_splits(m, 3 * 4096, 4096, 4096) == 2 and api.gemm_splits(m, 3 * 5120, 5120, 5120) == 2
+    assert api.gemm_splits(36, 3 * 6144, 6144, 6144) == 3 and api.gemm_splits(36, 3 * 8192, 8192, 8192) == 1
+
+
 def test_k_splits_follow_the_kernel_that_runs_and_the_slabs_there_is_room_for():
     """K splits of the few-row GEMMs (host logic only).  A launch that is part of a split norm runs on the K-split kernel,
     whose four waves share a split's K steps: none may be left without one, and the plan of the wide kernel, which
