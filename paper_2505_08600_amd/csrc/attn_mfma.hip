@@ -851,14 +851,24 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         //  * room for three to five (64 pairs, four layers): 477 -> 477 at 512, 482 -> 479 at 640, 477 -> 470 at 800, 526 -> 484 at 1480;
         //  * room for two (where one block has one helper), two layers: 128 pairs 298 -> 304 at 1150, 300 -> 307 at 1300, 306 -> 308
         //    at 1400; 96 pairs 285 -> 292, 288 -> 294, 290 -> 295: one block;
-        //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are): 128 pairs 583 -> 533 at 1480, 160 pairs 622 -> 589 at
-        //    1480, 256 pairs 728 -> 699; from 512 pairs on the three launches, whose blocks only stream, are ahead.
+        //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are); from 512 pairs on those, whose
+        //    blocks only stream, are ahead.  From 129 pairs on two blocks a pair may leave much of the chip without one in the last
+        //    round; on contexts of more than 96 tiles four fill it where that gains a seventh (shorter or ragged ones pay 1 to 3 % for the
+        //    two more meetings).  Three launches / two / four blocks a pair, four layers, at 1600, 4000 and 8000 tokens and (three batches)
+        //    ragged from 300 to 8000:
+        //      160 pairs 632 / 600 / 605, 753 / 751 / 724, 950 / 994 / 927, ragged 754 / 724 / 740, 789 / 758 / 767, 784 / 759 / 770
+        //      192 pairs 698 / 657 / 659, 854 / 815 / 803, 1118 / 1079 / 1040, ragged 859 / 845 / 850, 844 / 818 / 824, 879 / 845 / 853
+        //      256 pairs 743 / 712 / 726, 929 / 912 / 915, 1215 / 1205 / 1200, ragged 1004 / 977 / -, 933 / 940 / -, 932 / 944 / -
+        //      320 pairs 836 / 804 / 820, 1048 / 1038 / 1052, 1424 / 1446 / 1407, ragged 1136 / 1099 / 1118, 1044 / 1054 / 1034, 1032 / 1064 / 1029
+        //      416 pairs 1017 / 990 / 1013, 1309 / 1314 / 1298, 1844 / 1866 / 1807, ragged 1355 / 1330 / 1369, 1351 / 1327 / 1345, 1242 / 1254 / 1257
+        //      480 pairs 1060 / 1020 / 1060, 1374 / 1381 / 1389, 1943 / 1972 / 1973, ragged 1434 / 1406 / -, 1400 / 1379 / -, 1327 / 1318 / -
         const long pairs = (long)n_seq * H;
+        auto busy = [&](int s) { return (float)(pairs * s) / (256.f * (float)((pairs * s + 255) / 256)); }; // share of the units that have a block, over all rounds
         const int fit = (int)std::max(1L, std::min(8L, 256 / pairs));
         int S = 1;
         if (g_force_attn_split) S = g_force_attn_split;
         else if (g_force_attn_waves) S = 1; // (a forced shape keeps every pair in one block, whatever the context)
-        else if (tiles_upper > 48) S = pairs < 512 ? std::max(2, fit) : 1;
+        else if (tiles_upper > 48) S = pairs >= 512 ? 1 : fit == 1 && tiles_upper > 96 && busy(4) > busy(2) + 0.14f ? 4 : std::max(2, fit);
         else if (fit >= 3 && tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
         else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 16)) S = 4; // (the bound is the longest sequence's; shorter ones gain less)
         if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {

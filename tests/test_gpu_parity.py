@@ -2068,6 +2068,36 @@ def test_attention_split_over_blocks_matches_one_block_per_pair(shape_name, S):
     gm.close()
 
 
+@pytest.mark.parametrize("B,n,S", [(8, 3200, 4), (8, 3000, 2), (6, 3200, 2), (11, 3200, 2)])
+def test_long_contexts_are_split_so_that_blocks_fill_the_last_round(B, n, S):
+    """20 heads: 160 pairs take four blocks each beyond 96 tiles (two leave three eighths of the second round empty) and two up to
+    there, 120 and 220 pairs two.  The automatic choice gives the bits of that number forced, not of the other, and the logits of
+    the split kernel's three launches (attn_split = 1) to 2e-4 as for the kernels' other orders."""
+    _say(f"long contexts, {B} sequences of {n} tokens")
+    st_ = dataclasses.replace(dg.SHAPES["small_draft_bf16"], n_layers=1, d_model=1280, n_heads=20, d_ffn=512, name="split_20")
+    gm = api.Model(st_, dg.make_weights(st_, 55, BF16_LM_SCALE), max_rows=1024, max_pos=n + 16)
+    prompts = [[int(t) for t in dg.make_prompt(55, b, n - 37 * b, st_.vocab)] for b in range(B)]
+    cand = H.dev(dg.make_prompt(56, 0, B * 2, st_.vocab).reshape(B, 2).astype(np.int32))
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx = api.Context([n + 16] * B)
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    out = {}
+    try:
+        for split in (0, 1, 2, 4):
+            api.set_option("attn_split", split)
+            api.sd_verify(gm, ctx, None, B, 2, 0.0, cand, None, None, na, nx, commit=False)
+            out[split] = gm.last_logits().cpu().numpy()
+            for b in range(B):
+                ctx.truncate(gm, b, len(prompts[b]) - 1)
+    finally:
+        api.set_option("attn_split", 0)
+    assert np.isfinite(out[0]).all() and np.abs(out[0] - out[1]).max() < 2e-4 * np.abs(out[1]).max()
+    assert np.array_equal(out[0], out[S]) and not np.array_equal(out[0], out[6 - S])
+    ctx.close()
+    gm.close()
+
+
 def test_set_tokens_sets_what_is_named_and_nothing_else():
     """Sequences of 1 token, a whole capacity, 255 to 257 tokens, out of order and named twice (the last one counts); one that
     is refused ends the call behind those in front of it; the others keep their tokens."""
