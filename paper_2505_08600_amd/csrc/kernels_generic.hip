@@ -2789,6 +2789,9 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
     // 256, all resident at once.  Whole call, T = 0.7, 1024 / 512 / 256 threads (us): 270 rows of 128000 columns 53.2 / 48.8 /
     // 57.7, of 262144 91.5 / 81.1 / 95.7; 360 rows of 262144 94.9 / 90.0 / 99.5; 576 rows of 128000 74.4 / 77.2 / 70.7, of 262144 133 /
     // 136 / 122; 800 rows of 128000 104.3 / 103.9 / 104.2; 1350 rows of 128000 139 / 138 / 144.
+    // The upper edge, in turn in one process: 603, 675, 765 and 810 rows of 64000 columns 45.3 / 46.0 / 42.4, 46.7 / 47.3 / 45.1, 49.1 / 49.6 / 48.1, 53.9 / 53.9 /
+    // 53.9, of 128000 72.4 / 73.9 / 68.5, 75.3 / 76.2 / 73.5, 80.9 / 81.5 / 80.4, 90.1 / 91.4 / 90.3, of 262144 131.9 / 133.2 / 124.2, 137.2 / 138.4 / 134.8,
+    // 151.4 / 149.9 / 148.9, 171.2 / 170.7 / 169.9; greedy 3 to 10 % at 603 rows and 1 to 5 at 765.  (180000 columns, 765 rows: 2 % behind, greedy 7.)
     if ((size_t)n_rows * V > ((size_t)1 << (T > 0.f && gamma == 0 ? 26 : 25))) {
         if (n_rows > 256 && n_rows < 512) SD_STATS_WIDE(512, true);
         else if (n_rows > 512 && n_rows < 768) SD_STATS_WIDE(256, true);

@@ -243,11 +243,11 @@ def test_every_row_of_a_sequence_decides_for_itself(V, gamma):
 
 
 @pytest.mark.parametrize("V,gamma,copies", [(32772, 15, 1), (40960, 4, 1), (40964, 4, 1), (65536, 3, 1), (65540, 3, 1), (131072, 3, 1), (131076, 3, 1),
-                                            (131076, 1, 1), (66000, 3, 26), (64000, 3, 26)])
+                                            (131076, 1, 1), (66000, 3, 26), (64000, 3, 26), (44204, 3, 38)])
 def test_wide_rows_decide_by_the_sign_of_their_sums(V, gamma, copies):
     """Rows of more than 32768 columns: verdicts of every row, candidates outside the vocabulary, an empty residual; slices of
     2048, 4096 and 8192 vectors and one more (the pick's register forms and the form without), more than 128 MB of logits
-    (the nontemporal pass) and just less."""
+    (the nontemporal pass, in blocks of 256 threads at 520 and at 760 rows) and just less."""
     print(f"wide verdicts V={V} gamma={gamma} x{copies}", flush=True)
     logits, q, cand, u, expect = row_verdict_case(V, gamma)
     tile = lambda a: np.ascontiguousarray(np.concatenate([a] * copies))
@@ -264,11 +264,12 @@ def test_wide_rows_decide_by_the_sign_of_their_sums(V, gamma, copies):
     assert check_against_oracle(logits, q, cand, u, 1.0, na_h, nx_h) <= 1 + B // 50
 
 
-@pytest.mark.parametrize("V,B,T", [(33000, 160, 1.1), (33000, 270, 1.3), (33000, 270, 0.6), (128000, 100, 1.0), (128000, 150, 1.1), (128000, 150, 2.0)])
+@pytest.mark.parametrize("V,B,T", [(33000, 160, 1.1), (33000, 270, 1.3), (33000, 270, 0.6), (128000, 100, 1.0), (128000, 150, 1.1), (128000, 150, 2.0),
+                                      (66004, 257, 1.1), (128000, 300, 0.7), (44004, 383, 1.3)])
 def test_wide_rows_sum_their_exponentials_without_a_bias(V, B, T):
     """The sums wide rows leave in the workspace, against 64 bits at the factor 1 / T the kernel has (rounded to 32): their mean
-    error over 2 B rows.  Roundings of the sums and of each exponential's argument have no preferred sign: 1e-7 rms a row and
-    less, 6e-9 in the mean of 300 rows.  A factor log2(e) / T rounded once would put the same sign on every column, up to
+    error over 2 B rows (above 128 MB of logits in blocks of 512 threads up to 511 rows, of 256 from 513 to 767).
+    Roundings of the sums and of each exponential's argument have no preferred sign: 1e-7 rms a row and less, 6e-9 in the mean of 300 rows.  A factor log2(e) / T rounded once would put the same sign on every column, up to
     2^-24 of the mean of |x - max| / T weighted by the exponentials, 4 to 6 here: 7e-8 at T = 1.1, 3e-8 at 1.3."""
     print(f"wide sums V={V} B={B} T={T}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(5)
