@@ -2495,7 +2495,9 @@ __global__ __launch_bounds__(512) void verify_mass_wide_kernel(const float *logi
 // T > 0.  One block per sequence: the slice whose masses pass u * Z, searched with the rule of block_pick_cdf (segments
 // of 1024 vectors, then a scan of the segment that holds the target).  Without candidates (gamma == 0) there is one slice,
 // the whole row: its masses are left to block_pick_cdf and no launch before this one adds them up (one row of 32772
-// / 128000 / 262144 columns, whole call: 34 / 86 / 158 us with that launch, 27 / 65 / 118 without).
+// / 128000 / 262144 columns, whole call: 34 / 86 / 158 us with that launch, 27 / 65 / 118 without).  That is an instance of its own
+// (NSEG -1): sharing the one whose slices do not fit registers costs 8 rows of 33000 columns 25.8 us instead of 24.8, of 50000 31.5
+// instead of 30.4.
 template <int NSEG>
 __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *logits, const float *stats, int gamma, int V, float T,
                                                                 const int32_t *cand, const float *q, const float *u,
@@ -2516,11 +2518,10 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
                      inv_temperature(T), 1.0f / fabsf(st[3 * n_acc + 1])};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
     float Z = 0.f;
-    if (stride_g)
+    if (NSEG >= 0)
         for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
     int next;
-    const bool whole = NSEG == 0 && !stride_g, empty = w.q && !(Z > 0.f);
-    if (whole || empty) { // (whole: w.q is null anyway) numerically empty residual: draw from p
+    if (NSEG < 0 || (w.q && !(Z > 0.f))) { // the whole row (w.q is null anyway), or a numerically empty residual: draw from p
         const DrawWeights p = {w.row, nullptr, w.mx, w.invT, w.invZ};
         next = block_pick_cdf(p, V, uu, &ps, nullptr);
     } else {
@@ -2805,7 +2806,8 @@ hipError_t launch_verify_tail(hipStream_t s, const float *logits, int n_seq, int
     hipLaunchKernelGGL((verify_pick_wide_kernel<NSEG>), dim3(n_seq), dim3(1024), 0, s, logits, stats, gamma, V, T, cand, q, u, \
                        seq_ids, n_acc, next_tok, commit, cv)
         const int per = (V / 4 + gamma) / (gamma + 1); // vectors of a slice
-        if (gamma == 0 || per > 8192) SD_PICK_WIDE(0);
+        if (gamma == 0) SD_PICK_WIDE(-1);
+        else if (per > 8192) SD_PICK_WIDE(0);
         else if (per > 4096) SD_PICK_WIDE(8);
         else if (per > 2048) SD_PICK_WIDE(4);
         else SD_PICK_WIDE(2);
