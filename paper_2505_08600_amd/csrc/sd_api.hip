@@ -4,6 +4,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
+#include <new>
 
 #include "sd_internal.h"
 #include <cmath>
@@ -571,37 +573,39 @@ extern "C" int sd_ctx_set_tokens(sd_ctx *c, const int32_t *tokens, const int32_t
     if (!c || !tokens || !lens || n_seq < 1 || n_seq > c->B) return sd_fail(SD_EINVAL, "sd_ctx_set_tokens: bad argument");
     SD_HIP(hipDeviceSynchronize());
     // sequences in front of a refused one are set
-    int rc = SD_OK, n = 0, longest = 0;
-    std::vector<int> last(c->B, -1); // a sequence that is named twice gets what comes last
+    int rc = SD_OK, n = 0, n_set = 0, longest = 0;
+    std::unique_ptr<int32_t[]> last(new (std::nothrow) int32_t[c->B]); // a sequence that is named twice gets what comes last
+    if (!last) return sd_fail(SD_EHIP, "sd_ctx_set_tokens: out of host memory");
+    std::fill(last.get(), last.get() + c->B, -1);
     for (; n < n_seq; n++) {
         const int b = seq_ids ? seq_ids[n] : n;
         if (b < 0 || b >= c->B) rc = sd_fail(SD_EINVAL, "sd_ctx_set_tokens: sequence id out of range");
         else if (lens[n] < 1 || lens[n] > c->cap[b]) rc = sd_fail(SD_ECAP, "sd_ctx_set_tokens: length beyond capacity");
         if (rc) break;
+        n_set += last[b] < 0;
         last[b] = n;
         longest = std::max(longest, lens[n]);
     }
+    if (!n_set) return rc;
     // (sequence, length, place of its tokens) of each, then the tokens
-    std::vector<int32_t> head, body;
-    size_t pos = 0;
-    for (int j = 0; j < n; j++) {
-        const int b = seq_ids ? seq_ids[j] : j;
-        if (last[b] == j) {
-            const int32_t entry[3] = {b, lens[j], (int32_t)body.size()};
-            head.insert(head.end(), entry, entry + 3);
-            body.insert(body.end(), tokens + pos, tokens + pos + lens[j]);
-        }
-        pos += lens[j];
+    auto kept = [&](int j) { return last[seq_ids ? seq_ids[j] : j] == j; };
+    size_t n_tok = 0;
+    for (int j = 0; j < n; j++) n_tok += kept(j) ? lens[j] : 0;
+    std::unique_ptr<int32_t[]> staged(new (std::nothrow) int32_t[3 * (size_t)n_set + n_tok]);
+    if (!staged) return sd_fail(SD_EHIP, "sd_ctx_set_tokens: out of host memory");
+    int32_t *entry = staged.get(), *body = entry + 3 * (size_t)n_set, *end = body;
+    for (int j = 0; j < n; tokens += lens[j++]) {
+        if (!kept(j)) continue;
+        *entry++ = seq_ids ? seq_ids[j] : j;
+        *entry++ = lens[j];
+        *entry++ = (int32_t)(end - body);
+        end = std::copy(tokens, tokens + lens[j], end);
     }
-    const int n_set = (int)head.size() / 3;
-    if (n_set) {
-        head.insert(head.end(), body.begin(), body.end());
-        std::lock_guard<std::mutex> hold(c->staging_lock);
-        SD_HIP(hipMemcpy(c->d_staging, head.data(), sizeof(int32_t) * head.size(), hipMemcpyHostToDevice));
-        SD_HIP(launch_set_tokens(0, c->view(), c->d_staging, n_set));
-        SD_HIP(hipDeviceSynchronize());
-        c->len_upper = std::max(c->len_upper, longest);
-    }
+    std::lock_guard<std::mutex> hold(c->staging_lock);
+    SD_HIP(hipMemcpy(c->d_staging, staged.get(), sizeof(int32_t) * (end - staged.get()), hipMemcpyHostToDevice));
+    SD_HIP(launch_set_tokens(0, c->view(), c->d_staging, n_set));
+    SD_HIP(hipDeviceSynchronize());
+    c->len_upper = std::max(c->len_upper, longest);
     return rc;
 }
 

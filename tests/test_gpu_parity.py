@@ -2125,6 +2125,30 @@ def test_set_tokens_sets_what_is_named_and_nothing_else():
     ctx.close()
 
 
+def test_set_tokens_without_host_memory_reports_it():
+    """The host copy of the tokens cannot be allocated (the address space is limited to what the process has and 64 MB more, the
+    tokens take 160): an error status and the old tokens, and the same call succeeds with the limit lifted."""
+    import ctypes
+    import resource
+    _say("set_tokens without host memory")
+    n = 40 << 20
+    ctx = api.Context([n])
+    ctx.set_tokens([[7, 8, 9]])
+    tok, lens = np.full(n, 5, np.int32), np.array([n], np.int32)
+    call = lambda: api.lib().sd_ctx_set_tokens(ctx.h, tok.ctypes.data_as(ctypes.c_void_p), lens.ctypes.data_as(ctypes.c_void_p), None, 1)
+    soft, hard = resource.getrlimit(resource.RLIMIT_AS)
+    with open("/proc/self/statm") as f:
+        size = int(f.read().split()[0]) * resource.getpagesize()
+    resource.setrlimit(resource.RLIMIT_AS, (size + (64 << 20), hard))
+    try:
+        rc = call()
+    finally:
+        resource.setrlimit(resource.RLIMIT_AS, (soft, hard))
+    assert rc == api.SD_EHIP and ctx.sync()[0].tolist() == [3] and ctx.get_tokens(0).tolist() == [7, 8, 9]
+    assert call() == api.SD_OK and ctx.sync()[0].tolist() == [n]
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,heads,rank", [(768, 12, 8), (768, 12, 1), (1024, 16, 3), (1024, 16, 16), (128, 2, 12), (896, 14, 13)])
 def test_low_rank_update_carried_by_the_gemm_launch_matches_reference_kernels(d, heads, rank):
     """1 to 64 rows: the low-rank update runs as extra blocks of the QKV and O launches (one part of 768 outputs, a partial one, two
