@@ -2518,10 +2518,11 @@ __global__ __launch_bounds__(1024) void verify_pick_wide_kernel(const float *log
                      inv_temperature(T), 1.0f / fabsf(st[3 * n_acc + 1])};
     const int nvec = V / 4, per = (nvec + n_slices - 1) / n_slices;
     float Z = 0.f;
-    if (NSEG >= 0)
+    if (NSEG >= 0 && stride_g)
         for (int s = 0; s < n_slices; s++) Z += st[3 * s + 2];
     int next;
-    if (NSEG < 0 || (w.q && !(Z > 0.f))) { // the whole row (w.q is null anyway), or a numerically empty residual: draw from p
+    const bool whole = NSEG < 0 || (NSEG == 0 && !stride_g), empty = w.q && !(Z > 0.f);
+    if (whole || empty) { // (whole: w.q is null anyway) numerically empty residual: draw from p
         const DrawWeights p = {w.row, nullptr, w.mx, w.invT, w.invZ};
         next = block_pick_cdf(p, V, uu, &ps, nullptr);
     } else {
