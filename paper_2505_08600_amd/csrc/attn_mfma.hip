@@ -830,7 +830,7 @@ int g_force_attn_split = 0;
 hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                                   CtxView cv, int R, int n_seq, int H, int hd, const float2 *rope, int max_pos,
                                   void *Kl, void *Vtl, int64_t total_cap, int len_upper, void *obuf, ActView o_av,
-                                  int stream_nt, float *part, size_t part_floats, int32_t *arrivals, const void *wo_tiled,
+                                  int stream_nt, bool cached, float *part, size_t part_floats, int32_t *arrivals, const void *wo_tiled,
                                   int d_model, float *oslab, size_t oslab_floats, int *oproj_done)
 {
     if (oproj_done) *oproj_done = 0;
@@ -848,7 +848,11 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         //    at 640 with S = 4, 732 and 737 at 128 and 256 (720 and 729 without); a draft model with 32 pairs 961 ->
         //    948 at 384, 972 -> 962, 997 -> 965, 1003 -> 967 at 760 (S = 8: 992).  A model whose blocks apply the output
         //    projection as well loses that launch again: 318 -> 324 at 256 tokens, 324 -> 328 at 512, 329 -> 326 at 640, 334 -> 328 at 760;
-        //  * room for three to five (64 pairs, four layers): 477 -> 477 at 512, 482 -> 479 at 640, 477 -> 470 at 800, 526 -> 484 at 1480;
+        //  * room for three to five (64 pairs, four layers): 477 -> 477 at 512, 482 -> 479 at 640, 477 -> 470 at 800, 526 -> 484 at 1480.  Draft
+        //    phases of three tokens, 80 pairs of 64 dimensions: six 1024-wide layers 679 -> 663 at 820, 703 -> 682 at 1200, four (265 MB of weights)
+        //    469 -> 467, 502 -> 493.  Where blocks apply the output projection, or where the caches stay in the memory-side cache beside the
+        //    weights and one block draws faster, one block: two 768-wide layers, 48 pairs 219 -> 222 at 820, 227 -> 228 at 1200, 72 pairs 223 ->
+        //    229, 230 -> 236, 84 pairs 226 -> 234, 233 -> 241;
         //  * room for two (where one block has one helper), two layers: 128 pairs 298 -> 304 at 1150, 300 -> 307 at 1300, 306 -> 308
         //    at 1400; 96 pairs 285 -> 292, 288 -> 294, 290 -> 295: one block;
         //  * beyond 48 tiles one block a pair is not an alternative (the split kernel's three launches are); from 512 pairs on those, whose
@@ -869,7 +873,7 @@ hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, 
         if (g_force_attn_split) S = g_force_attn_split;
         else if (g_force_attn_waves) S = 1; // (a forced shape keeps every pair in one block, whatever the context)
         else if (tiles_upper > 48) S = pairs >= 512 ? 1 : fit == 1 && tiles_upper > 96 && busy(4) > busy(2) + 0.14f ? 4 : std::max(2, fit);
-        else if (fit >= 3 && tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
+        else if (fit >= (can_oproj || cached ? 6 : 3) && tiles_upper > 24) S = std::min(fit, tiles_upper / 4);
         else if (fit >= 6 && tiles_upper > (can_oproj ? 19 : 16)) S = 4; // (the bound is the longest sequence's; shorter ones gain less)
         if (S > 1 && pairs <= SD_ATTN_MAX_PAIRS && part && arrivals && (size_t)pairs * S * 16 * (hd + 2) <= part_floats) {
             const AttnSplit sp = {part, arrivals, S, (tiles_upper + S - 1) / S};

@@ -253,6 +253,7 @@ extern "C" int sd_load_model(const sd_model_config *cfg, const sd_weights *w, sd
         const size_t total = 2 * b_vd + b_g + (size_t)c.n_layers * (4 * b_dd + 3 * b_fd + 2 * b_g);
         // weights that cannot stay in the 256 MB memory-side cache from one forward to the next are streamed past it
         m->stream_nt = total > ((size_t)256 << 20);
+        m->weight_bytes = total;
         hipError_t we = hipMalloc(&m->wmem, total);
         if (we != hipSuccess) {
             delete m;
@@ -1033,8 +1034,9 @@ static int forward(sd_model *m, sd_ctx *c, int slot, hipStream_t s, int mode, in
         if (cf.dtype == SD_BF16 && !(g_force_generic & 2) && G == 1) {
             ProfScope ps(T_ATTN, s);
             const bool try_oproj = !fold && !lora_o && m->tiled_dd && !(g_force_generic & (1 | 8));
+            const bool cached = m->weight_bytes + (size_t)n_seq * kv_upper * cf.n_layers * d * 4 <= ((size_t)256 << 20); // (K and V, 2 bytes each)
             ea = launch_attn_fused_bf16(s, qkv_src, nq_slabs, (size_t)M * 3 * d, pv, cv, R, n_seq, H, hd, m->rope,
-                                        cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt, m->part,
+                                        cf.max_pos, Kl, Vtl, c->total_cap, kv_upper, m->obuf, avd, m->stream_nt, cached, m->part,
                                         m->part_floats, m->arrivals, try_oproj ? m->wo[l] : nullptr, d, m->gpart_r, m->gpart_r_floats, &oproj_done);
             if (ea == hipErrorNotSupported) ps.drop();
         }

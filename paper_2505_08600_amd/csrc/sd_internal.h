@@ -300,6 +300,7 @@ struct sd_model {
     void *lora_mem;
     int tiled_dd, tiled_fd, tiled_df, tiled_lm; // tile order used for [d][d], [F][d], [d][F], [V][d] matrices
     int esz; // bytes per weight / activation element
+    size_t weight_bytes; // all of them
     int stream_nt; // 1: the weights (and with them the caches) of this model exceed the memory-side cache: stream them with the nontemporal hint
     // workspace (device)
     float *x;       // [max_rows][d] residual stream
@@ -465,12 +466,13 @@ hipError_t launch_add_rmsnorm(hipStream_t s, int dtype, float *x, const float *p
                               ActView out_av);
 // wo_tiled / oslab (optional): let the attention blocks of a small model apply their head's columns of the
 // output projection themselves and leave H partial slabs [H][n_seq * R][d_model] in oslab; *oproj_done tells
-// whether they did (then obuf is not written and the projection launch is skipped).
+// whether they did (then obuf is not written and the projection launch is skipped).  cached: the model's weights and the
+// caches of these sequences fit the memory-side cache together.
 #define SD_OPROJ_MAX_HEADS 16
 hipError_t launch_attn_fused_bf16(hipStream_t s, const float *qkv, int n_slabs, size_t slab_stride, PlanView pv,
                                   CtxView cv, int R, int n_seq, int H, int hd, const float2 *rope, int max_pos,
                                   void *Kl, void *Vtl, int64_t total_cap, int len_upper, void *obuf, ActView o_av,
-                                  int stream_nt, float *part, size_t part_floats, int32_t *arrivals,
+                                  int stream_nt, bool cached, float *part, size_t part_floats, int32_t *arrivals,
                                   const void *wo_tiled = nullptr, int d_model = 0, float *oslab = nullptr,
                                   size_t oslab_floats = 0, int *oproj_done = nullptr);
 hipError_t launch_attn_mfma_bf16(hipStream_t s, const void *qbuf, ActView q_av, const void *Kl, const void *Vtl,

@@ -2068,6 +2068,35 @@ def test_attention_split_over_blocks_matches_one_block_per_pair(shape_name, S):
     gm.close()
 
 
+@pytest.mark.parametrize("B,gamma,S", [(6, 2, 1), (7, 0, 1), (3, 2, 7)])
+def test_contexts_of_a_cached_model_are_split_only_with_room_for_six_blocks(B, gamma, S):
+    """12 heads, weights and caches well inside the memory-side cache, 900 tokens (29 tiles): 72 and 84 pairs keep one block each, whether
+    it applies the output projection (18 rows) or the norm is split (7), 36 pairs take seven: the bits of that number forced."""
+    _say(f"cached model, {B} sequences, gamma {gamma}")
+    st_ = dataclasses.replace(dg.SHAPES["small_draft_bf16"], n_layers=2, d_model=768, n_heads=12, d_ffn=512, name="split_12")
+    gm = api.Model(st_, dg.make_weights(st_, 57, BF16_LM_SCALE), max_rows=256, max_pos=960)
+    prompts = [[int(t) for t in dg.make_prompt(57, b, 900 - 61 * b, st_.vocab)] for b in range(B)]
+    cand = H.dev(dg.make_prompt(58, 0, B * max(1, gamma), st_.vocab).reshape(B, -1).astype(np.int32))
+    na, nx = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx = api.Context([960] * B)
+    ctx.attach(gm)
+    H.gpu_prefill(ctx, [gm], prompts)
+    out = {}
+    try:
+        for split in (0, S, 3):
+            api.set_option("attn_split", split)
+            api.sd_verify(gm, ctx, None, B, gamma, 0.0, cand if gamma else None, None, None, na, nx, commit=False)
+            out[split] = gm.last_logits().cpu().numpy()
+            for b in range(B):
+                ctx.truncate(gm, b, len(prompts[b]) - 1)
+    finally:
+        api.set_option("attn_split", 0)
+    assert np.abs(out[0] - out[3]).max() < 2e-4 * np.abs(out[3]).max()
+    assert np.array_equal(out[0], out[S]) and not np.array_equal(out[0], out[3])
+    ctx.close()
+    gm.close()
+
+
 @pytest.mark.parametrize("B,n,S", [(8, 3200, 4), (8, 3000, 2), (6, 3200, 2), (11, 3200, 2)])
 def test_long_contexts_are_split_so_that_blocks_fill_the_last_round(B, n, S):
     """20 heads: 160 pairs take four blocks each beyond 96 tiles (two leave three eighths of the second round empty) and two up to
