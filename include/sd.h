@@ -389,8 +389,9 @@ int sd_debug_read(sd_model *m, const char *name, float *out, int32_t rows);
  * kind 3: key cache of one head, same arguments (32-token tiles in MFMA operand order).
  * Returns -1 for an unknown kind or arguments outside the layout's domain. */
 int64_t sd_debug_layout_index(int32_t kind, int64_t a, int64_t b, int64_t c, int64_t d);
-/* Host-only (no GPU call): the launch plan of a bf16 GEMM with more than 32 rows on the row-blocked kernel (up to 64
- * rows most shapes run on the few-row kernel instead).
+/* Host-only (no GPU call): the launch plan of a bf16 GEMM with more than 32 rows on the row-blocked kernel, were it to run
+ * there (up to 64 rows most shapes run on the few-row kernels instead, and up to 96 rows many of those with a K of 4096 and
+ * more).
  * mode 0 = plain projection, 2 = gate/up pair with the SwiGLU epilogue (n = output columns);
  * n_per_seg = output columns per weight segment (n for one matrix, n / 3 for q | k | v).
  * plan[0] = weight rows per block, [1] = rows per block, [2] = column tiles, [3] = row blocks,

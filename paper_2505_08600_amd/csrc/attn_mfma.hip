@@ -320,7 +320,7 @@ __global__ void attn_combine_kernel(const float *__restrict__ part, PlanView pv,
 // through L2 again (an 8192-token prompt at head width 128: 1.1 TB per 32 layers, the ceiling of what the L2s deliver);
 // here the block stages each 32-token K / V tile in LDS once, straight from memory, and every wave of a set takes its
 // operands from there, at the offsets it would have used in global memory, which divides the L2 traffic by WG.
-// Bound: the matrix units and the softmax beside them at the clock the power budget leaves (257 TFLOP of products in 240 us for
+// Bound: the matrix units and the softmax beside them at the clock the power budget leaves (0.257 TFLOP of products in 240 us for
 // 1024 rows behind 7168 tokens, 1.07 PFLOP/s, what the GEMMs of this shape issue) - if four waves a SIMD cover each other's
 // chains of LDS reads, score products, softmax and output products.  1024 rows of 32 heads are only two blocks of WG waves per
 // compute unit, so a block's tiles are dealt out to WS sets of waves, each with a running softmax and staging buffers of
@@ -541,8 +541,8 @@ struct OProj {
     size_t slab_stride; // rows * d_model
     int32_t d_model;
 };
-// SPLIT (few pairs, contexts of some 500 tokens and more): S blocks per pair, each with T consecutive tiles of it (a shorter sequence's last blocks have
-// none and leave at once).  A block rotates the query rows for itself, appends the new rows that fall into its tiles - so no
+// SPLIT (few pairs, contexts of some 500 tokens and more): S blocks per pair, each with T consecutive tiles of it (a shorter
+// sequence's last blocks have none and leave at once).  A block rotates the query rows for itself, appends the new rows that fall into its tiles - so no
 // block reads cache rows another one writes - and leaves (O, max, sum) of its tiles in `part`; the block of a pair that
 // arrives last, by a counter, merges the parts in order.  No block waits for another.  The parts cross the dies' L2s: they
 // are written and read with agent-scope accesses, and a block counts itself only after its stores have been acknowledged

@@ -522,8 +522,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_ksplit_kernel(const uint16_t 
     }
 }
 
-// Wide few-row GEMM (9 to 16 rows, to 64 where gemm_lds_kernel does not take the shape): like gemm_ksplit_kernel the waves of a block share out the K steps and meet in LDS,
-// but a block owns NW weight tiles instead of one or two.
+// Wide few-row GEMM (9 to 16 rows, to 64 where gemm_lds_kernel does not take the shape): like gemm_ksplit_kernel the waves
+// of a block share out the K steps and meet in LDS, but a block owns NW weight tiles instead of one or two.
 // Bound: bytes through L2 into the compute units (about 8.5 TB/s on this part for 16-byte loads), of which HBM only
 // supplies the weights: a block re-reads the activation rows of its K range, 4 M bytes per K element against 32 NW of
 // weights, so at M = 24 one gate/up pair per block pulled 270 MB of rows beside 180 MB of weights; six tiles pull 90 MB.
@@ -681,18 +681,21 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void gemm_wide_kernel(const uint16
 // One barrier per chunk, in front of its last MFMA group: behind it the next chunk's fragments are read and the buffer
 // just emptied is refilled.  Weight tiles lie in LDS as in memory (operand order, conflict free); rows of 128 bytes have their eight 16-byte
 // pieces exchanged by (row / 2) % 8, so that the 32 rows of an operand fall into all banks.
-// Measured alone, the slabs' reader included (gemm_wide_kernel before -> now, us): 4096 wide, M = 24: gate/up 34.6 -> 31.5, QKV 19.4 ->
-// 19.6, O 8.4 -> 8.6, down 18.5 -> 17.8; M = 64: gate/up 53.0 -> 42.9, QKV 30.7 -> 24.7, O 14.4 -> 13.1, down 27.5 -> 24.2, LM
-// head 63.7 -> 49.0; 5120 wide, M = 24: gate/up 52.2 -> 45.8, QKV 28.5 -> 27.3, down 27.3 -> 24.4; M = 64: gate/up 73.8 -> 57.1, QKV
-// 42.5 -> 34.2, down 40.0 -> 32.7; M = 80 (gemm_tile_kernel before, weights cold): gate/up 59.0 -> 53.5, QKV 35.6 -> 30.6, O 15.7 ->
-// 16.0, down 27.0 -> 26.9, LM head 60.1 -> 53.1, at 5120 wide 79.9 -> 68.8, 44.8 -> 40.6, 20.3 -> 19.9, 38.4 -> 39.2.  Deeper rings (5 stages of 64 x 96, 7 of 32 x 96) change nothing.  Verify pass of two 4096-wide
-// layers: 301 -> 293 at 18 rows, 307 -> 295 at 24, 340 -> 312 at 30, 410 -> 369 at 48, 488 -> 430 at 64.
+// Measured alone, the slabs' reader included (gemm_wide_kernel before -> now, us): 4096 wide, M = 24: gate/up 34.6 -> 31.5, QKV
+// 19.4 -> 19.6 (in a whole pass 0.8 ahead), down 18.5 -> 17.8; M = 64: gate/up 53.0 -> 42.9, QKV 30.7 -> 24.7, O 14.4 -> 13.1, down
+// 27.5 -> 24.2, LM head 63.7 -> 49.0; 5120 wide, M = 24: gate/up 52.2 -> 45.8, QKV 28.5 -> 27.3, down 27.3 -> 24.4; M = 64:
+// gate/up 73.8 -> 57.1, QKV 42.5 -> 34.2, down 40.0 -> 32.7; M = 80 (gemm_tile_kernel before, weights cold): gate/up 59.0 -> 53.5,
+// QKV 35.6 -> 30.6, O 15.7 -> 16.0, down 27.0 -> 26.9, LM head 60.1 -> 53.1, at 5120 wide 79.9 -> 68.8, 44.8 -> 40.6, 20.3 -> 19.9,
+// 38.4 -> 39.2.  Deeper rings (5 stages of 64 x 96, 7 of 32 x 96) change nothing.  Verify pass, four 4096-wide layers: 468 -> 448 at
+// 18 rows, 495 -> 461 at 24, 520 -> 476 at 30, 624 -> 560 at 48, 685 -> 596 at 64, 766 -> 697 at 72, 811 -> 758 at 96; two 8192 wide
+// 730 -> 690 at 18, 840 -> 734 at 30, 1079 -> 889 at 64.  Which launches it gets: lds_plan, lds_choice.
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_cvoid;
 template <int MODE, int WR, int WC, int NB, bool NT_HINT>
 __global__ __launch_bounds__(WR *WC * 64) void gemm_lds_kernel(const uint16_t *__restrict__ A, ActView a_av, WeightSeg w, int M, int N, int K,
-                                                            int k_per_split, float *__restrict__ C, size_t c_split_stride, uint16_t *__restrict__ Cact, ActView c_av, LmStats ls)
+                                                            int k_per_split, float *__restrict__ C, size_t c_split_stride,
+                                                            uint16_t *__restrict__ Cact, ActView c_av, LmStats ls)
 {
     constexpr bool SW = MODE == GEMM_SWIGLU; // weight tiles of the block: gate and up alternate
     constexpr int WAVES = WR * WC, BM = 32 * WR, BN = 32 * WC, COLS = SW ? BN / 2 : BN;
@@ -887,8 +890,8 @@ static WidePlan wide_plan(int mode, int M, int N, int K, int n_per_seg, int forc
 // 9; 768 wide 81.6 / 78.8 at 9, 89.0 / 82.5 at 16, 120 / 96 at 32.
 bool gemm_normfold_pays(int M, int d) { return M <= 8 || (M <= 10 && gemm_normfold_blocks(d) == 256); }
 
-// Block shapes of the row-blocked kernel (unsplit: the launch has one K split).  More than 64 rows: 96 rows x 256 columns (4 waves x 4 tiles; chunks
-// of half a K step) - the bytes a block pulls through L2 per MFMA halve against 48 x 128, which is what
+// Block shapes of the row-blocked kernel (unsplit: the launch has one K split).  More than 64 rows: 96 rows x 256 columns (4
+// waves x 4 tiles; chunks of half a K step) - the bytes a block pulls through L2 per MFMA halve against 48 x 128, which is what
 // bounds these GEMMs - or x 192 columns (3 tiles per wave) where that fills the 256 compute units better
 // (QKV at M = 192: 128 blocks x 2 K splits instead of 96 x 2); 64-row blocks of the same widths where they
 // pad M less (M = 128).  Up to 64 rows: 48-row blocks of 2 waves x
@@ -1015,8 +1018,8 @@ static TileShape tile_shape(int mode, int M, int N, int n_per_seg, int K, bool u
             // 64-row blocks when they pad M less (M = 128: 2 x 64 instead of 96 + 32) and do not cost more rounds; from 65 to 96
             // rows also where K is not split: one row block of the gate/up pair or the LM head leaves units idle (43 and 125
             // blocks at 2048 wide), and two of 64 rows pull little more than one of 96 (weights outweigh rows in every block):
-            // gate/up at 2048 / 5504 40 -> 25 us, a verify pass of two 4096-wide layers 518 -> 500 at 72 rows, 544 -> 525 at 96
-            // (from a K of 4096 on gemm_lds_kernel has these rows)
+            // gate/up at 2048 / 5504 40 -> 25 us, a verify pass of four 2048-wide layers 480 -> 439 at 66 rows, 497 -> 457 at 96, 3072 wide
+            // 645 -> 589, 664 -> 613 (from a K of 4096 on gemm_lds_kernel has most of these launches)
             const int ncol = (rows_w + cols - 1) / cols, nmb64 = (M + 63) / 64;
             auto rounds = [&](int rb) {
                 return die_rounds(ncol, rb, mode == GEMM_SWIGLU ? 1 : one_round_splits(ncol, rb, 256, steps), 256);
@@ -1106,7 +1109,9 @@ static hipError_t lds_launch(hipStream_t s, LdsPlan p, const uint16_t *a, ActVie
 {
     int kps, ny;
     split_geometry(K, p.ks, &kps, &ny);
-#define SD_LDS(WR, WC, NB)                                                                                                           hipLaunchKernelGGL((gemm_lds_kernel<MODE, WR, WC, NB, NT>), dim3(p.ncol, ny), dim3(WR * WC * 64), 0, s, a, a_av, w, M, N, K,                        kps, C, c_split_stride, ca, c_av, ls)
+#define SD_LDS(WR, WC, NB)                                                                                                    \
+    hipLaunchKernelGGL((gemm_lds_kernel<MODE, WR, WC, NB, NT>), dim3(p.ncol, ny), dim3(WR * WC * 64), 0, s, a, a_av, w, M, N, K, \
+                       kps, C, c_split_stride, ca, c_av, ls)
     if constexpr (!NT) {
         if (M > 64) {
             if (p.cols == 96) SD_LDS(3, 3, 4);

@@ -75,7 +75,7 @@ def test_row_blocked_gemm_plans_fit_the_busiest_die_in_one_round():
     split only as far as that die's 32 compute units (64 resident blocks for the 48-row shape) take in one round -
     counted over the whole chip instead, the 20 wide tiles of a 5120-wide projection would put 36 blocks on four
     dies.  (From 33 to 64 rows these are the plans the kernel would run; the launcher sends it only the shapes its 48-row
-    blocks fit, the others go to the wide few-row kernel.)  Blocks cover the matrix, plain projections with few column tiles take the 128-column shape, and the shapes
+    blocks fit, the others go to the few-row kernels, as do most from 65 to 96 rows with a K of 4096 and more.)  Blocks cover the matrix, plain projections with few column tiles take the 128-column shape, and the shapes
     of the measured configurations keep the plans they were measured with."""
     for d, f in ((4096, 11008), (5120, 13824), (8192, 28672), (2048, 5632)):
         for m in list(range(33, 200, 7)) + [256, 288, 384, 512, 576, 640, 768, 1024, 2048]:
@@ -109,13 +109,19 @@ def test_row_blocked_gemm_plans_fit_the_busiest_die_in_one_round():
 
 
 def test_unsplit_row_blocked_gemms_of_65_to_96_rows_run_as_two_row_blocks():
-    """Gate/up pairs and logits of 65 to 96 rows: two 64-row blocks per column tile while that is one round on the busiest
-    die, as at 97 to 128 rows; projections that split K, and grids that would run a second round, keep one 96-row block."""
-    for m in (65, 72, 96, 97, 128):
-        assert api.gemm_plan(2, m, 11008, 4096) == (192, 64, 115, 2, 1, 30)
+    """Gate/up pairs and logits of 65 to 96 rows in layers narrower than 4096 (wider ones are mostly the staged kernel's): two 64-row
+    blocks per column tile while that is one round on the busiest die, as at 97 to 128 rows; projections that split K, and grids
+    that would run a second round, keep one 96-row block."""
     for m in (65, 72, 96):
-        assert api.gemm_plan(2, m, 13824, 5120)[:4] == (192, 96, 144, 1)        # 288 blocks of 64 rows: two rounds
-        assert api.gemm_plan(0, m, 12288, 4096, 4096)[1] == 96 and api.gemm_plan(0, m, 4096, 11008)[1] == 96
+        assert api.gemm_plan(2, m, 5504, 2048) == (256, 64, 43, 2, 1, 12)
+        assert api.gemm_plan(2, m, 8192, 3072) == (256, 64, 64, 2, 1, 16)
+    for m in (97, 128):
+        assert api.gemm_plan(2, m, 5504, 2048) == (192, 64, 58, 2, 1, 16) and api.gemm_plan(2, m, 11008, 4096) == (192, 64, 115, 2, 1, 30)
+    for m in (65, 72, 96):
+        assert api.gemm_plan(2, m, 13824, 3072)[:4] == (192, 96, 144, 1)        # 288 blocks of 64 rows: two rounds
+        assert api.gemm_plan(0, m, 3 * 2048, 2048, 2048)[1] == 96 and api.gemm_plan(0, m, 2048, 5504)[1] == 96
+        for n, k, seg in ((3 * 2048, 2048, 2048), (2048, 2048, 2048), (2048, 5504, 2048), (3 * 3072, 3072, 3072), (3072, 8192, 3072)):
+            assert api.gemm_splits(m, n, k, seg) == api.gemm_plan(0, m, n, k, seg)[4]   # the kernel whose plans these are has them
 
 
 def test_wide_layers_of_17_to_96_rows_go_to_the_kernel_that_has_less_to_pull():
