@@ -520,7 +520,7 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const T *A, ActView a
 // row m).  A norm launch costs the small shapes as much as the GEMM behind it; above 16 rows the waves would repeat too
 // much of it (launch_gemm_f32_norm).  Whole step of the tiny pair, 12 norm launches of 67 fewer: 277 -> 233 us; the first
 // layer's reads the embedding rows themselves and the projection behind its attention adds to them, five launches of 49
-// fewer: 205 -> 190 us.
+// fewer: 205 -> 196 us.
 template <int MODE, int MR, bool NORM>
 __global__ __launch_bounds__(GF_WAVES * 64) void gemm_f32_rows_kernel(const float *__restrict__ A, WeightSeg w, int M, int N, int K, float *C,
                                                                       float *__restrict__ Cact, const float *__restrict__ gain,

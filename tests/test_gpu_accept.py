@@ -269,8 +269,9 @@ def test_wide_rows_decide_by_the_sign_of_their_sums(V, gamma, copies):
 def test_wide_rows_sum_their_exponentials_without_a_bias(V, B, T):
     """The sums wide rows leave in the workspace, against 64 bits at the factor 1 / T the kernel has (rounded to 32): their mean
     error over 2 B rows (above 128 MB of logits in blocks of 512 threads up to 511 rows, of 256 from 513 to 767).
-    Roundings of the sums and of each exponential's argument have no preferred sign: 1e-7 rms a row and less, 6e-9 in the mean of 300 rows.  A factor log2(e) / T rounded once would put the same sign on every column, up to
-    2^-24 of the mean of |x - max| / T weighted by the exponentials, 4 to 6 here: 7e-8 at T = 1.1, 3e-8 at 1.3."""
+    Roundings of the sums and of each exponential's argument have no preferred sign: 1e-7 rms a row and less, 6e-9 in the mean
+    of 300 rows.  A factor log2(e) / T rounded once would put the same sign on every column, up to 2^-24
+    of the mean of |x - max| / T weighted by the exponentials, 4 to 6 here: 7e-8 at T = 1.1, 3e-8 at 1.3."""
     print(f"wide sums V={V} B={B} T={T}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(5)
     x = 2.0 * torch.randn((B, 2, V), device="cuda", generator=g)

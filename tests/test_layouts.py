@@ -75,8 +75,9 @@ def test_row_blocked_gemm_plans_fit_the_busiest_die_in_one_round():
     split only as far as that die's 32 compute units (64 resident blocks for the 48-row shape) take in one round -
     counted over the whole chip instead, the 20 wide tiles of a 5120-wide projection would put 36 blocks on four
     dies.  (From 33 to 64 rows these are the plans the kernel would run; the launcher sends it only the shapes its 48-row
-    blocks fit, the others go to the few-row kernels, as do most from 65 to 96 rows with a K of 4096 and more.)  Blocks cover the matrix, plain projections with few column tiles take the 128-column shape, and the shapes
-    of the measured configurations keep the plans they were measured with."""
+    blocks fit, the others go to the few-row kernels, as do most from 65 to 96 rows with a K of 4096 and more.)  Blocks cover
+    the matrix, plain projections with few column tiles take the 128-column shape, and the shapes of the measured
+    configurations keep the plans they were measured with."""
     for d, f in ((4096, 11008), (5120, 13824), (8192, 28672), (2048, 5632)):
         for m in list(range(33, 200, 7)) + [256, 288, 384, 512, 576, 640, 768, 1024, 2048]:
             for mode, n, k, seg in ((0, 3 * d, d, d), (0, d, d, d), (2, f, d, f), (0, d, f, d), (0, 32000, d, 32000)):
